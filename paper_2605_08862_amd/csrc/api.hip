@@ -393,9 +393,8 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   const Shape& s = c->s;
   const int M_max = B * (k_max + 1);
   const Plan& p = c->plan;
-  int attn_s_min, attn_force;
-  attention_plan_params(s, B, k_max, &attn_s_min, &attn_force);
-  launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attn_s_min, attn_force, s.L, st);
+  launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attention_plan_params(s, B, k_max),
+              s.L, st);
   launch_embed(s, p, M_max, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
   SlabRule pending{0, 0, 0, 0, 0};              // slabs of the last residual projection not yet added to h
@@ -456,7 +455,7 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
   if (filter.on && V > kFilterMaxVocab) return fail(c, BS_ESHAPE, "accept_resample: top-k / top-p support at most 262136 vocabulary entries");
   if (filter.on && !given_logits && s.dtype == BS_BF16 && !c->filter_logits)
     return fail(c, BS_ESTATE, "accept_resample: top-k / top-p on a bf16 model need the logits scratch of bs_set_filter");
-  if (given_logits) launch_plan(p, c->kv, B, k_max, V, nullptr, nullptr, draft_tokens, draft_len, false, 0, 0, 0, st);
+  if (given_logits) launch_plan(p, c->kv, B, k_max, V, nullptr, nullptr, draft_tokens, draft_len, false, AttnPlan{}, 0, st);
   if (given_logits) {
     launch_logit_stats(p, M_max, V, given_logits, inv_temp, c->sb, st);
     n_vtiles = (V + 1023) / 1024;

@@ -13,8 +13,12 @@
 //   * Token chunks come from the step's work list (plan_kernel): one common chunk size for the whole
 //     batch, so a 32768-token sequence next to 512-token ones becomes many equal work items instead of
 //     one workgroup that runs 60 times longer than the others.  A sequence with one chunk writes its
-//     rows directly; with several, every workgroup stores a float32 partial (+ max, sum) and the LAST
-//     one to finish (device-scope counter, no waiting anywhere) merges them.
+//     rows directly; with several, every workgroup stores a float32 partial (+ max, sum) with
+//     write-through stores and the LAST one to finish (counter, no waiting anywhere) merges them (see
+//     publish_arrival in common.h).  With device-scope fences in the place of the write-through accesses,
+//     which is how the merge was published before, a launch with chunks cost 35 .. 60 us more: batch 1 x
+//     1000 tokens (1.5B heads, nine query rows) 47.7 -> 8.8 us, batch 48 x 1500 89 -> 21 us, batch 4 x 8192
+//     (7B heads) 59 -> 22 us, batch 1 x 30000 without drafts 98 -> 27 us.
 //   * The 4 waves of a workgroup take different 32-token tiles; each keeps its own online-softmax
 //     state (running max m, sum l) and output accumulator and they are merged once at the end.
 //   * K/V pages are stored in MFMA operand order (see common.h), so a wave's 16-byte-per-lane
@@ -48,7 +52,7 @@ __device__ __forceinline__ f16x8 pack_f16x8(const float* v) {
 // different query blocks stream the same K/V; the one-dimensional grid is decoded so that all workgroups of a
 // unit run on the same XCD (ids are dealt round-robin to the 8 XCDs) and are dispatched back to back, so the
 // second reader hits that XCD's L2 and HBM is still read once.
-// Partials (sequences with several chunks): part_ml [item][Hkv][RPT][2], part_o [item][Hkv][RPT][D], RPT =
+// Partials (sequences with several chunks): part_ml [slot][Hkv][RPT][2], part_o [slot][Hkv][RPT][D], RPT =
 // 32 * (query tiles of a unit); counters [sequence][Hkv][q_blocks], zero between launches; queue [8]: next
 // position of every XCD's queue, zeroed by the plan kernel for every layer of the step.
 // The read-only index arrays arrive as separate __restrict__ arguments (not inside the by-value Plan / KvView
@@ -74,10 +78,7 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
   constexpr int ROWS_W = 32 * NQ;       // query rows held by one wave
   constexpr int LDO = D + 4;            // row stride (floats) of an accumulator in LDS: 4 banks of skew per row
   extern __shared__ __align__(16) char lds_raw[];
-  constexpr int kListMax = 64;          // units with partials waiting for the next flush
-  __shared__ int s_list[kListMax];
-  __shared__ int s_nlist;
-  __shared__ int s_w;
+  __shared__ int s_w, s_last;
 
   // Persistent workgroups with one work queue per XCD.  Unit u belongs to XCD u % 8 (workgroup ids are dealt
   // round-robin to the XCDs), and that XCD's queue lists (unit, query block) pairs with the query blocks of a
@@ -88,6 +89,58 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, wgs_per_xcd = gridDim.x >> 3;
   const int n_live = min(attn_meta[1] * Hkv, n_units);
   const int total_w = (n_live > xcd ? (n_live - xcd + 7) / 8 : 0) * q_blocks;   // pairs of this XCD
+  // Combines the n_ch chunks of one (sequence, KV head, query block): called by the last workgroup to publish its
+  // partial rows.  Four chunks' loads are in flight together; the sums run in chunk order.
+  auto merge_unit = [&](const int b, const int h, const int qb, const int n_ch) {
+    const int G = Hq / Hkv, R = (seq_k[b] + 1) * G, row0 = row_start[b];
+    const size_t slot0 = ((size_t)item_start[b] * Hkv + h) * ((size_t)RP * q_blocks);
+    const wt_buf bo = wt_buffer(part_o + slot0 * D), bm = wt_buffer(part_ml + slot0 * 2);
+    constexpr int TPR = 256 / RP, CH = D / 4, CPT = CH / TPR, GC = 4;
+    const int wr = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+    const int qr = qb * RP + wr;
+    if (qr >= R) return;
+    const uint32_t step = (uint32_t)Hkv * RP * q_blocks;       // partial rows from one chunk to the next
+    float mt = -INFINITY;
+    for (int c0 = 0; c0 < n_ch; c0 += 8) {
+      float m[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m[u] = wt_load2(bm, (min(c0 + u, n_ch - 1) * step + qr) * 8)[0];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) mt = fmaxf(mt, m[u]);
+    }
+    float lt = 0.f;
+    f32x4 acc[CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < n_ch; c0 += GC) {
+      wt_f32x2 ml[GC];
+      f32x4 v[GC][CPT];
+#pragma unroll
+      for (int u = 0; u < GC; ++u) {
+        const uint32_t r = min(c0 + u, n_ch - 1) * step + qr;
+        ml[u] = wt_load2(bm, r * 8);
+#pragma unroll
+        for (int j = 0; j < CPT; ++j) v[u][j] = wt_load4(bo, (r * D + (sub + j * TPR) * 4) * 4);
+      }
+#pragma unroll
+      for (int u = 0; u < GC; ++u) {
+        if (c0 + u >= n_ch || ml[u][0] == -INFINITY) continue;
+        const float f = __builtin_amdgcn_exp2f(ml[u][0] - mt);
+        lt += ml[u][1] * f;
+#pragma unroll
+        for (int j = 0; j < CPT; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j][e] += v[u][j][e] * f;
+      }
+    }
+    const int iq = qr / G, hg = qr % G;
+    const float inv = 1.0f / lt;
+    f16* dst = out + (size_t)(row0 + iq) * Hq * D + (size_t)(h * G + hg) * D;
+#pragma unroll
+    for (int j = 0; j < CPT; ++j)
+      *(f16x4*)(dst + (sub + j * TPR) * 4) =
+          to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
+  };
   auto process = [&](const int unit, const int qb) {
   const int item = unit / Hkv, h = unit % Hkv;
   const int b = item_seq[item], chunk = item_chunk[item];
@@ -297,6 +350,8 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
     }
   }
   __syncthreads();
+  const size_t slot0 = ((size_t)item_start[b] * Hkv + h) * ((size_t)RP * q_blocks);   // partial row 0 of chunk 0
+  const wt_buf bo = wt_buffer(part_o + slot0 * D), bm = wt_buffer(part_ml + slot0 * 2);
   {
     constexpr int TPR = 256 / RP;                       // threads per query row
     constexpr int CH = D / 4;                           // 16-byte chunks per row
@@ -320,7 +375,7 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
       const int iq = qr / G, hg = qr % G;
       const float inv = 1.0f / lt;                      // row i always sees at least position c + i: lt > 0
       f16* dst = out + (size_t)(row0 + iq) * Hq * D + (size_t)(h * G + hg) * D;
-      const size_t pr = ((size_t)(item_start[b] + chunk) * Hkv + h) * ((size_t)RP * q_blocks) + qr;   // slot of (sequence, chunk, head)
+      const uint32_t pr = (uint32_t)(chunk * Hkv) * RP * q_blocks + qr;   // row of this chunk, counted from chunk 0 of (sequence, head)
 #pragma unroll
       for (int j = 0; j < CH / TPR; ++j) {
         const int ch = sub + j * TPR;
@@ -334,96 +389,31 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
         if (n_ch == 1) {
           *(f16x4*)(dst + ch * 4) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
         } else {
-          *(f32x4*)(part_o + pr * D + ch * 4) = acc;
+          wt_store4(bo, (pr * D + ch * 4) * 4, acc);
         }
       }
-      if (n_ch > 1 && sub == 0) { part_ml[pr * 2] = mt; part_ml[pr * 2 + 1] = lt; }
+      if (n_ch > 1 && sub == 0) wt_store2(bm, pr * 8, mt, lt);
     }
-    // several chunks: remember the unit; its partial is published and merged in flush() below
-    if (n_ch > 1 && threadIdx.x == 0) { s_list[s_nlist] = unit * q_blocks + qb; s_nlist = s_nlist + 1; }
   }
   };   // process
 
-  // Merge of the units with several chunks: the LAST workgroup of (sequence, KV head, query block) to publish
-  // its partial merges all of them; nobody waits.  Release: the workgroup's partial stores are made visible
-  // device-wide (one fence for all units in the list: a fence per unit, i.e. an L2 write-back and invalidate
-  // each, cost more than the attention itself on ragged batches) before the counters are bumped; acquire: a
-  // workgroup that reads n_ch - 1 sees the partials of all the others.
-  auto merge_unit = [&](const int unit, const int qb) {
-    const int item = unit / Hkv, h = unit % Hkv;
-    const int b = item_seq[item];
-    const int n_ch = item_start[b + 1] - item_start[b];
-    const int G = Hq / Hkv, R = (seq_k[b] + 1) * G, row0 = row_start[b];
-    constexpr int TPR = 256 / RP, CH = D / 4;
-    const int wr = threadIdx.x / TPR, sub = threadIdx.x % TPR;
-    const int qr = qb * RP + wr;
-    if (qr >= R) return;
-    const size_t rpt = (size_t)RP * q_blocks;
-    const size_t u0 = (size_t)item_start[b] * Hkv + h;           // unit of chunk 0; chunk c is Hkv units further
-    float mt = -INFINITY;
-    for (int c = 0; c < n_ch; ++c) mt = fmaxf(mt, part_ml[((u0 + (size_t)c * Hkv) * rpt + qr) * 2]);
-    float lt = 0.f;
-    f32x4 acc[CH / TPR];
-#pragma unroll
-    for (int j = 0; j < CH / TPR; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < n_ch; ++c) {
-      const size_t pc = (u0 + (size_t)c * Hkv) * rpt + qr;
-      const float m = part_ml[pc * 2];
-      if (m == -INFINITY) continue;
-      const float f = __builtin_amdgcn_exp2f(m - mt);
-      lt += part_ml[pc * 2 + 1] * f;
-#pragma unroll
-      for (int j = 0; j < CH / TPR; ++j) {
-        const f32x4 v = *(const f32x4*)(part_o + pc * D + (sub + j * TPR) * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[j][e] += v[e] * f;
-      }
-    }
-    const int iq = qr / G, hg = qr % G;
-    const float inv = 1.0f / lt;
-    f16* dst = out + (size_t)(row0 + iq) * Hq * D + (size_t)(h * G + hg) * D;
-#pragma unroll
-    for (int j = 0; j < CH / TPR; ++j)
-      *(f16x4*)(dst + (sub + j * TPR) * 4) =
-          to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
-  };
-  auto flush = [&]() {
-    __syncthreads();
-    const int n = s_nlist;
-    if (n == 0) return;                                 // uniform
-    __threadfence();
-    __syncthreads();
-    if ((int)threadIdx.x < n) {
-      const int unit = s_list[threadIdx.x] / q_blocks, qb = s_list[threadIdx.x] % q_blocks;
-      const int item = unit / Hkv, h = unit % Hkv, b = item_seq[item];
-      const int n_ch = item_start[b + 1] - item_start[b];
-      int32_t* cnt = counters + ((size_t)b * Hkv + h) * q_blocks + qb;
-      const int old = atomicAdd(cnt, 1);
-      const bool last = old == n_ch - 1;
-      if (last) *cnt = 0;                               // ready for the next launch (stream order)
-      else s_list[threadIdx.x] = -1;
-    }
-    __syncthreads();
-    __threadfence();
-    for (int i = 0; i < n; ++i)
-      if (s_list[i] >= 0) merge_unit(s_list[i] / q_blocks, s_list[i] % q_blocks);
-    __syncthreads();
-    if (threadIdx.x == 0) s_nlist = 0;
-  };
-
-  if (threadIdx.x == 0) s_nlist = 0;
   int w = slot;                                         // position in this XCD's queue
   while (w < total_w) {
     __syncthreads();                                    // LDS of the previous unit is no longer read
-    if (s_nlist == kListMax) flush();
-    process(xcd + 8 * (w / q_blocks), w % q_blocks);
+    const int unit = xcd + 8 * (w / q_blocks), qb = w % q_blocks;
+    process(unit, qb);
+    // several chunks: the last workgroup of (sequence, KV head, query block) to arrive merges all of them (workgroups
+    // without query rows in this block count as arrived too: the merge has no rows then)
+    {
+      const int b = item_seq[unit / Hkv], h = unit % Hkv, n_ch = item_start[b + 1] - item_start[b];
+      if (n_ch > 1 && publish_arrival(counters + ((size_t)b * Hkv + h) * q_blocks + qb, n_ch, &s_last)) merge_unit(b, h, qb, n_ch);
+    }
     if (total_w <= wgs_per_xcd) break;                  // at most one pair per workgroup: nothing to take
     __syncthreads();
     if (threadIdx.x == 0) s_w = atomicAdd(queue + xcd, 1) + wgs_per_xcd;
     __syncthreads();
     w = __builtin_amdgcn_readfirstlane(s_w);         // keeps everything derived from it on the scalar unit
   }
-  flush();
 }
 
 static int rows_padded(const Shape& s, int k_max) {
@@ -475,10 +465,24 @@ static void launch_shape(const Shape& s, int B, int k_max, int& q_blocks, int& s
   force_chunks = g_force_n_chunks;
 }
 
-void attention_plan_params(const Shape& s, int B, int k_max, int* s_min, int* force_chunks) {
-  if (s.dtype != BS_BF16) { *s_min = 0; *force_chunks = 0; return; }
+// Constants of the launch-time model, fitted to launches of one to 128 sequences of 1000 .. 30000 tokens in 1 .. 32
+// chunks on both model shapes.  Examples, measured (chunks of the model's choice first): 1.5B heads, nine query rows:
+// batch 1 x 1000 tokens, 4 chunks 8.7 us, 1 chunk 12.0, 16 chunks 10.9; batch 16 x 1500, 4 chunks 11.5, 1 chunk 16.5, 6
+// chunks (a second round) 19.2; batch 48 x 1500, 1 chunk 21.8, 2 chunks 30.6.  7B heads: batch 4 x 8192, 8 chunks 21.4, 4
+// chunks 27.4, 12 chunks 31.9.
+AttnPlan attention_plan_params(const Shape& s, int B, int k_max) {
+  AttnPlan a{};
+  if (s.dtype != BS_BF16) return a;
   int q_blocks;
-  launch_shape(s, B, k_max, q_blocks, *s_min, *force_chunks);
+  launch_shape(s, B, k_max, q_blocks, a.s_min, a.force_chunks);
+  a.pairs = (float)(s.Hkv * q_blocks);
+  const float bytes = s.D / 128.0f;                                 // a tile's bytes against head size 128
+  if (rows_padded(s, k_max) / 32 / q_blocks <= 2) {                 // four waves, a tile each: length in rows of four tiles
+    a.c_item = 8.0f; a.t_scale = 0.25f; a.t_lat = 1.1f; a.t_full = 2.7f * bytes / q_blocks; a.c_merge = 0.f; a.t_merge = 0.15f;
+  } else {                                                          // eight waves on two or four phases
+    a.c_item = 16.0f; a.t_scale = 1.0f; a.t_lat = 0.53f; a.t_full = 0.72f * bytes; a.c_merge = 6.0f; a.t_merge = 0.25f;
+  }
+  return a;
 }
 
 __global__ void zero_i32_kernel(int32_t* p, int n) {
@@ -511,7 +515,7 @@ static void launch_mfma_attn(const Shape& s, const Plan& p, const KvView& kv, in
   // one workgroup per CU (every instantiation for head size 128 needs more than half of a CU's registers);
   // fewer when the work list cannot be longer
   const int cap_w = (n_units * q_blocks + 7) / 8 * 8;
-  const int grid = cap_w < 256 ? cap_w : 256;
+  const int grid = cap_w < kAttnWorkgroups ? cap_w : kAttnWorkgroups;
   if (prof_token) attention_prof_mark(prof_token, st, true);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, p.seq_k, p.seq_c, p.row_start, p.seq_slot, p.attn_meta,
                      p.item_start, p.item_seq, p.item_chunk, kv.block_table, kv.max_pages, kv.n_pages, n_units, s.Hq,
@@ -537,14 +541,12 @@ static void launch_wide_attn(const Shape& s, const Plan& p, const KvView& kv, in
   static bool attr_set = false;
   if (!attr_set) { (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); attr_set = true; }
   const int cap_w = (n_units + 7) / 8 * 8;
-  const int grid = cap_w < 256 ? cap_w : 256;                          // one workgroup of eight waves per CU
+  const int grid = cap_w < kAttnWorkgroups ? cap_w : kAttnWorkgroups;                          // one workgroup of eight waves per CU
   if (prof_token) attention_prof_mark(prof_token, st, true);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, p.seq_k, p.seq_c, p.row_start, p.seq_slot, p.attn_meta,
                      p.item_start, p.item_seq, p.item_chunk, kv.block_table, kv.max_pages, kv.n_pages, n_units, s.Hq,
                      s.Hkv, scale_log2e, (const f16*)q, (const f16*)k_pages, (const f16*)v_pages, (f16*)out, part_o,
-                     part_ml, p.attn_queue + 8 * layer, p.status);
-  hipLaunchKernelGGL(attn_wide_merge_kernel<D>, dim3(B * s.Hkv), dim3(512), 0, st, p.seq_k, p.row_start, p.item_start, s.Hq,
-                     s.Hkv, part_o, part_ml, (f16*)out, p.status);
+                     part_ml, (int32_t*)scratch, p.attn_queue + 8 * layer, p.status);
   if (prof_token) attention_prof_mark(prof_token, st, false);
 }
 

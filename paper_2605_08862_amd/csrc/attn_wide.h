@@ -1,6 +1,6 @@
 // Verify attention for batches in which a sequence may have three or four 32-row query tiles per KV head
 // ((k_b + 1) * G > 64 query rows: long draft blocks on wide GQA groups, Sec. 3.3's "unified" launch at its
-// widest).  Same work list, page layout, partial results and last-arriver merge as attn_mfma_kernel in
+// widest).  Same work list, page layout, partial results and last-arriver merge (write-through, no fence) as attn_mfma_kernel in
 // attention.hip; what differs is how a workgroup spends a CU.
 //
 // With four query tiles the step is no longer a pure stream: per 32-token K/V tile (16 KiB at head size 128) a
@@ -34,7 +34,8 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
                                                         const f16* __restrict__ q, const f16* __restrict__ k_pages,
                                                         const f16* __restrict__ v_pages, f16* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
-                                                        int32_t* __restrict__ queue, int32_t* __restrict__ status) {
+                                                        int32_t* __restrict__ counters, int32_t* __restrict__ queue,
+                                                        int32_t* __restrict__ status) {
   constexpr int KS = D / 16;            // MFMA K-steps of the QK^T product = K fragments of a tile
   constexpr int DT = D / 32;            // 32-wide d tiles of the output; V fragments of a tile = 2 DT
   constexpr int NF = KS + 2 * DT;       // 1 KiB fragments of one K/V tile
@@ -42,7 +43,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
   constexpr int LDO = D + 4;            // row stride (floats) of an accumulator in LDS: 4 banks of skew per row
   constexpr int THREADS = 512;
   extern __shared__ __align__(16) char lds_raw[];
-  __shared__ int s_w;
+  __shared__ int s_w, s_last;
 
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, wgs_per_xcd = gridDim.x >> 3;
   const int n_live = min(attn_meta[1] * Hkv, n_units);
@@ -51,6 +52,58 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int ln = lane & 31, lg = lane >> 5;
   const size_t page_elems = kv_page_elems(Hkv, D);
+
+  // Combines the n_ch chunks of one (sequence, KV head): called by the last workgroup to publish its partial rows.
+  // Four threads per query row; two chunks' loads are in flight together, the sums run in chunk order.
+  auto merge_unit = [&](const int b, const int h, const int n_ch) {
+    constexpr int TPR = THREADS / RPT, CH = D / 4, CPT = CH / TPR, GC = 2;
+    const size_t slot0 = ((size_t)item_start[b] * Hkv + h) * RPT;
+    const wt_buf bo = wt_buffer(part_o + slot0 * D), bm = wt_buffer(part_ml + slot0 * 2);
+    const int G = Hq / Hkv, R = (seq_k[b] + 1) * G;
+    const int qr = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+    if (qr >= R) return;
+    const uint32_t step = (uint32_t)Hkv * RPT;             // partial rows from one chunk to the next
+    float mt = -INFINITY;
+    for (int c0 = 0; c0 < n_ch; c0 += 8) {
+      float m[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m[u] = wt_load2(bm, (min(c0 + u, n_ch - 1) * step + qr) * 8)[0];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) mt = fmaxf(mt, m[u]);
+    }
+    float lt = 0.f;
+    f32x4 acc[CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < n_ch; c0 += GC) {
+      wt_f32x2 ml[GC];
+      f32x4 v[GC][CPT];
+#pragma unroll
+      for (int u = 0; u < GC; ++u) {
+        const uint32_t r = min(c0 + u, n_ch - 1) * step + qr;
+        ml[u] = wt_load2(bm, r * 8);
+#pragma unroll
+        for (int j = 0; j < CPT; ++j) v[u][j] = wt_load4(bo, (r * D + (sub + j * TPR) * 4) * 4);
+      }
+#pragma unroll
+      for (int u = 0; u < GC; ++u) {
+        if (c0 + u >= n_ch || ml[u][0] == -INFINITY) continue;
+        const float f = __builtin_amdgcn_exp2f(ml[u][0] - mt);
+        lt += ml[u][1] * f;
+#pragma unroll
+        for (int j = 0; j < CPT; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j][e] += v[u][j][e] * f;
+      }
+    }
+    const int iq = qr / G, hg = qr % G;
+    const float inv = 1.0f / lt;
+    f16* dst = out + (size_t)(row_start[b] + iq) * Hq * D + (size_t)(h * G + hg) * D;
+#pragma unroll
+    for (int j = 0; j < CPT; ++j)
+      *(f16x4*)(dst + (sub + j * TPR) * 4) =
+          to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
+  };
 
   // One unit with NQT query tiles (2 or 4).
   auto run = [&](auto nqt_tag, const int unit) {
@@ -203,6 +256,8 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
               f32x4{o[dt][4 * i4], o[dt][4 * i4 + 1], o[dt][4 * i4 + 2], o[dt][4 * i4 + 3]};
     }
     __syncthreads();
+    const size_t slot0 = ((size_t)item_start[b] * Hkv + h) * RPT;       // partial row 0 of chunk 0
+    const wt_buf bo = wt_buffer(part_o + slot0 * D), bm = wt_buffer(part_ml + slot0 * 2);
     {
       constexpr int TPR = THREADS / (32 * NQT);          // threads per query row: 8 or 4
       constexpr int CH = D / 4;                          // 16-byte chunks per row
@@ -225,7 +280,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
         const int iq = wr / G, hg = wr % G;
         const float inv = 1.0f / lt;                     // a single-chunk row always sees position c + i: lt > 0
         f16* dst = out + (size_t)(row0 + iq) * Hq * D + (size_t)(h * G + hg) * D;
-        const size_t pr = ((size_t)(item_start[b] + chunk) * Hkv + h) * RPT + wr;   // slot of (sequence, chunk, head)
+        const uint32_t pr = (uint32_t)(chunk * Hkv) * RPT + wr;   // row of this chunk, counted from chunk 0 of (sequence, head)
 #pragma unroll
         for (int j = 0; j < CH / TPR; ++j) {
           const int ch = sub + j * TPR;
@@ -237,9 +292,9 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
             for (int e = 0; e < 4; ++e) acc[e] += v[e] * mw[w];
           }
           if (n_ch == 1) *(f16x4*)(dst + ch * 4) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
-          else *(f32x4*)(part_o + pr * D + ch * 4) = acc;
+          else wt_store4(bo, (pr * D + ch * 4) * 4, acc);
         }
-        if (n_ch > 1 && sub == 0) { part_ml[pr * 2] = mt; part_ml[pr * 2 + 1] = lt; }
+        if (n_ch > 1 && sub == 0) wt_store2(bm, pr * 8, mt, lt);
       }
     }
   };   // run
@@ -250,6 +305,9 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     if (k < 0) return;                                   // workgroup-uniform
     if ((k + 1) * (Hq / Hkv) > 64) run(std::integral_constant<int, 4>{}, unit);
     else run(std::integral_constant<int, 2>{}, unit);
+    // several chunks: the last workgroup of (sequence, KV head) to arrive merges all of them
+    const int h = unit % Hkv, n_ch = item_start[b + 1] - item_start[b];
+    if (n_ch > 1 && publish_arrival(counters + ((size_t)b * Hkv + h) * 4, n_ch, &s_last)) merge_unit(b, h, n_ch);
   };
 
   int w = slot;                                         // position in this XCD's queue
@@ -262,63 +320,4 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     __syncthreads();
     w = __builtin_amdgcn_readfirstlane(s_w);
   }
-}
-
-// Second, small launch of the wide path: one workgroup per (sequence, KV head) combines the partial results of a
-// sequence that was cut into several chunks (float32 rows + (max, sum) per chunk, slot-addressed) into the final
-// float16 rows; sequences with one chunk were written by attn_wide_kernel itself and their workgroups exit at once.
-// (Merging inside the attention kernel by the last workgroup to arrive, as attn_mfma_kernel does, needs a
-// device-scope fence per publication: once per unit it tripled the kernel's time on the long-tail batch, once per
-// workgroup it left every merge to the end of the kernel, 80 us mean / 118 us worst per workgroup with nothing
-// streaming meanwhile.  The kernel boundary orders the partial results for free.)
-template <int D>
-__global__ void __launch_bounds__(512) attn_wide_merge_kernel(const int32_t* __restrict__ seq_k, const int32_t* __restrict__ row_start,
-                                                              const int32_t* __restrict__ item_start, int Hq, int Hkv,
-                                                              const float* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                              f16* __restrict__ out, int32_t* __restrict__ status) {
-  constexpr int RPT = 128, TPR = 512 / RPT, CH = D / 4, CPT = CH / TPR;   // 4 threads per row, CPT 16-byte chunks each
-  const int b = blockIdx.x / Hkv, h = blockIdx.x % Hkv;
-  const int n_ch = item_start[b + 1] - item_start[b];
-  const int k = seq_k[b];
-  if (n_ch <= 1 || k < 0) return;
-  const int G = Hq / Hkv, R = (k + 1) * G;
-  const int qr = threadIdx.x / TPR, sub = threadIdx.x % TPR;
-  if (qr >= R) return;
-  const size_t u0 = (size_t)item_start[b] * Hkv + h;             // slot of chunk 0; chunk c is Hkv slots further
-  float mt = -INFINITY;
-  for (int cc = 0; cc < n_ch; ++cc) mt = fmaxf(mt, part_ml[((u0 + (size_t)cc * Hkv) * RPT + qr) * 2]);
-  float lt = 0.f;
-  f32x4 acc[CPT];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // two chunks per round: their loads are requested together (chunk order of the sums is kept)
-  for (int c0 = 0; c0 < n_ch; c0 += 2) {
-    float m2[2], l2[2];
-    f32x4 v[2][CPT];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const size_t pc = (u0 + (size_t)min(c0 + u, n_ch - 1) * Hkv) * RPT + qr;
-      m2[u] = part_ml[pc * 2];
-      l2[u] = part_ml[pc * 2 + 1];
-#pragma unroll
-      for (int j = 0; j < CPT; ++j) v[u][j] = *(const f32x4*)(part_o + pc * D + (sub + j * TPR) * 4);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (c0 + u >= n_ch || m2[u] == -INFINITY) continue;
-      const float f = __builtin_amdgcn_exp2f(m2[u] - mt);
-      lt += l2[u] * f;
-#pragma unroll
-      for (int j = 0; j < CPT; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[j][e] += v[u][j][e] * f;
-    }
-  }
-  const int iq = qr / G, hg = qr % G;
-  const float inv = 1.0f / lt;
-  f16* dst = out + (size_t)(row_start[b] + iq) * Hq * D + (size_t)(h * G + hg) * D;
-#pragma unroll
-  for (int j = 0; j < CPT; ++j)
-    *(f16x4*)(dst + (sub + j * TPR) * 4) =
-        to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
 }

@@ -44,6 +44,54 @@ __device__ __forceinline__ f16x4 to_f16x4_guarded(float a, float b, float c, flo
   return v;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Results that workgroups of ONE launch hand to each other (partial results merged by the last workgroup to arrive).
+// The eight XCDs have an L2 each, so a plain store may sit in the writer's L2 and a plain load may hit a stale line of
+// the reader's.  A device-scope fence repairs that by writing back and invalidating a whole L2: measured 40 us per
+// launch in which 256 workgroups publish 4 KiB each.  The accesses below carry the coherence themselves (sc1: agent
+// scope, written through, never served from a stale line): the same launch costs nothing measurable over an empty one.
+//   writer:  wt_store*(...) by any threads; publish_arrival() by all threads of the workgroup
+//   reader:  the workgroup for which publish_arrival() returned true reads everything with wt_load*
+// ---------------------------------------------------------------------------------------------
+typedef float wt_f32x4 __attribute__((ext_vector_type(4)));
+typedef float wt_f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t wt_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t wt_u32x2 __attribute__((ext_vector_type(2)));
+constexpr int kWriteThrough = 16;      // cache-policy bit sc1
+typedef __amdgpu_buffer_rsrc_t wt_buf;
+// `base` must be uniform within the wave; accesses are addressed by a 32-bit byte offset from it
+__device__ __forceinline__ wt_buf wt_buffer(const void* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xffffffffu, 0x00020000);
+}
+__device__ __forceinline__ void wt_store4(wt_buf b, uint32_t off, wt_f32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(wt_u32x4, v), b, (int)off, 0, kWriteThrough);
+}
+__device__ __forceinline__ void wt_store2(wt_buf b, uint32_t off, float x, float y) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(wt_u32x2, wt_f32x2{x, y}), b, (int)off, 0, kWriteThrough);
+}
+__device__ __forceinline__ wt_f32x4 wt_load4(wt_buf b, uint32_t off) {
+  return __builtin_bit_cast(wt_f32x4, __builtin_amdgcn_raw_buffer_load_b128(b, (int)off, 0, kWriteThrough));
+}
+__device__ __forceinline__ wt_f32x2 wt_load2(wt_buf b, uint32_t off) {
+  return __builtin_bit_cast(wt_f32x2, __builtin_amdgcn_raw_buffer_load_b64(b, (int)off, 0, kWriteThrough));
+}
+// Called by every thread of the workgroup (uniformly) after its wt_stores; `flag` is a __shared__ int.  Counts the
+// workgroup as arrived at `counter` and returns true in the one that completes the count n; the counter is then zero
+// again for the next launch.  Nobody waits for anybody.
+__device__ __forceinline__ bool publish_arrival(int32_t* counter, int n, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this thread's stores have reached the coherence point
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const bool last = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    if (last) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last ? 1 : 0;
+  }
+  __syncthreads();
+  const bool r = *flag != 0;
+  __syncthreads();                                       // the flag may be reused
+  return r;
+}
+
 constexpr int kPage = BS_PAGE_TOKENS;   // tokens per KV page
 constexpr int kTile = 32;               // tokens per MFMA tile inside a page (bf16 layout)
 
@@ -121,6 +169,19 @@ struct Plan {
 // items (see plan_kernel): sum_b chunks(b) <= B + S with S <= 4 max(B, s_min).
 __host__ __device__ __forceinline__ int attn_item_capacity(int B, int s_min) { return 5 * (B > s_min ? B : s_min); }
 constexpr int kAttnMaxSmin = 256;
+constexpr int kAttnWorkgroups = 256;   // persistent workgroups of an attention launch (one per CU)
+
+// How long an attention launch takes for a given chunk size (microseconds; measured, see attention.hip).  A task is one
+// (item, KV head, query block).  tasks running together: c_item + length * max(t_lat, t_full * tasks / workgroups).
+struct AttnPlan {
+  int s_min;            // 0: no work list; else items that fill the chip once (capacity of the list)
+  int force_chunks;     // > 0 (tests): chunk size such that the longest sequence has that many chunks
+  float pairs;          // tasks per item
+  float c_item;         // fixed cost of a task: metadata, first loads, merge of its waves
+  float t_scale;        // length of a task per 32-token tile
+  float t_lat, t_full;  // time per unit of length: alone on the memory system, with every CU streaming
+  float c_merge, t_merge;   // merge of a sequence's chunks: fixed, per chunk
+};
 
 struct KvView {
   int n_pages, n_slots, max_pages;
@@ -136,11 +197,10 @@ struct Shape {
 
 // ---- launchers (each .hip file defines its own kernels and these host wrappers) ---------------
 // plan.hip
-// attn_s_min > 0: also build the attention work list (wanted number of items, at most kAttnMaxSmin);
-// attn_force_chunks > 0 (tests): chunk size such that the longest sequence has that many chunks.
+// attn.s_min > 0: also build the attention work list.
 void launch_plan(const Plan& p, const KvView& kv, int B, int k_max, int vocab, const int32_t* seq_slot,
                  const int32_t* last_token, const int32_t* draft_tokens, const int32_t* draft_len,
-                 bool need_kv, int attn_s_min, int attn_force_chunks, int n_layers, hipStream_t st);
+                 bool need_kv, const AttnPlan& attn, int n_layers, hipStream_t st);
 void launch_commit(const Plan& p, const KvView& kv, int B, const int32_t* seq_slot,
                    const int32_t* n_commit, hipStream_t st);
 void launch_clear_status(int32_t* status, hipStream_t st);
@@ -217,7 +277,7 @@ void launch_pack_weight(const void* w_bf16, int N, int K, void* packed_f16, int3
 // attention.hip
 // attention_plan_params gives the work-list parameters launch_plan needs for the same (B, k_max);
 // launch_attention_init clears the completion counters once, at context creation.
-void attention_plan_params(const Shape& s, int B, int k_max, int* s_min, int* force_chunks);
+AttnPlan attention_plan_params(const Shape& s, int B, int k_max);
 void launch_attention_init(const Shape& s, int B_max, void* scratch, hipStream_t st);
 void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int k_max, int M_max,
                       const void* q, const void* k_pages, const void* v_pages, void* out, void* scratch,

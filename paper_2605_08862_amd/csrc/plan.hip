@@ -5,27 +5,61 @@
 // lengths ride in one batch) is computed here, on the device, with no host round trip.
 #include "common.h"
 
-__global__ void __launch_bounds__(256) plan_kernel(Plan p, KvView kv, int B, int k_max, int vocab,
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanMaxB = 4096;                     // checked at context creation
+
+// Exclusive prefix sum over the workgroup of one value per thread; `total` receives the sum.  s_part: kPlanThreads / 64
+// words.  Called by all threads.
+__device__ __forceinline__ int block_exclusive_scan(int v, int* s_part, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  __syncthreads();                                  // s_part of an earlier scan is no longer read
+  if (lane == 63) s_part[wave] = incl;
+  __syncthreads();
+  int before = 0, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    const int t = s_part[w];
+    if (w < wave) before += t;
+    sum += t;
+  }
+  total = sum;
+  return before + incl - v;
+}
+
+// One workgroup plans the step, and every later kernel waits for it: what bounds it is the chain of dependent loads
+// (slot -> committed length -> block table -> lists), so every phase spreads over 1024 threads and no phase is walked
+// by one thread.  Measured, 7B shape: batch 8 (contexts near 20000) 33 -> 13 us, batch 128 (512 .. 32768) 48 -> 18 us.
+__global__ void __launch_bounds__(kPlanThreads) plan_kernel(Plan p, KvView kv, int B, int k_max, int vocab,
                                                    const int32_t* __restrict__ seq_slot,
                                                    const int32_t* __restrict__ last_token,
                                                    const int32_t* __restrict__ draft_tokens,
-                                                   const int32_t* __restrict__ draft_len, int need_kv, int attn_s_min,
-                                                   int attn_force_chunks, int n_layers) {
+                                                   const int32_t* __restrict__ draft_len, int need_kv, AttnPlan attn,
+                                                   int n_layers) {
   __shared__ int s_fault;
-  __shared__ int s_slot[4096];                      // B <= 4096 (checked at context creation)
-  __shared__ int s_k[4096];                         // validated k_b (-1: skipped)
-  __shared__ int s_c[4096];                         // c_b
-  __shared__ int s_pr[256], s_pt[256];              // per-thread partial row / draft counts, then their prefix
+  __shared__ int s_slot[kPlanMaxB];
+  __shared__ int s_k[kPlanMaxB];                    // validated k_b (-1: skipped)
+  __shared__ int s_c[kPlanMaxB];                    // c_b, later the sequence's number of tiles
+  __shared__ int s_r[kPlanMaxB];                    // first packed row
+  __shared__ int s_part[kPlanThreads / 64];
   const int tid = threadIdx.x;
   if (tid == 0) s_fault = 0;
   if (need_kv)
-    for (int b = tid; b < B; b += blockDim.x) s_slot[b] = seq_slot[b];
+    for (int b = tid; b < B; b += kPlanThreads) s_slot[b] = seq_slot[b];
+  if (need_kv && attn.s_min > 0)
+    for (int i = tid; i < 8 * n_layers; i += kPlanThreads) p.attn_queue[i] = 0;
   __syncthreads();
-  // phase 1: per-sequence validation.  Four lanes share a sequence: each repeats the scalar checks (same addresses:
-  // one transaction) and takes a quarter of the duplicate-slot scan and of the block-table entries, eight loads at a
-  // time, so that a context of 2048 tokens (33 pages) costs two memory round trips instead of five.
-  for (int b = tid >> 2; b < B; b += blockDim.x >> 2) {
-    const int sub = tid & 3;
+  // phase 1: per-sequence validation.  16 lanes share a sequence: each repeats the scalar checks (same addresses: one
+  // transaction) and takes a share of the duplicate-slot scan, of the block-table entries (four loads in flight) and of
+  // the token ids.
+  constexpr int SUBS = 16;
+  for (int b = tid / SUBS; b < B; b += kPlanThreads / SUBS) {
+    const int sub = tid % SUBS;
     int k = draft_len[b], fault = 0, c = 0, slot = 0;
     if (k < 0 || k > k_max) { fault |= BS_FAULT_DRAFT_LEN; }
     if (need_kv) {
@@ -33,39 +67,39 @@ __global__ void __launch_bounds__(256) plan_kernel(Plan p, KvView kv, int B, int
       if (slot < 0 || slot >= kv.n_slots) {
         fault |= BS_FAULT_SLOT;
       } else {
-        for (int b2 = sub; b2 < b; b2 += 4) if (s_slot[b2] == slot) fault |= BS_FAULT_SLOT;
         c = kv.ctx_len[slot];
+        for (int b2 = sub; b2 < b; b2 += SUBS) if (s_slot[b2] == slot) fault |= BS_FAULT_SLOT;
         if (!(fault & BS_FAULT_DRAFT_LEN)) {
           if (c < 0 || (long)c + k + 1 > (long)kv.max_pages * kPage) {
             fault |= BS_FAULT_KV_PAGES;
           } else {
             const int32_t* bt = kv.block_table + (size_t)slot * kv.max_pages;
             const int last = (c + k) / kPage;
-            for (int pg0 = sub * 8; pg0 <= last; pg0 += 32) {
-              int id[8];
+            for (int pg0 = sub; pg0 <= last; pg0 += 4 * SUBS) {
+              int id[4];
 #pragma unroll
-              for (int u = 0; u < 8; ++u) id[u] = bt[min(pg0 + u, last)];
+              for (int u = 0; u < 4; ++u) id[u] = bt[min(pg0 + u * SUBS, last)];
 #pragma unroll
-              for (int u = 0; u < 8; ++u) if (id[u] < 0 || id[u] >= kv.n_pages) fault |= BS_FAULT_KV_PAGES;
+              for (int u = 0; u < 4; ++u) if (id[u] < 0 || id[u] >= kv.n_pages) fault |= BS_FAULT_KV_PAGES;
             }
           }
         }
       }
     }
-    // token ids of the sequence's rows (the last token and the k drafts), a quarter per lane: a sequence with an id
-    // outside the vocabulary is skipped like one with a bad draft length (no row is embedded, appended or judged)
+    // token ids of the sequence's rows (the last token and the k drafts): a sequence with an id outside the
+    // vocabulary is skipped like one with a bad draft length (no row is embedded, appended or judged)
     if (!(fault & BS_FAULT_DRAFT_LEN)) {
       if (sub == 0 && last_token) {
         const int t = last_token[b];
         if (t < 0 || t >= vocab) fault |= BS_FAULT_TOKEN_ID;
       }
-      for (int i = sub; i < k; i += 4) {
+      for (int i = sub; i < k; i += SUBS) {
         const int t = draft_tokens[(size_t)b * k_max + i];
         if (t < 0 || t >= vocab) fault |= BS_FAULT_TOKEN_ID;
       }
     }
-    fault |= __shfl_xor(fault, 1);
-    fault |= __shfl_xor(fault, 2);
+#pragma unroll
+    for (int o = 1; o < SUBS; o <<= 1) fault |= __shfl_xor(fault, o);
     if (sub == 0) {
       p.seq_k[b] = fault ? -1 : k;
       s_k[b] = fault ? -1 : k;
@@ -76,39 +110,35 @@ __global__ void __launch_bounds__(256) plan_kernel(Plan p, KvView kv, int B, int
     }
   }
   __syncthreads();
-  // phase 2: prefix sums over the sequences (each thread a contiguous range, partials scanned by thread 0)
-  const int per = (B + 255) / 256;
+  // phase 2: prefix sums over the sequences (each thread a contiguous range)
+  const int per = (B + kPlanThreads - 1) / kPlanThreads;
   const int b_lo = min(tid * per, B), b_hi = min(b_lo + per, B);
   {
-    int r = 0, t = 0;
+    int r = 0, t = 0, n_r, n_t;
     for (int b = b_lo; b < b_hi; ++b) if (s_k[b] >= 0) { r += s_k[b] + 1; t += s_k[b]; }
-    s_pr[tid] = r; s_pt[tid] = t;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int r = 0, t = 0;
-    for (int i = 0; i < 256; ++i) { const int a = s_pr[i], c2 = s_pt[i]; s_pr[i] = r; s_pt[i] = t; r += a; t += c2; }
-    p.row_start[B] = r;
-    p.draft_start[B] = t;
-    p.n_rows[0] = r;
-    p.n_rows[1] = t;
-  }
-  __syncthreads();
-  {
-    int r = s_pr[tid], t = s_pt[tid];
+    r = block_exclusive_scan(r, s_part, n_r);
+    t = block_exclusive_scan(t, s_part, n_t);
     for (int b = b_lo; b < b_hi; ++b) {
       p.row_start[b] = r;
+      s_r[b] = r;
       p.draft_start[b] = t;
       if (s_k[b] >= 0) { r += s_k[b] + 1; t += s_k[b]; }
+    }
+    if (tid == 0) {
+      p.row_start[B] = n_r;
+      p.draft_start[B] = n_t;
+      p.n_rows[0] = n_r;
+      p.n_rows[1] = n_t;
+      if (s_fault) atomicOr(p.status, s_fault);
     }
   }
   __syncthreads();
   // phase 3: per-row maps (parallel over sequences x positions)
-  for (int idx = tid; idx < B * (k_max + 1); idx += blockDim.x) {
+  for (int idx = tid; idx < B * (k_max + 1); idx += kPlanThreads) {
     int b = idx / (k_max + 1), i = idx % (k_max + 1);
     int k = s_k[b];
     if (k < 0 || i > k) continue;
-    int r = p.row_start[b] + i;
+    int r = s_r[b] + i;
     // every id was validated in phase 1 (a sequence with a bad one has s_k[b] = -1 and is skipped above)
     const int tok = (i == 0) ? (last_token ? last_token[b] : 0) : draft_tokens[(size_t)b * k_max + i - 1];
     const int tgt = (i < k) ? draft_tokens[(size_t)b * k_max + i] : -1;
@@ -117,43 +147,84 @@ __global__ void __launch_bounds__(256) plan_kernel(Plan p, KvView kv, int B, int
     p.row_tok[r] = tok;
     p.row_target[r] = tgt;
   }
-  __syncthreads();
-  if (tid == 0 && s_fault) atomicOr(p.status, s_fault);
-  if (!need_kv || attn_s_min <= 0) return;
-  for (int i = tid; i < 8 * n_layers; i += blockDim.x) p.attn_queue[i] = 0;
+  if (!need_kv || attn.s_min <= 0) return;
 
   // phase 4: attention work list.  The (sequence, KV head) streams of a ragged batch differ in length by
-  // orders of magnitude (contexts of 512 .. 32768 tokens in one step), so the token range of every sequence
-  // is cut into chunks of a common size; the attention kernel's persistent workgroups walk the (sequence,
-  // chunk) items.  T = tiles in total, S0 = max(B, s_min) = items that fill the GPU once:
-  //   * lengths within 25 % of their mean: chunk = ceil(1.25 T / S0) if S0 = B (one chunk per sequence: no
-  //     partial results), ceil(T / S0) if the batch is smaller than s_min (equal chunks, one round);
-  //   * ragged batch: chunk = ceil(T / s_min), one workgroup's fair share of the step: a longer sequence is cut
-  //     into fair shares, the shorter ones and the last chunks are whole items, and the list hands them out in
-  //     decreasing size (see the ordering below), so the queues run dry on the smallest items.  Measured on the
-  //     long-tail batch (128 sequences of 512 .. 32768 tokens, 7B heads): chunks of 1/4, 1/2, 3/4, 1, 1.5 and 2 fair
-  //     shares take 335, 310, 301, 297, 393 and 483 us per layer.
-  // sum_b chunks(b) <= B + T / chunk <= B + 4 S0 always (the work list's capacity).
-  __shared__ int s_red[256];
+  // orders of magnitude (contexts of 512 .. 32768 tokens in one step), and a small batch has fewer streams than the
+  // chip has CUs, so the token range of every sequence is cut into chunks of a common size; the attention kernel's
+  // persistent workgroups walk the (sequence, chunk) items, of which each is `pairs` workgroup tasks (KV heads x query
+  // blocks).  The size is the one that the model of AttnPlan says is fastest among 128 candidates (one per pair of
+  // threads): the longest sequence in 1 .. 64 equal parts, and 1/4 .. 9/4 of the fair share of one CU.
+  // sum_b chunks(b) <= B + 4 S, S = max(B, s_min), always (the work list's capacity).
+  __shared__ float s_cost[128];
+  __shared__ int s_cand[128];
   __shared__ int s_cht;
-  auto tiles_of = [&](int b) { return s_k[b] < 0 ? 0 : (s_c[b] + s_k[b] + 1 + kTile - 1) / kTile; };
+  int T, nv, mx = 0;
   {
-    int t = 0, mx = 0, nv = 0;
-    for (int b = b_lo; b < b_hi; ++b) { const int n = tiles_of(b); t += n; mx = max(mx, n); nv += n > 0; }
-    s_pr[tid] = t; s_red[tid] = mx; s_pt[tid] = nv;
+    int t = 0, n_valid = 0;
+    for (int b = b_lo; b < b_hi; ++b) {
+      const int n = s_k[b] < 0 ? 0 : (s_c[b] + s_k[b] + 1 + kTile - 1) / kTile;
+      s_c[b] = n;                                        // from here on: tiles of the sequence
+      t += n; mx = max(mx, n); n_valid += n > 0;
+    }
+    block_exclusive_scan(t, s_part, T);
+    block_exclusive_scan(n_valid, s_part, nv);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o));
+    __syncthreads();
+    if ((tid & 63) == 0) s_part[tid >> 6] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kPlanThreads / 64; ++w) mx = max(mx, s_part[w]);
   }
-  __syncthreads();
-  if (tid == 0) {
-    long long T = 0; int mx = 0; long long s_valid = 0;
-    for (int i = 0; i < 256; ++i) { T += s_pr[i]; mx = max(mx, s_red[i]); s_valid += s_pt[i]; }
-    const int S = max(B, attn_s_min), cap = attn_item_capacity(B, attn_s_min);
-    long long cht = (S > B) ? (T + S - 1) / S : (5 * T + 4LL * S - 1) / (4LL * S);
-    if (4LL * mx * s_valid > 5 * T) cht = (T + attn_s_min - 1) / attn_s_min;   // ragged: longest > 1.25 x mean
-    if (attn_force_chunks > 0) cht = (mx + attn_force_chunks - 1) / attn_force_chunks;
-    const long long floor_cht = (T + (cap - B) - 1) / (cap - B);      // keeps sum_b ceil(n_b / cht) <= cap
-    if (cht < floor_cht) cht = floor_cht;
-    if (cht < 1) cht = 1;
-    s_cht = (int)min(cht, (long long)0x3fffffff);
+  const int cap = attn_item_capacity(B, attn.s_min);
+  // keeps sum_b ceil(n_b / cht) <= cap, and at most 512 chunks per sequence (32-bit offsets of the partial rows)
+  const int floor_cht = max(max((T + (cap - B) - 1) / (cap - B), (mx + 511) / 512), 1);
+  if (attn.force_chunks > 0) {
+    if (tid == 0) s_cht = max((mx + attn.force_chunks - 1) / attn.force_chunks, floor_cht);
+  } else {
+    const int cand = tid >> 3, sub = tid & 7;            // eight threads share a candidate's count of items
+    const float slots = (float)kAttnWorkgroups, fair = (float)T * attn.pairs / slots;
+    int cht = cand < 64 ? (mx + cand) / (cand + 1) : (int)(fair * (0.25f + (cand - 64) * 0.03125f)) + 1;
+    cht = max(min(cht, max(mx, 1)), floor_cht);
+    const float inv = 1.0f / (float)cht;
+    int items = 0;
+    for (int b = sub; b < B; b += 8) items += (int)((float)(s_c[b] + cht - 1) * inv + 1e-4f);   // chunks (a model: +-1 is fine)
+    items += __shfl_xor(items, 1);
+    items += __shfl_xor(items, 2);
+    items += __shfl_xor(items, 4);
+    if (sub == 0) {
+      const float tasks = (float)items * attn.pairs, len = cht * attn.t_scale;
+      float cost;
+      if (tasks <= slots) {                              // all tasks at once
+        cost = attn.c_item + len * fmaxf(attn.t_lat, attn.t_full * tasks / slots);
+      } else if (4LL * mx * nv <= 5LL * T) {             // equal tasks: whole rounds and a last one
+        const float full = floorf(tasks / slots), rem = tasks - full * slots;
+        cost = full * (attn.c_item + len * attn.t_full);
+        if (rem > 0.f) cost += attn.c_item + len * fmaxf(attn.t_lat, attn.t_full * rem / slots);
+      } else {                                           // ragged: handed out longest first
+        const float avg = (tasks * attn.c_item + (float)T * attn.pairs * attn.t_scale * attn.t_full) / slots;
+        cost = fmaxf(avg, attn.c_item + len * attn.t_full) + 0.5f * attn.c_item;
+      }
+      if (cht < mx) cost += attn.c_merge + attn.t_merge * (float)((mx + cht - 1) / cht);
+      s_cost[cand] = cost;
+      s_cand[cand] = cht;
+    }
+    __syncthreads();
+    if (tid < 64) {                                      // cheapest candidate; equal cost: the larger chunk
+      float c0 = s_cost[tid];
+      int h0 = s_cand[tid];
+      const float c1 = s_cost[tid + 64];
+      const int h1 = s_cand[tid + 64];
+      if (c1 < c0 || (c1 == c0 && h1 > h0)) { c0 = c1; h0 = h1; }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const float co = __shfl_xor(c0, o);
+        const int ho = __shfl_xor(h0, o);
+        if (co < c0 || (co == c0 && ho > h0)) { c0 = co; h0 = ho; }
+      }
+      if (tid == 0) s_cht = h0;
+    }
   }
   __syncthreads();
   const int cht = s_cht;
@@ -162,44 +233,42 @@ __global__ void __launch_bounds__(256) plan_kernel(Plan p, KvView kv, int B, int
   // handed out when the queues run dry is the smallest there is.  item_start[b] keeps numbering a sequence's
   // chunks contiguously (slot item_start[b] + chunk): the partial results are addressed by slot, not by position.
   __shared__ int s_hist[64], s_base[64];
-  auto chunks_of = [&](int b) { return (tiles_of(b) + cht - 1) / cht; };
+  auto chunks_of = [&](int b) { return (s_c[b] + cht - 1) / cht; };
   auto size_class = [&](int rem) { return 63 - min(63, (int)(((long long)rem * 64 - 1) / cht)); };   // rem in 1 .. cht
-  {
-    int n = 0, nf = 0;
-    for (int b = b_lo; b < b_hi; ++b) { const int nc = chunks_of(b); n += nc; nf += max(nc - 1, 0); }
-    s_pr[tid] = n; s_pt[tid] = nf;
-  }
   if (tid < 64) s_hist[tid] = 0;
-  __syncthreads();
+  int n = 0, pf = 0, n_all, n_full;
+  for (int b = b_lo; b < b_hi; ++b) { const int nc = chunks_of(b); n += nc; pf += max(nc - 1, 0); }
+  n = block_exclusive_scan(n, s_part, n_all);
+  pf = block_exclusive_scan(pf, s_part, n_full);
   if (tid == 0) {
-    int n = 0, nf = 0;
-    for (int i = 0; i < 256; ++i) { const int a = s_pr[i], f = s_pt[i]; s_pr[i] = n; s_pt[i] = nf; n += a; nf += f; }
-    p.item_start[B] = n;
+    p.item_start[B] = n_all;
     p.attn_meta[0] = cht;
-    p.attn_meta[1] = n;
-    s_red[0] = nf;                                       // full-size chunks that are not the last of their sequence
+    p.attn_meta[1] = n_all;
+  }
+  for (int b = b_lo; b < b_hi; ++b) {
+    p.item_start[b] = n;
+    const int nc = chunks_of(b);
+    for (int c = 0; c + 1 < nc; ++c, ++pf) { p.item_seq[pf] = b; p.item_chunk[pf] = c; }
+    if (nc > 0) atomicAdd(&s_hist[size_class(s_c[b] - (nc - 1) * cht)], 1);
+    n += nc;
   }
   __syncthreads();
-  {
-    int n = s_pr[tid], pf = s_pt[tid];
-    for (int b = b_lo; b < b_hi; ++b) {
-      p.item_start[b] = n;
-      const int nc = chunks_of(b);
-      for (int c = 0; c + 1 < nc; ++c, ++pf) { p.item_seq[pf] = b; p.item_chunk[pf] = c; }
-      if (nc > 0) atomicAdd(&s_hist[size_class(tiles_of(b) - (nc - 1) * cht)], 1);
-      n += nc;
+  if (tid < 64) {
+    const int v = s_hist[tid];
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o);
+      if (tid >= o) incl += t;
     }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int at = s_red[0];
-    for (int i = 0; i < 64; ++i) { s_base[i] = at; at += s_hist[i]; s_hist[i] = 0; }
+    s_base[tid] = n_full + incl - v;                     // after the full-size chunks
+    s_hist[tid] = 0;
   }
   __syncthreads();
   for (int b = b_lo; b < b_hi; ++b) {
     const int nc = chunks_of(b);
     if (nc == 0) continue;
-    const int cl = size_class(tiles_of(b) - (nc - 1) * cht);
+    const int cl = size_class(s_c[b] - (nc - 1) * cht);
     const int pos = s_base[cl] + atomicAdd(&s_hist[cl], 1);
     p.item_seq[pos] = b;
     p.item_chunk[pos] = nc - 1;
@@ -231,9 +300,9 @@ __global__ void kv_lengths_kernel(KvView kv, int B, const int32_t* __restrict__ 
 
 void launch_plan(const Plan& p, const KvView& kv, int B, int k_max, int vocab, const int32_t* seq_slot,
                  const int32_t* last_token, const int32_t* draft_tokens, const int32_t* draft_len,
-                 bool need_kv, int attn_s_min, int attn_force_chunks, int n_layers, hipStream_t st) {
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(256), 0, st, p, kv, B, k_max, vocab, seq_slot, last_token,
-                     draft_tokens, draft_len, need_kv ? 1 : 0, attn_s_min, attn_force_chunks, n_layers);
+                 bool need_kv, const AttnPlan& attn, int n_layers, hipStream_t st) {
+  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, p, kv, B, k_max, vocab, seq_slot, last_token,
+                     draft_tokens, draft_len, need_kv ? 1 : 0, attn, n_layers);
 }
 void launch_commit(const Plan& p, const KvView& kv, int B, const int32_t* seq_slot, const int32_t* n_commit,
                    hipStream_t st) {
