@@ -29,6 +29,8 @@ struct bs_ctx {
   void* attn_out;      // [M_max, Hq D]
   void* act;           // [M_max, F]
   void* hf;            // final-norm rows  [M_max, d]
+  SkinnyBufs sk;
+  float* ssq;          // [d / 32][kSkinnyRows] sums of squares of the residual's rows (steps of at most kSkinnyRows rows)
   void* attn_scratch;
   float* full_logits;  // float32 models only: [M_max, V]
   SamplerBufs sb;
@@ -68,6 +70,8 @@ struct Carver {
   }
 };
 
+// one counter per unit of a skinny launch that is split across workgroups (only launches of fewer units than CUs are)
+constexpr size_t kSkinnyCounters = 256;
 size_t elt(int dtype) { return dtype == BS_F32 ? 4 : 2; }
 
 bs_status check_desc(const bs_model_desc* d, int B_max, int k_max) {
@@ -145,18 +149,22 @@ size_t carve(bs_ctx* c, char* base) {
   const Shape& s = c->s;
   const int B = c->B_max, M = c->M_max;
   carve_plan(w, c->plan, B, M, true, s.L);
-  c->h = w.take<float>((size_t)M * s.d);
+  const size_t Mp = (M + 31) / 32 * 32;       // fragment-ordered activations are stored in whole 32-row tiles
+  c->h = w.take<float>(Mp * s.d);
+  c->ssq = w.take<float>((size_t)(s.d / 32) * kSkinnyRows);
   c->inv_freq = w.take<double>(64);
   c->rope_cos = w.take<float>((size_t)M * 64);
   c->rope_sin = w.take<float>((size_t)M * 64);
-  c->a = w.take<char>((size_t)M * s.d * elt(s.dtype));          // float16 and bf16 have the same size
+  c->a = w.take<char>(Mp * s.d * elt(s.dtype));          // float16 and bf16 have the same size
   c->qkv = w.take<float>((size_t)M * s.Nqkv());
   c->q = w.take<char>((size_t)M * s.Hq * s.D * elt(s.dtype));
   c->slabs = (s.dtype == BS_BF16)
-                 ? w.take<float>((size_t)kMaxGemmSplit * M * (s.Nqkv() > s.d ? s.Nqkv() : s.d))
+                 ? w.take<float>((size_t)kMaxGemmSplit * Mp * (s.Nqkv() > s.d ? s.Nqkv() : s.d))
                  : nullptr;
-  c->attn_out = w.take<char>((size_t)M * s.Hq * s.D * elt(s.dtype));
-  c->act = w.take<char>((size_t)M * s.F * elt(s.dtype));
+  c->sk.part = c->slabs;                      // as large as the partial tiles of up to kMaxGemmSplit K splits
+  c->sk.counters = w.take<int32_t>(kSkinnyCounters);
+  c->attn_out = w.take<char>(Mp * s.Hq * s.D * elt(s.dtype));
+  c->act = w.take<char>(Mp * s.F * elt(s.dtype));
   c->hf = w.take<char>((size_t)M * s.d * elt(s.dtype));
   c->attn_scratch = w.take<char>(attention_scratch_bytes(s, B, c->k_max));
   c->n_vtiles = lmhead_vtiles(s.V);
@@ -299,6 +307,7 @@ bs_status bs_create(const bs_model_desc* desc, const bs_weights* w, const bs_kv_
   c->kv = KvView{kv->n_pages, kv->n_slots, kv->max_pages_per_seq, kv->block_table, kv->ctx_len};
   launch_rope_table(c->s, c->inv_freq, (hipStream_t)stream);
   launch_attention_init(c->s, c->B_max, c->attn_scratch, (hipStream_t)stream);
+  launch_zero_i32(c->sk.counters, (int)kSkinnyCounters, (hipStream_t)stream);
   st = check_hip(c);
   if (st != BS_OK) { bs_destroy(c); return st; }
   *out = c;
@@ -395,11 +404,27 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   const Plan& p = c->plan;
   launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attention_plan_params(s, B, k_max),
               s.L, st);
-  launch_embed(s, p, M_max, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  const bool skinny = skinny_applies(s, M_max) && !c->unfused_qkv;
+  if (skinny) launch_skinny_embed(s, p, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  else launch_embed(s, p, M_max, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
   SlabRule pending{0, 0, 0, 0, 0};              // slabs of the last residual projection not yet added to h
   for (int l = 0; l < s.L; ++l) {
     { ProfScope ps(c, BS_PROF_EMPTY, st); }
+    if (skinny) {
+      { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
+        launch_skinny_qkv(s, p, c->kv, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
+                          c->q, c->k_pages[l], c->v_pages[l], c->sk, st); }
+      launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, true,
+                       c->attn_scratch, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
+      { ProfScope ps(c, BS_PROF_GEMM_O, st);
+        launch_skinny_resid(s, p, s.Hq * s.D, c->attn_out, c->wo[l], c->h, c->ssq, c->sk, st); }
+      { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
+        launch_skinny_gate_up(s, p, c->h, c->ssq, s.d / 32, c->mlp_norm[l], c->a, c->w_gate_up[l], c->act, st); }
+      { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
+        launch_skinny_resid(s, p, s.F, c->act, c->w_down[l], c->h, c->ssq, c->sk, st); }
+      continue;
+    }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->attn_norm[l], c->a, st);
     if (qkv_rope_supported(s) && !c->unfused_qkv) {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
@@ -412,7 +437,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq > 0 ? nq : 1, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
-    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, c->attn_scratch,
+    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, false, c->attn_scratch,
                      c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
     { ProfScope ps(c, BS_PROF_GEMM_O, st);
       pending = launch_gemm_resid(s.dtype, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],
@@ -424,7 +449,8 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       pending = launch_gemm_resid(s.dtype, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
                                   slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st); }
   }
-  launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->final_norm, c->hf, st);
+  if (skinny) launch_skinny_final_norm(s, p, M_max, c->h, c->ssq, c->final_norm, c->hf, st);
+  else launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->final_norm, c->hf, st);
   if (logits_debug && s.dtype == BS_F32)
     launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, nullptr, c->lm_head, logits_debug, p.status, st);
   if (logits_debug && s.dtype == BS_BF16) {

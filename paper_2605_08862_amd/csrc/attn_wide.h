@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
                                                         const f16* __restrict__ v_pages, f16* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         int32_t* __restrict__ counters, int32_t* __restrict__ queue,
-                                                        int32_t* __restrict__ status) {
+                                                        int out_frag, int32_t* __restrict__ status) {
   constexpr int KS = D / 16;            // MFMA K-steps of the QK^T product = K fragments of a tile
   constexpr int DT = D / 32;            // 32-wide d tiles of the output; V fragments of a tile = 2 DT
   constexpr int NF = KS + 2 * DT;       // 1 KiB fragments of one K/V tile
@@ -53,6 +53,9 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
   const int ln = lane & 31, lg = lane >> 5;
   const size_t page_elems = kv_page_elems(Hkv, D);
 
+  auto out_index = [&](int row, int col) -> size_t {
+    return out_frag ? act_frag_index(row, col, Hq * D / 64) : (size_t)row * Hq * D + col;
+  };
   // Combines the n_ch chunks of one (sequence, KV head): called by the last workgroup to publish its partial rows.
   // Four threads per query row; two chunks' loads are in flight together, the sums run in chunk order.
   auto merge_unit = [&](const int b, const int h, const int n_ch) {
@@ -98,10 +101,10 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     }
     const int iq = qr / G, hg = qr % G;
     const float inv = 1.0f / lt;
-    f16* dst = out + (size_t)(row_start[b] + iq) * Hq * D + (size_t)(h * G + hg) * D;
+    const int orow = row_start[b] + iq, ocol = (h * G + hg) * D;
 #pragma unroll
     for (int j = 0; j < CPT; ++j)
-      *(f16x4*)(dst + (sub + j * TPR) * 4) =
+      *(f16x4*)(out + out_index(orow, ocol + (sub + j * TPR) * 4)) =
           to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
   };
 
@@ -279,7 +282,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
         }
         const int iq = wr / G, hg = wr % G;
         const float inv = 1.0f / lt;                     // a single-chunk row always sees position c + i: lt > 0
-        f16* dst = out + (size_t)(row0 + iq) * Hq * D + (size_t)(h * G + hg) * D;
+        const int orow = row0 + iq, ocol = (h * G + hg) * D;
         const uint32_t pr = (uint32_t)(chunk * Hkv) * RPT + wr;   // row of this chunk, counted from chunk 0 of (sequence, head)
 #pragma unroll
         for (int j = 0; j < CH / TPR; ++j) {
@@ -291,7 +294,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[e] += v[e] * mw[w];
           }
-          if (n_ch == 1) *(f16x4*)(dst + ch * 4) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
+          if (n_ch == 1) *(f16x4*)(out + out_index(orow, ocol + ch * 4)) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
           else wt_store4(bo, (pr * D + ch * 4) * 4, acc);
         }
         if (n_ch > 1 && sub == 0) wt_store2(bm, pr * 8, mt, lt);

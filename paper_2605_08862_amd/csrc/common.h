@@ -183,6 +183,22 @@ struct AttnPlan {
   float c_merge, t_merge;   // merge of a sequence's chunks: fixed, per chunk
 };
 
+// cos / sin of the rotary angle of packed row r (absolute position c_b + i) and pair j.  The angle is formed in
+// float64 (at positions of 3e4 a float32 angle is already off by ~2e-3 rad), reduced to [-pi, pi] in float64 and
+// only then handed to the float32 sine / cosine.
+__device__ __forceinline__ void rope_angle(const Plan& p, int r, int j, int half, const double* __restrict__ inv_freq,
+                                           float* __restrict__ cos_t, float* __restrict__ sin_t) {
+  const int pos = p.seq_c[p.row_seq[r]] + p.row_pos[r];
+  const double ang = (double)pos * inv_freq[j];
+  const double two_pi_hi = 6.283185307179586, two_pi_lo = 2.4492935982947064e-16;
+  const double n = rint(ang * 0.15915494309189535);
+  const double red = fma(-n, two_pi_lo, fma(-n, two_pi_hi, ang));
+  float sn, cs;
+  sincosf((float)red, &sn, &cs);
+  cos_t[(size_t)r * half + j] = cs;
+  sin_t[(size_t)r * half + j] = sn;
+}
+
 struct KvView {
   int n_pages, n_slots, max_pages;
   const int32_t* block_table;
@@ -274,13 +290,41 @@ int launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_ma
                 int32_t* status, hipStream_t st);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weight(const void* w_bf16, int N, int K, void* packed_f16, int32_t* status, hipStream_t st);
+// skinny.hip   decoder layer of steps with at most kSkinnyRows packed rows (bf16 models with head size 128); activations and the
+// residual in fragment order.
+constexpr int kSkinnyRows = 32;
+// Offset of element (row, k) of a float16 activation matrix with nk K tiles of 64, in MFMA fragment order (the layout of the
+// packed weights: 4 KiB blocks [K-step][lane][8] per (32 rows, K tile)); elements k .. k + 7, k % 8 == 0, are contiguous.
+__host__ __device__ __forceinline__ size_t act_frag_index(int row, int k, int nk) {
+  return ((size_t)((row >> 5) * nk + (k >> 6)) * 4 + ((k >> 3) & 3)) * 512 + (((k >> 5) & 1) * 32 + (row & 31)) * 8 + (k & 7);
+}
+// The same for the float32 residual: a fragment is two contiguous KiB, k .. k + 3 (k % 4 == 0) contiguous.
+__host__ __device__ __forceinline__ size_t h_frag_index(int row, int k, int nk) {
+  return ((size_t)((row >> 5) * nk + (k >> 6)) * 8 + ((k >> 3) & 3) * 2 + ((k >> 2) & 1)) * 256 + (((k >> 5) & 1) * 32 + (row & 31)) * 4 + (k & 3);
+}
+struct SkinnyBufs { float* part; int32_t* counters; };   // partial tiles of K splits; arrival counters (zero between launches)
+bool skinny_applies(const Shape& s, int M_max);
+// ssq: [parts][32] sums of squares of the residual's rows over column ranges (embed: 1 part, residual projections: d / 32)
+void launch_skinny_embed(const Shape& s, const Plan& p, const void* embed, float* h, float* ssq, const double* inv_freq,
+                         float* cos_t, float* sin_t, hipStream_t st);
+void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, const float* gain,
+                              void* out, hipStream_t st);
+void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, const float* h, const float* ssq, int ssq_parts,
+                       const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages,
+                       void* v_pages, const SkinnyBufs& sk, hipStream_t st);
+void launch_skinny_gate_up(const Shape& s, const Plan& p, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
+                           const void* W, void* act, hipStream_t st);      // a: scratch for the normalised rows
+void launch_skinny_resid(const Shape& s, const Plan& p, int K, const void* X, const void* W, float* h, float* ssq,
+                         const SkinnyBufs& sk, hipStream_t st);
 // attention.hip
+// out_frag: the output rows in fragment order (act_frag_index) instead of row-major (bf16 models).
 // attention_plan_params gives the work-list parameters launch_plan needs for the same (B, k_max);
 // launch_attention_init clears the completion counters once, at context creation.
 AttnPlan attention_plan_params(const Shape& s, int B, int k_max);
 void launch_attention_init(const Shape& s, int B_max, void* scratch, hipStream_t st);
+void launch_zero_i32(int32_t* p, int n, hipStream_t st);
 void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int k_max, int M_max,
-                      const void* q, const void* k_pages, const void* v_pages, void* out, void* scratch,
+                      const void* q, const void* k_pages, const void* v_pages, void* out, bool out_frag, void* scratch,
                       void* prof_token, hipStream_t st);
 void attention_prof_mark(void* token, hipStream_t st, bool begin);   // api.hip: event pair around the main kernel
 size_t attention_scratch_bytes(const Shape& s, int B_max, int k_max);

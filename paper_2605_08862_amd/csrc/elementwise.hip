@@ -5,22 +5,6 @@
 #include "common.h"
 #include <type_traits>
 
-// cos / sin of the rotary angle of packed row r (absolute position c_b + i) and pair j.  The angle is formed in
-// float64 (at positions of 3e4 a float32 angle is already off by ~2e-3 rad), reduced to [-pi, pi] in float64 and
-// only then handed to the float32 sine / cosine.
-__device__ __forceinline__ void rope_angle(const Plan& p, int r, int j, int half, const double* __restrict__ inv_freq,
-                                           float* __restrict__ cos_t, float* __restrict__ sin_t) {
-  const int pos = p.seq_c[p.row_seq[r]] + p.row_pos[r];
-  const double ang = (double)pos * inv_freq[j];
-  const double two_pi_hi = 6.283185307179586, two_pi_lo = 2.4492935982947064e-16;
-  const double n = rint(ang * 0.15915494309189535);
-  const double red = fma(-n, two_pi_lo, fma(-n, two_pi_hi, ang));
-  float sn, cs;
-  sincosf((float)red, &sn, &cs);
-  cos_t[(size_t)r * half + j] = cs;
-  sin_t[(size_t)r * half + j] = sn;
-}
-
 // Token embedding of every packed row and, in the same launch, the row's rotary cos / sin table entries (the table
 // [M_max][D/2] is shared by all layers of the step).
 template <typename T>
