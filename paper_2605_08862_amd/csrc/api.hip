@@ -32,7 +32,8 @@ struct bs_ctx {
   SkinnyBufs sk;
   float* ssq;          // [d / 32][kSkinnyRows] sums of squares of the residual's rows (steps of at most kSkinnyRows rows)
   void* attn_scratch;
-  float* full_logits;  // float32 models only: [M_max, V]
+  float* full_logits;  // float32 models: [M_max, V]; bf16 models: [logit_rows, V]
+  int logit_rows = 0;  // bf16 models: calls of at most this many rows keep every row's logits (see lmhead_logit_rows)
   SamplerBufs sb;
   int n_vtiles;
   // pool
@@ -174,8 +175,10 @@ size_t carve(bs_ctx* c, char* base) {
     c->full_logits = w.take<float>((size_t)M * s.V);
     sb.sel_logits = nullptr;
   } else {
-    c->full_logits = nullptr;
-    sb.sel_logits = w.take<float>((size_t)B * s.V);
+    c->logit_rows = lmhead_logit_rows(s);
+    if (c->logit_rows > M) c->logit_rows = M;
+    c->full_logits = w.take<float>((size_t)c->logit_rows * s.V);
+    sb.sel_logits = c->logit_rows < M ? w.take<float>((size_t)B * s.V) : nullptr;
     c->pk_qkv.assign(s.L, nullptr); c->pk_o.assign(s.L, nullptr); c->pk_gu.assign(s.L, nullptr); c->pk_down.assign(s.L, nullptr);
     for (int l = 0; l < s.L; ++l) {
       c->pk_qkv[l] = w.take<uint16_t>(packed_weight_elems(s.Nqkv(), s.d));
@@ -492,11 +495,13 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
     n_vtiles = (V + 1023) / 1024;
     sample_base = c->full_logits;
   } else {
+    // with every row's logits in memory the sampled rows need no second LM-head pass
+    float* all_rows = filter.on ? c->filter_logits : M_max <= c->logit_rows && temperature > 0.f ? c->full_logits : nullptr;
     { ProfScope ps(c, BS_PROF_LMHEAD, st);
-      launch_lmhead_stats(s, p, M_max, c->hf, c->lm_head, inv_temp, c->sb, filter.on ? c->filter_logits : nullptr, st); }
+      launch_lmhead_stats(s, p, M_max, c->hf, c->lm_head, inv_temp, c->sb, all_rows, st); }
     n_vtiles = (V + 63) / 64;
-    if (filter.on) {
-      sample_base = c->filter_logits;                  // every row is in memory: no second LM-head pass
+    if (all_rows) {
+      sample_base = all_rows;
     } else {
       sample_base = c->sb.sel_logits;
       rows_selected = true;

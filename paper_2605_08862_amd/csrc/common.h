@@ -354,6 +354,7 @@ __device__ __forceinline__ bool filter_keeps(uint32_t key, int j, uint32_t f_key
 }
 struct FilterArgs { int on; int top_k; float top_p; const float* logits; int V; };
 int lmhead_vtiles(int V);
+int lmhead_logit_rows(const Shape& s);
 void launch_lmhead_stats(const Shape& s, const Plan& p, int M_max, const void* hf, const void* lm_head,
                          float inv_temp, const SamplerBufs& sb, float* logits_debug, hipStream_t st);
 void launch_logit_stats(const Plan& p, int M_max, int V, const float* logits, float inv_temp,

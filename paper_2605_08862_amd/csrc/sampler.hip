@@ -20,6 +20,13 @@ int lmhead_vtiles(int V) {
   return a > b ? a : b;
 }
 
+// Row limit up to which phase 1 stores all logits (float32, 4 V bytes per row) instead of recomputing the sampled row of
+// every sequence, which reads the 2 d V bytes of weights again.  Measured, phase 1 with stores against the second pass it
+// saves: 7B shape, 64 rows + 10 us / 210, 288 rows + 38 / 203, 576 rows + 87 / 205, 1152 rows no gain; 1.5B shape, 9 rows
+// + 4 / 85, 288 rows + 38 / 95, 432 rows no gain, 576 rows + 97 / 100.  (Storing whole lines by way of LDS changed nothing:
+// the writes compete with the weight stream, not with the issue slots.)
+int lmhead_logit_rows(const Shape& s) { return s.dtype == BS_BF16 ? s.d / 4 : 0; }
+
 // ------------------------------------------------------------------ phase 1 / phase 2 GEMM (bf16)
 // STATS = true : rows are the packed query rows; epilogue writes statistics (+ optional debug logits).
 // STATS = false: rows are gathered through sel_row (one per sequence); epilogue stores float32 logits
