@@ -1,5 +1,7 @@
-// Plain (non-MFMA) verify attention, any dtype / page layout: one workgroup per (packed row,
-// query head).  Used by float32 models (the tiny parity configuration).  Sec. 3.3: every query
+// Plain (non-MFMA) verify attention on row-major pages: one workgroup per (packed row, query
+// head), 256 tokens per pass.  Latency bound (few, small workgroups): pages of a pass come from LDS and a thread
+// requests sixteen tokens' elements before it uses the first (20 rows x 4 heads, about 200 tokens: 16.5 us with a
+// page lookup per load and one load at a time, 9.9 us).  Used by float32 models (the tiny parity configuration).  Sec. 3.3: every query
 // length 1..k_max+1 is served by this one launch; row i of sequence b attends to cache
 // positions 0 .. c_b + i (committed context plus the tentative rows up to itself).
 #pragma once
@@ -9,7 +11,11 @@ template <typename T, typename TO>
 __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int Hq, int Hkv, int D, float scale,
                                                           const TO* __restrict__ q, const T* __restrict__ k_pages,
                                                           const T* __restrict__ v_pages, TO* __restrict__ out) {
-  __shared__ float s_q[128], s_p[256], s_red[4], s_acc[2][128];
+  static_assert(std::is_same<T, float>::value, "the dot product below loads four row-major floats at a time");
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) float s_q[128];
+  __shared__ float s_p[256], s_red[4], s_acc[256];
+  __shared__ int s_pg[256 / kPage];                     // pages of the 256 tokens of a chunk
   const int r = blockIdx.x, hq = blockIdx.y;
   if (r >= p.n_rows[0]) return;
   const int b = p.row_seq[r];
@@ -21,16 +27,22 @@ __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int
   if (tid < D) s_q[tid] = to_f32<TO>(q[(size_t)r * Hq * D + (size_t)hq * D + tid]);
   float m_run = -INFINITY, l_run = 0.f, acc = 0.f;      // acc: thread (tid%D, tid/D) partial of out[d]
   const int dd = tid % D, part = tid / D, nparts = 256 / D;
-  __syncthreads();
   for (int t0 = 0; t0 < n_tok; t0 += 256) {
+    if (tid < 256 / kPage) s_pg[tid] = min(max(bt[min(t0 + tid * kPage, n_tok - 1) / kPage], 0), kv.n_pages - 1);
+    __syncthreads();
     const int t = t0 + tid;
     float s = -INFINITY;
     if (t < n_tok) {
-      int page = min(max(bt[t / kPage], 0), kv.n_pages - 1);
-      const T* kp = k_pages + (size_t)page * page_elems;
-      float dot = 0.f;
-      for (int d = 0; d < D; ++d) dot += s_q[d] * to_f32<T>(kp[k_index<T>(D, kvh, t % kPage, d)]);
-      s = dot * scale;
+      const int page = s_pg[tid / kPage];
+      const T* kp = k_pages + (size_t)page * page_elems + k_index<T>(D, kvh, t % kPage, 0);   // row-major: D contiguous elements
+      float dot[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+      for (int d = 0; d < D; d += 4) {
+        const f4 kv4 = *(const f4*)(kp + d), q4 = *(const f4*)(s_q + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot[e] += q4[e] * kv4[e];
+      }
+      s = ((dot[0] + dot[1]) + (dot[2] + dot[3])) * scale;
     }
     float mx = s;
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
@@ -50,19 +62,24 @@ __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int
     m_run = m_new;
     acc *= alpha;
     const int cnt = min(256, n_tok - t0);
-    for (int j = part; j < cnt; j += nparts) {
-      int tt = t0 + j;
-      int page = min(max(bt[tt / kPage], 0), kv.n_pages - 1);
-      acc += s_p[j] * to_f32<T>(v_pages[(size_t)page * page_elems + v_index<T>(D, kvh, tt % kPage, dd)]);
+    for (int j0 = part; j0 < cnt; j0 += 16 * nparts) {   // sixteen tokens' V elements in flight (a token past the end has weight 0)
+      float v[16], w[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int j = min(j0 + u * nparts, cnt - 1);
+        v[u] = to_f32<T>(v_pages[(size_t)s_pg[j / kPage] * page_elems + v_index<T>(D, kvh, j % kPage, dd)]);
+        w[u] = j0 + u * nparts < cnt ? s_p[j] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc += w[u] * v[u];
     }
     __syncthreads();
   }
-  // combine the nparts partial sums per d
-  if (part < 2) s_acc[part][dd] = 0.f;
+  s_acc[tid] = acc;                                      // nparts partial sums per d
   __syncthreads();
-  for (int pp = 0; pp < nparts; ++pp) {
-    if (part == pp) s_acc[0][dd] += acc;
-    __syncthreads();
+  if (tid < D) {
+    float o = s_acc[tid];
+    for (int pp = 1; pp < nparts; ++pp) o += s_acc[pp * D + tid];
+    out[(size_t)r * Hq * D + (size_t)hq * D + tid] = from_f32<TO>(o / l_run);
   }
-  if (tid < D) out[(size_t)r * Hq * D + (size_t)hq * D + tid] = from_f32<TO>(s_acc[0][tid] / l_run);
 }

@@ -1,0 +1,58 @@
+"""Tile edges of the float32 path (32-row / 32-column matrix tiles, K split over eight waves) against the oracle, and segment
+edges of the plain-logits sampler (16 segments per row, four tokens per load, row starts of every alignment)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as OD
+from paper_2605_08862_amd import workloads as W
+from paper_2605_08862_amd.runtime import Engine, fuse_weights
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("n_seq,vocab", [(1, 17), (31, 4096), (8, 1003), (11, 33)])     # 1, 31, 32 and 33 rows
+def test_float32_step_at_tile_edges(n_seq, vocab):
+    k = {8: 3, 11: 2}.get(n_seq, 0)
+    desc = W.shape("tiny", vocab=vocab)
+    w = W.make_weights(desc, seed=5)
+    eng = Engine(desc, fuse_weights(w, desc["dtype"], DEV), 31, 64, B_max=31, k_max=3)
+    wn, od = W.weights_to_numpy(w), H.oracle_desc(desc)
+    rng = np.random.default_rng(n_seq)
+    blk = rng.integers(0, vocab, (n_seq, k + 1))
+    dl = H.dev_i32(np.full(n_seq, k))
+    drafts = H.dev_i32(blk[:, 1:]) if k else None
+    logits = eng.verify_step(H.dev_i32(np.arange(n_seq)), H.dev_i32(blk[:, 0]), drafts, dl, k, want_logits=True)
+    got = logits[:n_seq * (k + 1)].cpu().numpy().reshape(n_seq, k + 1, vocab)
+    for b in range(n_seq):
+        ref = OD.verify_block(od, wn, OD.SeqCache(od), blk[b])
+        assert np.abs(got[b] - ref).max() <= H.TOL_LOGITS[W.BS_F32]
+    assert eng.poll_status() == 0
+    eng.close()
+
+
+@pytest.mark.parametrize("q_mode", ["bf16", "f32", None])
+@pytest.mark.parametrize("vocab", [2, 3, 5, 63, 64, 67, 130, 8191, 16385])
+def test_plain_logits_sampler_at_segment_edges(vocab, q_mode):
+    desc = W.shape("tiny", n_layers=1, vocab=vocab)
+    eng = Engine(desc, fuse_weights(W.make_weights(desc, seed=3), W.BS_F32, DEV), 1, 64, B_max=16, k_max=2)
+    rng = np.random.default_rng(vocab)
+    Bn, k = 16, 2
+    k_b = rng.integers(0, k + 1, Bn)
+    M, Td = int(k_b.sum() + Bn), int(k_b.sum())
+    logits = rng.normal(0, 2.0, (M, vocab)).astype(np.float32)
+    logits[:, vocab // 2] = logits[:, vocab - 1] = logits.max() + 1.0                   # equal maxima in two segments
+    drafts = rng.integers(0, vocab, (Bn, k)).astype(np.int32)
+    q = qn = None
+    if q_mode:
+        q = torch.tensor(rng.normal(0, 2.0, (Td, vocab)), dtype=torch.bfloat16 if q_mode == "bf16" else torch.float32)
+        qn = q.float().numpy()
+    ua, us = W.uniforms(vocab, Bn, k)
+    for T in (0.9, 0.0):
+        out = eng.accept_resample(H.dev_i32(drafts), H.dev_i32(k_b), k, H.dev_f32(ua), H.dev_f32(us),
+                                  q_logits=None if q is None else q.to(DEV), logits=H.dev_f32(logits), temperature=T)
+        exact, near, _ = H.compare_sampler(out, logits, drafts, k_b, ua, us, qn, T)
+        assert exact + near == Bn and near <= 2
+    eng.close()
