@@ -337,7 +337,7 @@ struct SamplerBufs {
   float* q_max; float* q_lse; float* q_target;           // [M_max] per query row that judges a draft
   int32_t* sel_row; int32_t* sel_mode; int32_t* sel_qrow; int32_t* sel_tok; // [B_max]
   float* sel_pmax; float* sel_qmax;                      // [B_max] raw maxima of the sampled row / its q row
-  double* samp_sum; double* samp_mass;                   // [B_max, 32 chunks, 2] sampling partials
+  double* samp_sum; double* samp_mass;                   // [B_max, 32 chunks, 2], [B_max, 32] sampling partials
   float* sel_logits;                                     // [B_max, V]
   uint32_t* f_key; int32_t* f_idx; float* f_lse;         // [M_max] top-k / top-p threshold of each row (filter.hip)
 };
@@ -353,6 +353,7 @@ __device__ __forceinline__ bool filter_keeps(uint32_t key, int j, uint32_t f_key
   return key > f_key || (key == f_key && j <= f_idx);
 }
 struct FilterArgs { int on; int top_k; float top_p; const float* logits; int V; };
+constexpr int kRowSegs = 16;           // statistics entries per row of the plain-logits path: vocabulary segments
 int lmhead_vtiles(int V);
 int lmhead_logit_rows(const Shape& s);
 void launch_lmhead_stats(const Shape& s, const Plan& p, int M_max, const void* hf, const void* lm_head,

@@ -13,11 +13,10 @@ enum { MODE_NONE = 0, MODE_PLAIN = 1, MODE_RESID_ONEHOT = 2, MODE_RESID_DENSE = 
 constexpr int kLmNT = 2;                            // LM-head wave tile: 32*MT rows x 64 vocab entries
 constexpr int kLmVtile = kLmNT * 32;                // vocab entries per statistics tile (bf16 path)
 constexpr int kSampleChunks = 32;                   // vocabulary chunks per sequence in the sampling kernels
-constexpr int kRowVtile = 1024;                     // vocab entries per statistics tile (logits path)
 
 int lmhead_vtiles(int V) {
-  int a = (V + kLmVtile - 1) / kLmVtile, b = (V + kRowVtile - 1) / kRowVtile;
-  return a > b ? a : b;
+  const int a = (V + kLmVtile - 1) / kLmVtile;
+  return a > kRowSegs ? a : kRowSegs;
 }
 
 // Row limit up to which phase 1 stores all logits (float32, 4 V bytes per row) instead of recomputing the sampled row of
@@ -166,46 +165,81 @@ __global__ void __launch_bounds__(256, (kLmMT <= 3 ? 2 : 1)) lmhead_kernel(const
 }
 
 // ------------------------------------------------------------------ statistics of given float32 logits
+// One workgroup per (row, vocabulary segment), one entry of (max, sum exp, arg max) each; HBM bound: the row is read once,
+// sixteen bytes per load, four loads in flight per thread, maximum and rescaled sum kept online (batch 128 x 9 rows of 151936
+// logits, 700 MB: 232 us with one workgroup per 1024 entries and four-byte loads, 114 us).
 __global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int V, const float* __restrict__ logits,
                                                           float inv_temp, SamplerBufs sb) {
   __shared__ float s_mx[4], s_sum[4];
   __shared__ int s_arg[4];
-  const int m = blockIdx.y, vt = blockIdx.x;
+  const int m = blockIdx.y, seg = blockIdx.x, tid = threadIdx.x;
   if (m >= p.n_rows[0]) return;
   const int tgt = p.row_target[m];
   const float* z = logits + (size_t)m * V;
-  const int base = vt * kRowVtile;
-  float v[4];
-  float mx = -INFINITY;
+  const int len = ((V + kRowSegs - 1) / kRowSegs + 3) & ~3;
+  const int j0 = min(seg * len, V), j1 = min(j0 + len, V);
+  float mx = -INFINITY, sum[4] = {0.f, 0.f, 0.f, 0.f};
   int arg = 0x7fffffff;
+  auto absorb = [&](const float* x, int n, int cnt) {    // cnt values of indices n ..
+    float vm = x[0];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    int n = base + j * 256 + threadIdx.x;
-    v[j] = (n < V) ? z[n] : -INFINITY;
-    if (n < V && n == tgt) sb.z_target[m] = v[j];
-    if (v[j] > mx) { mx = v[j]; arg = n; }
+    for (int e = 1; e < 4; ++e) vm = e < cnt ? fmaxf(vm, x[e]) : vm;
+    if (vm > mx) {
+      const float f = __expf((mx - vm) * inv_temp);      // 0 on the first values
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[e] *= f;
+      mx = vm;
+#pragma unroll
+      for (int e = 3; e >= 0; --e) if (e < cnt && x[e] == vm) arg = n + e;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) if (e < cnt) sum[e] += x[e] == -INFINITY ? 0.f : __expf((x[e] - mx) * inv_temp);
+  };
+  const int v0 = min(j0 + (int)((16 - ((uintptr_t)(z + j0) & 15)) & 15) / 4, j1);   // first token of an aligned group of four
+  const int n4 = (j1 - v0) / 4;
+  int i = tid;
+  for (; i + 3 * 256 < n4; i += 4 * 256) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const f32x4*)(z + v0 + 4 * (i + u * 256));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { const float x[4] = {v[u][0], v[u][1], v[u][2], v[u][3]}; absorb(x, v0 + 4 * (i + u * 256), 4); }
   }
+  for (; i < n4; i += 256) {
+    const f32x4 v = *(const f32x4*)(z + v0 + 4 * i);
+    const float x[4] = {v[0], v[1], v[2], v[3]};
+    absorb(x, v0 + 4 * i, 4);
+  }
+  // up to three tokens before and after the groups; the first threads take them last, so compare indices of equal maxima
+  for (int e = tid; e < 6; e += 256) {
+    const int n = e < 3 ? j0 + e : v0 + 4 * n4 + e - 3;
+    if (e < 3 ? n >= v0 : n >= j1) continue;
+    const float x[4] = {z[n], 0.f, 0.f, 0.f};
+    if (x[0] == mx && mx > -INFINITY && n < arg) arg = n;
+    absorb(x, n, 1);
+  }
+  if (tid == 0 && tgt >= j0 && tgt < j1) sb.z_target[m] = z[tgt];
+  float s = (sum[0] + sum[1]) + (sum[2] + sum[3]);
   for (int o = 32; o > 0; o >>= 1) {
-    float mo = __shfl_xor(mx, o);
-    int ao = __shfl_xor(arg, o);
-    if (mo > mx || (mo == mx && ao < arg)) { mx = mo; arg = ao; }
+    const float mo = __shfl_xor(mx, o), so = __shfl_xor(s, o);
+    const int ao = __shfl_xor(arg, o);
+    if (mo > mx) { s = s * __expf((mx - mo) * inv_temp) + so; mx = mo; arg = ao; }
+    else if (mo > -INFINITY) { s += so * __expf((mo - mx) * inv_temp); if (mo == mx && ao < arg) arg = ao; }
   }
-  if ((threadIdx.x & 63) == 0) { s_mx[threadIdx.x >> 6] = mx; s_arg[threadIdx.x >> 6] = arg; }
+  if ((tid & 63) == 0) { s_mx[tid >> 6] = mx; s_sum[tid >> 6] = s; s_arg[tid >> 6] = arg; }
   __syncthreads();
-  mx = s_mx[0]; arg = s_arg[0];
-  for (int w = 1; w < 4; ++w)
-    if (s_mx[w] > mx || (s_mx[w] == mx && s_arg[w] < arg)) { mx = s_mx[w]; arg = s_arg[w]; }
-  float sum = 0.f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) sum += (v[j] == -INFINITY) ? 0.f : __expf((v[j] - mx) * inv_temp);
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const size_t o = (size_t)vt * M_max + m;
-    sb.part_max[o] = mx;
-    sb.part_sum[o] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-    sb.part_arg[o] = arg;
+  if (tid == 0) {
+    float mt = s_mx[0], st = s_sum[0];
+    int at = s_arg[0];
+    for (int w = 1; w < 4; ++w) {
+      const float mo = s_mx[w];
+      if (mo > mt) { st = st * __expf((mt - mo) * inv_temp) + s_sum[w]; mt = mo; at = s_arg[w]; }
+      else if (mo > -INFINITY) { st += s_sum[w] * __expf((mo - mt) * inv_temp); if (mo == mt && s_arg[w] < at) at = s_arg[w]; }
+    }
+    const size_t o = (size_t)seg * M_max + m;
+    sb.part_max[o] = mt;
+    sb.part_sum[o] = st;
+    sb.part_arg[o] = at;
   }
 }
 
@@ -258,7 +292,7 @@ __global__ void __launch_bounds__(256) row_stats_fold_kernel(Plan p, int M_max, 
   }
 }
 
-// Stage 2 (also the only stage for the few 1024-entry tiles of the plain-logits path):
+// Stage 2 (also the only stage for the few segments of the plain-logits path):
 __global__ void __launch_bounds__(256) row_stats_kernel(Plan p, int M_max, int n_vtiles, float inv_temp, SamplerBufs sb,
                                                         const float* __restrict__ t_max, const float* __restrict__ t_sum,
                                                         const int32_t* __restrict__ t_arg) {
@@ -437,7 +471,7 @@ __global__ void __launch_bounds__(64) accept_scan_kernel(Plan p, int B, int k_ma
 
 // ------------------------------------------------------------------ inverse-CDF sampling (Eq. 3)
 // The vocabulary of each sampled row is cut into kSampleChunks chunks so that B x 32 workgroups share
-// the float64 exponentials.  Three small kernels: normaliser partials, chunk masses, pick.
+// the float64 exponentials.  Three small kernels: normaliser partials, chunk masses (dense proposals), pick.
 //   p_j = exp(z_j/T - max) / sum_p ;  q_j likewise ;  w_j = p_j | p_j [j != draft] | max(0, p_j - q_j)
 // Divisions by per-row constants (T, the two normalisers) are multiplications by their float64 reciprocals: a
 // float64 division costs about as much as the exponential next to it, and the one-ulp difference is far below
@@ -452,8 +486,6 @@ struct SampleRow {
     return exp((double)zj * inv_T - mxp);
   }
   __device__ double e_q_v(float qj) const { return exp((double)qj - mxq); }
-  __device__ double e_p(int j) const { return e_p_v(j, z[j]); }
-  __device__ double e_q(int j) const { return e_q_v(to_f32<Q>(q[j])); }
   // inv_sp, inv_sq: reciprocals of the normalisers
   __device__ double weight_v(int j, float zj, float qj, double inv_sp, double inv_sq, int mode_now) const {
     const double pj = e_p_v(j, zj) * inv_sp;
@@ -490,6 +522,28 @@ __device__ __forceinline__ double block_sum_f64(double v, double* red) {     // 
   return red[0] + red[1] + red[2] + red[3];
 }
 
+// length of a vocabulary chunk: a multiple of four, so that chunks of aligned rows start aligned
+__host__ __device__ __forceinline__ int sample_chunk_len(int V) { return ((V + kSampleChunks - 1) / kSampleChunks + 3) & ~3; }
+
+// f(j, z_j, q_j) for j0 <= j < j1 over the workgroup's 256 threads; four consecutive tokens per load where the rows are aligned
+template <typename Q, bool FILT, typename F>
+__device__ __forceinline__ void for_each_token(const SampleRow<Q, FILT>& r, int j0, int j1, F f) {
+  typedef Q q4 __attribute__((ext_vector_type(4)));
+  const bool vec = ((uintptr_t)(r.z + j0) & 15) == 0 && ((uintptr_t)(r.q + j0) & (4 * sizeof(Q) - 1)) == 0;
+  const int n4 = vec ? (j1 - j0) / 4 : 0;
+  for (int i = threadIdx.x; i < n4; i += 256) {
+    const int j = j0 + 4 * i;
+    const f32x4 z = *(const f32x4*)(r.z + j);
+    q4 q = {};
+    if (r.q) q = *(const q4*)(r.q + j);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f(j + e, z[e], to_f32<Q>(q[e]));
+  }
+  for (int j = j0 + 4 * n4 + threadIdx.x; j < j1; j += 256) f(j, r.z[j], r.q ? to_f32<Q>(r.q[j]) : 0.f);
+}
+
+// Per chunk: sum of e_p, and the sum of e_q (dense residual) or of e_p without the rejected draft (one-hot residual).  Without a
+// dense proposal these are the chunk masses up to the common factor, and sample_mass_kernel has nothing to do.
 template <typename Q, bool FILT>
 __global__ void __launch_bounds__(256) sample_sum_kernel(int V, const float* __restrict__ logit_base, int rows_are_selected,
                                                          const Q* __restrict__ q_logits, float temperature, SamplerBufs sb) {
@@ -497,12 +551,13 @@ __global__ void __launch_bounds__(256) sample_sum_kernel(int V, const float* __r
   const int c = blockIdx.x, b = blockIdx.y;
   if (sb.sel_mode[b] == MODE_NONE) return;
   const SampleRow<Q, FILT> r = sample_row<Q, FILT>(b, V, logit_base, rows_are_selected, q_logits, temperature, sb);
-  const int chunk = (V + kSampleChunks - 1) / kSampleChunks;
+  const int chunk = sample_chunk_len(V);
   const int j0 = min(c * chunk, V), j1 = min(j0 + chunk, V);
   double sp = 0.0, sq = 0.0;
-  for (int j = j0 + threadIdx.x; j < j1; j += 256) {
-    sp += r.e_p(j);
-    if (r.q) sq += r.e_q(j);
+  if (r.q) {
+    for_each_token(r, j0, j1, [&](int j, float zj, float qj) { sp += r.e_p_v(j, zj); sq += r.e_q_v(qj); });
+  } else {
+    for_each_token(r, j0, j1, [&](int j, float zj, float) { const double e = r.e_p_v(j, zj); sp += e; sq += j == r.tgt ? 0.0 : e; });
   }
   sp = block_sum_f64(sp, red);
   sq = block_sum_f64(sq, red);
@@ -512,40 +567,36 @@ __global__ void __launch_bounds__(256) sample_sum_kernel(int V, const float* __r
   }
 }
 
-// Reciprocals of the two normalisers of sequence b (0 for an absent proposal).
-__device__ __forceinline__ void sample_totals(const SamplerBufs& sb, int b, double& inv_sp, double& inv_sq) {
+// Reciprocals of the two normalisers (0 for an absent proposal) from the chunk sums; every workgroup of a sequence sums in the
+// same order.  s_sum: [kSampleChunks][2] in LDS.
+__device__ __forceinline__ void sample_totals(const double* s_sum, double& inv_sp, double& inv_sq) {
   double sp = 0.0, sq = 0.0;
-  for (int c = 0; c < kSampleChunks; ++c) {          // fixed order: every workgroup gets the same totals
-    sp += sb.samp_sum[((size_t)b * kSampleChunks + c) * 2];
-    sq += sb.samp_sum[((size_t)b * kSampleChunks + c) * 2 + 1];
+  _Pragma("unroll 4") for (int c = 0; c < kSampleChunks; ++c) {
+    sp += s_sum[2 * c];
+    sq += s_sum[2 * c + 1];
   }
   inv_sp = 1.0 / sp;
   inv_sq = sq > 0.0 ? 1.0 / sq : 0.0;
 }
 
-// chunk masses of the residual (index 0) and of p itself (index 1, used when the residual is empty)
+// Chunk masses of the residual against a dense proposal, max(0, p - q): needs both normalisers.
 template <typename Q, bool FILT>
 __global__ void __launch_bounds__(256) sample_mass_kernel(int V, const float* __restrict__ logit_base, int rows_are_selected,
                                                           const Q* __restrict__ q_logits, float temperature, SamplerBufs sb) {
-  __shared__ double red[4];
+  __shared__ double red[4], s_sum[2 * kSampleChunks];
   const int c = blockIdx.x, b = blockIdx.y;
-  if (sb.sel_mode[b] == MODE_NONE) return;
+  if (sb.sel_mode[b] != MODE_RESID_DENSE) return;
+  if (threadIdx.x < 2 * kSampleChunks) s_sum[threadIdx.x] = sb.samp_sum[(size_t)b * kSampleChunks * 2 + threadIdx.x];
   const SampleRow<Q, FILT> r = sample_row<Q, FILT>(b, V, logit_base, rows_are_selected, q_logits, temperature, sb);
+  __syncthreads();
   double sp, sq;
-  sample_totals(sb, b, sp, sq);
-  const int chunk = (V + kSampleChunks - 1) / kSampleChunks;
+  sample_totals(s_sum, sp, sq);
+  const int chunk = sample_chunk_len(V);
   const int j0 = min(c * chunk, V), j1 = min(j0 + chunk, V);
-  double mw = 0.0, mp = 0.0;
-  for (int j = j0 + threadIdx.x; j < j1; j += 256) {
-    mw += r.weight(j, sp, sq, r.mode);
-    mp += r.e_p(j) * sp;
-  }
+  double mw = 0.0;
+  for_each_token(r, j0, j1, [&](int j, float zj, float qj) { mw += r.weight_v(j, zj, qj, sp, sq, MODE_RESID_DENSE); });
   mw = block_sum_f64(mw, red);
-  mp = block_sum_f64(mp, red);
-  if (threadIdx.x == 0) {
-    sb.samp_mass[((size_t)b * kSampleChunks + c) * 2] = mw;
-    sb.samp_mass[((size_t)b * kSampleChunks + c) * 2 + 1] = mp;
-  }
+  if (threadIdx.x == 0) sb.samp_mass[(size_t)b * kSampleChunks + c] = mw;
 }
 
 constexpr int kPickThreads = 1024;
@@ -556,28 +607,37 @@ __global__ void __launch_bounds__(kPickThreads) sample_pick_kernel(int V, const 
                                                           const int32_t* __restrict__ n_accepted, int k_max,
                                                           int32_t* __restrict__ out_tokens, int32_t* __restrict__ n_emitted,
                                                           uint32_t* __restrict__ near_tie) {
-  __shared__ double s_scan[kPickThreads];
+  __shared__ double s_sum[2 * kSampleChunks], s_mass[kSampleChunks], s_wave[kPickThreads / 64];
   __shared__ int s_i[2];
   const int b = blockIdx.x, tid = threadIdx.x;
   if (sb.sel_mode[b] == MODE_NONE) return;
   const SampleRow<Q, FILT> r = sample_row<Q, FILT>(b, V, logit_base, rows_are_selected, q_logits, temperature, sb);
+  if (tid < 2 * kSampleChunks) s_sum[tid] = sb.samp_sum[(size_t)b * kSampleChunks * 2 + tid];
+  if (tid == 0) { s_i[0] = 0x7fffffff; s_i[1] = -1; }
+  __syncthreads();
   double sp, sq;
-  sample_totals(sb, b, sp, sq);
-  // chunk level (every thread walks the 32 chunk masses: same result in all threads)
+  sample_totals(s_sum, sp, sq);
+  // chunk level: masses of the residual (or of p itself), then every thread walks the 32 of them: same result in all threads
   int mode = r.mode;
+  if (tid < kSampleChunks)
+    s_mass[tid] = mode == MODE_RESID_DENSE ? sb.samp_mass[(size_t)b * kSampleChunks + tid]
+                                           : s_sum[2 * tid + (mode == MODE_RESID_ONEHOT ? 1 : 0)] * sp;
+  __syncthreads();
   double total = 0.0;
-  for (int c = 0; c < kSampleChunks; ++c) total += sb.samp_mass[((size_t)b * kSampleChunks + c) * 2];
+  _Pragma("unroll 4") for (int c = 0; c < kSampleChunks; ++c) total += s_mass[c];
   if (!(total > 0.0) && mode != MODE_PLAIN) {       // empty residual: fall back to the target itself
     mode = MODE_PLAIN;
+    __syncthreads();
+    if (tid < kSampleChunks) s_mass[tid] = s_sum[2 * tid] * sp;
+    __syncthreads();
     total = 0.0;
-    for (int c = 0; c < kSampleChunks; ++c) total += sb.samp_mass[((size_t)b * kSampleChunks + c) * 2 + 1];
+    _Pragma("unroll 4") for (int c = 0; c < kSampleChunks; ++c) total += s_mass[c];
   }
-  const int mi = (mode == r.mode) ? 0 : 1;
   const double t = (double)u_sample[b] * total;
   int cs = -1, last_c = -1;
   double excl_c = 0.0, run = 0.0, last_excl = 0.0;
-  for (int c = 0; c < kSampleChunks; ++c) {
-    const double m = sb.samp_mass[((size_t)b * kSampleChunks + c) * 2 + mi];
+  _Pragma("unroll 4") for (int c = 0; c < kSampleChunks; ++c) {
+    const double m = s_mass[c];
     if (m > 0.0) { last_c = c; last_excl = run; }
     if (cs < 0 && run + m > t) { cs = c; excl_c = run; }
     run += m;
@@ -585,7 +645,7 @@ __global__ void __launch_bounds__(kPickThreads) sample_pick_kernel(int V, const 
   if (cs < 0) { cs = last_c; excl_c = last_excl; }  // rounding left no chunk: last chunk with weight
   if (cs < 0) return;                               // no weight anywhere (cannot happen for finite logits)
   // slice level inside the chosen chunk
-  const int chunk = (V + kSampleChunks - 1) / kSampleChunks;
+  const int chunk = sample_chunk_len(V);
   const int c0 = min(cs * chunk, V), c1 = min(c0 + chunk, V);
   const int slice = (c1 - c0 + kPickThreads - 1) / kPickThreads;
   const int j0 = min(c0 + tid * slice, c1), j1 = min(j0 + slice, c1);
@@ -607,23 +667,27 @@ __global__ void __launch_bounds__(kPickThreads) sample_pick_kernel(int V, const 
 #pragma unroll
     for (int i = 0; i < kW; ++i) {
       wv[i] = 0.0;
-      if (j0 + i < j1) wv[i] = r.weight_v(j0 + i, zr[i], qr[i], sp, sq, mode);
-      csum += wv[i];
+      if (i < slice) {                                // uniform: the 8 bodies stay apart (interleaved they spill)
+        if (j0 + i < j1) wv[i] = r.weight_v(j0 + i, zr[i], qr[i], sp, sq, mode);
+        csum += wv[i];
+      }
     }
   } else {
     for (int j = j0; j < j1; ++j) csum += r.weight(j, sp, sq, mode);
   }
-  s_scan[tid] = csum;
-  __syncthreads();
-  for (int o = 1; o < kPickThreads; o <<= 1) {
-    const double v = (tid >= o) ? s_scan[tid - o] : 0.0;
-    __syncthreads();
-    s_scan[tid] += v;
-    __syncthreads();
+  // inclusive scan over the workgroup: within a wave, then over the wave totals in order
+  double incl = csum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double v = __shfl_up(incl, o);
+    if ((tid & 63) >= o) incl += v;
   }
-  const double incl = excl_c + s_scan[tid], excl = incl - csum;
-  if (tid == 0) { s_i[0] = 0x7fffffff; s_i[1] = -1; }
+  if ((tid & 63) == 63) s_wave[tid >> 6] = incl;
   __syncthreads();
+  double before = excl_c;
+  for (int w = 0; w < (tid >> 6); ++w) before += s_wave[w];
+  incl += before;
+  const double excl = incl - csum;
   if (csum > 0.0) {
     if (incl > t && excl <= t) atomicMin(&s_i[0], tid);
     atomicMax(&s_i[1], tid);
@@ -702,8 +766,7 @@ void launch_lmhead_rows(const Shape& s, int B, const void* hf, const void* lm_he
 }
 void launch_logit_stats(const Plan& p, int M_max, int V, const float* logits, float inv_temp, const SamplerBufs& sb,
                         hipStream_t st) {
-  dim3 grid((V + kRowVtile - 1) / kRowVtile, M_max);
-  hipLaunchKernelGGL(logit_stats_kernel, grid, dim3(256), 0, st, p, M_max, V, logits, inv_temp, sb);
+  hipLaunchKernelGGL(logit_stats_kernel, dim3(kRowSegs, M_max), dim3(256), 0, st, p, M_max, V, logits, inv_temp, sb);
 }
 void launch_q_stats(const Plan& p, int M_max, int V, const void* q_logits, int q_dtype, const SamplerBufs& sb,
                     hipStream_t st) {
@@ -732,7 +795,8 @@ static void launch_sample_t(int B, int k_max, int V, const float* logit_base, bo
                             int32_t* out_tokens, int32_t* n_emitted, uint32_t* near_tie, hipStream_t st) {
   const int sel = rows_are_selected ? 1 : 0;
   hipLaunchKernelGGL((sample_sum_kernel<Q, FILT>), dim3(kSampleChunks, B), dim3(256), 0, st, V, logit_base, sel, q_logits, temperature, sb);
-  hipLaunchKernelGGL((sample_mass_kernel<Q, FILT>), dim3(kSampleChunks, B), dim3(256), 0, st, V, logit_base, sel, q_logits, temperature, sb);
+  if (q_logits)                                      // only a dense proposal leaves anything to do
+    hipLaunchKernelGGL((sample_mass_kernel<Q, FILT>), dim3(kSampleChunks, B), dim3(256), 0, st, V, logit_base, sel, q_logits, temperature, sb);
   hipLaunchKernelGGL((sample_pick_kernel<Q, FILT>), dim3(B), dim3(kPickThreads), 0, st, V, logit_base, sel, q_logits, temperature, u_sample, sb,
                      n_accepted, k_max, out_tokens, n_emitted, near_tie);
 }
