@@ -210,10 +210,10 @@ __global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int
   }
 }
 
-template <typename T, typename TP>
-__global__ void __launch_bounds__(256) kv_copy_kernel(KvView kv, int Hkv, int D, int slot, int pos0, TP* __restrict__ k_pages,
-                                                      TP* __restrict__ v_pages, T* __restrict__ k_rows,
-                                                      T* __restrict__ v_rows, int to_pages, int32_t* __restrict__ status) {
+// Export / import of cached rows, float32 pages: they are row-major, so a row is one contiguous run.
+__global__ void __launch_bounds__(256) kv_copy_f32_kernel(KvView kv, int Hkv, int D, int slot, int pos0, float* __restrict__ k_pages,
+                                                          float* __restrict__ v_pages, float* __restrict__ k_rows,
+                                                          float* __restrict__ v_rows, int to_pages) {
   int i = blockIdx.x, pos = pos0 + i;
   int page = kv.block_table[(size_t)slot * kv.max_pages + pos / kPage];
   if (page < 0 || page >= kv.n_pages) return;
@@ -221,23 +221,88 @@ __global__ void __launch_bounds__(256) kv_copy_kernel(KvView kv, int Hkv, int D,
   size_t pbase = (size_t)page * kv_page_elems(Hkv, D);
   for (int idx = threadIdx.x; idx < Hkv * D; idx += blockDim.x) {
     int kh = idx / D, dd = idx % D;
-    size_t ki = pbase + k_index<TP>(D, kh, tok, dd), vi = pbase + v_index<TP>(D, kh, tok, dd);
+    size_t ki = pbase + k_index<float>(D, kh, tok, dd), vi = pbase + v_index<float>(D, kh, tok, dd);
     size_t ri = (size_t)i * Hkv * D + idx;
-    if (to_pages) {
-      float kx = to_f32<T>(k_rows[ri]), vx = to_f32<T>(v_rows[ri]);
-      if constexpr (std::is_same<TP, f16>::value) {      // imported bf16 values beyond the float16 range
-        if (!(fabsf(kx) <= 65504.f) || !(fabsf(vx) <= 65504.f)) {
-          kx = f16_saturate(kx); vx = f16_saturate(vx);
-          atomicOr(status, BS_FAULT_RANGE);
+    if (to_pages) { k_pages[ki] = k_rows[ri]; v_pages[vi] = v_rows[ri]; }
+    else          { k_rows[ri] = k_pages[ki]; v_rows[ri] = v_pages[vi]; }
+  }
+}
+
+// Export / import of cached rows, float16 pages <-> bf16 rows.  One workgroup per (tile of 32 tokens, KV head, K or V); a thread
+// moves the sixteen bytes that are contiguous in the page: eight dims of one token (K) or one dim of eight tokens (V).  Latency
+// bound at these sizes (1900 rows x 2 heads x 128: 3.9 MB; one workgroup per row with two-byte accesses took 5.3 us, this takes 4.9, three dependent memory trips), hence every
+// load of a thread before its first store.  vec: the rows start on sixteen bytes.
+__global__ void __launch_bounds__(256) kv_copy_f16_kernel(KvView kv, int Hkv, int D, int slot, int pos0, int n, f16* __restrict__ k_pages,
+                                                          f16* __restrict__ v_pages, bf16* __restrict__ k_rows,
+                                                          bf16* __restrict__ v_rows, int to_pages, int vec, int32_t* __restrict__ status) {
+  typedef f16 h8 __attribute__((ext_vector_type(8)));
+  typedef bf16 b8 __attribute__((ext_vector_type(8)));
+  const int t0 = (pos0 / kTile + blockIdx.x) * kTile;            // first token of the tile
+  const int kh = blockIdx.y >> 1, is_v = blockIdx.y & 1;
+  const int page = kv.block_table[(size_t)slot * kv.max_pages + t0 / kPage];
+  if (page < 0 || page >= kv.n_pages) return;
+  f16* pg = (is_v ? v_pages : k_pages) + (size_t)page * kv_page_elems(Hkv, D);
+  bf16* rows = (is_v ? v_rows : k_rows) + kh * D;
+  const int ld = Hkv * D, lo = pos0 - t0, hi = pos0 + n - t0;     // tokens [lo, hi) of the tile are the caller's
+  const int nchunk = kTile * D / 8;
+  bool out_of_range = false;
+  auto enc = [&](bf16 x) {
+    float f = to_f32<bf16>(x);
+    if (!(fabsf(f) <= 65504.f)) { f = f16_saturate(f); out_of_range = true; }   // imported bf16 values beyond the float16 range
+    return from_f32<f16>(f);
+  };
+  auto dec = [](f16 x) { return from_f32<bf16>(to_f32<f16>(x)); };
+  for (int c = threadIdx.x; c < nchunk; c += 256) {
+    if (!is_v) {                                         // consecutive threads: consecutive dims of a token
+      const int t = c / (D / 8), d = c % (D / 8) * 8;
+      if (t < lo || t >= hi) continue;
+      h8* pp = (h8*)(pg + k_index<f16>(D, kh, (t0 + t) % kPage, d));
+      bf16* rp = rows + (size_t)(t - lo) * ld + d;
+      if (to_pages) {
+        b8 x; h8 y;
+        if (vec) x = *(const b8*)rp;
+        else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = rp[e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = enc(x[e]);
+        *pp = y;
+      } else {
+        const h8 y = *pp;
+        b8 x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = dec(y[e]);
+        if (vec) *(b8*)rp = x;
+        else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) rp[e] = x[e];
         }
       }
-      k_pages[ki] = from_f32<TP>(kx);
-      v_pages[vi] = from_f32<TP>(vx);
-    } else {
-      k_rows[ri] = from_f32<T>(to_f32<TP>(k_pages[ki]));
-      v_rows[ri] = from_f32<T>(to_f32<TP>(v_pages[vi]));
+    } else {                                             // consecutive threads: consecutive dims of eight tokens
+      const int t = c / D * 8, d = c % D;
+      if (t + 8 <= lo || t >= hi) continue;
+      f16* pp = pg + v_index<f16>(D, kh, (t0 + t) % kPage, d);
+      bf16* rp = rows + ((ptrdiff_t)t - lo) * ld + d;    // only rows in [lo, hi) are touched
+      if (to_pages) {
+        bf16 x[8]; h8 y;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = rp[(ptrdiff_t)(min(max(t + e, lo), hi - 1) - t) * ld];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = enc(x[e]);
+        if (t >= lo && t + 8 <= hi) *(h8*)pp = y;
+        else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) if (t + e >= lo && t + e < hi) pp[e] = y[e];
+        }
+      } else {
+        const h8 y = *(const h8*)pp;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) if (t + e >= lo && t + e < hi) rp[(ptrdiff_t)e * ld] = dec(y[e]);
+      }
     }
   }
+  if (out_of_range) atomicOr(status, BS_FAULT_RANGE);
 }
 
 void launch_embed(const Shape& s, const Plan& p, int M_max, const void* embed, float* h, const double* inv_freq,
@@ -271,10 +336,13 @@ void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_m
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,
                     void* k_rows, void* v_rows, bool to_pages, int32_t* status, hipStream_t st) {
   if (n <= 0) return;
-  if (s.dtype == BS_F32)
-    hipLaunchKernelGGL((kv_copy_kernel<float, float>), dim3(n), dim3(256), 0, st, kv, s.Hkv, s.D, slot, pos0, (float*)k_pages,
-                       (float*)v_pages, (float*)k_rows, (float*)v_rows, to_pages ? 1 : 0, status);
-  else
-    hipLaunchKernelGGL((kv_copy_kernel<bf16, f16>), dim3(n), dim3(256), 0, st, kv, s.Hkv, s.D, slot, pos0, (f16*)k_pages,
-                       (f16*)v_pages, (bf16*)k_rows, (bf16*)v_rows, to_pages ? 1 : 0, status);
+  if (s.dtype == BS_F32) {
+    hipLaunchKernelGGL(kv_copy_f32_kernel, dim3(n), dim3(256), 0, st, kv, s.Hkv, s.D, slot, pos0, (float*)k_pages, (float*)v_pages,
+                       (float*)k_rows, (float*)v_rows, to_pages ? 1 : 0);
+    return;
+  }
+  const int tiles = (pos0 + n - 1) / kTile - pos0 / kTile + 1;
+  const int vec = (((uintptr_t)k_rows | (uintptr_t)v_rows) & 15) == 0;
+  hipLaunchKernelGGL(kv_copy_f16_kernel, dim3(tiles, 2 * s.Hkv), dim3(256), 0, st, kv, s.Hkv, s.D, slot, pos0, n, (f16*)k_pages,
+                     (f16*)v_pages, (bf16*)k_rows, (bf16*)v_rows, to_pages ? 1 : 0, vec, status);
 }
