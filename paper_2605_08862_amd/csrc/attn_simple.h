@@ -13,6 +13,7 @@ __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int
                                                           const T* __restrict__ v_pages, TO* __restrict__ out) {
   static_assert(std::is_same<T, float>::value, "the dot product below loads four row-major floats at a time");
   typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f4_u __attribute__((ext_vector_type(4), aligned(4)));   // the caller's pages: aligned to their elements only
   __shared__ __align__(16) float s_q[128];
   __shared__ float s_p[256], s_red[4], s_acc[256];
   __shared__ int s_pg[256 / kPage];                     // pages of the 256 tokens of a chunk
@@ -38,7 +39,7 @@ __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int
       float dot[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 16
       for (int d = 0; d < D; d += 4) {
-        const f4 kv4 = *(const f4*)(kp + d), q4 = *(const f4*)(s_q + d);
+        const f4 kv4 = *(const f4_u*)(kp + d), q4 = *(const f4*)(s_q + d);
 #pragma unroll
         for (int e = 0; e < 4; ++e) dot[e] += q4[e] * kv4[e];
       }

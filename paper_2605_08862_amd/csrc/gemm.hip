@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64 * kF32Waves) gemm_f32_kernel(const int32_t*
       const int k = min(i + u, i1 - 1) * 8;
       a[u] = *(const f32x4*)(ap + k);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) w[nb][u] = *(const f32x4*)(wp[nb] + k);
+      for (int nb = 0; nb < NB; ++nb) w[nb][u] = *(const f32x4_u*)(wp[nb] + k);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)

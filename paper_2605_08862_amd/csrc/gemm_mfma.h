@@ -31,6 +31,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // of a caller's array: aligned to its elements only
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 64;                    // K tile (elements)

@@ -1,4 +1,4 @@
-// Decoder layer for steps of few packed rows (at most 64: one to a few sequences, or plain decoding of a small batch).
+// Decoder layer for steps of few packed rows (at most 32: one to a few sequences, or plain decoding of a small batch).
 //
 // With so few rows a layer is bound by streaming its weights once, and the first obstacle is latency: 1.5B shape, nine
 // rows, the weights of a layer are 94 MB = 15 us at the rate a streaming read reaches, and the tiled GEMMs took 62 us
@@ -127,7 +127,7 @@ skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* _
   if (NORM) {                                           // sums of squares and the gain first (waited for first), then the streams
     float ss = 0.f;
     for (int i = tid >> 5; i < nin.parts; i += GROUPS) ss += nin.ssq[(size_t)i * 32 + ln];
-    for (int i = tid * 4; i < K; i += 64 * WS * 4) *(f32x4*)(s_gain + i) = *(const f32x4*)(nin.gain + i);
+    for (int i = tid * 4; i < K; i += 64 * WS * 4) *(f32x4*)(s_gain + i) = *(const f32x4_u*)(nin.gain + i);
     s_ss[tid >> 5][ln] = ss;
   }
   u32x4 w[RING][4], x[RX][NORM ? 8 : 4];                // NORM: [K-step][half] of the residual
@@ -356,7 +356,7 @@ __global__ void __launch_bounds__(256) norm_frag_kernel(Plan p, int K, float eps
   const f32x4* hp = (const f32x4*)h + ((size_t)kt * 8 + 2 * s) * 64 + lane;
   const f32x4 a = hp[0], b = hp[64];
   const float* gp = gain + kt * kBK + lg * 32 + s * 8;
-  const f32x4 ga = *(const f32x4*)gp, gb = *(const f32x4*)(gp + 4);
+  const f32x4 ga = *(const f32x4_u*)gp, gb = *(const f32x4_u*)(gp + 4);
   float ss = 0.f;
   for (int i = tid >> 5; i < parts; i += 8) ss += ssq[(size_t)i * 32 + ln];
   s_ss[tid >> 5][ln] = ss;
@@ -381,7 +381,7 @@ void launch_t(int units, int n_split, int K, const Shape& s, const Plan& p, cons
 __global__ void __launch_bounds__(256) embed_frag_kernel(Plan p, int d, const bf16* __restrict__ embed, float* __restrict__ h,
                                                          float* __restrict__ ssq, int D, const double* __restrict__ inv_freq,
                                                          float* __restrict__ cos_t, float* __restrict__ sin_t) {
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4), aligned(2)));   // a caller's array: aligned to its elements only
   __shared__ float red[4];
   const int r = blockIdx.x;
   const bool live = r < p.n_rows[0];
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__(256) final_norm_frag_kernel(Plan p, int d, flo
   __syncthreads();
   const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
   for (int i = threadIdx.x * 4; i < d; i += 1024) {
-    const f32x4 v = *(const f32x4*)(h + h_frag_index(r, i, d / kBK)), g = *(const f32x4*)(gain + i);
+    const f32x4 v = *(const f32x4*)(h + h_frag_index(r, i, d / kBK)), g = *(const f32x4_u*)(gain + i);
     *(f16x4*)(out + (size_t)r * d + i) = to_f16x4_guarded(v[0] * inv * g[0], v[1] * inv * g[1], v[2] * inv * g[2], v[3] * inv * g[3], p.status);
   }
 }

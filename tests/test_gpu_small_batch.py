@@ -3,8 +3,11 @@ waves and workgroups, fragment-ordered activations) at the edges of its range, a
 
 The oracle is the fp64 forward; the bound is the logit tolerance of all bf16 cases (float16 operands, 2e-2 max-abs)."""
 import pytest
+import torch
 
 from paper_2605_08862_amd import workloads as W
+from paper_2605_08862_amd.runtime import Engine, fuse_weights
+from tests import helpers as H
 from tests.test_gpu_bf16 import _run_case
 
 pytestmark = pytest.mark.gpu
@@ -24,3 +27,27 @@ pytestmark = pytest.mark.gpu
 def test_small_row_counts(ctx_lens, k_b, k_max, over):
     desc = W.shape("mini_bf16", **over)
     _run_case(desc, ctx_lens=ctx_lens, k_b=k_b, k_max=k_max, seed=51)
+
+
+@pytest.mark.parametrize("name,moved", [("tiny", ["embed", "lm_head", "wqkv", "wo", "w_gate_up", "w_down"]),
+                                        ("mini_bf16", ["embed"])])
+def test_weights_aligned_to_their_elements_only(name, moved):
+    """Views into a larger buffer start at any element; the bits of the logits do not depend on it."""
+    desc = W.shape(name)
+    w = fuse_weights(W.make_weights(desc, seed=8), desc["dtype"], "cuda:0")
+
+    def shifted(t):
+        if isinstance(t, list):
+            return [shifted(x) for x in t]
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:].copy_(t.reshape(-1))
+        return buf[1:].view(t.shape)
+
+    got = []
+    for weights in (w, {n: shifted(t) if n in moved else t for n, t in w.items()}):
+        eng = Engine(desc, weights, 2, 64, B_max=2, k_max=3)
+        got.append(eng.verify_step(H.dev_i32([0, 1]), H.dev_i32([3, 4]), H.dev_i32([[5, 6, 7], [8, 9, 10]]),
+                                   H.dev_i32([3, 1]), 3, want_logits=True)[:6].cpu())
+        assert eng.poll_status() == 0
+        eng.close()
+    assert torch.equal(got[0], got[1])
