@@ -42,13 +42,13 @@ def classify(names):
     out, marker = [], None
     for n in names:
         cls = None
-        if "attn_mfma_kernel" in n or "attn_wide_kernel" in n or "attn_wide_merge_kernel" in n:
+        if "attn_mfma_kernel" in n or "attn_wide_kernel" in n:
             cls, marker = "attention", "attention"
-        elif "qkv_rope_kernel" in n:
+        elif "qkv_rope_kernel" in n or "skinny_kernelILi0E" in n:
             cls = "gemm_qkv"
-        elif "gemm8_kernel" in n or "gemm_ring2_swiglu_kernel" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi2E", n):
+        elif "gemm8_kernel" in n or "skinny_glu_kernel" in n or "gemm_ring2_swiglu_kernel" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi2E", n):
             cls, marker = "gemm_gate_up", "gate_up"
-        elif "gemm_resid_kernel" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi1E", n):
+        elif "gemm_resid_kernel" in n or "skinny_kernelILi1E" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi1E", n):
             cls = "gemm_down" if marker == "gate_up" else "gemm_o"
         elif re.search(r"gemm_mfma_kernelILi\dELi\dELi3E", n):
             cls = "gemm_qkv"                                   # unfused QKV projection (head sizes other than 128)
