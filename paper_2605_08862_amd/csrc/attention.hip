@@ -484,6 +484,7 @@ AttnPlan attention_plan_params(const Shape& s, int B, int k_max) {
     a.c_item = 8.0f; a.t_scale = 0.25f; a.t_lat = 1.1f; a.t_full = 2.7f * bytes / q_blocks; a.c_merge = 0.f; a.t_merge = 0.15f;
   } else {                                                          // eight waves on two or four phases
     a.c_item = 16.0f; a.t_scale = 1.0f; a.t_lat = 0.53f; a.t_full = 0.72f * bytes; a.c_merge = 6.0f; a.t_merge = 0.25f;
+    a.ragged_fair = 1;
   }
   return a;
 }

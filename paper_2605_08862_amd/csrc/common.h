@@ -181,6 +181,10 @@ struct AttnPlan {
   float t_scale;        // length of a task per 32-token tile
   float t_lat, t_full;  // time per unit of length: alone on the memory system, with every CU streaming
   float c_merge, t_merge;   // merge of a sequence's chunks: fixed, per chunk
+  // Ragged batches: pieces near the fair share of a CU instead of the modelled time.  Wide kernel: with c_item in the average
+  // the model prefers pieces above the fair share, and those end the launch late (7B long-tail batch, 128 sequences of 512 .. 32768
+  // tokens, whole step: model 27.38 ms, fair share 27.05; prefill, 61 prompts around 512 tokens, 5.95 and 5.75).
+  int ragged_fair;
 };
 
 // cos / sin of the rotary angle of packed row r (absolute position c_b + i) and pair j.  The angle is formed in

@@ -202,6 +202,8 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(Plan p, KvView kv, i
         const float full = floorf(tasks / slots), rem = tasks - full * slots;
         cost = full * (attn.c_item + len * attn.t_full);
         if (rem > 0.f) cost += attn.c_item + len * fmaxf(attn.t_lat, attn.t_full * rem / slots);
+      } else if (attn.ragged_fair) {                     // ragged, wide kernel: nearest to the fair share of a CU
+        cost = fabsf((float)cht - fair);
       } else {                                           // ragged: handed out longest first
         const float avg = (tasks * attn.c_item + (float)T * attn.pairs * attn.t_scale * attn.t_full) / slots;
         cost = fmaxf(avg, attn.c_item + len * attn.t_full) + 0.5f * attn.c_item;
