@@ -14,6 +14,12 @@ constexpr int kLmNT = 2;                            // LM-head wave tile: 32*MT 
 constexpr int kLmVtile = kLmNT * 32;                // vocab entries per statistics tile (bf16 path)
 constexpr int kSampleChunks = 32;                   // vocabulary chunks per sequence in the sampling kernels
 
+// Factor that carries a sum of exponentials from an old running maximum to a new, larger one.  The sum is still empty while the
+// maximum is -inf, and (-inf) * inv_temp is NaN at infinite temperature (inv_temp = 0): the factor is 0 there.
+__device__ __forceinline__ float rescale_exp(float from, float to, float inv_temp) {
+  return from == -INFINITY ? 0.f : __expf((from - to) * inv_temp);
+}
+
 int lmhead_vtiles(int V) {
   const int a = (V + kLmVtile - 1) / kLmVtile;
   return a > kRowSegs ? a : kRowSegs;
@@ -185,7 +191,7 @@ __global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int
 #pragma unroll
     for (int e = 1; e < 4; ++e) vm = e < cnt ? fmaxf(vm, x[e]) : vm;
     if (vm > mx) {
-      const float f = __expf((mx - vm) * inv_temp);      // 0 on the first values
+      const float f = rescale_exp(mx, vm, inv_temp);     // 0 on the first values
 #pragma unroll
       for (int e = 0; e < 4; ++e) sum[e] *= f;
       mx = vm;
@@ -223,7 +229,7 @@ __global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int
   for (int o = 32; o > 0; o >>= 1) {
     const float mo = __shfl_xor(mx, o), so = __shfl_xor(s, o);
     const int ao = __shfl_xor(arg, o);
-    if (mo > mx) { s = s * __expf((mx - mo) * inv_temp) + so; mx = mo; arg = ao; }
+    if (mo > mx) { s = s * rescale_exp(mx, mo, inv_temp) + so; mx = mo; arg = ao; }
     else if (mo > -INFINITY) { s += so * __expf((mo - mx) * inv_temp); if (mo == mx && ao < arg) arg = ao; }
   }
   if ((tid & 63) == 0) { s_mx[tid >> 6] = mx; s_sum[tid >> 6] = s; s_arg[tid >> 6] = arg; }
@@ -233,7 +239,7 @@ __global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int
     int at = s_arg[0];
     for (int w = 1; w < 4; ++w) {
       const float mo = s_mx[w];
-      if (mo > mt) { st = st * __expf((mt - mo) * inv_temp) + s_sum[w]; mt = mo; at = s_arg[w]; }
+      if (mo > mt) { st = st * rescale_exp(mt, mo, inv_temp) + s_sum[w]; mt = mo; at = s_arg[w]; }
       else if (mo > -INFINITY) { st += s_sum[w] * __expf((mo - mt) * inv_temp); if (mo == mt && s_arg[w] < at) at = s_arg[w]; }
     }
     const size_t o = (size_t)seg * M_max + m;
@@ -260,7 +266,7 @@ __global__ void __launch_bounds__(256) row_stats_fold_kernel(Plan p, int M_max, 
   float mx = -INFINITY, sum = 0.f;
   int arg = 0x7fffffff;
   auto fold = [&](float m2, float s2, int a2) {
-    if (m2 > mx) { sum = sum * __expf((mx - m2) * inv_temp) + s2; mx = m2; arg = a2; }
+    if (m2 > mx) { sum = sum * rescale_exp(mx, m2, inv_temp) + s2; mx = m2; arg = a2; }
     else if (m2 > -INFINITY) { sum += s2 * __expf((m2 - mx) * inv_temp); if (m2 == mx && a2 < arg) arg = a2; }
   };
   if (valid) {

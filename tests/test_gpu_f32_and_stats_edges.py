@@ -56,3 +56,32 @@ def test_plain_logits_sampler_at_segment_edges(vocab, q_mode):
         exact, near, _ = H.compare_sampler(out, logits, drafts, k_b, ua, us, qn, T)
         assert exact + near == Bn and near <= 2
     eng.close()
+
+
+@pytest.mark.parametrize("source,vocab", [("logits", 5), ("logits", 1003), ("logits", 70000), ("tiny", 4096),
+                                          ("mini_bf16", 1003), ("mini_bf16", 8200)])     # 129 statistics tiles: the fold pass runs
+def test_infinite_temperature_is_the_uniform_law(source, vocab):
+    """1 / T = 0 is a legal scaling: p is uniform, so a one-hot draft is accepted with probability 1 / V and the sums start
+    from an empty running maximum (-inf) without producing (-inf) * 0."""
+    name = "tiny" if source == "logits" else source
+    desc = W.shape(name, vocab=vocab, **(dict(n_layers=1) if source == "logits" else {}))
+    Bn, k = 6, 3
+    eng = Engine(desc, fuse_weights(W.make_weights(desc, seed=3), desc["dtype"], DEV), Bn, 64, B_max=Bn, k_max=k)
+    rng = np.random.default_rng(vocab)
+    blk = rng.integers(0, vocab, (Bn, k + 1))
+    k_b = np.array([3, 3, 2, 1, 0, 3])
+    drafts, dl = H.dev_i32(blk[:, 1:]), H.dev_i32(k_b)
+    ua, us = W.uniforms(vocab, Bn, k)
+    ua[0, 0] = 0.25 / vocab                                                             # accepted: below 1 / V
+    M = int((k_b + 1).sum())
+    if source == "logits":
+        rows = rng.normal(0, 2.0, (M, vocab)).astype(np.float32)
+        out = eng.accept_resample(drafts, dl, k, H.dev_f32(ua), H.dev_f32(us), logits=H.dev_f32(rows), temperature=float("inf"))
+    else:
+        logits = eng.verify_step(H.dev_i32(np.arange(Bn)), H.dev_i32(blk[:, 0]), drafts, dl, k, want_logits=True)
+        rows = logits[:M].cpu().numpy()
+        out = eng.accept_resample(drafts, dl, k, H.dev_f32(ua), H.dev_f32(us), temperature=float("inf"))
+    exact, near, _ = H.compare_sampler(out, rows, blk[:, 1:], k_b, ua, us, temperature=float("inf"))
+    assert exact + near == Bn and near <= 1
+    assert eng.poll_status() == 0
+    eng.close()
