@@ -63,16 +63,17 @@ __global__ void __launch_bounds__(256) attn_simple_kernel(Plan p, KvView kv, int
     m_run = m_new;
     acc *= alpha;
     const int cnt = min(256, n_tok - t0);
-    for (int j0 = part; j0 < cnt; j0 += 16 * nparts) {   // sixteen tokens' V elements in flight (a token past the end has weight 0)
+    for (int j0 = part; j0 < cnt; j0 += 16 * nparts) {   // sixteen tokens' V elements in flight
       float v[16], w[16];
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int j = min(j0 + u * nparts, cnt - 1);
         v[u] = to_f32<T>(v_pages[(size_t)s_pg[j / kPage] * page_elems + v_index<T>(D, kvh, j % kPage, dd)]);
-        w[u] = j0 + u * nparts < cnt ? s_p[j] : 0.f;
+        w[u] = s_p[j];
       }
 #pragma unroll
-      for (int u = 0; u < 16; ++u) acc += w[u] * v[u];
+      for (int u = 0; u < 16; ++u)                       // beyond the end: the last token read again, not added (0 * inf is NaN)
+        acc += j0 + u * nparts < cnt ? w[u] * v[u] : 0.f;
     }
     __syncthreads();
   }

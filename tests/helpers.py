@@ -1,10 +1,13 @@
 """Shared test helpers: glue between the seeded workloads, the oracle and the HIP library.
 (Only tests import this; it calls the oracle and the binding side by side.)"""
+import ctypes as C
+
 import numpy as np
 import torch
 
 from oracle import accept as OA
 from oracle import decoder as OD
+from paper_2605_08862_amd import binding as B
 from paper_2605_08862_amd import workloads as W
 
 TOL_LOGITS = {W.BS_F32: 1e-4, W.BS_BF16: 2e-2}      # max-abs logit tolerance (spec bar)
@@ -25,6 +28,15 @@ def dev_i32(x, device="cuda:0"):
 
 def dev_f32(x, device="cuda:0"):
     return torch.as_tensor(np.ascontiguousarray(x), dtype=torch.float32).to(device)
+
+
+def debug_buffer(eng, which, n):
+    """First n float32 elements of an intermediate buffer of the last step (bs_debug_buffer numbering)."""
+    f = B.lib().bs_debug_copy
+    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p], C.c_int
+    out = torch.empty(n, dtype=torch.float32, device="cuda:0")
+    assert f(eng.ctx, which, out.data_ptr(), n * 4, torch.cuda.current_stream().cuda_stream) == B.BS_OK
+    return out
 
 
 def pack_rows(last_token, draft_tokens, draft_len):

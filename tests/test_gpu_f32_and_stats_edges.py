@@ -85,3 +85,23 @@ def test_infinite_temperature_is_the_uniform_law(source, vocab):
     assert exact + near == Bn and near <= 1
     assert eng.poll_status() == 0
     eng.close()
+
+
+@pytest.mark.parametrize("n_ctx", [0, 1, 30, 255, 256])
+def test_float32_attention_keeps_an_infinite_value(n_ctx):
+    """V of the step's own row overflows in one element: the attention output is infinite there (weight > 0), not NaN, and
+    finite everywhere else.  The row is the last one of its last group of tokens, which the kernel reads again as filler."""
+    desc = W.shape("tiny", n_layers=1)
+    w = W.make_weights(desc, seed=2)
+    w["embed"][:, 0] = 0.0
+    w["embed"][7, 0] = 10.0                                                             # normalised to about sqrt(d) = 16
+    w["layers"][0]["wv"][0, 0] = 1e38                                                   # V of KV head 0, element 0
+    eng = Engine(desc, fuse_weights(w, desc["dtype"], DEV), 1, 320, B_max=1, k_max=0)
+    if n_ctx:
+        rows = torch.randn(n_ctx, desc["n_kv_heads"], desc["head_dim"], device=DEV)
+        eng.kv_write(0, 0, 0, rows, rows)
+        eng.ctx_len.fill_(n_ctx)
+    eng.verify_step(H.dev_i32([0]), H.dev_i32([7]), None, H.dev_i32([0]), 0)
+    out = H.debug_buffer(eng, 4, desc["n_q_heads"] * desc["head_dim"]).cpu()
+    assert out[0] == float("inf") and torch.isfinite(out[1:]).all()
+    eng.close()
