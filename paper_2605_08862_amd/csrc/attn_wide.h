@@ -53,6 +53,11 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
   const int ln = lane & 31, lg = lane >> 5;
   const size_t page_elems = kv_page_elems(Hkv, D);
 
+  // threadIdx.x as a value the compiler cannot move.  What the two epilogues derive from it would otherwise be computed once,
+  // before the loop over the units, and live through the tile loop: 256 registers and 43 spilled ones instead of 206.  Measured
+  // per launch (7B heads unless stated): 128 sequences of 512 .. 32768 tokens 347 -> 341 us, one of 1000 tokens 26.8 -> 21.6,
+  // 1.5B heads, 61 prompts around 512 tokens 35.4 -> 30.3.
+  auto thread_now = [&]() { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t; };
   auto out_index = [&](int row, int col) -> size_t {
     return out_frag ? act_frag_index(row, col, Hq * D / 64) : (size_t)row * Hq * D + col;
   };
@@ -63,7 +68,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     const size_t slot0 = ((size_t)item_start[b] * Hkv + h) * RPT;
     const wt_buf bo = wt_buffer(part_o + slot0 * D), bm = wt_buffer(part_ml + slot0 * 2);
     const int G = Hq / Hkv, R = (seq_k[b] + 1) * G;
-    const int qr = threadIdx.x / TPR, sub = threadIdx.x % TPR;
+    const int tid = thread_now(), qr = tid / TPR, sub = tid % TPR;
     if (qr >= R) return;
     const uint32_t step = (uint32_t)Hkv * RPT;             // partial rows from one chunk to the next
     float mt = -INFINITY;
@@ -264,7 +269,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     {
       constexpr int TPR = THREADS / (32 * NQT);          // threads per query row: 8 or 4
       constexpr int CH = D / 4;                          // 16-byte chunks per row
-      const int wr = threadIdx.x / TPR, sub = threadIdx.x % TPR;      // wr = query row of the unit, 0 .. 32 NQT - 1
+      const int tid = thread_now(), wr = tid / TPR, sub = tid % TPR;      // wr = query row of the unit, 0 .. 32 NQT - 1
       const int tq = wr / 32, lr = wr % 32;
       if (wr < R) {
         float mw[NPH], mt = -INFINITY;
