@@ -468,24 +468,24 @@ static void launch_shape(const Shape& s, int B, int k_max, int& q_blocks, int& s
   force_chunks = g_force_n_chunks;
 }
 
-// Constants of the launch-time model, fitted to launches of one to 128 sequences of 1000 .. 30000 tokens in 1 .. 32
-// chunks on both model shapes.  Examples, measured (chunks of the model's choice first): 1.5B heads, nine query rows:
-// batch 1 x 1000 tokens, 4 chunks 8.7 us, 1 chunk 12.0, 16 chunks 10.9; batch 16 x 1500, 4 chunks 11.5, 1 chunk 16.5, 6
-// chunks (a second round) 19.2; batch 48 x 1500, 1 chunk 21.8, 2 chunks 30.6.  7B heads: batch 4 x 8192, 8 chunks 21.4, 4
-// chunks 27.4, 12 chunks 31.9.
+// The model's constants (attn_plan_constants) are fitted to launches cut into 1 .. 64 chunks.  Four-wave kernel, one to 128
+// sequences of 1000 .. 30000 tokens on both model shapes; examples, measured (chunks of the model's choice first): 1.5B heads,
+// nine query rows: batch 1 x 1000 tokens, 4 chunks 8.7 us, 1 chunk 12.0, 16 chunks 10.9; batch 16 x 1500, 4 chunks 11.5, 1 chunk
+// 16.5, 6 chunks (a second round) 19.2; batch 48 x 1500, 1 chunk 21.8, 2 chunks 30.6.
+// Wide kernel, 31 batches of 1 .. 220 sequences around 128 .. 30000 tokens, equal and ragged (lognormal, sigma 0.3 .. 1), up to
+// twenty chunk sizes each: the choice is within 6 % of the fastest size in all but one (12 %).  17 query rows; chunk size of the
+// choice, the fastest one, and the fair share of a workgroup (in tiles, time in us):
+//   7B,   16 sequences around 128, sigma 1:      9 tiles 21.0,   7: 20.2,    1: 53.5 (464 tasks: a second round)
+//   7B,    3 around 700, sigma 1:               12: 23.8,       10: 23.1,    1: 85.6
+//   1.5B, 61 around 512, sigma 0.5:             14: 23.4,       14: 23.4,    9: 29.8
+//   7B,    1 of 30000:                          47: 64.0,       43: 62.6,   15: 96.6
+//   7B,  128 around 4096, sigma 1:             391: 339,       257: 331,  404: 341, 513: 374
 AttnPlan attention_plan_params(const Shape& s, int B, int k_max) {
   AttnPlan a{};
   if (s.dtype != BS_BF16) return a;
   int q_blocks;
   launch_shape(s, B, k_max, q_blocks, a.s_min, a.force_chunks);
-  a.pairs = (float)(s.Hkv * q_blocks);
-  const float bytes = s.D / 128.0f;                                 // a tile's bytes against head size 128
-  if (rows_padded(s, k_max) / 32 / q_blocks <= 2) {                 // four waves, a tile each: length in rows of four tiles
-    a.c_item = 8.0f; a.t_scale = 0.25f; a.t_lat = 1.1f; a.t_full = 2.7f * bytes / q_blocks; a.c_merge = 0.f; a.t_merge = 0.15f;
-  } else {                                                          // eight waves on two or four phases
-    a.c_item = 16.0f; a.t_scale = 1.0f; a.t_lat = 0.53f; a.t_full = 0.72f * bytes; a.c_merge = 6.0f; a.t_merge = 0.25f;
-    a.ragged_fair = 1;
-  }
+  attn_plan_constants(a, rows_padded(s, k_max) / 32 / q_blocks, q_blocks, s.Hkv, s.D);
   return a;
 }
 

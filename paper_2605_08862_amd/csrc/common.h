@@ -171,8 +171,9 @@ __host__ __device__ __forceinline__ int attn_item_capacity(int B, int s_min) { r
 constexpr int kAttnMaxSmin = 256;
 constexpr int kAttnWorkgroups = 256;   // persistent workgroups of an attention launch (one per CU)
 
-// How long an attention launch takes for a given chunk size (microseconds; measured, see attention.hip).  A task is one
-// (item, KV head, query block).  tasks running together: c_item + length * max(t_lat, t_full * tasks / workgroups).
+// How long an attention launch takes for a given chunk size: microseconds throughout, so that candidates of different branches
+// of attn_chunk_cost can be compared (constants and what they were fitted to: attention.hip).  A task is one (item, KV head,
+// query block); tasks running together take c_item + length * max(t_lat, t_full * tasks / workgroups).
 struct AttnPlan {
   int s_min;            // 0: no work list; else items that fill the chip once (capacity of the list)
   int force_chunks;     // > 0 (tests): chunk size such that the longest sequence has that many chunks
@@ -180,12 +181,48 @@ struct AttnPlan {
   float c_item;         // fixed cost of a task: metadata, first loads, merge of its waves
   float t_scale;        // length of a task per 32-token tile
   float t_lat, t_full;  // time per unit of length: alone on the memory system, with every CU streaming
+  float t_long, c_tail; // ragged batches of more tasks than workgroups: time per unit of length of the longest piece, end of the launch
   float c_merge, t_merge;   // merge of a sequence's chunks: fixed, per chunk
-  // Ragged batches: pieces near the fair share of a CU instead of the modelled time.  Wide kernel: with c_item in the average
-  // the model prefers pieces above the fair share, and those end the launch late (7B long-tail batch, 128 sequences of 512 .. 32768
-  // tokens, whole step: model 27.38 ms, fair share 27.05; prefill, 61 prompts around 512 tokens, 5.95 and 5.75).
-  int ragged_fair;
 };
+constexpr int kAttnCandidates = 128;
+// Candidate i of the common chunk size (tiles) of a batch of T tiles whose longest sequence has mx: the longest sequence in
+// 1 .. 64 equal parts, and 1/4 .. 9/4 of the fair share of one workgroup.
+__host__ __device__ __forceinline__ int attn_chunk_candidate(const AttnPlan& a, int i, int T, int mx, int floor_cht) {
+  const float fair = (float)T * a.pairs / (float)kAttnWorkgroups;
+  int cht = i < 64 ? (mx + i) / (i + 1) : (int)(fair * (0.25f + (i - 64) * 0.03125f)) + 1;
+  cht = cht < (mx > 1 ? mx : 1) ? cht : (mx > 1 ? mx : 1);
+  return cht > floor_cht ? cht : floor_cht;
+}
+// Modelled time of the launch when a batch of nv sequences with T tiles, the longest mx, is cut into `items` chunks of cht tiles.
+__host__ __device__ __forceinline__ float attn_chunk_cost(const AttnPlan& a, int cht, int items, int T, int mx, int nv) {
+  const float slots = (float)kAttnWorkgroups, tasks = (float)items * a.pairs, len = cht * a.t_scale;
+  float cost;
+  if (tasks <= slots) {                                  // all tasks at once
+    cost = a.c_item + len * fmaxf(a.t_lat, a.t_full * tasks / slots);
+  } else if (4LL * mx * nv <= 5LL * T) {                 // equal tasks: whole rounds and a last one
+    const float full = floorf(tasks / slots), rem = tasks - full * slots;
+    cost = full * (a.c_item + len * a.t_full);
+    if (rem > 0.f) cost += a.c_item + len * fmaxf(a.t_lat, a.t_full * rem / slots);
+  } else {                                               // ragged: handed out longest first
+    const float avg = (tasks * a.c_item + (float)T * a.pairs * a.t_scale * a.t_full) / slots;
+    cost = fmaxf(avg, a.c_item + len * a.t_long) + a.c_tail;
+  }
+  if (cht < mx) cost += a.c_merge + a.t_merge * (float)((mx + cht - 1) / cht);
+  return cost;
+}
+// Constants for launches whose workgroups hold `tiles_wg` query tiles (1, 2: four waves, a tile each, length in rows of four
+// tiles; 4: the wide kernel, eight waves on two or four phases), q_blocks workgroups per (item, KV head).
+inline void attn_plan_constants(AttnPlan& a, int tiles_wg, int q_blocks, int Hkv, int D) {
+  const float bytes = D / 128.0f;                        // a tile's bytes against head size 128
+  a.pairs = (float)(Hkv * q_blocks);
+  if (tiles_wg <= 2) {
+    a.c_item = 8.0f; a.t_scale = 0.25f; a.t_lat = 1.1f; a.t_full = 2.7f * bytes / q_blocks;
+    a.t_long = a.t_full; a.c_tail = 4.0f; a.c_merge = 0.f; a.t_merge = 0.15f;
+  } else {
+    a.c_item = 14.0f; a.t_scale = 1.0f; a.t_lat = 0.6f; a.t_full = 0.66f * bytes;
+    a.t_long = 0.72f * bytes; a.c_tail = 6.0f; a.c_merge = 2.0f; a.t_merge = 1.2f;
+  }
+}
 
 // cos / sin of the rotary angle of packed row r (absolute position c_b + i) and pair j.  The angle is formed in
 // float64 (at positions of 3e4 a float32 angle is already off by ~2e-3 rad), reduced to [-pi, pi] in float64 and

@@ -153,11 +153,10 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(Plan p, KvView kv, i
   // orders of magnitude (contexts of 512 .. 32768 tokens in one step), and a small batch has fewer streams than the
   // chip has CUs, so the token range of every sequence is cut into chunks of a common size; the attention kernel's
   // persistent workgroups walk the (sequence, chunk) items, of which each is `pairs` workgroup tasks (KV heads x query
-  // blocks).  The size is the one that the model of AttnPlan says is fastest among 128 candidates (one per pair of
-  // threads): the longest sequence in 1 .. 64 equal parts, and 1/4 .. 9/4 of the fair share of one CU.
+  // blocks).  The size is the one that attn_chunk_cost says is fastest among kAttnCandidates (eight threads each).
   // sum_b chunks(b) <= B + 4 S, S = max(B, s_min), always (the work list's capacity).
-  __shared__ float s_cost[128];
-  __shared__ int s_cand[128];
+  __shared__ float s_cost[kAttnCandidates];
+  __shared__ int s_cand[kAttnCandidates];
   __shared__ int s_cht;
   int T, nv, mx = 0;
   {
@@ -184,9 +183,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(Plan p, KvView kv, i
     if (tid == 0) s_cht = max((mx + attn.force_chunks - 1) / attn.force_chunks, floor_cht);
   } else {
     const int cand = tid >> 3, sub = tid & 7;            // eight threads share a candidate's count of items
-    const float slots = (float)kAttnWorkgroups, fair = (float)T * attn.pairs / slots;
-    int cht = cand < 64 ? (mx + cand) / (cand + 1) : (int)(fair * (0.25f + (cand - 64) * 0.03125f)) + 1;
-    cht = max(min(cht, max(mx, 1)), floor_cht);
+    const int cht = attn_chunk_candidate(attn, cand, T, mx, floor_cht);
     const float inv = 1.0f / (float)cht;
     int items = 0;
     for (int b = sub; b < B; b += 8) items += (int)((float)(s_c[b] + cht - 1) * inv + 1e-4f);   // chunks (a model: +-1 is fine)
@@ -194,22 +191,7 @@ __global__ void __launch_bounds__(kPlanThreads) plan_kernel(Plan p, KvView kv, i
     items += __shfl_xor(items, 2);
     items += __shfl_xor(items, 4);
     if (sub == 0) {
-      const float tasks = (float)items * attn.pairs, len = cht * attn.t_scale;
-      float cost;
-      if (tasks <= slots) {                              // all tasks at once
-        cost = attn.c_item + len * fmaxf(attn.t_lat, attn.t_full * tasks / slots);
-      } else if (4LL * mx * nv <= 5LL * T) {             // equal tasks: whole rounds and a last one
-        const float full = floorf(tasks / slots), rem = tasks - full * slots;
-        cost = full * (attn.c_item + len * attn.t_full);
-        if (rem > 0.f) cost += attn.c_item + len * fmaxf(attn.t_lat, attn.t_full * rem / slots);
-      } else if (attn.ragged_fair) {                     // ragged, wide kernel: nearest to the fair share of a CU
-        cost = fabsf((float)cht - fair);
-      } else {                                           // ragged: handed out longest first
-        const float avg = (tasks * attn.c_item + (float)T * attn.pairs * attn.t_scale * attn.t_full) / slots;
-        cost = fmaxf(avg, attn.c_item + len * attn.t_full) + 0.5f * attn.c_item;
-      }
-      if (cht < mx) cost += attn.c_merge + attn.t_merge * (float)((mx + cht - 1) / cht);
-      s_cost[cand] = cost;
+      s_cost[cand] = attn_chunk_cost(attn, cht, items, T, mx, nv);
       s_cand[cand] = cht;
     }
     __syncthreads();
