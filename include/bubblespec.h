@@ -109,7 +109,10 @@ typedef struct {
 
 typedef struct bs_ctx bs_ctx;
 
-/* Bytes of device workspace a context for (desc, B_max, k_max) needs. 0 on invalid arguments. */
+/* Bytes of device workspace a context for (desc, B_max, k_max) needs. 0 on invalid arguments.  For bf16 models that includes
+ * float32 logits of up to d_model / 4 packed rows (they share memory with the activations of the layers), with which accept
+ * calls of so few rows need no second pass over the LM-head weights.  bs_create also takes a smaller workspace, down to the
+ * layers' buffers and B_max rows of logits: the same results up to rounding, small calls slower. */
 size_t bs_workspace_bytes(const bs_model_desc* desc, int B_max, int k_max);
 
 /* Creates the host-side context.  `workspace` (dev, 256-byte aligned, >= bs_workspace_bytes)

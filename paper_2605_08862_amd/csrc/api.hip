@@ -23,7 +23,7 @@ struct bs_ctx {
   std::vector<void*> pk_qkv, pk_o, pk_gu, pk_down;         // bf16 models: packed copies in the workspace
   void* pk_lm = nullptr;
   void* a;             // normed rows      [M_max, d] (GEMM operand type: float32 / float16)
-  float* qkv;          // [M_max, (Hq+2Hkv) D] float32 projection (rounded once, after the rotation)
+  float* qkv;          // float32 models: [M_max, (Hq+2Hkv) D] projection
   void* q;             // [M_max, Hq D] rotated queries
   float* slabs;        // bf16 models: K-split slabs of the float32 GEMM epilogues [8][M_max, max(Nqkv, d)]
   void* attn_out;      // [M_max, Hq D]
@@ -32,8 +32,11 @@ struct bs_ctx {
   SkinnyBufs sk;
   float* ssq;          // [d / 32][kSkinnyRows] sums of squares of the residual's rows (steps of at most kSkinnyRows rows)
   void* attn_scratch;
-  float* full_logits;  // float32 models: [M_max, V]; bf16 models: [logit_rows, V]
+  // Logits: float32 models [M_max, V]; bf16 models [max(logit_rows, B_max), V], on top of a .. act, which nothing reads once
+  // bs_verify_step has left the final rows in hf
+  float* full_logits;
   int logit_rows = 0;  // bf16 models: calls of at most this many rows keep every row's logits (see lmhead_logit_rows)
+  bool fragments = false;   // workspace laid out for the fragment-ordered small steps (skinny.hip)
   SamplerBufs sb;
   int n_vtiles;
   // pool
@@ -114,8 +117,8 @@ void carve_plan(Carver& w, Plan& p, int B, int M, bool with_attention, int n_lay
   p.attn_queue = w.take<int32_t>((size_t)8 * n_layers);
 }
 
-// Sampler buffers of B sequences / M packed rows with n_vtiles statistics tiles per row (sel_logits and the
-// filter thresholds are laid out by the caller that needs them).
+// Sampler buffers of B sequences / M packed rows with n_vtiles statistics tiles per row (sel_logits is laid out by the
+// caller that needs it).
 void carve_sampler(Carver& w, SamplerBufs& sb, int B, int M, int n_vtiles) {
   sb.part_max = w.take<float>((size_t)n_vtiles * M);
   sb.part_sum = w.take<float>((size_t)n_vtiles * M);
@@ -133,7 +136,7 @@ void carve_sampler(Carver& w, SamplerBufs& sb, int B, int M, int n_vtiles) {
   sb.sel_pmax = w.take<float>(B);
   sb.sel_qmax = w.take<float>(B);
   sb.samp_sum = w.take<double>((size_t)B * 32 * 2);
-  sb.samp_mass = w.take<double>((size_t)B * 32 * 2);
+  sb.samp_mass = w.take<double>((size_t)B * 32);
   sb.sel_row = w.take<int32_t>(B);
   sb.sel_mode = w.take<int32_t>(B);
   sb.sel_qrow = w.take<int32_t>(B);
@@ -144,41 +147,28 @@ void carve_sampler(Carver& w, SamplerBufs& sb, int B, int M, int n_vtiles) {
   sb.sel_logits = nullptr;
 }
 
-// Lays the workspace out; with base == nullptr only measures it.
-size_t carve(bs_ctx* c, char* base) {
+// Lays the workspace of `bytes` bytes out (base == nullptr: only measures).  Returns the bytes the layout cannot do without;
+// `full` receives the bytes with which every call that gains from it keeps all its logits.
+size_t carve(bs_ctx* c, char* base, size_t bytes, bool fragments, size_t* full) {
   Carver w{base};
   const Shape& s = c->s;
   const int B = c->B_max, M = c->M_max;
   carve_plan(w, c->plan, B, M, true, s.L);
-  const size_t Mp = (M + 31) / 32 * 32;       // fragment-ordered activations are stored in whole 32-row tiles
+  c->fragments = fragments;
+  const size_t Mp = fragments ? (M + 31) / 32 * 32 : M;       // fragment-ordered activations are stored in whole 32-row tiles
   c->h = w.take<float>(Mp * s.d);
-  c->ssq = w.take<float>((size_t)(s.d / 32) * kSkinnyRows);
+  c->ssq = fragments ? w.take<float>((size_t)(s.d / 32) * kSkinnyRows) : nullptr;
+  c->sk.counters = fragments ? w.take<int32_t>(kSkinnyCounters) : nullptr;
   c->inv_freq = w.take<double>(64);
   c->rope_cos = w.take<float>((size_t)M * 64);
   c->rope_sin = w.take<float>((size_t)M * 64);
-  c->a = w.take<char>(Mp * s.d * elt(s.dtype));          // float16 and bf16 have the same size
-  c->qkv = w.take<float>((size_t)M * s.Nqkv());
-  c->q = w.take<char>((size_t)M * s.Hq * s.D * elt(s.dtype));
-  c->slabs = (s.dtype == BS_BF16)
-                 ? w.take<float>((size_t)kMaxGemmSplit * Mp * (s.Nqkv() > s.d ? s.Nqkv() : s.d))
-                 : nullptr;
-  c->sk.part = c->slabs;                      // as large as the partial tiles of up to kMaxGemmSplit K splits
-  c->sk.counters = w.take<int32_t>(kSkinnyCounters);
-  c->attn_out = w.take<char>(Mp * s.Hq * s.D * elt(s.dtype));
-  c->act = w.take<char>(Mp * s.F * elt(s.dtype));
   c->hf = w.take<char>((size_t)M * s.d * elt(s.dtype));
   c->attn_scratch = w.take<char>(attention_scratch_bytes(s, B, c->k_max));
   c->n_vtiles = lmhead_vtiles(s.V);
-  SamplerBufs& sb = c->sb;
-  carve_sampler(w, sb, B, M, c->n_vtiles);
+  carve_sampler(w, c->sb, B, M, c->n_vtiles);
   if (s.dtype == BS_F32) {
     c->full_logits = w.take<float>((size_t)M * s.V);
-    sb.sel_logits = nullptr;
   } else {
-    c->logit_rows = lmhead_logit_rows(s);
-    if (c->logit_rows > M) c->logit_rows = M;
-    c->full_logits = w.take<float>((size_t)c->logit_rows * s.V);
-    sb.sel_logits = c->logit_rows < M ? w.take<float>((size_t)B * s.V) : nullptr;
     c->pk_qkv.assign(s.L, nullptr); c->pk_o.assign(s.L, nullptr); c->pk_gu.assign(s.L, nullptr); c->pk_down.assign(s.L, nullptr);
     for (int l = 0; l < s.L; ++l) {
       c->pk_qkv[l] = w.take<uint16_t>(packed_weight_elems(s.Nqkv(), s.d));
@@ -188,7 +178,30 @@ size_t carve(bs_ctx* c, char* base) {
     }
     c->pk_lm = w.take<uint16_t>(packed_weight_elems(s.V, s.d));
   }
-  return (w.off + 255) & ~(size_t)255;
+  // what only the layers of a step use comes last, and the logits of the accept call lie on top of it
+  float* const step0 = w.take<float>(0);
+  const size_t off0 = w.off;
+  c->a = w.take<char>(Mp * s.d * elt(s.dtype));          // float16 and bf16 have the same size
+  c->q = w.take<char>((size_t)M * s.Hq * s.D * elt(s.dtype));
+  c->qkv = s.dtype == BS_F32 ? w.take<float>((size_t)M * s.Nqkv()) : nullptr;
+  c->slabs = (s.dtype == BS_BF16)
+                 ? w.take<float>((size_t)kMaxGemmSplit * Mp * (s.Nqkv() > s.d ? s.Nqkv() : s.d))
+                 : nullptr;
+  c->sk.part = c->slabs;                      // as large as the partial tiles of up to kMaxGemmSplit K splits
+  c->attn_out = w.take<char>(Mp * s.Hq * s.D * elt(s.dtype));
+  c->act = w.take<char>(Mp * s.F * elt(s.dtype));
+  size_t least = w.off;
+  *full = least;
+  if (s.dtype == BS_BF16) {
+    const size_t row = (size_t)s.V * sizeof(float), room = bytes > off0 ? (bytes - off0) / row : 0;
+    const int rows = lmhead_logit_rows(s) < M ? lmhead_logit_rows(s) : M;
+    c->full_logits = c->sb.sel_logits = step0;
+    c->logit_rows = room < (size_t)rows ? (int)room : rows;
+    if (off0 + B * row > least) least = off0 + B * row;
+    if (off0 + (rows > B ? rows : B) * row > *full) *full = off0 + (rows > B ? rows : B) * row;
+  }
+  *full = (*full + 255) & ~(size_t)255;
+  return least;
 }
 
 void fill_shape(bs_ctx* c, const bs_model_desc* d, int B_max, int k_max) {
@@ -252,7 +265,9 @@ size_t bs_workspace_bytes(const bs_model_desc* desc, int B_max, int k_max) {
   if (check_desc(desc, B_max, k_max) != BS_OK) return 0;
   bs_ctx tmp;
   fill_shape(&tmp, desc, B_max, k_max);
-  return carve(&tmp, nullptr);
+  size_t full;
+  carve(&tmp, nullptr, SIZE_MAX, skinny_applies(tmp.s, 1), &full);
+  return full;
 }
 
 bs_status bs_create(const bs_model_desc* desc, const bs_weights* w, const bs_kv_desc* kv, void* workspace,
@@ -271,8 +286,11 @@ bs_status bs_create(const bs_model_desc* desc, const bs_weights* w, const bs_kv_
   bs_ctx* c = new (std::nothrow) bs_ctx();
   if (!c) return BS_EINVAL;
   fill_shape(c, desc, B_max, k_max);
-  if (carve(c, nullptr) > workspace_bytes) { delete c; return BS_ECAPACITY; }
-  carve(c, (char*)workspace);
+  size_t full;
+  bool fragments = skinny_applies(c->s, 1);
+  if (fragments && carve(c, nullptr, workspace_bytes, true, &full) > workspace_bytes) fragments = false;   // small steps on the tiled kernels
+  if (carve(c, nullptr, workspace_bytes, fragments, &full) > workspace_bytes) { delete c; return BS_ECAPACITY; }
+  carve(c, (char*)workspace, workspace_bytes, fragments, &full);
   const int L = desc->n_layers;
   launch_clear_status(c->plan.status, (hipStream_t)stream);   // before the packing kernels, which may set BS_FAULT_RANGE
   for (int l = 0; l < L; ++l) {
@@ -310,7 +328,7 @@ bs_status bs_create(const bs_model_desc* desc, const bs_weights* w, const bs_kv_
   c->kv = KvView{kv->n_pages, kv->n_slots, kv->max_pages_per_seq, kv->block_table, kv->ctx_len};
   launch_rope_table(c->s, c->inv_freq, (hipStream_t)stream);
   launch_attention_init(c->s, c->B_max, c->attn_scratch, (hipStream_t)stream);
-  launch_zero_i32(c->sk.counters, (int)kSkinnyCounters, (hipStream_t)stream);
+  if (fragments) launch_zero_i32(c->sk.counters, (int)kSkinnyCounters, (hipStream_t)stream);
   st = check_hip(c);
   if (st != BS_OK) { bs_destroy(c); return st; }
   *out = c;
@@ -407,7 +425,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   const Plan& p = c->plan;
   launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attention_plan_params(s, B, k_max),
               s.L, st);
-  const bool skinny = skinny_applies(s, M_max) && !c->unfused_qkv;
+  const bool skinny = c->fragments && skinny_applies(s, M_max) && !c->unfused_qkv;
   if (skinny) launch_skinny_embed(s, p, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
   else launch_embed(s, p, M_max, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
@@ -503,7 +521,7 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
     if (all_rows) {
       sample_base = all_rows;
     } else {
-      sample_base = c->sb.sel_logits;
+      sample_base = c->sb.sel_logits;                  // at least B_max rows
       rows_selected = true;
     }
   }
@@ -705,9 +723,11 @@ bs_status bs_accept_resample_logits_noalloc(int B, int vocab, const float* logit
 // for models that would use the fused kernel, so that tests cover both.
 void bs_debug_unfused_qkv(bs_ctx* c, int on) { if (c) c->unfused_qkv = on != 0; }
 
-// Not part of the public ABI: address of an intermediate buffer of the last verify step, for
-// kernel-level debugging (0 h, 1 normed rows, 2 qkv f32, 3 q, 4 attention out, 5 mlp act, 6 final rows), or of
-// the last accept step (7, 8, 9: per-row filter threshold key, index cut, log of the kept mass).
+// Not part of the public ABI: address of an intermediate buffer, for kernel-level debugging.  Of the last verify step: 0 h, 1
+// normed rows, 2 qkv (float32 models), 3 q, 4 attention out, 5 mlp act, 6 final rows; 1 .. 5 hold until the next accept call
+// (bf16 models: it writes logits there).  bf16 steps of at most 32 rows (skinny.hip): 0, 4 and 5 are in fragment order
+// (h_frag_index, act_frag_index), and 1 holds the rows in front of gate/up only, in fragment order too.  Of the last accept step:
+// 7, 8, 9 per-row filter threshold key, index cut, log of the kept mass.
 void* bs_debug_buffer(bs_ctx* c, int which) {
   if (!c) return nullptr;
   switch (which) {

@@ -74,3 +74,26 @@ def test_bench_setup_guard_stops_on_non_finite_logits():
         with pytest.raises(SystemExit) as e:
             bench.check_finite(z, "set-up decode step 4 of stub")
         assert "set-up decode step 4" in str(e.value) and e.value.code != 0
+
+
+@pytest.mark.parametrize("name,B_max,k_max,accepted", [
+    ("s7b", 128, 16, 15160072192), ("s7b", 32, 8, 14409985792), ("s7b", 64, 0, 14282450432), ("s7b", 1, 0, 14226674432),
+    ("s1p5b", 256, 16, 4019766272), ("s1p5b", 64, 8, 3291568128), ("s1p5b", 1, 8, 3174217984), ("s1p5b", 61, 16, 3439172096),
+    ("mini_bf16", 4, 7, 48531456), ("mini_bf16", 1, 0, 46870784), ("tiny", 4, 4, 625664)])
+def test_workspace_sizes_that_were_enough_stay_enough(lib, name, B_max, k_max, accepted):
+    """Workspace sizes from before accept calls kept logits: a program that laid out its memory for them is not refused, and
+    the size that is asked for is at most 140 MB more.  The size is checked before anything is launched (the pointers here
+    are made up, so without a GPU a call that passes the check ends in BS_EHIP)."""
+    import torch
+    from paper_2605_08862_amd import workloads as W
+    if torch.cuda.is_available():
+        pytest.skip("made-up device pointers")
+    desc = W.shape(name)
+    cdesc, L = B.make_desc(desc), desc["n_layers"]
+    assert B.bs_workspace_bytes(cdesc, B_max, k_max) <= accepted + (140 << 20)
+    ptrs = (C.c_void_p * L)(*[4096] * L)
+    w = B.bs_weights(4096, 4096, 4096, ptrs, ptrs, ptrs, ptrs, ptrs, ptrs)
+    kv = B.bs_kv_desc(1, 1, 1, ptrs, ptrs, 4096, 4096)
+    create = lambda n: lib.bs_create(C.byref(cdesc), C.byref(w), C.byref(kv), 4096, n, B_max, k_max, None, C.byref(C.c_void_p()))
+    assert create(accepted) == B.BS_EHIP
+    assert create(accepted * 9 // 10) == B.BS_ECAPACITY
