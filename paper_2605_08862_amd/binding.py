@@ -107,11 +107,14 @@ def _ptr(t):
 
 
 def _stream():
-    """Current stream of the current device as an address (torch.cuda.current_stream() builds a Stream object around the same
-    value, 2.8 us a call: more than the launch it is fetched for)."""
+    """Current stream of the current device as an address.  torch.cuda.current_stream() builds a Stream object around the same
+    value, 2.8 us a call (more than the launch it is fetched for), so the address is read directly where torch has that."""
     if not torch.cuda.is_initialized():
         torch.cuda.init()
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _check(ctx, st):

@@ -97,3 +97,12 @@ def test_workspace_sizes_that_were_enough_stay_enough(lib, name, B_max, k_max, a
     create = lambda n: lib.bs_create(C.byref(cdesc), C.byref(w), C.byref(kv), 4096, n, B_max, k_max, None, C.byref(C.c_void_p()))
     assert create(accepted) == B.BS_EHIP
     assert create(accepted * 9 // 10) == B.BS_ECAPACITY
+
+
+def test_stream_address_without_the_private_torch_functions(monkeypatch):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert B._stream() == 77
