@@ -5,6 +5,7 @@ The oracle is the fp64 forward; the bound is the logit tolerance of all bf16 cas
 import pytest
 import torch
 
+from paper_2605_08862_amd import binding as B
 from paper_2605_08862_amd import workloads as W
 from paper_2605_08862_amd.runtime import Engine, fuse_weights
 from tests import helpers as H
@@ -51,3 +52,22 @@ def test_weights_aligned_to_their_elements_only(name, moved):
         assert eng.poll_status() == 0
         eng.close()
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("n_chunks", [0, 1, 3, 7])       # the rule's choice; one piece; several, merged by the last workgroup
+@pytest.mark.parametrize("heads,head_dim,k_max,ctx_lens,k_b", [
+    (14, 128, 16, [500], [16]),                       # G = 7: 119 query rows, four query tiles
+    (14, 128, 16, [333], [8]),                        # 63 rows: the two-tile variant of the wide kernel
+    (12, 128, 16, [0], [16]),                         # G = 6, empty cache
+    (6, 128, 30, [700], [30]),                        # G = 3: 93 rows, 31 packed rows
+    (6, 128, 30, [64], [0]),                          # three live query rows under a wide row limit
+])
+def test_wide_attention_in_front_of_the_small_step_kernels(heads, head_dim, k_max, ctx_lens, k_b, n_chunks):
+    """At most 32 packed rows and more than 64 query rows per KV head: the wide kernel writes its rows in fragment order, from
+    the workgroup itself (one chunk) and from the merge."""
+    desc = W.shape("mini_bf16", n_q_heads=heads, n_kv_heads=2, head_dim=head_dim, d_model=320, vocab=777)
+    B.bs_debug_attention_shape(0, n_chunks)
+    try:
+        _run_case(desc, ctx_lens=ctx_lens, k_b=k_b, k_max=k_max, seed=61)
+    finally:
+        B.bs_debug_attention_shape(0, 0)
