@@ -507,12 +507,12 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
   if (given_logits) launch_plan(p, c->kv, B, k_max, V, nullptr, nullptr, draft_tokens, draft_len, false, AttnPlan{}, 0, st);
   if (given_logits) {
     launch_logit_stats(p, M_max, V, given_logits, inv_temp, c->sb, st);
-    n_vtiles = kRowSegs;
+    n_vtiles = row_segs(V);
     sample_base = given_logits;
   } else if (s.dtype == BS_F32) {
     launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, nullptr, c->lm_head, c->full_logits, p.status, st);
     launch_logit_stats(p, M_max, V, c->full_logits, inv_temp, c->sb, st);
-    n_vtiles = kRowSegs;
+    n_vtiles = row_segs(V);
     sample_base = c->full_logits;
   } else {
     // with every row's logits in memory the sampled rows need no second LM-head pass
@@ -687,7 +687,7 @@ bs_status noalloc_state(bs_ctx** out) {
     for (int pass = 0; pass < 2; ++pass) {               // measure, then lay out
       Carver w{pass ? (char*)ptr : nullptr};
       carve_plan(w, c->plan, kNoAllocMaxB, kNoAllocMaxRows, false, 0);
-      carve_sampler(w, c->sb, kNoAllocMaxB, kNoAllocMaxRows, kRowSegs);
+      carve_sampler(w, c->sb, kNoAllocMaxB, kNoAllocMaxRows, kMaxRowSegs);
       if (w.off > kNoAllocScratchBytes) { delete c; return BS_ECAPACITY; }
     }
     g_noalloc[dev].ctx = c;

@@ -394,7 +394,10 @@ __device__ __forceinline__ bool filter_keeps(uint32_t key, int j, uint32_t f_key
   return key > f_key || (key == f_key && j <= f_idx);
 }
 struct FilterArgs { int on; int top_k; float top_p; const float* logits; int V; };
-constexpr int kRowSegs = 16;           // statistics entries per row of the plain-logits path: vocabulary segments
+// Statistics entries per row of the plain-logits path: vocabulary segments, a workgroup each.  No shorter than 1024 entries (four
+// per thread): with 16 segments whatever the length, 990 rows of 1000 entries took 69 us for the whole call, with one 59.
+constexpr int kMaxRowSegs = 16;
+inline int row_segs(int V) { return V >= kMaxRowSegs * 1024 ? kMaxRowSegs : (V + 1023) / 1024; }
 int lmhead_vtiles(int V);
 int lmhead_logit_rows(const Shape& s);
 void launch_lmhead_stats(const Shape& s, const Plan& p, int M_max, const void* hf, const void* lm_head,

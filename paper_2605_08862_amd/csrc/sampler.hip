@@ -22,7 +22,7 @@ __device__ __forceinline__ float rescale_exp(float from, float to, float inv_tem
 
 int lmhead_vtiles(int V) {
   const int a = (V + kLmVtile - 1) / kLmVtile;
-  return a > kRowSegs ? a : kRowSegs;
+  return a > kMaxRowSegs ? a : kMaxRowSegs;
 }
 
 // Row limit up to which phase 1 stores all logits (float32, 4 V bytes per row) instead of recomputing the sampled row of
@@ -172,9 +172,9 @@ __global__ void __launch_bounds__(256, (kLmMT <= 3 ? 2 : 1)) lmhead_kernel(const
 
 // ------------------------------------------------------------------ statistics of given float32 logits
 // One workgroup per (row, vocabulary segment), one entry of (max, sum exp, arg max) each; HBM bound: the row is read once,
-// sixteen bytes per load, four loads in flight per thread, maximum and rescaled sum kept online (batch 128 x 9 rows of 151936
+// sixteen bytes per load, four loads in flight per thread, maximum and rescaled sum kept online; len: entries per segment (batch 128 x 9 rows of 151936
 // logits, 700 MB: 232 us with one workgroup per 1024 entries and four-byte loads, 114 us).
-__global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int V, const float* __restrict__ logits,
+__global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int V, int len, const float* __restrict__ logits,
                                                           float inv_temp, SamplerBufs sb) {
   __shared__ float s_mx[4], s_sum[4];
   __shared__ int s_arg[4];
@@ -182,7 +182,6 @@ __global__ void __launch_bounds__(256) logit_stats_kernel(Plan p, int M_max, int
   if (m >= p.n_rows[0]) return;
   const int tgt = p.row_target[m];
   const float* z = logits + (size_t)m * V;
-  const int len = ((V + kRowSegs - 1) / kRowSegs + 3) & ~3;
   const int j0 = min(seg * len, V), j1 = min(j0 + len, V);
   float mx = -INFINITY, sum[4] = {0.f, 0.f, 0.f, 0.f};
   int arg = 0x7fffffff;
@@ -772,7 +771,8 @@ void launch_lmhead_rows(const Shape& s, int B, const void* hf, const void* lm_he
 }
 void launch_logit_stats(const Plan& p, int M_max, int V, const float* logits, float inv_temp, const SamplerBufs& sb,
                         hipStream_t st) {
-  hipLaunchKernelGGL(logit_stats_kernel, dim3(kRowSegs, M_max), dim3(256), 0, st, p, M_max, V, logits, inv_temp, sb);
+  const int segs = row_segs(V), len = ((V + segs - 1) / segs + 3) & ~3;      // whole groups of four
+  hipLaunchKernelGGL(logit_stats_kernel, dim3(segs, M_max), dim3(256), 0, st, p, M_max, V, len, logits, inv_temp, sb);
 }
 void launch_q_stats(const Plan& p, int M_max, int V, const void* q_logits, int q_dtype, const SamplerBufs& sb,
                     hipStream_t st) {

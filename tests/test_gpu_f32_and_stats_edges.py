@@ -105,3 +105,8 @@ def test_float32_attention_keeps_an_infinite_value(n_ctx):
     out = H.debug_buffer(eng, 4, desc["n_q_heads"] * desc["head_dim"]).cpu()
     assert out[0] == float("inf") and torch.isfinite(out[1:]).all()
     eng.close()
+
+
+@pytest.mark.parametrize("vocab", [1024, 1025, 2049, 15360, 15361, 16383, 16384])      # one segment per started 1024 entries, at most 16
+def test_plain_logits_sampler_where_the_segment_count_changes(vocab):
+    test_plain_logits_sampler_at_segment_edges(vocab, "bf16")
