@@ -1,10 +1,11 @@
 // LM head fused with softmax statistics, the accept scan of Alg. 1 and the residual / bonus
-// sampling of Eq. 2-3.  The [M, V] probabilities are never formed in HBM:
+// sampling of Eq. 2-3.  The [M, V] probabilities are never formed in HBM, and the logits only where phase 2 costs more than
+// writing them (up to lmhead_logit_rows rows):
 //   phase 1  LM-head GEMM over all M rows whose epilogue keeps, per (row, vocabulary tile), only
 //            (max, sum exp, arg max) of z/T and the logit of the draft token judged by the row;
 //   scan     per sequence, the first rejected draft (Eq. 2, general form min(1, p/q));
-//   phase 2  the one row per sequence that is sampled from (recovered, bonus or plain token) is
-//            recomputed by the same MFMA loop (bit-identical logits) and sampled by inverse CDF in
+//   phase 2  the one row per sequence that is sampled from (recovered, bonus or plain token) is read back, or
+//            recomputed by the same MFMA loop (bit-identical logits), and sampled by inverse CDF in
 //            vocabulary order with float64 running sums (Eq. 3 / max(0, p - q)).
 #include "gemm_mfma.h"
 
@@ -29,7 +30,8 @@ int lmhead_vtiles(int V) {
 // every sequence, which reads the 2 d V bytes of weights again.  Measured, phase 1 with stores against the second pass it
 // saves: 7B shape, 64 rows + 10 us / 210, 288 rows + 38 / 203, 576 rows + 87 / 205, 1152 rows no gain; 1.5B shape, 9 rows
 // + 4 / 85, 288 rows + 38 / 95, 432 rows no gain, 576 rows + 97 / 100.  (Storing whole lines by way of LDS changed nothing:
-// the writes compete with the weight stream, not with the issue slots.)
+// the writes compete with the weight stream, not with the issue slots.)  The rows lie on top of the layers' activations
+// and enlarge a workspace by what they exceed those: 7B shape, 288 rows (175 MB of logits) by 116 MB, 2176 rows (545 MB) by 95.
 int lmhead_logit_rows(const Shape& s) { return s.dtype == BS_BF16 ? s.d / 4 : 0; }
 
 // ------------------------------------------------------------------ phase 1 / phase 2 GEMM (bf16)

@@ -3,7 +3,7 @@
 // With so few rows a layer is bound by streaming its weights once, and the first obstacle is latency: 1.5B shape, nine
 // rows, the weights of a layer are 94 MB = 15 us at the rate a streaming read reaches, and the tiled GEMMs took 62 us
 // over six launches (normalisation, QKV, O, normalisation, gate/up, down), each with a pipeline fill, a tail and slabs.
-// Here a layer is four launches besides attention, shaped for that:
+// Here a layer is five launches besides attention (QKV, O, normalisation, gate/up, down), shaped for that:
 //   * one workgroup = one or two 32-row weight tiles, its waves split K between them: every wave streams its own part of
 //     the packed weights HBM -> registers, one contiguous KiB per load, and the partial tiles meet in LDS at the end.
 //     Where that gives fewer workgroups than CUs, K is also split across workgroups and the last one to arrive adds the
@@ -12,8 +12,8 @@
 //     KiB from L2 straight into operand registers: no LDS staging, no swizzle, no barrier in the main loop;
 //   * O and down add their result to the residual themselves and write the sum of squares of their 32 columns per row.  QKV
 //     adds those up and normalises the residual as it reads it; in front of gate/up the normalisation is one small
-//     element-wise kernel.  (A kernel costs about 2.4 us of launch besides its work.  In QKV the extra work is hidden, 1.5B shape:
-//     8.1 us against 6.1 + 4.0.  Gate/up has a wave per tile and every wave would convert the whole residual: 7B shape, staged
+//     element-wise kernel.  (A kernel costs about 2.4 us of launch besides its work.  In QKV the extra work is hidden, 1.5B shape,
+//     launch subtracted: 8.1 us against 6.1 + 4.0.  Gate/up has a wave per tile and every wave would convert the whole residual: 7B shape, staged
 //     in LDS once per workgroup, 56 us against 45 + 4.)
 // Loads are issued in the order in which they are waited for (the memory counter is in order).
 #include "gemm_mfma.h"

@@ -18,6 +18,11 @@ Typical use, one workload (every run from /tmp with TMPDIR=/tmp; W = workload na
   rocprofv3 --pmc WRITE_SIZE -d OUT/write -o w -- python3 bench.py --config W --no-sub --no-cpu-baseline --steps 3 --warmup 1 --copy-calibration
   python3 -m paper_2605_08862_amd.profile_summary --workload W --kt OUT/kt --fetch OUT/fetch --write OUT/write \\
           --bench-log OUT/kt.log > profiles/W_kernels.txt
+
+A case of perf/cases.py (C = its name) instead of a bench.py workload, kernel trace only; the poll after the warm-up passes marks
+the main phase there too (a sampler case clears the status word in every call):
+  PYTHONPATH=<checkout> rocprofv3 --kernel-trace --stats -d OUT/kt -o kt -- python3 -c "<CASE_DRIVER>" C
+  python3 -m paper_2605_08862_amd.profile_summary --case C --kt OUT/kt >> profiles/cases_kernels.txt
 """
 import argparse
 import glob
@@ -27,6 +32,8 @@ import sqlite3
 import sys
 
 CLASS_ORDER = ["attention", "gemm_qkv", "gemm_o", "gemm_gate_up", "gemm_down", "lmhead"]
+CASE_DRIVER = ("import sys, torch; from perf import cases as C; s = C.prepare([c for c in C.listed() if c['name'] == sys.argv[1]][0], 1); "
+               "[C.run(s) for _ in range(5)]; 'eng' in s and s['eng'].poll_status(); [C.run(s) for _ in range(30)]; torch.cuda.synchronize()")
 CALIBRATION_KIB = 262144.0          # the 256 MiB copy of bench.py --copy-calibration
 
 
@@ -185,7 +192,8 @@ def derived_rates(c, ordered, classes, lines):
 
 def main():
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
-    ap.add_argument("--workload", required=True)
+    ap.add_argument("--workload")
+    ap.add_argument("--case", help="a case of perf/cases.py was run instead of a bench.py workload")
     ap.add_argument("--kt", help="directory of the --kernel-trace run")
     ap.add_argument("--fetch", help="directory of the --pmc FETCH_SIZE run (with --copy-calibration)")
     ap.add_argument("--write", help="directory of the --pmc WRITE_SIZE run (with --copy-calibration)")
@@ -194,6 +202,11 @@ def main():
     ap.add_argument("--bench-args", default="", help="further bench.py arguments every pass was run with (e.g. '--layers 2')")
     ap.add_argument("--note", action="append", default=[], help="free text for the header (repeatable)")
     args = ap.parse_args()
+    if args.case:
+        lines = ["rocprofv3 --kernel-trace --stats -d OUT/kt -o kt -- python3 -c \"<CASE_DRIVER of profile_summary.py>\" %s   (one MI355X)" % args.case]
+        kernel_trace(args.kt, lines)
+        print("\n".join(lines) + "\n")
+        return
     lines = ["rocprofv3 summary of bench.py --config %s (one MI355X), written by paper_2605_08862_amd/profile_summary.py." % args.workload,
              "Only the main phase of each run is counted (set-up steps are cut off).  Commands, each run from /tmp with",
              "TMPDIR=/tmp and bench.py given by its path in the checkout:"]
