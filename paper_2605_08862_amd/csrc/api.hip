@@ -430,15 +430,16 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   const bool skinny = c->fragments && skinny_applies(s, M_max) && !c->unfused_qkv;
   if (skinny) launch_skinny_embed(s, p, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
   else launch_embed(s, p, M_max, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  const bool fused_qkv = qkv_rope_applies(s, M_max) && !c->unfused_qkv;
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
-  SlabRule pending{0, 0, 0, 0, 0};              // slabs of the last residual projection not yet added to h
+  SlabRule pending{0, 0, 0, 0, 0, 0};             // slabs of the last residual projection not yet added to h
   for (int l = 0; l < s.L; ++l) {
     { ProfScope ps(c, BS_PROF_EMPTY, st); }
     if (skinny) {
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
         launch_skinny_qkv(s, p, c->kv, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
                           c->q, c->k_pages[l], c->v_pages[l], c->sk, st); }
-      launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, true,
+      launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, kSkinnyRows,
                        c->attn_scratch, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
       { ProfScope ps(c, BS_PROF_GEMM_O, st);
         launch_skinny_resid(s, p, s.Hq * s.D, c->attn_out, c->wo[l], c->h, c->ssq, c->sk, st); }
@@ -449,33 +450,33 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       continue;
     }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->attn_norm[l], c->a, st);
-    if (qkv_rope_supported(s) && !c->unfused_qkv) {
+    if (fused_qkv) {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
       launch_qkv_rope(s, p, c->kv, M_max, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
     } else {
-      int nq;
+      SlabRule nq;
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-        nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, nullptr, c->wqkv[l],
+        nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
                          slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st); }
-      launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq > 0 ? nq : 1, c->q,
+      launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
-    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, false, c->attn_scratch,
+    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, M_max, c->attn_scratch,
                      c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
     { ProfScope ps(c, BS_PROF_GEMM_O, st);
-      pending = launch_gemm_resid(s.dtype, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],
-                                  slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st); }
+      pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st); }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->mlp_norm[l], c->a, st);
     { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
-      launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, nullptr, c->w_gate_up[l], c->act, p.status, st); }
+      launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, c->w_gate_up[l], c->act, p.status, st); }
     { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
-      pending = launch_gemm_resid(s.dtype, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
-                                  slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st); }
+      pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st); }
   }
   if (skinny) launch_skinny_final_norm(s, p, M_max, c->h, c->ssq, c->final_norm, c->hf, st);
   else launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->final_norm, c->hf, st);
   if (logits_debug && s.dtype == BS_F32)
-    launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, nullptr, c->lm_head, logits_debug, p.status, st);
+    launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, c->lm_head, logits_debug, p.status, st);
   if (logits_debug && s.dtype == BS_BF16) {
     // same kernel and loop order as the fused path of bs_accept_resample, so the values are identical
     launch_lmhead_stats(s, p, M_max, c->hf, c->lm_head, 1.0f, c->sb, logits_debug, st);
@@ -510,7 +511,7 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
     n_vtiles = row_segs(V);
     sample_base = given_logits;
   } else if (s.dtype == BS_F32) {
-    launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, nullptr, c->lm_head, c->full_logits, p.status, st);
+    launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.V, s.d, c->hf, c->lm_head, c->full_logits, p.status, st);
     launch_logit_stats(p, M_max, V, c->full_logits, inv_temp, c->sb, st);
     n_vtiles = row_segs(V);
     sample_base = c->full_logits;
@@ -534,7 +535,7 @@ static bs_status accept_common(bs_ctx* c, int B, int V, const float* given_logit
   launch_accept_scan(p, B, k_max, M_max, n_vtiles, q_logits != nullptr, temperature, eos_id, emit_bonus, u_accept, c->sb,
                      filter, n_accepted, out_tokens, n_emitted, near_tie, st);
   if (temperature > 0.f) {
-    if (rows_selected) launch_lmhead_rows(s, B, c->hf, c->lm_head, c->sb, st);
+    if (rows_selected) launch_lmhead_rows(s, B, M_max, c->hf, c->h, c->lm_head, c->sb, st);   // the residual is not needed any more
     ProfScope ps(c, BS_PROF_SAMPLE, st);
     launch_sample(B, k_max, V, sample_base, rows_selected, q_logits, q_dtype, temperature, filter.on != 0, u_sample, c->sb,
                   n_accepted, out_tokens, n_emitted, near_tie, st);
@@ -725,10 +726,10 @@ bs_status bs_accept_resample_logits_noalloc(int B, int vocab, const float* logit
 // for models that would use the fused kernel, so that tests cover both.
 void bs_debug_unfused_qkv(bs_ctx* c, int on) { if (c) c->unfused_qkv = on != 0; }
 
-// Not part of the public ABI: address of an intermediate buffer, for kernel-level debugging.  Of the last verify step: 0 h, 1
+// Not part of the public ABI: address of an intermediate buffer, for kernel-level debugging.  Of the last verify step: 0 h (until an accept call gathers rows there), 1
 // normed rows, 2 qkv (float32 models), 3 q, 4 attention out, 5 mlp act, 6 final rows; 1 .. 5 hold until the next accept call
-// (bf16 models: it writes logits there).  bf16 steps of at most 32 rows (skinny.hip): 0, 4 and 5 are in fragment order
-// (h_frag_index, act_frag_index), and 1 holds the rows in front of gate/up only, in fragment order too.  Of the last accept step:
+// (bf16 models: it writes logits there).  bf16 models: 1, 4, 5 and 6 are in chunk order (act_index), ld = row limit of the step; steps of at
+// most 32 rows (skinny.hip): 0 is in fragment order (h_frag_index), 1, 4 and 5 have ld = 32, and 1 holds the rows in front of gate/up only.  Of the last accept step:
 // 7, 8, 9 per-row filter threshold key, index cut, log of the kept mass.
 void* bs_debug_buffer(bs_ctx* c, int which) {
   if (!c) return nullptr;

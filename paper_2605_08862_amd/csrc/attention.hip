@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
                                                         const f16* __restrict__ v_pages, f16* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         int32_t* __restrict__ counters, int32_t* __restrict__ queue,
-                                                        int q_blocks, int out_frag, int32_t* __restrict__ status) {
+                                                        int q_blocks, int out_ld, int32_t* __restrict__ status) {
   constexpr int KS = D / 16;            // MFMA K-steps of the QK^T product
   constexpr int DT = D / 32;            // 32-wide d tiles of the output
   constexpr int RP = 32 * NQ * QG;      // padded query rows per workgroup
@@ -89,9 +89,6 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, wgs_per_xcd = gridDim.x >> 3;
   const int n_live = min(attn_meta[1] * Hkv, n_units);
   const int total_w = (n_live > xcd ? (n_live - xcd + 7) / 8 : 0) * q_blocks;   // pairs of this XCD
-  auto out_index = [&](int row, int col) -> size_t {
-    return out_frag ? act_frag_index(row, col, Hq * D / 64) : (size_t)row * Hq * D + col;
-  };
   // Combines the n_ch chunks of one (sequence, KV head, query block): called by the last workgroup to publish its
   // partial rows.  Four chunks' loads are in flight together; the sums run in chunk order.
   auto merge_unit = [&](const int b, const int h, const int qb, const int n_ch) {
@@ -140,9 +137,10 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
     const float inv = 1.0f / lt;
     const int orow = row0 + iq, ocol = (h * G + hg) * D;
 #pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      *(f16x4*)(out + out_index(orow, ocol + (sub + j * TPR) * 4)) =
-          to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
+    for (int j = 0; j < CPT; j += 2)
+      store_chunk_pair(out, orow, ocol, sub + j * TPR, TPR, out_ld,
+                       to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status),
+                       to_f16x4_guarded(acc[j + 1][0] * inv, acc[j + 1][1] * inv, acc[j + 1][2] * inv, acc[j + 1][3] * inv, status));
   };
   auto process = [&](const int unit, const int qb) {
   const int item = unit / Hkv, h = unit % Hkv;
@@ -380,20 +378,24 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
       const int orow = row0 + iq, ocol = (h * G + hg) * D;
       const uint32_t pr = (uint32_t)(chunk * Hkv) * RP * q_blocks + qr;   // row of this chunk, counted from chunk 0 of (sequence, head)
 #pragma unroll
-      for (int j = 0; j < CH / TPR; ++j) {
-        const int ch = sub + j * TPR;
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < CH / TPR; j += 2) {
+        f32x4 acc[2];
 #pragma unroll
-        for (int w = 0; w < WPG; ++w) {
-          const f32x4 v = *(const f32x4*)(s_o + ((size_t)(g * WPG + w) * ROWS_W + lr) * LDO + ch * 4);
+        for (int u = 0; u < 2; ++u) {
+          const int ch = sub + (j + u) * TPR;
+          acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += v[e] * mw[w];
+          for (int w = 0; w < WPG; ++w) {
+            const f32x4 v = *(const f32x4*)(s_o + ((size_t)(g * WPG + w) * ROWS_W + lr) * LDO + ch * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[u][e] += v[e] * mw[w];
+          }
+          if (n_ch > 1) wt_store4(bo, (pr * D + ch * 4) * 4, acc[u]);
         }
-        if (n_ch == 1) {
-          *(f16x4*)(out + out_index(orow, ocol + ch * 4)) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
-        } else {
-          wt_store4(bo, (pr * D + ch * 4) * 4, acc);
-        }
+        if (n_ch == 1)
+          store_chunk_pair(out, orow, ocol, sub + j * TPR, TPR, out_ld,
+                           to_f16x4_guarded(acc[0][0] * inv, acc[0][1] * inv, acc[0][2] * inv, acc[0][3] * inv, status),
+                           to_f16x4_guarded(acc[1][0] * inv, acc[1][1] * inv, acc[1][2] * inv, acc[1][3] * inv, status));
       }
       if (n_ch > 1 && sub == 0) wt_store2(bm, pr * 8, mt, lt);
     }
@@ -504,7 +506,7 @@ void launch_attention_init(const Shape& s, int B_max, void* scratch, hipStream_t
 
 template <int NQ, int QG, int D>
 static void launch_mfma_attn(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int M_max, const void* q,
-                             const void* k_pages, const void* v_pages, void* out, bool out_frag, void* scratch, int q_blocks,
+                             const void* k_pages, const void* v_pages, void* out, int out_ld, void* scratch, int q_blocks,
                              int s_min, void* prof_token, hipStream_t st) {
   constexpr int RP = 32 * NQ * QG;
   const int rpt = RP * q_blocks;                                       // padded query rows of a unit
@@ -528,13 +530,13 @@ static void launch_mfma_attn(const Shape& s, const Plan& p, const KvView& kv, in
                      p.item_start, p.item_seq, p.item_chunk, kv.block_table, kv.max_pages, kv.n_pages, n_units, s.Hq,
                      s.Hkv, scale_log2e, (const f16*)q,
                      (const f16*)k_pages, (const f16*)v_pages, (f16*)out, part_o, part_ml, counters, p.attn_queue + 8 * layer, q_blocks,
-                     out_frag ? 1 : 0, p.status);
+                     out_ld, p.status);
   if (prof_token) attention_prof_mark(prof_token, st, false);
 }
 
 template <int D>
 static void launch_wide_attn(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, const void* q,
-                             const void* k_pages, const void* v_pages, void* out, bool out_frag, void* scratch, int s_min,
+                             const void* k_pages, const void* v_pages, void* out, int out_ld, void* scratch, int s_min,
                              void* prof_token, hipStream_t st) {
   constexpr int NF = D / 16 + 2 * (D / 32);
   size_t lds = (size_t)8 * 32 * (D + 4) * 4 + 2 * 8 * 32 * 4;          // merge: accumulators of 8 waves + statistics
@@ -553,12 +555,12 @@ static void launch_wide_attn(const Shape& s, const Plan& p, const KvView& kv, in
   hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, st, p.seq_k, p.seq_c, p.row_start, p.seq_slot, p.attn_meta,
                      p.item_start, p.item_seq, p.item_chunk, kv.block_table, kv.max_pages, kv.n_pages, n_units, s.Hq,
                      s.Hkv, scale_log2e, (const f16*)q, (const f16*)k_pages, (const f16*)v_pages, (f16*)out, part_o,
-                     part_ml, (int32_t*)scratch, p.attn_queue + 8 * layer, out_frag ? 1 : 0, p.status);
+                     part_ml, (int32_t*)scratch, p.attn_queue + 8 * layer, out_ld, p.status);
   if (prof_token) attention_prof_mark(prof_token, st, false);
 }
 
 void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int k_max, int M_max,
-                      const void* q, const void* k_pages, const void* v_pages, void* out, bool out_frag, void* scratch,
+                      const void* q, const void* k_pages, const void* v_pages, void* out, int out_ld, void* scratch,
                       void* prof_token, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)s.D);
   if (s.dtype == BS_F32) {
@@ -571,12 +573,12 @@ void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer
   const int tiles_wg = rows_padded(s, k_max) / 32 / q_blocks;      // query tiles per workgroup: 1, 2 or 4
 #define BS_ATTN(NQ, QG)                                                                                         \
   do {                                                                                                          \
-    if (s.D == 128) launch_mfma_attn<NQ, QG, 128>(s, p, kv, layer, B, B_max, M_max, q, k_pages, v_pages, out, out_frag, scratch, q_blocks, s_min, prof_token, st); \
-    else launch_mfma_attn<NQ, QG, 64>(s, p, kv, layer, B, B_max, M_max, q, k_pages, v_pages, out, out_frag, scratch, q_blocks, s_min, prof_token, st);   \
+    if (s.D == 128) launch_mfma_attn<NQ, QG, 128>(s, p, kv, layer, B, B_max, M_max, q, k_pages, v_pages, out, out_ld, scratch, q_blocks, s_min, prof_token, st); \
+    else launch_mfma_attn<NQ, QG, 64>(s, p, kv, layer, B, B_max, M_max, q, k_pages, v_pages, out, out_ld, scratch, q_blocks, s_min, prof_token, st);   \
   } while (0)
   if (tiles_wg == 1) BS_ATTN(1, 1);
   else if (tiles_wg == 2) BS_ATTN(2, 1);
-  else if (s.D == 128) launch_wide_attn<128>(s, p, kv, layer, B, B_max, q, k_pages, v_pages, out, out_frag, scratch, s_min, prof_token, st);
-  else launch_wide_attn<64>(s, p, kv, layer, B, B_max, q, k_pages, v_pages, out, out_frag, scratch, s_min, prof_token, st);
+  else if (s.D == 128) launch_wide_attn<128>(s, p, kv, layer, B, B_max, q, k_pages, v_pages, out, out_ld, scratch, s_min, prof_token, st);
+  else launch_wide_attn<64>(s, p, kv, layer, B, B_max, q, k_pages, v_pages, out, out_ld, scratch, s_min, prof_token, st);
 #undef BS_ATTN
 }

@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
                                                         const f16* __restrict__ v_pages, f16* __restrict__ out,
                                                         float* __restrict__ part_o, float* __restrict__ part_ml,
                                                         int32_t* __restrict__ counters, int32_t* __restrict__ queue,
-                                                        int out_frag, int32_t* __restrict__ status) {
+                                                        int out_ld, int32_t* __restrict__ status) {
   constexpr int KS = D / 16;            // MFMA K-steps of the QK^T product = K fragments of a tile
   constexpr int DT = D / 32;            // 32-wide d tiles of the output; V fragments of a tile = 2 DT
   constexpr int NF = KS + 2 * DT;       // 1 KiB fragments of one K/V tile
@@ -58,9 +58,6 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
   // per launch (7B heads unless stated): 128 sequences of 512 .. 32768 tokens 347 -> 341 us, one of 1000 tokens 26.8 -> 21.6,
   // 1.5B heads, 61 prompts around 512 tokens 35.4 -> 30.3.
   auto thread_now = [&]() { int t = threadIdx.x; asm volatile("" : "+v"(t)); return t; };
-  auto out_index = [&](int row, int col) -> size_t {
-    return out_frag ? act_frag_index(row, col, Hq * D / 64) : (size_t)row * Hq * D + col;
-  };
   // Combines the n_ch chunks of one (sequence, KV head): called by the last workgroup to publish its partial rows.
   // Four threads per query row; two chunks' loads are in flight together, the sums run in chunk order.
   auto merge_unit = [&](const int b, const int h, const int n_ch) {
@@ -108,9 +105,10 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     const float inv = 1.0f / lt;
     const int orow = row_start[b] + iq, ocol = (h * G + hg) * D;
 #pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      *(f16x4*)(out + out_index(orow, ocol + (sub + j * TPR) * 4)) =
-          to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status);
+    for (int j = 0; j < CPT; j += 2)
+      store_chunk_pair(out, orow, ocol, sub + j * TPR, TPR, out_ld,
+                       to_f16x4_guarded(acc[j][0] * inv, acc[j][1] * inv, acc[j][2] * inv, acc[j][3] * inv, status),
+                       to_f16x4_guarded(acc[j + 1][0] * inv, acc[j + 1][1] * inv, acc[j + 1][2] * inv, acc[j + 1][3] * inv, status));
   };
 
   // One unit with NQT query tiles (2 or 4).
@@ -290,17 +288,24 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
         const int orow = row0 + iq, ocol = (h * G + hg) * D;
         const uint32_t pr = (uint32_t)(chunk * Hkv) * RPT + wr;   // row of this chunk, counted from chunk 0 of (sequence, head)
 #pragma unroll
-        for (int j = 0; j < CH / TPR; ++j) {
-          const int ch = sub + j * TPR;
-          f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < CH / TPR; j += 2) {
+          f32x4 acc[2];
 #pragma unroll
-          for (int w = 0; w < NPH; ++w) {
-            const f32x4 v = *(const f32x4*)(s_o + ((size_t)(w * NQT + tq) * 32 + lr) * LDO + ch * 4);
+          for (int u = 0; u < 2; ++u) {
+            const int ch = sub + (j + u) * TPR;
+            acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] += v[e] * mw[w];
+            for (int w = 0; w < NPH; ++w) {
+              const f32x4 v = *(const f32x4*)(s_o + ((size_t)(w * NQT + tq) * 32 + lr) * LDO + ch * 4);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[u][e] += v[e] * mw[w];
+            }
+            if (n_ch > 1) wt_store4(bo, (pr * D + ch * 4) * 4, acc[u]);
           }
-          if (n_ch == 1) *(f16x4*)(out + out_index(orow, ocol + ch * 4)) = to_f16x4_guarded(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv, status);
-          else wt_store4(bo, (pr * D + ch * 4) * 4, acc);
+          if (n_ch == 1)
+            store_chunk_pair(out, orow, ocol, sub + j * TPR, TPR, out_ld,
+                             to_f16x4_guarded(acc[0][0] * inv, acc[0][1] * inv, acc[0][2] * inv, acc[0][3] * inv, status),
+                             to_f16x4_guarded(acc[1][0] * inv, acc[1][1] * inv, acc[1][2] * inv, acc[1][3] * inv, status));
         }
         if (n_ch > 1 && sub == 0) wt_store2(bm, pr * 8, mt, lt);
       }

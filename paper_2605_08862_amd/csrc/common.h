@@ -268,6 +268,7 @@ void launch_embed(const Shape& s, const Plan& p, int M_max, const void* embed, f
                   float* cos_t, float* sin_t, hipStream_t st);
 // h[r] += sum of n_slabs slabs [M_max, d] (n_slabs may be 0), then out[r] = RMSNorm(h[r]).
 struct SlabRule;
+// float32 models: out row-major; bf16 models: chunk order, ld = M_max
 void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabRule& n_slabs,
                     const float* gain, void* out, hipStream_t st);
 // qkv is the float32 projection, given as n_slabs >= 1 slabs [M_max, Nqkv] that are summed.
@@ -275,71 +276,96 @@ void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const fl
 void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st);
 // cos_t / sin_t: [M_max][D/2] tables of the step's packed rows (filled by launch_embed, once per step).
 void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
-                        const float* qkv, int n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
+                        const float* qkv, const SlabRule& slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,
                     void* k_rows, void* v_rows, bool to_pages, int32_t* status, hipStream_t st);
 // qkv_rope.hip   QKV projection + rotary + KV append in one kernel (bf16 models with head size 128); A = normed
 // rows (float16), Wp = packed wqkv.
-bool qkv_rope_supported(const Shape& s);
+bool qkv_rope_applies(const Shape& s, int M_max);
 void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
+// Float16 activations of bf16 models (normalised rows, attention output, gated activation, final rows), "chunk order": the eight
+// elements k .. k + 7 (k % 8 == 0) of a row are one 16-byte chunk, and the chunks of one k of all rows are neighbours, ld chunks
+// from one k to the next (ld: row limit of the step).  The order of the k is that of the packed weights, so a fragment of
+// the MFMA (32 rows x 16 of K) is two runs of 512 bytes: GEMMs copy it to LDS as it is, no buffer needs padding rows, and an
+// epilogue whose lanes are rows stores runs instead of pieces of rows.
+__host__ __device__ __forceinline__ size_t act_index(int row, int k, int ld) {
+  return ((size_t)((k >> 6) * 8 + ((k >> 3) & 3) * 2 + ((k >> 5) & 1)) * ld + row) * 8 + (k & 7);
+}
+// Stores columns 4 ch .. 4 ch + 3 (y0) and 4 (ch + n) .. (y1) of a row, n even: lanes 2 i and 2 i + 1 hold neighbouring ch and exchange
+// halves, so that every store is a whole chunk.
+__device__ __forceinline__ void store_chunk_pair(f16* out, int row, int col, int ch, int n, int ld, f16x4 y0, f16x4 y1) {
+  const bool odd = ch & 1;
+  typedef int i2 __attribute__((ext_vector_type(2)));
+  const i2 own = __builtin_bit_cast(i2, odd ? y1 : y0), give = __builtin_bit_cast(i2, odd ? y0 : y1);
+  const i2 got{__builtin_amdgcn_mov_dpp(give[0], 0xB1, 0xf, 0xf, true), __builtin_amdgcn_mov_dpp(give[1], 0xB1, 0xf, 0xf, true)};   // quad_perm 1 0 3 2
+  typedef int i4 __attribute__((ext_vector_type(4)));
+  const i4 v = odd ? i4{got[0], got[1], own[0], own[1]} : i4{own[0], own[1], got[0], got[1]};
+  *(i4*)(out + act_index(row, col + 4 * (odd ? ch - 1 + n : ch), ld)) = v;
+}
 // gemm.hip   C[M,N] (+)= A[M,K] * W[N,K]^T with an epilogue.  float32 models: A, W float32 row-major.
-// bf16 models: A float16 row-major, W the packed float16 copy made by launch_pack_weight.
-enum GemmEpilogue { EPI_STORE = 0, EPI_RESID_ADD = 1, EPI_SWIGLU = 2, EPI_STORE_F32 = 3 };
-// Returns the number of K-split slabs written (bf16 models, EPI_RESID_ADD / EPI_STORE_F32: `out` is the
-// slab buffer [split][M_max][N] and the consumer sums the slabs), or 0 when `out` was updated in place
-// (float32 models).
+// bf16 models: A float16 in chunk order with ld = M_max, W the packed float16 copy made by launch_pack_weight.
+enum GemmEpilogue { EPI_RESID_ADD = 1, EPI_SWIGLU = 2, EPI_STORE_F32 = 3 };
 constexpr int kMaxGemmSplit = 8;
+// Time of a float32-result GEMM launch in units of 0.01 us, without its fixed part: rounds of the CUs (cap = two workgroups per CU)
+// x K tiles per split x time of a K tile, and what a further slab costs its writer and its reader.
+__host__ __device__ __forceinline__ int gemm_split_cost(int tiles, int nk, int cap, int s, int t_tile, int t_slab) {
+  const int rounds = (int)ceilf((float)(tiles * s) * (2.0f / (float)cap));
+  return (rounds > 0 ? rounds : 1) * ((nk + s - 1) / s) * t_tile + (s - 1) * t_slab;
+}
+// One slab of M x N float32 written and read at 4.5 TB/s.
+__host__ __device__ __forceinline__ int gemm_slab_cost(int M, int N) { return (int)((float)M * (float)N * (1.0f / 5625.0f)); }
+// Number of K splits: the one of least time, at most 6, at least 4 K tiles each, all workgroups resident at once.
+__host__ __device__ __forceinline__ int gemm_adaptive_split(int tiles, int nk, int cap, int t_tile = 90, int t_slab = 0) {
+  int best = 1, cost = gemm_split_cost(tiles, nk, cap, 1, t_tile, t_slab);
+#pragma unroll
+  for (int s = 2; s <= 6; ++s) {
+    const int c = gemm_split_cost(tiles, nk, cap, s, t_tile, t_slab);
+    if (4 * s <= nk && tiles * s <= cap && c < cost) { best = s; cost = c; }
+  }
+  return best;
+}
 // Number of K-split slabs a float32-epilogue GEMM writes: fixed on the host (bm == 0), or decided on the DEVICE from
 // the step's row count M, which only the device knows (draft lengths may come straight from the lookup kernel): the
-// launch is sized for the row limit, the kernel and the consumer of the slabs both evaluate slabs(M).  The rule: as
-// many K splits (at most 4, at least 4 K tiles each) as keep all workgroups of the live row blocks resident at once.
-__host__ __device__ __forceinline__ int gemm_adaptive_split(int tiles, int nk, int cap) {
-  int s = tiles > 0 ? cap / tiles : 1;
-  if (s > 4) s = 4;
-  if (s > nk / 4) s = nk / 4;
-  return s < 1 ? 1 : s;
-}
+// launch is sized for the row limit, the kernel and the consumer of the slabs both evaluate slabs(M).
 struct SlabRule {
   int fixed;                    // slab count when bm == 0 (0: the output was updated in place)
   int bm, n_blocks, nk, cap;    // device rule: row tile, column blocks, K tiles, resident workgroups
   int bm_alt;                   // second row tile the producer may choose on the device (0: none)
-  // Row tile of the step: with two candidates, the one whose launch is shorter by this model: all workgroups of a
-  // round run at once, a workgroup's time ~ rows of its tile x K tiles of its split, and the 128-row loop does
-  // about 5 % more work per unit of time.
+  int n_blocks_alt = 0;         // its column blocks (0: the same)
+  int t = 90, t_alt = 90;       // time of a K tile (gemm_split_cost)
+  int slab_cols = 0;            // columns of the output (0: slabs cost nothing)
+  __host__ __device__ int slab_cost(int M) const { return gemm_slab_cost(M, slab_cols); }
+  __host__ __device__ int blocks(int b) const { return b == bm_alt && n_blocks_alt > 0 ? n_blocks_alt : n_blocks; }
+  // Row tile of the step: with two candidates, the one whose launch is shorter.
   __host__ __device__ int tile_rows(int M) const {
     if (bm_alt == 0) return bm;
-    long cost[2];
+    int cost[2];
     for (int i = 0; i < 2; ++i) {
-      const int b = i ? bm_alt : bm, tiles = ((M + b - 1) / b) * n_blocks, s = gemm_adaptive_split(tiles, nk, cap);
-      const int rounds = (tiles * s + cap - 1) / cap;
-      cost[i] = (long)b * ((nk + s - 1) / s) * (rounds > 0 ? rounds : 1) * (b == 128 ? 19 : 20);
+      const int b = i ? bm_alt : bm, tiles = ((M + b - 1) / b) * blocks(b), tt = i ? t_alt : t;
+      cost[i] = gemm_split_cost(tiles, nk, cap, gemm_adaptive_split(tiles, nk, cap, tt, slab_cost(M)), tt, slab_cost(M));
     }
     return cost[1] < cost[0] ? bm_alt : bm;
   }
   __host__ __device__ int slabs(int M) const {
     if (bm == 0) return fixed;
     const int b = tile_rows(M);
-    return gemm_adaptive_split(((M + b - 1) / b) * n_blocks, nk, cap);
+    return gemm_adaptive_split(((M + b - 1) / b) * blocks(b), nk, cap, bm_alt != 0 && b == bm_alt ? t_alt : t, slab_cost(M));
   }
 };
-// status: the step's device status word (float16-range faults of the float16 epilogues).
-SlabRule launch_gemm_resid(int dtype, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W,
-                           void* out, int32_t* status, hipStream_t st);
-int launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K,
-                const void* A, const int32_t* a_rows /*optional gather*/, const void* W, void* out,
-                int32_t* status, hipStream_t st);
+// status: the step's device status word (float16-range faults of the float16 epilogues).  Returns the slabs written (bf16 models,
+// EPI_RESID_ADD / EPI_STORE_F32: `out` is the slab buffer [split][M_max][N] and the consumer sums them), none where `out` was
+// updated in place (float32 models).
+SlabRule launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
+                     int32_t* status, hipStream_t st);
+// time (0.01 us, without the fixed part of a launch) of an EPI_STORE_F32 launch of at most 640 rows
+int gemm_slab_time(int M_max, int N, int K);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weight(const void* w_bf16, int N, int K, void* packed_f16, int32_t* status, hipStream_t st);
-// skinny.hip   decoder layer of steps with at most kSkinnyRows packed rows (bf16 models with head size 128); activations and the
-// residual in fragment order.
+// skinny.hip   decoder layer of steps with at most kSkinnyRows packed rows (bf16 models with head size 128); activations in chunk
+// order with ld = kSkinnyRows (a fragment is one contiguous KiB), the residual in fragment order.
 constexpr int kSkinnyRows = 32;
-// Offset of element (row, k) of a float16 activation matrix with nk K tiles of 64, in MFMA fragment order (the layout of the
-// packed weights: 4 KiB blocks [K-step][lane][8] per (32 rows, K tile)); elements k .. k + 7, k % 8 == 0, are contiguous.
-__host__ __device__ __forceinline__ size_t act_frag_index(int row, int k, int nk) {
-  return ((size_t)((row >> 5) * nk + (k >> 6)) * 4 + ((k >> 3) & 3)) * 512 + (((k >> 5) & 1) * 32 + (row & 31)) * 8 + (k & 7);
-}
-// The same for the float32 residual: a fragment is two contiguous KiB, k .. k + 3 (k % 4 == 0) contiguous.
+// The float32 residual of these steps: a fragment (act_index) is two contiguous KiB, k .. k + 3 (k % 4 == 0) contiguous.
 __host__ __device__ __forceinline__ size_t h_frag_index(int row, int k, int nk) {
   return ((size_t)((row >> 5) * nk + (k >> 6)) * 8 + ((k >> 3) & 3) * 2 + ((k >> 2) & 1)) * 256 + (((k >> 5) & 1) * 32 + (row & 31)) * 4 + (k & 3);
 }
@@ -358,14 +384,14 @@ void launch_skinny_gate_up(const Shape& s, const Plan& p, const float* h, const 
 void launch_skinny_resid(const Shape& s, const Plan& p, int K, const void* X, const void* W, float* h, float* ssq,
                          const SkinnyBufs& sk, hipStream_t st);
 // attention.hip
-// out_frag: the output rows in fragment order (act_frag_index) instead of row-major (bf16 models).
+// out_ld: ld of the output rows (bf16 models: chunk order, act_index).
 // attention_plan_params gives the work-list parameters launch_plan needs for the same (B, k_max);
 // launch_attention_init clears the completion counters once, at context creation.
 AttnPlan attention_plan_params(const Shape& s, int B, int k_max);
 void launch_attention_init(const Shape& s, int B_max, void* scratch, hipStream_t st);
 void launch_zero_i32(int32_t* p, int n, hipStream_t st);
 void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int k_max, int M_max,
-                      const void* q, const void* k_pages, const void* v_pages, void* out, bool out_frag, void* scratch,
+                      const void* q, const void* k_pages, const void* v_pages, void* out, int out_ld, void* scratch,
                       void* prof_token, hipStream_t st);
 void attention_prof_mark(void* token, hipStream_t st, bool begin);   // api.hip: event pair around the main kernel
 size_t attention_scratch_bytes(const Shape& s, int B_max, int k_max);
@@ -404,7 +430,8 @@ void launch_lmhead_stats(const Shape& s, const Plan& p, int M_max, const void* h
                          float inv_temp, const SamplerBufs& sb, float* logits_debug, hipStream_t st);
 void launch_logit_stats(const Plan& p, int M_max, int V, const float* logits, float inv_temp,
                         const SamplerBufs& sb, hipStream_t st);
-void launch_lmhead_rows(const Shape& s, int B, const void* hf, const void* lm_head, const SamplerBufs& sb,
+// rows: scratch for the B selected rows [d] of hf (chunk order, ld = M_max; sb.sel_row), float16
+void launch_lmhead_rows(const Shape& s, int B, int M_max, const void* hf, void* rows, const void* lm_head, const SamplerBufs& sb,
                         hipStream_t st);
 void launch_q_stats(const Plan& p, int M_max, int V, const void* q_logits, int q_dtype, const SamplerBufs& sb,
                     hipStream_t st);

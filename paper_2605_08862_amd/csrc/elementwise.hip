@@ -29,7 +29,7 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 }
 
 // out[r] = h[r] * gain / sqrt(mean(h[r]^2) + eps), float32 in; out is the GEMM operand type
-// (float32 for float32 models, float16 for bf16 models).
+// (float32 for float32 models: row-major; float16 for bf16 models: chunk order with ld rows).
 // With n_slabs > 0 the row first absorbs the K-split slabs of the preceding residual projection:
 // h[r] += sum_s slabs[s][r] (the updated residual is written back).
 // One workgroup per row; the row (d <= 1024 * NV floats) stays in registers between the sum of squares
@@ -38,12 +38,16 @@ template <typename T> struct Vec4;
 template <> struct Vec4<float> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct Vec4<f16> { typedef _Float16 type __attribute__((ext_vector_type(4))); };
 
-template <typename T, int NV>
-__global__ void __launch_bounds__(256) rmsnorm_kernel(Plan p, int d, float eps, float* __restrict__ h,
+template <typename T, int NV, int NT = 256>
+__global__ void __launch_bounds__(NT) rmsnorm_kernel(Plan p, int d, float eps, float* __restrict__ h,
                                                       const float* __restrict__ slabs, SlabRule rule, size_t slab_stride,
-                                                      const float* __restrict__ gain, T* __restrict__ out) {
-  __shared__ float red[4];
-  const int r = blockIdx.x;
+                                                      const float* __restrict__ gain, T* __restrict__ out, int ld) {
+  constexpr bool CHUNKS = std::is_same<T, f16>::value;
+  __shared__ float red[NT / 64];
+  // Workgroup ids are dealt round-robin to the 8 XCDs.  In chunk order a 128-byte line holds eight rows' chunks: eight consecutive
+  // rows go to one XCD, whose L2 then puts the line together.
+  const int id = blockIdx.x, r = CHUNKS ? (id & ~63) + (id & 7) * 8 + ((id >> 3) & 7) : id;
+  if (CHUNKS && r >= ld) return;
   const int n_rows = p.n_rows[0];                        // a fixed slab count leaves this wait until the row's loads are in flight
   // With the device rule the slab count needs the row count before the first slab load anyway, so the rows beyond
   // the count leave here instead of loading what they never store (a step with 1185 of at most 2176 rows fetched
@@ -56,7 +60,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(Plan p, int d, float eps, 
   f4 v[NV], gn[NV];
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
-    const int i = (it * 256 + threadIdx.x) * 4;          // d is a multiple of 64: 16-byte accesses throughout
+    const int i = (it * NT + threadIdx.x) * 4;          // d is a multiple of 64: 16-byte accesses throughout
     v[it] = f4{0.f, 0.f, 0.f, 0.f};
     gn[it] = v[it];
     if (i < d) {
@@ -64,9 +68,9 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(Plan p, int d, float eps, 
       gn[it] = *(const f4*)(gain + i);
     }
   }
-  // slabs are added in index order; four slabs' loads are issued together (a slab index past the end is clamped
+  // slabs are added in index order; four slabs' loads (eight with few rows) are issued together (a slab index past the end is clamped
   // and its value dropped), so that a row costs one memory round trip instead of one per slab
-  constexpr int GS = NV <= 4 ? 4 : 1;
+  constexpr int GS = NT > 256 ? 8 : NV <= 4 ? 4 : 1;
   for (int s0 = 0; s0 < n_slabs; s0 += GS) {
     f4 t[GS][NV];
 #pragma unroll
@@ -74,7 +78,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(Plan p, int d, float eps, 
       const int s = min(s0 + u, n_slabs - 1);
 #pragma unroll
       for (int it = 0; it < NV; ++it) {
-        const int i = (it * 256 + threadIdx.x) * 4;
+        const int i = (it * NT + threadIdx.x) * 4;
         t[u][it] = f4{0.f, 0.f, 0.f, 0.f};
         if (i < d) t[u][it] = *(const f4*)(sl + (size_t)s * slab_stride + i);
       }
@@ -90,31 +94,107 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(Plan p, int d, float eps, 
   float ss = 0.f;
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
-    const int i = (it * 256 + threadIdx.x) * 4;
+    const int i = (it * NT + threadIdx.x) * 4;
     if (n_slabs > 0 && i < d) *(f4*)(x + i) = v[it];
     ss += v[it][0] * v[it][0] + v[it][1] * v[it][1] + v[it][2] * v[it][2] + v[it][3] * v[it][3];
   }
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
-  ss = red[0] + red[1] + red[2] + red[3];
+  ss = 0.f;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) ss += red[w];
   const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  T* o = out + (size_t)r * d;
 #pragma unroll
   for (int it = 0; it < NV; ++it) {
-    const int i = (it * 256 + threadIdx.x) * 4;
+    const int i = (it * NT + threadIdx.x) * 4;
     if (i < d) {
-      if constexpr (std::is_same<T, f16>::value) {
-        *(f16x4*)(o + i) = to_f16x4_guarded(v[it][0] * inv * gn[it][0], v[it][1] * inv * gn[it][1],
-                                            v[it][2] * inv * gn[it][2], v[it][3] * inv * gn[it][3], p.status);
+      if constexpr (CHUNKS) {
+        *(f16x4*)(out + act_index(r, i, ld)) = to_f16x4_guarded(v[it][0] * inv * gn[it][0], v[it][1] * inv * gn[it][1],
+                                                                v[it][2] * inv * gn[it][2], v[it][3] * inv * gn[it][3], p.status);
       } else {
         typename Vec4<T>::type w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = from_f32<T>(v[it][e] * inv * gn[it][e]);
-        *(typename Vec4<T>::type*)(o + i) = w;
+        *(typename Vec4<T>::type*)(out + (size_t)r * d + i) = w;
       }
     }
   }
+}
+
+// Many rows, chunk order: four rows per workgroup, two waves each, put together in LDS so that a store instruction writes the four
+// rows' chunks of 16 k as runs of 64 bytes; two groups of four (a 128-byte line) go to one XCD.  Row per workgroup, 16-byte
+// pieces: 23.2 us at 3700 rows of 1536 and one slab, 18.6 here.
+__global__ void __launch_bounds__(512) rmsnorm_rows_kernel(Plan p, int d, float eps, float* __restrict__ h, const float* __restrict__ slabs,
+                                                           SlabRule rule, size_t slab_stride, const float* __restrict__ gain,
+                                                           f16* __restrict__ out, int ld) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) char lds[];            // [4][d] float16, rows 32 bytes apart in the banks
+  __shared__ float red[8];
+  const int id = blockIdx.x, r0 = ((id & ~15) + (id & 7) * 2 + ((id >> 3) & 1)) * 4;
+  const int n_rows = min(p.n_rows[0], ld);
+  if (r0 >= n_rows) return;
+  const int n_slabs = rule.slabs(n_rows);
+  const int wave = threadIdx.x >> 6, rr = wave >> 1, t128 = threadIdx.x & 127, lds_row = 2 * d + 32;
+  const int r = min(r0 + rr, n_rows - 1);                // a row past the end is computed again and stored by nobody
+  float* x = h + (size_t)r * d;
+  const float* sl = slabs + (size_t)r * d;
+  constexpr int NV = 4;                                  // d <= 2048
+  f4 v[NV], gn[NV];
+#pragma unroll
+  for (int it = 0; it < NV; ++it) {
+    const int i = (it * 128 + t128) * 4;
+    v[it] = f4{0.f, 0.f, 0.f, 0.f};
+    gn[it] = v[it];
+    if (i < d) {
+      v[it] = *(const f4*)(x + i);
+      gn[it] = *(const f4*)(gain + i);
+    }
+  }
+  constexpr int GS = 4;                                  // slabs in flight together
+  for (int s0 = 0; s0 < n_slabs; s0 += GS) {
+    f4 t[GS][NV];
+#pragma unroll
+    for (int u = 0; u < GS; ++u) {
+      const int s = s0 + u;
+#pragma unroll
+      for (int it = 0; it < NV; ++it) {
+        const int i = (it * 128 + t128) * 4;
+        t[u][it] = f4{0.f, 0.f, 0.f, 0.f};
+        if (i < d && s < n_slabs) t[u][it] = *(const f4*)(sl + (size_t)s * slab_stride + i);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < GS; ++u)
+      if (s0 + u < n_slabs) {
+#pragma unroll
+        for (int it = 0; it < NV; ++it) v[it] += t[u][it];
+      }
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int it = 0; it < NV; ++it) {
+    const int i = (it * 128 + t128) * 4;
+    if (n_slabs > 0 && i < d && r0 + rr < n_rows) *(f4*)(x + i) = v[it];
+    ss += v[it][0] * v[it][0] + v[it][1] * v[it][1] + v[it][2] * v[it][2] + v[it][3] * v[it][3];
+  }
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((threadIdx.x & 63) == 0) red[wave] = ss;
+  __syncthreads();
+  ss = red[wave & 6] + red[wave | 1];
+  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+  for (int it = 0; it < NV; ++it) {
+    const int i = (it * 128 + t128) * 4;
+    if (i < d && r0 + rr < n_rows)
+      *(f16x4*)(lds + rr * lds_row + i * 2) = to_f16x4_guarded(v[it][0] * inv * gn[it][0], v[it][1] * inv * gn[it][1],
+                                                               v[it][2] * inv * gn[it][2], v[it][3] * inv * gn[it][3], p.status);
+  }
+  __syncthreads();
+  const int row = r0 + (threadIdx.x & 3);
+  if (row < n_rows)
+    for (int c = threadIdx.x >> 2; c < d / 8; c += 128)
+      *(f4*)(out + act_index(row, c * 8, ld)) = *(const f4*)(lds + (threadIdx.x & 3) * lds_row + c * 16);
 }
 
 // Inverse rotary frequencies theta^(-2j/D), j < D/2, in float64 (filled once per context).
@@ -128,84 +208,93 @@ __global__ void rope_table_kernel(int D, float theta, double* __restrict__ inv_f
 // float32, as n_slabs K-split slabs that are summed here (so each of q, k, v is rounded exactly once, after
 // the rotation): q goes to the query buffer (float16 for bf16 models: it is an attention operand, not
 // cache data), k and v to the slot's page in the cache dtype.
-// One workgroup per row; a work item is four consecutive rotation pairs of one head (two 16-byte loads
-// per slab, 8-byte stores) or four consecutive v elements.
+// A work item is four consecutive rotation pairs of one head (two 16-byte loads per slab, 8-byte stores) or four consecutive v
+// elements; a thread has one, a row several workgroups.  Latency bound: the loads of four slabs go out together, before the row is
+// known to be live or its page is known (64 .. 136 rows of the 7B shape, 5 .. 7 slabs one after the other and three items a thread: 8.4 .. 11.8 us).
 template <typename T, typename TQ, typename TP>
 __global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int Hq, int Hkv, int D,
                                                           const float* __restrict__ cos_t, const float* __restrict__ sin_t,
-                                                          const float* __restrict__ qkv, int n_slabs, size_t slab_stride,
+                                                          const float* __restrict__ qkv, SlabRule rule, size_t slab_stride,
                                                           TQ* __restrict__ q_out, TP* __restrict__ k_pages,
                                                           TP* __restrict__ v_pages) {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  const int r = blockIdx.x;
-  if (r >= p.n_rows[0]) return;
+  const int r = blockIdx.x, idx = blockIdx.y * 256 + threadIdx.x;
+  const int n_rows = p.n_rows[0];
+  if (rule.bm != 0 && r >= n_rows) return;               // the device rule needs the row count before the first slab load anyway
+  const int n_slabs = max(rule.slabs(n_rows), 1);
+  const int half = D / 2, groups = half / 4;
+  const int n_rot = (Hq + Hkv) * groups, n_items = n_rot + Hkv * D / 4;
+  if (idx >= n_items) return;
+  const bool rot = idx < n_rot;
+  const int hh = rot ? idx / groups : 0, j = rot ? (idx % groups) * 4 : 0;
+  const int e0 = rot ? 0 : (idx - n_rot) * 4;            // four consecutive v elements of one head
+  const float* x = qkv + (size_t)r * (Hq + 2 * Hkv) * D + (rot ? hh * D + j : (Hq + Hkv) * D + e0);
+  const int x2_at = rot ? half : 0;
+  f4 x1 = f4{0.f, 0.f, 0.f, 0.f}, x2 = x1, c = x1, sn = x1;
+  if (rot) { c = *(const f4*)(cos_t + (size_t)r * half + j); sn = *(const f4*)(sin_t + (size_t)r * half + j); }
+  for (int s0 = 0; s0 < n_slabs; s0 += 4) {              // added in index order; an index past the end is clamped and its value dropped
+    f4 t1[4], t2[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* xs = x + (size_t)min(s0 + u, n_slabs - 1) * slab_stride;
+      t1[u] = *(const f4*)xs;
+      t2[u] = *(const f4*)(xs + x2_at);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < n_slabs) { x1 += t1[u]; x2 += t2[u]; }
+  }
+  if (r >= n_rows) return;                               // rows beyond the count: loaded (in bounds), never stored
+  float y1[4], y2[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    y1[e] = x1[e] * c[e] - x2[e] * sn[e];
+    y2[e] = x2[e] * c[e] + x1[e] * sn[e];
+  }
+  if (rot && hh < Hq) {
+    TQ* qrow = q_out + (size_t)r * Hq * D;
+    if constexpr (std::is_same<TQ, f16>::value) {
+      *(f16x4*)(qrow + hh * D + j) = to_f16x4_guarded(y1[0], y1[1], y1[2], y1[3], p.status);
+      *(f16x4*)(qrow + hh * D + j + half) = to_f16x4_guarded(y2[0], y2[1], y2[2], y2[3], p.status);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        qrow[hh * D + j + e] = from_f32<TQ>(y1[e]);
+        qrow[hh * D + j + half + e] = from_f32<TQ>(y2[e]);
+      }
+    }
+    return;
+  }
   const int b = p.row_seq[r];
   const int pos = p.seq_c[b] + p.row_pos[r];
-  const int half = D / 2, groups = half / 4;
-  const float* row = qkv + (size_t)r * (Hq + 2 * Hkv) * D;
-  const int n_rot = (Hq + Hkv) * groups, n_items = n_rot + Hkv * D / 4;
-  TQ* qrow = q_out + (size_t)r * Hq * D;
   const int page = kv.block_table[(size_t)p.seq_slot[b] * kv.max_pages + pos / kPage];
   const int tok = pos % kPage;
   const size_t pbase = (size_t)page * kv_page_elems(Hkv, D);
-  for (int idx = threadIdx.x; idx < n_items; idx += 256) {
-    if (idx < n_rot) {
-      const int hh = idx / groups, j = (idx % groups) * 4;
-      const float* x = row + (size_t)hh * D + j;
-      f4 x1 = f4{0.f, 0.f, 0.f, 0.f}, x2 = x1;
-      for (int sl = 0; sl < n_slabs; ++sl) { x1 += *(const f4*)(x + sl * slab_stride); x2 += *(const f4*)(x + sl * slab_stride + half); }
-      const f4 c = *(const f4*)(cos_t + (size_t)r * half + j), sn = *(const f4*)(sin_t + (size_t)r * half + j);
-      float y1[4], y2[4];
+  // rounded to the cache dtype T, stored in the page encoding TP
+  auto rt = [](float v) { return to_f32<T>(from_f32<T>(v)); };
+  if (rot) {
+    const int kh = hh - Hq;
+    TP* k1 = k_pages + pbase + k_index<TP>(D, kh, tok, j);   // four consecutive d are contiguous in both page layouts
+    TP* k2 = k_pages + pbase + k_index<TP>(D, kh, tok, j + half);
+    if constexpr (std::is_same<TP, f16>::value) {
+      *(f16x4*)k1 = to_f16x4_guarded(rt(y1[0]), rt(y1[1]), rt(y1[2]), rt(y1[3]), p.status);
+      *(f16x4*)k2 = to_f16x4_guarded(rt(y2[0]), rt(y2[1]), rt(y2[2]), rt(y2[3]), p.status);
+    } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        y1[e] = x1[e] * c[e] - x2[e] * sn[e];
-        y2[e] = x2[e] * c[e] + x1[e] * sn[e];
+        k1[e] = from_f32<TP>(rt(y1[e]));
+        k2[e] = from_f32<TP>(rt(y2[e]));
       }
-      if (hh < Hq) {
-        if constexpr (std::is_same<TQ, f16>::value) {
-          *(f16x4*)(qrow + hh * D + j) = to_f16x4_guarded(y1[0], y1[1], y1[2], y1[3], p.status);
-          *(f16x4*)(qrow + hh * D + j + half) = to_f16x4_guarded(y2[0], y2[1], y2[2], y2[3], p.status);
-        } else {
+    }
+  } else {
+    const int kh = e0 / D, dd = e0 % D;
+    if constexpr (std::is_same<TP, f16>::value) {
+      const f16x4 w = to_f16x4_guarded(rt(x1[0]), rt(x1[1]), rt(x1[2]), rt(x1[3]), p.status);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            qrow[hh * D + j + e] = from_f32<TQ>(y1[e]);
-            qrow[hh * D + j + half + e] = from_f32<TQ>(y2[e]);
-          }
-        }
-      } else {
-        const int kh = hh - Hq;
-        // rounded to the cache dtype T, stored in the page encoding TP (four consecutive d are contiguous in
-        // both page layouts)
-        TP* k1 = k_pages + pbase + k_index<TP>(D, kh, tok, j);
-        TP* k2 = k_pages + pbase + k_index<TP>(D, kh, tok, j + half);
-        if constexpr (std::is_same<TP, f16>::value) {
-          auto rt = [](float x) { return to_f32<T>(from_f32<T>(x)); };
-          *(f16x4*)k1 = to_f16x4_guarded(rt(y1[0]), rt(y1[1]), rt(y1[2]), rt(y1[3]), p.status);
-          *(f16x4*)k2 = to_f16x4_guarded(rt(y2[0]), rt(y2[1]), rt(y2[2]), rt(y2[3]), p.status);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            k1[e] = from_f32<TP>(to_f32<T>(from_f32<T>(y1[e])));
-            k2[e] = from_f32<TP>(to_f32<T>(from_f32<T>(y2[e])));
-          }
-        }
-      }
+      for (int e = 0; e < 4; ++e) v_pages[pbase + v_index<TP>(D, kh, tok, dd + e)] = w[e];
     } else {
-      const int e0 = (idx - n_rot) * 4;                  // four consecutive v elements of one head
-      const int kh = e0 / D, dd = e0 % D;
-      const float* x = row + (size_t)(Hq + Hkv) * D + e0;
-      f4 v = f4{0.f, 0.f, 0.f, 0.f};
-      for (int sl = 0; sl < n_slabs; ++sl) v += *(const f4*)(x + sl * slab_stride);
-      if constexpr (std::is_same<TP, f16>::value) {
-        auto rt = [](float x) { return to_f32<T>(from_f32<T>(x)); };
-        const f16x4 w = to_f16x4_guarded(rt(v[0]), rt(v[1]), rt(v[2]), rt(v[3]), p.status);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v_pages[pbase + v_index<TP>(D, kh, tok, dd + e)] = w[e];
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          v_pages[pbase + v_index<TP>(D, kh, tok, dd + e)] = from_f32<TP>(to_f32<T>(from_f32<T>(v[e])));
-      }
+      for (int e = 0; e < 4; ++e) v_pages[pbase + v_index<TP>(D, kh, tok, dd + e)] = from_f32<TP>(rt(x1[e]));
     }
   }
 }
@@ -315,22 +404,30 @@ void launch_embed(const Shape& s, const Plan& p, int M_max, const void* embed, f
 void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabRule& n_slabs,
                     const float* gain, void* out, hipStream_t st) {
   const size_t stride = (size_t)M_max * s.d;
-#define BS_RMS(T_, NV_) hipLaunchKernelGGL((rmsnorm_kernel<T_, NV_>), dim3(M_max), dim3(256), 0, st, p, s.d, s.eps, h, slabs, n_slabs, stride, gain, (T_*)out)
-  if (s.dtype == BS_F32) { if (s.d <= 2048) BS_RMS(float, 2); else if (s.d <= 4096) BS_RMS(float, 4); else BS_RMS(float, 16); }
-  else                   { if (s.d <= 2048) BS_RMS(f16, 2);   else if (s.d <= 4096) BS_RMS(f16, 4);   else BS_RMS(f16, 16); }
+#define BS_RMS(T_, NV_, NT_) hipLaunchKernelGGL((rmsnorm_kernel<T_, NV_, NT_>), dim3(s.dtype == BS_F32 ? M_max : (M_max + 63) / 64 * 64), dim3(NT_), 0, st, p, s.d, s.eps, h, slabs, n_slabs, stride, gain, (T_*)out, M_max)
+  if (s.dtype == BS_F32) { if (s.d <= 2048) BS_RMS(float, 2, 256); else if (s.d <= 4096) BS_RMS(float, 4, 256); else BS_RMS(float, 16, 256); }
+  else if (s.d > 4096) BS_RMS(f16, 16, 256);
+  // Few rows are one round of workgroups at most, and up to 8 slabs of them: all of a row's loads in one trip.
+  else if (M_max <= 640) { if (s.d <= 2048) BS_RMS(f16, 1, 512); else BS_RMS(f16, 2, 512); }
+  // Four rows per workgroup need several rounds of workgroups: 3700 rows of 1536 23.2 -> 18.6 us; 976 rows 8.6 -> 9.2; 1185 rows of
+  // 3584 (28 floats a thread) 17.4 -> 25.8.
+  else if (s.d <= 2048 && M_max > 2048)
+    hipLaunchKernelGGL(rmsnorm_rows_kernel, dim3((M_max + 63) / 64 * 16), dim3(512), 4 * (2 * s.d + 32), st, p, s.d, s.eps, h, slabs, n_slabs, stride, gain, (f16*)out, M_max);
+  else { if (s.d <= 2048) BS_RMS(f16, 2, 256); else BS_RMS(f16, 4, 256); }
 #undef BS_RMS
 }
 void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st) {
   hipLaunchKernelGGL(rope_table_kernel, dim3(1), dim3(64), 0, st, s.D, s.theta, inv_freq);
 }
 void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
-                        const float* qkv, int n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
+                        const float* qkv, const SlabRule& n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const size_t stride = (size_t)M_max * s.Nqkv();
+  const int y = ((s.Hq + s.Hkv) * s.D / 8 + s.Hkv * s.D / 4 + 255) / 256;
   if (s.dtype == BS_F32)
-    hipLaunchKernelGGL((rope_append_kernel<float, float, float>), dim3(M_max), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
+    hipLaunchKernelGGL((rope_append_kernel<float, float, float>), dim3(M_max, y), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
                        qkv, n_slabs, stride, (float*)q_out, (float*)k_pages, (float*)v_pages);
   else
-    hipLaunchKernelGGL((rope_append_kernel<bf16, f16, f16>), dim3(M_max), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
+    hipLaunchKernelGGL((rope_append_kernel<bf16, f16, f16>), dim3(M_max, y), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
                        qkv, n_slabs, stride, (f16*)q_out, (f16*)k_pages, (f16*)v_pages);
 }
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,

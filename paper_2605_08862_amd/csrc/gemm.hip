@@ -1,9 +1,9 @@
 // Projection GEMMs of the verify pass (Sec. 3.3 "token-wise" linear layers):
 //   QKV (float32 out), O (+residual), gate/up (+SwiGLU), down (+residual).
-// bf16 models run on the f16 MFMA main loop of gemm_mfma.h over packed weights; float32 models (the
+// bf16 models run on the f16 MFMA main loop of gemm_dma.h over packed weights; float32 models (the
 // tiny parity configuration, latency bound) run on the float32 MFMA.
-#include "gemm_mfma.h"
-#include "gemm_ring2.h"
+#include "gemm_dma.h"
+#include <type_traits>
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 // same function with the hardware reciprocal (1 ulp): used in the MFMA epilogue, where a full-precision
@@ -121,394 +121,289 @@ void launch_pack_weight(const void* w_bf16, int N, int K, void* packed_f16, int3
                      N, K, (f16*)packed_f16, n_chunks, status);
 }
 
-// ------------------------------------------------------------------ MFMA kernel (bf16 models)
-constexpr int kOneRound = 512;    // workgroups that are certainly resident at once (256 CUs, up to two per CU)
-// Workgroup tile: BM = 32*MT rows x 4 waves x NT weight row tiles.  For SwiGLU NT == 2 and the two row
-// tiles of a wave are the gate rows and the matching up rows of the same 32 output features, so both
-// land in the same lane.  Grid: one dimension.  Workgroup ids are dealt round-robin to the 8 XCDs,
-// each with its own L2, so the id is decoded XCD-first: the (K split, N block, M block) space, M block
-// fastest, is cut into 8 contiguous ranges, one per XCD.  The M blocks that share a weight tile then run back
-// to back on one XCD and hit its L2, and an XCD touches one or two K ranges of the activation matrix only
-// (measured before this mapping: the down projection fetched 122 MB per launch for 38 MB of operands, every L2
-// pulling the whole matrix).
-// The float32 epilogues (QKV projection, residual projections) write one partial [M_max, N] slab per K split,
-// out[split][m][n]; the consumer (rotary kernel, RMSNorm kernel) sums the slabs.  Float atomics into the
-// residual were measured at ~25 us per launch and are not used.
-template <int MT, int NT, int EPI>
-__global__ void __launch_bounds__(256, (MT <= 3 ? 2 : 1)) gemm_mfma_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K,
-                                                        const f16* __restrict__ A, const int32_t* __restrict__ a_rows,
-                                                        const f16* __restrict__ Wp, void* __restrict__ out,
-                                                        int m_blocks, int n_blocks, int n_split, int defer_rows,
-                                                        int32_t* __restrict__ status, int adaptive_cap) {
-  // accumulators hold C^T tiles (SWAP): a lane owns one activation row and, per group of four
-  // registers, four consecutive output columns, so the epilogue stores 8 or 16 bytes per lane
-  using G = MfmaGemm<MT, NT, true>;
-  extern __shared__ __align__(16) char lds[];
-  // The row count lives in device memory.  A launch that fits the chip in one round does not wait for it before
-  // its first loads (defer_rows): it reads and multiplies all M_max rows - those at or beyond the count are stale
-  // rows of the same buffer, each affecting only its own output row - and applies the count to the stores.  A
-  // many-round launch reads it first and skips the row blocks beyond it.
-  int M = (!defer_rows && n_rows_dev) ? min(*n_rows_dev, M_max) : M_max;
-  if (adaptive_cap > 0) {
-    // The launch is sized for the row limit; the row blocks that are live and the number of K splits follow from
-    // the step's row count (SlabRule: the consumer of the slabs evaluates the same rule)
-    m_blocks = (M + G::BM - 1) / G::BM;
-    n_split = gemm_adaptive_split(m_blocks * n_blocks, K / kBK, adaptive_cap);
-  }
-  // XCD-first decoding: the (split, N block, M block) space, M block fastest, is cut into 8 contiguous ranges,
-  // one per XCD (workgroup ids are dealt round-robin to the XCDs)
-  const int tiles = m_blocks * n_blocks, total = tiles * n_split;
-  const int per_xcd = (total + 7) / 8;
-  const int flat = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if ((int)(blockIdx.x / 8) >= per_xcd || flat >= total) return;
-  const int split = flat / tiles, id = flat % tiles;
-  const int mb = id % m_blocks, nb = id / m_blocks;
-  const int m0 = mb * G::BM;
-  if (m0 >= M) return;
-  constexpr bool GLU = (EPI == EPI_SWIGLU);
-  static_assert(!GLU || NT == 2, "SwiGLU pairs one gate tile with one up tile per wave");
-  constexpr int NOUT_W = GLU ? 32 : NT * 32;            // output columns per wave
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n_wave0 = (nb * 4 + wave) * NOUT_W;
-  const int nk = K / kBK;
-  const int n_tiles = (N + 31) / 32;                    // row tiles of the packed matrix (per half for SwiGLU)
-
-  typename G::Operands op;
+// ------------------------------------------------------------------ bf16 models
+// ---- gate/up projection + SwiGLU.  F = features; the packed matrix holds the F gate rows, then the F up rows.  Both rows of a
+// feature land in the same lane:
+//   NW even  the wave's weight tiles alternate: gate tile, up tile of the same 32 features;
+//   NW == 1  ("mixed") a tile is 16 gate rows and their 16 up rows, put together by the lanes' addresses: accumulator registers i
+//            and i + 8.  16 features per wave instead of 32 fill 256 CUs in finer steps.
+struct GluArgs {
+  const int32_t* n_rows_dev;
+  int M_max, F, K;
+  const f16 *A, *Wp;
+  f16* out;
+  int32_t* status;
+};
+// Tiles id, id + stride, .. of m_blocks x n_blocks, M block fastest.
+template <typename G>
+__device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_blocks, int id0, int stride, int n, char* lds) {
+  constexpr bool MIX = G::NW == 1;
+  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
+  const size_t tile_bytes = (size_t)(g.K / kBK) * 4096, half = (size_t)(g.F / 32) * tile_bytes;    // up rows behind the gate rows
+  const int t_last = g.F / 32 - 1;
+  const uint32_t w_lane = MIX ? (lg * 32 + (ln & 15)) * 16u + (ln >= 16 ? (uint32_t)half : 0u) : lane * 16u;
+  auto operands = [&](typename G::Operands& op, int id) {
+    const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT;
+    // position t: features 16 (t0 + t) .. (mixed), or the gate (t even) / up (t odd) rows of features 32 ((t0 + t) / 2) ..
+    auto w_at = [&](int t) -> size_t { return min((t0 + t) >> 1, t_last) * tile_bytes + (((t0 + t) & 1) ? (MIX ? 256 : half) : 0); };
+    G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp, w_at, w_lane, 0);
+  };
+  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int id) {
+    const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT, M = min(*g.n_rows_dev, g.M_max);
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    int row, g, s;
-    G::chunk_of(i, row, g, s);
-    int r = min(m0 + row, M - 1);
-    if (a_rows) r = a_rows[r];
-    op.x_rows[i] = A + (size_t)r * K + g * 32 + s * 8;
-    op.x_lds[i] = G::chunk_lds_offset(row, g, s);
-  }
+    for (int a = 0; a < G::MW; ++a) {
+      const int m = m0 + (wm * G::MW + a) * 32 + ln;
+      if (m >= M) continue;
 #pragma unroll
-  for (int ni = 0; ni < NT; ++ni) {
-    int nt;
-    if (GLU) nt = min(n_wave0 / 32, n_tiles - 1) + (ni ? n_tiles : 0);
-    else     nt = min(n_wave0 / 32 + ni, n_tiles - 1);
-    op.w_tiles[ni] = Wp + (size_t)nt * nk * kWBlock + lane * 8;
-  }
-  f32x16 acc[MT][NT];
+      for (int b = 0; b < (MIX ? 1 : G::NW / 2); ++b) {
+        const int f0 = (t0 + wn * G::NW + 2 * b) * 16;   // first feature of the tile, or pair of tiles
+        if (f0 >= g.F) continue;                         // F is a multiple of 64: whole tiles only
 #pragma unroll
-  for (int mi = 0; mi < MT; ++mi)
+        for (int i4 = 0; i4 < (MIX ? 2 : 4); ++i4) {
+          float y[4];
 #pragma unroll
-    for (int ni = 0; ni < NT; ++ni)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-  const int kt0 = (int)((long)nk * split / n_split), kt1 = (int)((long)nk * (split + 1) / n_split);
-  G::run(acc, op, kt0, kt1, lds);
-  if (defer_rows && n_rows_dev) M = min(*n_rows_dev, M_max);
-
-  const int ln = lane & 31, lg = lane >> 5;
-#pragma unroll
-  for (int mi = 0; mi < MT; ++mi) {
-    const int m = m0 + mi * 32 + ln;
-    if (m >= M) continue;
-    if (GLU) {
-      if (n_wave0 >= N) continue;                        // N is a multiple of 32: whole tiles only
-      f16* dst = (f16*)out + (size_t)m * N + n_wave0 + 4 * lg;
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        float y[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = silu_fast(acc[mi][0][4 * i4 + j]) * acc[mi][NT - 1][4 * i4 + j];
-        *(f16x4*)(dst + 8 * i4) = to_f16x4_guarded(y[0], y[1], y[2], y[3], status);
-      }
-    } else {
-#pragma unroll
-      for (int ni = 0; ni < NT; ++ni) {
-        const int n0 = n_wave0 + ni * 32;
-        if (n0 >= N) continue;
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const size_t o = (size_t)m * N + n0 + 8 * i4 + 4 * lg;
-          if (EPI == EPI_STORE) {
-            *(f16x4*)((f16*)out + o) = to_f16x4_guarded(acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2],
-                                                        acc[mi][ni][4 * i4 + 3], status);
-          } else {
-            *(f32x4*)((float*)out + (size_t)split * M_max * N + o) =
-                f32x4{acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2], acc[mi][ni][4 * i4 + 3]};
+          for (int j = 0; j < 4; ++j) {
+            const int i = 4 * i4 + j;
+            y[j] = silu_fast(acc[a][MIX ? 0 : 2 * b][i]) * (MIX ? acc[a][0][(i + 8) & 15] : acc[a][(2 * b + 1) % G::NW][i]);
           }
+          *(f16x4*)(g.out + act_index(m, f0 + 8 * i4 + 4 * lg, g.M_max)) = to_f16x4_guarded(y[0], y[1], y[2], y[3], g.status);
         }
       }
     }
-  }
+  };
+  G::run(id0, stride, n, g.K / 32, lds, operands, finish);
 }
-
-template <int MT, int NT, int EPI>
-static void launch_mfma(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const int32_t* a_rows,
-                        const void* W, void* out, int n_split, int32_t* status, hipStream_t st) {
-  using G = MfmaGemm<MT, NT, true>;
-  constexpr int nout = (EPI == EPI_SWIGLU) ? 4 * 32 : 4 * NT * 32;
-  int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + nout - 1) / nout;
-  int total = m_blocks * n_blocks * n_split;
-  int grid = 8 * ((total + 7) / 8);
-  static bool attr_set = false;              // more than 64 KiB of dynamic LDS needs an opt-in (192-row tiles)
-  if (!attr_set) { (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<MT, NT, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES); attr_set = true; }
-  hipLaunchKernelGGL((gemm_mfma_kernel<MT, NT, EPI>), dim3(grid), dim3(256), G::LDS_BYTES, st, n_rows_dev, M_max,
-                     N, K, (const f16*)A, a_rows, (const f16*)W, out, m_blocks, n_blocks, n_split, total <= kOneRound ? 1 : 0,
-                     status, 0);
-}
-
-
-// Eight-wave kernel (see MfmaGemm8): 192 rows x 128 SwiGLU features (EPI_SWIGLU: gate tile and up tile of the
-// same 32 features in one wave) or x 256 output columns (EPI_STORE) per workgroup of 512 threads.
-template <int EPI>
-__global__ void __launch_bounds__(512) gemm8_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K,
-                                                    const f16* __restrict__ A, const int32_t* __restrict__ a_rows,
-                                                    const f16* __restrict__ Wp, void* __restrict__ out, int m_blocks,
-                                                    int n_blocks, int defer_rows, int32_t* __restrict__ status) {
-  using G = MfmaGemm8;
+// One tile per workgroup.  A launch of one round does not wait for the row count before its first loads (rows beyond it are stale
+// rows of the same buffer, each affecting only its own output row); one of several rounds leaves the row blocks beyond it out.
+constexpr int kFewRows = 320;
+template <typename G>
+__global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_kernel(GluArgs g, int m_blocks, int n_blocks) {
   extern __shared__ __align__(16) char lds[];
-  int M = (!defer_rows && n_rows_dev) ? min(*n_rows_dev, M_max) : M_max;     // see gemm_mfma_kernel
-  const int total = m_blocks * n_blocks, per_xcd = (total + 7) / 8;
-  const int id = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
-  const int mb = id % m_blocks, nb = id / m_blocks;
-  const int m0 = mb * G::BM;
-  if (m0 >= M) return;
-  constexpr bool GLU = (EPI == EPI_SWIGLU);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm = wave >> 2, wn = wave & 3;
-  const int nk = K / kBK;
-  const int n_tiles = (N + 31) / 32;
+  if (m_blocks * n_blocks > G::WGS * kCUs) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
+  const int id = xcd_flat(m_blocks * n_blocks);
+  if (id >= 0) glu_tiles<G>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
+}
+// More rows: 192 or 256 rows x 128 features per tile, persistent workgroups, one per CU (rows_by_rounds).
+typedef DmaGemm<3, 2, 2, 4, 5> GemmRows192;
+typedef DmaGemm<4, 2, 2, 4, 4> GemmRows256;
+__global__ void __launch_bounds__(512) glu_rows_kernel(GluArgs g, int n_blocks) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(*g.n_rows_dev, g.M_max), bm = rows_by_rounds(M, n_blocks), m_blocks = (M + bm - 1) / bm;
+  int stride, end;
+  const int id = xcd_first(m_blocks * n_blocks, stride, end);
+  if (id >= end) return;
+  if (bm == 256) glu_tiles<GemmRows256>(g, m_blocks, n_blocks, id, stride, end, lds);
+  else glu_tiles<GemmRows192>(g, m_blocks, n_blocks, id, stride, end, lds);
+}
 
-  G::Operands op;
-  op.x_base = (const char*)A;
-  op.w_base = (const char*)Wp;
+// ---- float32 results (O and down projections, unfused QKV projection): one partial [M_max, N] slab per K split,
+// out[split][m][n]; the consumer (RMSNorm, rotary kernel) sums the slabs.  Float atomics into the residual were measured at
+// ~25 us per launch and are not used.
+template <typename G>
+__device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
+                                          const f16* __restrict__ Wp, float* __restrict__ out, int m0, int nb, int split, int n_split, char* lds) {
+  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
+  const size_t tile_bytes = (size_t)(K / kBK) * 4096;
+  const int t0 = nb * G::CT, t_last = N / 32 - 1;
+  const int nk = K / kBK, s0 = 2 * (int)((long)nk * split / n_split), s1 = 2 * (int)((long)nk * (split + 1) / n_split);
+  auto operands = [&](typename G::Operands& op, int) {
+    G::make_operands(op, A, M_max, [&](int r) { return min(m0 + r, M_max - 1); }, Wp, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, lane * 16u, s0);
+  };
+  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int) {
+    const int M = min(*n_rows_dev, M_max);
+    float* dst = out + (size_t)split * M_max * N;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    int row, g, s;
-    G::chunk_of(i, row, g, s);
-    int r = min(m0 + row, M - 1);
-    if (a_rows) r = a_rows[r];
-    op.x_off[i] = (uint32_t)(((size_t)r * K + g * 32 + s * 8) * 2);
-    op.x_lds[i] = G::chunk_lds_offset(row, g, s);
-  }
+    for (int a = 0; a < G::MW; ++a) {
+      const int m = m0 + (wm * G::MW + a) * 32 + ln;
+      if (m >= M) continue;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ni = threadIdx.x >> 8;
-    int nt;
-    if (GLU) nt = min(nb * 4 + i, n_tiles - 1) + ni * n_tiles;
-    else     nt = min(nb * 8 + i * 2 + ni, n_tiles - 1);
-    op.w_off[i] = (uint32_t)(((size_t)nt * nk * kWBlock + (threadIdx.x & 255) * 8) * 2);
-  }
-  f32x16 acc[3][2];
+      for (int b = 0; b < G::NW; ++b) {
+        const int n0 = (t0 + wn * G::NW + b) * 32;
+        if (n0 >= N) continue;                           // N is a multiple of 32: whole tiles only
 #pragma unroll
-  for (int mi = 0; mi < 3; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-    G::run(acc, op, 0, nk, lds);
-  if (defer_rows && n_rows_dev) M = min(*n_rows_dev, M_max);
-
-  const int ln = lane & 31, lg = lane >> 5;
-  const int n_wave0 = GLU ? (nb * 4 + wn) * 32 : (nb * 4 + wn) * 64;
-#pragma unroll
-  for (int mi = 0; mi < 3; ++mi) {
-    const int m = m0 + wm * 96 + mi * 32 + ln;
-    if (m >= M) continue;
-    if (GLU) {
-      if (n_wave0 >= N) continue;
-      f16* dst = (f16*)out + (size_t)m * N + n_wave0 + 4 * lg;
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        float y[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = silu_fast(acc[mi][0][4 * i4 + j]) * acc[mi][1][4 * i4 + j];
-        *(f16x4*)(dst + 8 * i4) = to_f16x4_guarded(y[0], y[1], y[2], y[3], status);
+        for (int i4 = 0; i4 < 4; ++i4)
+          *(f32x4*)(dst + (size_t)m * N + n0 + 8 * i4 + 4 * lg) = f32x4{acc[a][b][4 * i4], acc[a][b][4 * i4 + 1], acc[a][b][4 * i4 + 2], acc[a][b][4 * i4 + 3]};
       }
+    }
+  };
+  G::run(0, 1, 1, s1 - s0, lds, operands, finish);
+}
+// Tile and number of splits fixed by the launch (rule.bm == 0: see glu_kernel), or the splits from the step's row count.
+template <typename G>
+__global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) slab_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
+                                                          const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, SlabRule rule) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = rule.bm ? min(*n_rows_dev, M_max) : M_max;
+  const int m_blocks = (M + G::BM - 1) / G::BM, tiles = m_blocks * n_blocks, n_split = __builtin_amdgcn_readfirstlane(rule.slabs(M));
+  const int id = xcd_flat(tiles * n_split);
+  if (id < 0) return;
+  slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, id % tiles % m_blocks * G::BM, id % tiles / m_blocks, id / tiles, n_split, lds);
+}
+// Two tiles to choose from: tile and splits both from the step's row count (SlabRule::tile_rows).
+template <typename G, typename GA>
+__global__ void __launch_bounds__(256, 2) slab_alt_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
+                                                          const f16* __restrict__ Wp, float* __restrict__ out, SlabRule rule) {
+  extern __shared__ __align__(16) char lds[];
+  // (what comes out of the float arithmetic of the rule is made scalar: everything is derived from it)
+  const int M = min(*n_rows_dev, M_max), bm = __builtin_amdgcn_readfirstlane(rule.tile_rows(M));
+  const int m_blocks = (M + bm - 1) / bm, tiles = m_blocks * rule.blocks(bm), n_split = __builtin_amdgcn_readfirstlane(rule.slabs(M));
+  const int id = xcd_flat(tiles * n_split);
+  if (id < 0) return;
+  const int split = id / tiles, tile = id % tiles, m0 = tile % m_blocks * bm, nb = tile / m_blocks;
+  if (bm == G::BM) slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, m0, nb, split, n_split, lds);
+  else slab_tile<GA>(n_rows_dev, M_max, N, K, A, Wp, out, m0, nb, split, n_split, lds);
+}
+
+// ------------------------------------------------------------------ launchers
+template <typename K_>
+static void allow_lds(K_ kern, int bytes, bool& done) {  // more than 64 KiB of dynamic LDS needs an opt-in
+  if (!done) { (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); done = true; }
+}
+static int grid8(int n) { return (n + 7) / 8 * 8; }
+
+template <typename G>
+static void launch_glu_t(const GluArgs& g, hipStream_t st) {
+  const int m_blocks = (g.M_max + G::BM - 1) / G::BM, n_blocks = (g.F / 16 + G::CT - 1) / G::CT;
+  static bool done = false;
+  allow_lds(glu_kernel<G>, G::LDS_BYTES, done);
+  hipLaunchKernelGGL(glu_kernel<G>, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
+}
+// Measured in us (gate/up of the 1.5B shape, 8960 features, and of the 7B shape, 18944; the loops with weights in registers and
+// activations staged through registers that were here before in brackets):
+//   64 rows 13.3 (22.3) / 48.4 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 87.3 (104)
+//   432 rows 29.1 (44.7)    576 rows 36.2 (41.4)    1037 rows 63.0 (73.0)    1185 rows - / 283 (324)    3480 rows 169.5 (190.9)
+static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const void* A, const void* W, void* out, int32_t* status, hipStream_t st) {
+  const GluArgs g{n_rows_dev, M_max, F, K, (const f16*)A, (const f16*)W, (f16*)out, status};
+  const int rt = (M_max + 31) / 32, n128 = (F + 127) / 128;
+  const bool wide = F / 16 > 3 * kCUs;                   // more columns than 256 workgroups of three waves with 16 features each take
+  const bool mix = packed_weight_elems(F, K) * 2 < ((size_t)1 << 32);      // the mixed tiles address the up rows with a 32-bit offset
+  if (rt <= 5 && mix) {
+    // one row block, columns in steps of 16 features per wave: one workgroup per CU
+    if (wide) {
+      if (rt <= 2) launch_glu_t<StreamGemm<2, 1, 5, 3>>(g, st);
+      else if (rt == 3) launch_glu_t<StreamGemm<3, 1, 5, 3>>(g, st);
+      else if (rt == 4) launch_glu_t<StreamGemm<4, 1, 5, 6, 2>>(g, st);
+      else launch_glu_t<StreamGemm<5, 1, 5, 6, 2>>(g, st);
     } else {
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int n0 = n_wave0 + ni * 32;
-        if (n0 >= N) continue;
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *(f16x4*)((f16*)out + (size_t)m * N + n0 + 8 * i4 + 4 * lg) =
-              to_f16x4_guarded(acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2], acc[mi][ni][4 * i4 + 3], status);
-      }
+      if (rt <= 2) launch_glu_t<StreamGemm<2, 1, 3, 3>>(g, st);
+      else if (rt == 3) launch_glu_t<StreamGemm<3, 1, 3, 3>>(g, st);
+      else if (rt == 4) launch_glu_t<StreamGemm<4, 1, 3, 3>>(g, st);
+      else launch_glu_t<StreamGemm<5, 1, 3, 3>>(g, st);
     }
+    return;
   }
+  if (M_max <= kFewRows && wide && mix) {
+    // the same for two or three groups of waves side by side in the rows: 288 rows 87 us, 95 with 96-row tiles of 128 features
+    if (rt == 6) launch_glu_t<DmaGemm<3, 1, 2, 5, 7>>(g, st);
+    else if (rt <= 8) launch_glu_t<DmaGemm<4, 1, 2, 5, 6>>(g, st);
+    else if (rt == 9) launch_glu_t<DmaGemm<3, 1, 3, 5, 5>>(g, st);
+    else launch_glu_t<DmaGemm<5, 1, 2, 5, 5>>(g, st);
+    return;
+  }
+  if (M_max <= 640) {
+    // 128 features per workgroup; rows by time of a K tile (0.01 us) x rounds of the CUs
+    auto cost = [&](int bm, int t) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * t; };
+    const int c96 = cost(96, 83), c128 = cost(128, 92), c160 = cost(160, 113), c192 = cost(192, 128);
+    if (c192 < c96 && c192 < c128 && c192 < c160) launch_glu_t<GemmRows192>(g, st);
+    else if (c160 < c96 && c160 < c128) launch_glu_t<StreamGemm<5, 2, 4, 2>>(g, st);
+    else if (c128 < c96) launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st);
+    else launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
+    return;
+  }
+  // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows: 283 us, 290 with 128-row tiles), 128-row
+  // tiles, two workgroups per CU, for a short one, where filling and storing a tile is a larger part (1.5B shape, 1037 rows: 63 us
+  // against 67; 3480 rows: 169.5 against 171).
+  if (K / kBK < 32) { launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st); return; }
+  constexpr int lds = GemmRows192::LDS_BYTES > GemmRows256::LDS_BYTES ? GemmRows192::LDS_BYTES : GemmRows256::LDS_BYTES;
+  static bool done = false;
+  allow_lds(glu_rows_kernel, lds, done);
+  const int tiles = (M_max + 191) / 192 * n128;
+  hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
 }
 
-// Large-batch kernels (row limit above 640) on the MfmaGemmRing2 loop: 128 rows x 8 weight row tiles per workgroup,
-// two workgroups per CU.  The row count is read first (these launches run several rounds of the CUs) and row blocks
-// beyond it exit.
-//
-// SwiGLU: wave w holds the gate tile and the up tile of features 32 w .. 32 w + 31 of the block's 128 features.
-__global__ void __launch_bounds__(256, 2) gemm_ring2_swiglu_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K,
-                                                                  const f16* __restrict__ A, const f16* __restrict__ Wp,
-                                                                  f16* __restrict__ out, int m_blocks, int n_blocks,
-                                                                  int32_t* __restrict__ status) {
-  using G = MfmaGemmRing2;
-  extern __shared__ __align__(16) char lds[];
-  const int M = min(*n_rows_dev, M_max);
-  const int total = m_blocks * n_blocks, per_xcd = (total + 7) / 8;
-  const int id = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;      // XCD-first decoding, M block fastest
-  if ((int)(blockIdx.x / 8) >= per_xcd || id >= total) return;
-  const int mb = id % m_blocks, nb = id / m_blocks;
-  const int m0 = mb * G::BM;
-  if (m0 >= M) return;
-  // the wave index is made scalar so that the weight stream's base address stays on the scalar unit
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+template <typename G>
+static SlabRule launch_slab(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule,
+                            hipStream_t st) {
+  const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + G::CT * 32 - 1) / (G::CT * 32), tiles = m_blocks * n_blocks;
+  // with the device rule tiles(M) * splits(M) never exceeds max(tiles(M_max), cap)
+  const int n = rule.bm ? (tiles > rule.cap ? tiles : rule.cap) : tiles * rule.fixed;
+  static bool done = false;
+  allow_lds(slab_kernel<G>, G::LDS_BYTES, done);
+  hipLaunchKernelGGL(slab_kernel<G>, dim3(grid8(n)), dim3(G::THREADS), G::LDS_BYTES, st, n_rows_dev, M_max, N, K, (const f16*)A, (const f16*)W,
+                     (float*)out, n_blocks, rule);
+  return rule;
+}
+template <typename G, typename GA>
+static SlabRule launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, int t, int t_alt, hipStream_t st) {
+  const int nb = (N + G::CT * 32 - 1) / (G::CT * 32), nba = (N + GA::CT * 32 - 1) / (GA::CT * 32);
+  const SlabRule rule{0, G::BM, nb, K / kBK, 2 * kCUs, GA::BM, nba, t, t_alt, N};
+  const int ta = (M_max + G::BM - 1) / G::BM * nb, tb = (M_max + GA::BM - 1) / GA::BM * nba, tiles = ta > tb ? ta : tb;
+  constexpr int lds = G::LDS_BYTES > GA::LDS_BYTES ? G::LDS_BYTES : GA::LDS_BYTES;
+  static bool done = false;
+  allow_lds(slab_alt_kernel<G, GA>, lds, done);
+  // tiles(M) * splits(M) never exceeds max(tiles(M_max), cap)
+  hipLaunchKernelGGL((slab_alt_kernel<G, GA>), dim3(grid8(tiles > rule.cap ? tiles : rule.cap)), dim3(256), lds, st, n_rows_dev, M_max, N, K, (const f16*)A,
+                     (const f16*)W, (float*)out, rule);
+  return rule;
+}
+// Tile and split of a float32-result GEMM: the cheapest of the tiles below by gemm_split_cost, whose times of a K tile are those of
+// launches that fill the CUs once (a tile of 32 MW rows x 128 NW columns).  Measured in us, down projection of the 1.5B and the 7B
+// shape (before, with the loops that staged activations through registers):
+//   64 rows 10.0 (19.2) / 26.7 (38.8)    144 rows 12.8 (20.5) / 35.1 (44.1)    288 rows 16.7 (21.5) / 47.9 (66.3)
+//   576 rows 24.0 (24.6) / 82 (130)    1100 rows 36.0 (48.5) / 147 (159)
+typedef StreamGemm<2, 1, 2, 4> T64x64;
+typedef StreamGemm<2, 1, 4, 4> T64x128;
+typedef StreamGemm<3, 1, 4, 3> T96x128;
+typedef StreamGemm<4, 1, 4, 3> T128x128;
+typedef StreamGemm<5, 1, 4, 3> T160x128;
+typedef StreamGemm<3, 2, 4, 2> T96x256;
+typedef StreamGemm<4, 2, 4, 2> T128x256;
+typedef StreamGemm<5, 2, 4, 2> T160x256;
+struct SlabPick { int tile, split, cost; };
+static SlabPick pick_slab(int M_max, int N, int nk) {
+  static const struct { int bm, bn, t; } cfg[] = {{64, 64, 30}, {64, 128, 35}, {96, 128, 46}, {128, 128, 51}, {160, 128, 68}, {96, 256, 83}, {128, 256, 92}, {160, 256, 113}};
+  SlabPick best{0, 1, 0x7fffffff};
+  for (int i = 0; i < 8; ++i) {
+    const int tiles = (M_max + cfg[i].bm - 1) / cfg[i].bm * ((N + cfg[i].bn - 1) / cfg[i].bn);
+    for (int s = 1; s <= kMaxGemmSplit && (s == 1 || 4 * s <= nk); ++s) {
+      const int c = gemm_split_cost(tiles, nk, 2 * kCUs, s, cfg[i].t, gemm_slab_cost(M_max, N));
+      if (c < best.cost) best = SlabPick{i, s, c};
+    }
+  }
+  return best;
+}
+int gemm_slab_time(int M_max, int N, int K) { return pick_slab(M_max, N, K / kBK).cost; }
+static SlabRule launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, hipStream_t st) {
   const int nk = K / kBK;
-  const int n_tiles = (N + 31) / 32;                    // row tiles of each half of the packed gate/up matrix
-  const int n_wave0 = (nb * 4 + wave) * 32;
-  const int gate_tile = min(n_wave0 / 32, n_tiles - 1);
-  const int ln = lane & 31, lg = lane >> 5;
-  // the last row block of a step with at most 64 live rows computes two row tiles instead of four
-  auto tile = [&](auto mt_tag) {
-    constexpr int MT = decltype(mt_tag)::value;
-    using GT = MfmaGemmRing2T<MT>;
-    typename GT::Operands op;
-    GT::make_operands(op, A, K, m0, M, Wp, nk, gate_tile, gate_tile + n_tiles);
-    f32x16 acc[MT][2];
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-    GT::run(acc, op, 0, nk, lds);
-    if (n_wave0 >= N) return;                           // N is a multiple of 32: whole tiles only
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-      const int m = m0 + mi * 32 + ln;
-      if (m >= M) continue;
-      f16* dst = out + (size_t)m * N + n_wave0 + 4 * lg;
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        float y[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = silu_fast(acc[mi][0][4 * i4 + j]) * acc[mi][1][4 * i4 + j];
-        *(f16x4*)(dst + 8 * i4) = to_f16x4_guarded(y[0], y[1], y[2], y[3], status);
-      }
+  if (M_max <= 640) {
+    const SlabPick pick = pick_slab(M_max, N, nk);
+    const SlabRule r{pick.split, 0, 0, 0, 0, 0};
+#define BS_SLAB(T_) return launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
+    switch (pick.tile) {
+      case 0: BS_SLAB(T64x64);
+      case 1: BS_SLAB(T64x128);
+      case 2: BS_SLAB(T96x128);
+      case 3: BS_SLAB(T128x128);
+      case 4: BS_SLAB(T160x128);
+      case 5: BS_SLAB(T96x256);
+      case 6: BS_SLAB(T128x256);
+      default: BS_SLAB(T160x256);
     }
-  };
-  if (M - m0 <= 64) tile(std::integral_constant<int, 2>{});
-  else tile(std::integral_constant<int, 4>{});
-}
-
-// Residual projections above 640 rows, 256 output columns per workgroup, float32 K-split slabs.  The row tile (96
-// rows on the MfmaGemm<3, 2> loop or 128 rows on the MfmaGemmRing2 loop), the live row blocks and the number of K
-// splits all follow from the step's row count (SlabRule: the consumer of the slabs evaluates the same rule): which
-// tile fills the 512 resident workgroup slots better depends on the row count, which only the device knows
-// (measured, down projection: 7B shape at 1185 rows, 96-row tiles 2 x 182 workgroups 194 us, 128-row tiles 3 x 140
-// workgroups 172 us; 1.5B shape at 3952 rows, 96-row tiles 2 x 252 workgroups 108 us, 128-row tiles 2 x 186 120 us).
-__global__ void __launch_bounds__(256, 2) gemm_resid_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K,
-                                                           const f16* __restrict__ A, const f16* __restrict__ Wp,
-                                                           float* __restrict__ out, SlabRule rule) {
-  extern __shared__ __align__(16) char lds[];
-  const int M = min(*n_rows_dev, M_max);
-  const int bm = rule.tile_rows(M);
-  const int m_blocks = (M + bm - 1) / bm, tiles = m_blocks * rule.n_blocks;
-  const int nk = rule.nk;
-  const int n_split = gemm_adaptive_split(tiles, nk, rule.cap);
-  // XCD-first decoding: the (split, N block, M block) space, M block fastest, is cut into 8 contiguous ranges
-  const int total = tiles * n_split, per_xcd = (total + 7) / 8;
-  const int flat = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if ((int)(blockIdx.x / 8) >= per_xcd || flat >= total) return;
-  const int split = flat / tiles, id = flat % tiles;
-  const int mb = id % m_blocks, nb = id / m_blocks;
-  const int m0 = mb * bm;
-  // the wave index is made scalar so that the weight stream's base address stays on the scalar unit
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int ln = lane & 31, lg = lane >> 5;
-  const int n_tiles = (N + 31) / 32;
-  const int n_wave0 = (nb * 4 + wave) * 64;
-  const int tile0 = min(n_wave0 / 32, n_tiles - 1), tile1 = min(n_wave0 / 32 + 1, n_tiles - 1);
-  const int kt0 = (int)((long)nk * split / n_split), kt1 = (int)((long)nk * (split + 1) / n_split);
-  float* dst = out + (size_t)split * M_max * N;
-  auto store = [&](auto& acc, auto mt_tag) {
-    constexpr int MT = decltype(mt_tag)::value;
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi) {
-      const int m = m0 + mi * 32 + ln;
-      if (m >= M) continue;
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int n0 = n_wave0 + ni * 32;
-        if (n0 >= N) continue;
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *(f32x4*)(dst + (size_t)m * N + n0 + 8 * i4 + 4 * lg) =
-              f32x4{acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2], acc[mi][ni][4 * i4 + 3]};
-      }
-    }
-  };
-  if (bm == MfmaGemmRing2::BM) {
-    using G = MfmaGemmRing2;
-    G::Operands op;
-    G::make_operands(op, A, K, m0, M, Wp, nk, tile0, tile1);
-    f32x16 acc[4][2];
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-    G::run(acc, op, kt0, kt1, lds);
-    store(acc, std::integral_constant<int, 4>{});
-  } else {
-    using G = MfmaGemm<3, 2, true>;
-    typename G::Operands op;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      int row, g, s;
-      G::chunk_of(i, row, g, s);
-      const int r = min(m0 + row, M - 1);
-      op.x_rows[i] = A + (size_t)r * K + g * 32 + s * 8;
-      op.x_lds[i] = G::chunk_lds_offset(row, g, s);
-    }
-    op.w_tiles[0] = Wp + (size_t)tile0 * nk * kWBlock + lane * 8;
-    op.w_tiles[1] = Wp + (size_t)tile1 * nk * kWBlock + lane * 8;
-    f32x16 acc[3][2];
-#pragma unroll
-    for (int mi = 0; mi < 3; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-    G::run(acc, op, kt0, kt1, lds);
-    store(acc, std::integral_constant<int, 3>{});
+#undef BS_SLAB
   }
-}
-
-// The ring2 kernels address the activation matrix with 32-bit byte offsets.
-static bool ring2_applies(int M_max, int K) { return (size_t)M_max * K * 2 < ((size_t)1 << 32); }
-
-static void launch_ring2_swiglu(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                                int32_t* status, hipStream_t st) {
-  using G = MfmaGemmRing2;
-  const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + 127) / 128;
-  const int grid = 8 * ((m_blocks * n_blocks + 7) / 8);
-  hipLaunchKernelGGL(gemm_ring2_swiglu_kernel, dim3(grid), dim3(256), G::LDS_BYTES, st, n_rows_dev, M_max, N, K, (const f16*)A,
-                     (const f16*)W, (f16*)out, m_blocks, n_blocks, status);
-}
-
-template <int EPI>
-static void launch_gemm8(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const int32_t* a_rows,
-                         const void* W, void* out, int32_t* status, hipStream_t st) {
-  using G = MfmaGemm8;
-  constexpr int nout = (EPI == EPI_SWIGLU) ? 128 : 256;
-  const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + nout - 1) / nout;
-  const int grid = 8 * ((m_blocks * n_blocks + 7) / 8);
-  static bool attr_set = false;
-  if (!attr_set) { (void)hipFuncSetAttribute((const void*)gemm8_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES); attr_set = true; }
-  hipLaunchKernelGGL((gemm8_kernel<EPI>), dim3(grid), dim3(512), G::LDS_BYTES, st, n_rows_dev, M_max, N, K,
-                     (const f16*)A, a_rows, (const f16*)W, out, m_blocks, n_blocks, m_blocks * n_blocks <= kOneRound ? 1 : 0, status);
-}
-
-// The eight-wave kernel addresses both matrices with 32-bit byte offsets and pays off when 192-row blocks fit
-// the row count without much padding.
-static bool gemm8_applies(int M_max, int N, int K, int w_rows) {
-  if ((size_t)M_max * K * 2 >= ((size_t)1 << 32) || packed_weight_elems(w_rows, K) * 2 >= ((size_t)1 << 32)) return false;
-  const int pad6 = (M_max + 191) / 192 * 192, pad4 = (M_max + 127) / 128 * 128;
-  return M_max > 128 && pad6 <= pad4;
+  const int nb128 = (N + 127) / 128, nb256 = (N + 255) / 256;
+  if (nk < 96) {                                         // the second tile: the better one at the row limit
+    auto cost = [&](int bm, int t) {
+      const int tiles = (M_max + bm - 1) / bm * nb128, tsl = gemm_slab_cost(M_max, N);
+      return gemm_split_cost(tiles, nk, 2 * kCUs, gemm_adaptive_split(tiles, nk, 2 * kCUs, t, tsl), t, tsl);
+    };
+    if (cost(128, 51) < cost(160, 68)) return launch_slab_alt<T96x256, T128x128>(n_rows_dev, M_max, N, K, A, W, out, 83, 51, st);
+    return launch_slab_alt<T96x256, T160x128>(n_rows_dev, M_max, N, K, A, W, out, 83, 68, st);
+  }
+  if ((M_max + 95) / 96 * nb256 >= 128) return launch_slab_alt<T96x256, T128x256>(n_rows_dev, M_max, N, K, A, W, out, 83, 92, st);
+  return launch_slab<T128x128>(n_rows_dev, M_max, N, K, A, W, out, SlabRule{0, T128x128::BM, nb128, nk, 2 * kCUs, 0, 0, 51, 51, N}, st);
 }
 
 template <int EPI>
@@ -517,138 +412,16 @@ static void launch_f32(const int32_t* n_rows_dev, int M_max, int N, int K, const
                      (const float*)A, (const float*)W, (float*)out);
 }
 
-// Tile choice.  MT: smallest row tiling that covers M_max with the least padding (576 rows -> 3 x 192).
-// NT: two row tiles per wave (256 columns per workgroup) when that still yields enough workgroups for
-// 256 CUs, else one.  K split (residual epilogue only) when even that leaves most CUs idle.
-static int pick_mt(int M_max) {
-  if (M_max <= 32) return 1;
-  if (M_max <= 64) return 2;
-  if (M_max <= 128) return 4;
-  const int pad6 = (M_max + 191) / 192 * 192, pad4 = (M_max + 127) / 128 * 128;
-  return pad6 <= pad4 ? 6 : 4;
-}
-
-template <int EPI>
-static int dispatch(int dtype, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A,
-                    const int32_t* a_rows, const void* W, void* out, int32_t* status, hipStream_t st) {
-  if (dtype == BS_F32) { launch_f32<EPI>(n_rows_dev, M_max, N, K, A, W, out, st); return 0; }
-  bool small_tiles = false;
-  if constexpr (EPI == EPI_SWIGLU) {
-    // large batches: 128-row tiles on the in-place two-tile ring (see gemm_ring2.h), two workgroups per CU
-    // (measured against the 96-row tiles below: 7B shape at 1185 rows 316 -> 302 us, 1.5B shape at 3952 rows 220 -> 216)
-    if (M_max > 640 && n_rows_dev && !a_rows && ring2_applies(M_max, K)) {
-      launch_ring2_swiglu(n_rows_dev, M_max, N, K, A, W, out, status, st);
-      return 1;
-    }
-    bool want = true;
-    if (M_max > 128) {
-      // 192-row tiles, one workgroup per CU, against 96-row tiles, two per CU: whichever needs less time by rounds of
-      // the 256 CUs.  In a single round the small tiles are about 10 % slower per unit of work; over several rounds
-      // they are faster, because one workgroup's pipeline fill and epilogue overlap the other's main loop.
-      // Measured, 7B shape (18944 features): 288 rows, 2 x 148 workgroups = two rounds against 3 x 148 small ones at
-      // once: 133 -> 96 us; 1152 rows, 3.5 rounds either way: 308 -> 290 us.
-      const int nb = (N + 127) / 128;
-      const long r6 = ((M_max + 191) / 192 * nb + 255) / 256, r3 = ((M_max + 95) / 96 * nb + 511) / 512;
-      const long cost6 = r6 * 60, cost3 = r3 * (r3 > 1 ? 57 : 66);
-      if (cost3 < cost6) { want = false; small_tiles = true; }
-    }
-    if (want && gemm8_applies(M_max, N, K, 2 * N)) {
-      launch_gemm8<EPI>(n_rows_dev, M_max, N, K, A, a_rows, W, out, status, st);
-      return 1;
-    }
+SlabRule launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
+                     int32_t* status, hipStream_t st) {
+  const SlabRule none{0, 0, 0, 0, 0, 0};
+  if (dtype == BS_F32) {
+    if (epi == EPI_SWIGLU) launch_f32<EPI_SWIGLU>(n_rows_dev, M_max, N, K, A, W, out, st);
+    else if (epi == EPI_RESID_ADD) launch_f32<EPI_RESID_ADD>(n_rows_dev, M_max, N, K, A, W, out, st);
+    else launch_f32<EPI_STORE_F32>(n_rows_dev, M_max, N, K, A, W, out, st);
+    return none;
   }
-  int mt = small_tiles ? 3 : pick_mt(M_max);
-  // float32-epilogue GEMMs have narrow outputs (N = d or Nqkv): measured on MI355X at M = 576, smaller row
-  // tiles with at most 4 K splits beat 192-row tiles with 7 splits (down projection 50 -> 33 us, O 17 -> 13 us)
-  if ((EPI == EPI_RESID_ADD || EPI == EPI_STORE_F32) && M_max > 64) mt = (K / kBK <= 32) ? 2 : 4;
-  const int m_blocks = (M_max + mt * 32 - 1) / (mt * 32);
-  int nt = 2;
-  if (EPI != EPI_SWIGLU) {
-    // 256-column tiles (two weight row tiles per wave: half the LDS reads per MFMA) if they can fill the chip, for
-    // the float32 epilogues with the help of two K splits (more slabs would cost the consumer more than the tiles
-    // gain; 7B shape, 1152 rows, down projection: 126 tiles x 2 splits take 147 us, 252 tiles of 128 columns 172 us)
-    int blocks2 = m_blocks * ((N + 255) / 256);
-    if (EPI == EPI_RESID_ADD || EPI == EPI_STORE_F32) {
-      int s2 = (256 + blocks2 / 2) / blocks2;
-      if (s2 > K / kBK / 4) s2 = K / kBK / 4;
-      if (s2 > 2) s2 = 2;
-      if (s2 > 1) blocks2 *= s2;
-    }
-    if (blocks2 < 200) nt = 1;
-  }
-  const int nout = (EPI == EPI_SWIGLU) ? 128 : nt * 128;
-  const int blocks = m_blocks * ((N + nout - 1) / nout);
-  int n_split = 1;
-  if (EPI == EPI_RESID_ADD || EPI == EPI_STORE_F32) {
-    const int nk = K / kBK;
-    if (blocks < 160) n_split = (256 + blocks / 2) / blocks;
-    if (n_split > nk / 4) n_split = nk / 4 > 0 ? nk / 4 : 1;       // at least 4 K tiles per split
-    if (n_split < 1) n_split = 1;
-    if (n_split > 4) n_split = 4;
-    if (n_split > nk) n_split = nk;
-  }
-#define BS_GEMM(MT_, NT_) launch_mfma<MT_, NT_, EPI>(n_rows_dev, M_max, N, K, A, a_rows, W, out, n_split, status, st)
-  if constexpr (EPI != EPI_SWIGLU) {
-    if (nt == 1) {
-      switch (mt) { case 1: BS_GEMM(1, 1); break; case 2: BS_GEMM(2, 1); break; case 3: BS_GEMM(3, 1); break; case 4: BS_GEMM(4, 1); break; default: BS_GEMM(6, 1); }
-      return n_split;
-    }
-  }
-  switch (mt) { case 1: BS_GEMM(1, 2); break; case 2: BS_GEMM(2, 2); break; case 3: BS_GEMM(3, 2); break; case 4: BS_GEMM(4, 2); break; default: BS_GEMM(6, 2); }
-#undef BS_GEMM
-  return n_split;
-}
-
-// Residual projections (O, down): float32 K-split slabs, summed into the residual by the next RMSNorm.
-// Above 64 rows: 96-row tiles, two workgroups per CU, 256 output columns per workgroup when the row limit gives
-// enough of them (else 128), and the number of K splits decided on the device from the step's row count: with the
-// split fixed for the row limit B (k_max + 1), a ragged step (1185 of at most 2176 rows, 7B shape) ran the down
-// projection as 140 live workgroups of 128 x 256 on 256 CUs, 239 us; one resident round of 2 x 182 takes 189 us.
-template <int NT>
-static SlabRule launch_resid_adaptive(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W,
-                                      void* out, int32_t* status, hipStream_t st) {
-  using G = MfmaGemm<3, NT, true>;
-  constexpr int nout = 4 * NT * 32, cap = 512;
-  const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + nout - 1) / nout, nk = K / kBK;
-  const int tiles_max = m_blocks * n_blocks;
-  const int grid = 8 * (((tiles_max > cap ? tiles_max : cap) + 7) / 8);     // tiles(M) * splits(M) never exceeds this
-  static bool attr_set = false;
-  if (!attr_set) { (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<3, NT, EPI_RESID_ADD>, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES); attr_set = true; }
-  hipLaunchKernelGGL((gemm_mfma_kernel<3, NT, EPI_RESID_ADD>), dim3(grid), dim3(256), G::LDS_BYTES, st, n_rows_dev, M_max, N, K,
-                     (const f16*)A, nullptr, (const f16*)W, out, m_blocks, n_blocks, 1, 0, status, cap);
-  return SlabRule{0, G::BM, n_blocks, nk, cap, 0};
-}
-
-SlabRule launch_gemm_resid(int dtype, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W,
-                           void* out, int32_t* status, hipStream_t st) {
-  // (up to 640 rows the fixed launches below are tuned for one resident round and start their loads before the row
-  // count arrives; measured at 576 rows, 1.5B shape, the device-side rule costs the down projection 22 -> 27 us)
-  if (dtype == BS_BF16 && M_max > 640 && n_rows_dev) {
-    const int tiles2 = (M_max + 95) / 96 * ((N + 255) / 256);
-    if (tiles2 >= 128) {
-      constexpr int cap = 512;
-      const bool dual = ring2_applies(M_max, K);
-      const int n_blocks = (N + 255) / 256, nk = K / kBK;
-      const int tiles_max = (M_max + 95) / 96 * n_blocks;                      // the smaller tile gives more of them
-      const int grid = 8 * (((tiles_max > cap ? tiles_max : cap) + 7) / 8);   // tiles(M) * splits(M) never exceeds this
-      const SlabRule rule{0, 96, n_blocks, nk, cap, dual ? MfmaGemmRing2::BM : 0};
-      constexpr int lds = MfmaGemm<3, 2, true>::LDS_BYTES > MfmaGemmRing2::LDS_BYTES ? MfmaGemm<3, 2, true>::LDS_BYTES : MfmaGemmRing2::LDS_BYTES;
-      hipLaunchKernelGGL(gemm_resid_kernel, dim3(grid), dim3(256), lds, st, n_rows_dev, M_max, N, K, (const f16*)A,
-                         (const f16*)W, (float*)out, rule);
-      return rule;
-    }
-    return launch_resid_adaptive<1>(n_rows_dev, M_max, N, K, A, W, out, status, st);
-  }
-  const int n = launch_gemm(dtype, EPI_RESID_ADD, n_rows_dev, M_max, N, K, A, nullptr, W, out, status, st);
-  return SlabRule{n, 0, 0, 0, 0, 0};
-}
-
-int launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A,
-                const int32_t* a_rows, const void* W, void* out, int32_t* status, hipStream_t st) {
-  switch (epi) {
-    case EPI_STORE: return dispatch<EPI_STORE>(dtype, n_rows_dev, M_max, N, K, A, a_rows, W, out, status, st);
-    case EPI_RESID_ADD: return dispatch<EPI_RESID_ADD>(dtype, n_rows_dev, M_max, N, K, A, a_rows, W, out, status, st);
-    case EPI_SWIGLU: return dispatch<EPI_SWIGLU>(dtype, n_rows_dev, M_max, N, K, A, a_rows, W, out, status, st);
-    default: return dispatch<EPI_STORE_F32>(dtype, n_rows_dev, M_max, N, K, A, a_rows, W, out, status, st);
-  }
+  if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, st);
+  launch_glu(n_rows_dev, M_max, N, K, A, W, out, status, st);
+  return none;
 }

@@ -1,0 +1,309 @@
+// Main loop of the GEMMs on the f16 MFMA with both operands copied to LDS by the memory pipeline (global -> LDS loads).
+//
+//   C^T[N, M] = W[N, K] * X[M, K]^T      W = packed weights (gemm_mfma.h), X = activations in chunk order (act_index).
+//
+// Why this shape.
+//   * Both operands lie in memory in MFMA fragment order, so a fragment (1 KiB: 32 rows x 16 of K) is one load instruction
+//     whose bytes land in LDS as they are: no registers hold what is in flight, no LDS stores are issued, and every LDS read is a
+//     conflict-free 1 KiB sweep.  Loops with the weights in a register ring (three tiles of them plus the activations' staging
+//     registers) had 8 .. 24 KiB per wave in flight; here it is up to 130 KiB per CU, whatever the accumulators take.
+//   * A stage is 32 of K (two MFMA steps) of every row tile; NST stages are in LDS, NST - 2 of them in flight.  One barrier per
+//     stage, between its two steps: the second step already reads the next stage's first fragments, so a stage starts with its
+//     operands in registers, and the slot of the previous stage is free for stage i + NST - 1.
+//   * The tile (MW x NW accumulator tiles per wave, WM x WN waves) is a template parameter: few rows take all rows and few
+//     columns per workgroup, so that a weight is read once and as many CUs stream as columns allow; many rows take 192 x 256 or
+//     256 x 256, where LDS (128 bytes per clock) delivers what the matrix unit asks for.
+// What bounds it (MI355X, 7B shape, gate/up): 64 rows 55 -> 48 us, 5.7 TB/s of weights: memory.  1185 rows 321 -> 295 us: power; the
+// same launch takes 231 us when the activations are zeros and 270 us without its loads.
+#pragma once
+#include "gemm_mfma.h"
+
+// Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2: a launch's (K split, N block, M block) space, M block
+// fastest, is cut into 8 contiguous ranges, one per XCD, so that the M blocks that share weights run back to back on one XCD.
+// Returns the position of this workgroup in that space, or -1.
+__device__ __forceinline__ int xcd_flat(int total) {
+  const int per_xcd = (total + 7) / 8, flat = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  return (int)(blockIdx.x / 8) < per_xcd && flat < total ? flat : -1;
+}
+
+// The same for persistent workgroups: first tile of this one, step to its next ones, end of its XCD's range.
+__device__ __forceinline__ int xcd_first(int total, int& stride, int& end) {
+  const int per_xcd = (total + 7) / 8, x = (int)(blockIdx.x % 8);
+  stride = (int)(gridDim.x / 8);                         // the grid is a multiple of 8
+  end = min((x + 1) * per_xcd, total);
+  return x * per_xcd + (int)(blockIdx.x / 8);
+}
+constexpr int kCUs = 256;
+
+// Many rows, one workgroup per CU: 192 or 256 rows per workgroup, whichever takes fewer rows x rounds of the CUs.
+__host__ __device__ inline int rows_by_rounds(int M, int n_blocks) {
+  const int r192 = ((M + 191) / 192 * n_blocks + kCUs - 1) / kCUs, r256 = ((M + 255) / 256 * n_blocks + kCUs - 1) / kCUs;
+  return 4 * r256 <= 3 * r192 ? 256 : 192;
+}
+
+template <int MW_, int NW_, int WM_, int WN_, int NST_>
+struct DmaGemm {
+  static constexpr int MW = MW_, NW = NW_, WM = WM_, WN = WN_, NST = NST_;
+  static constexpr int RT = MW * WM, CT = NW * WN, BM = 32 * RT, WAVES = WM * WN, THREADS = 64 * WAVES;
+  static constexpr int PIECES = 2 * (RT + CT);                    // 1 KiB pieces of a stage: activation tiles, then weight tiles
+  static constexpr int PPW = (PIECES + WAVES - 1) / WAVES;        // pieces a wave requests (where they do not divide, the last one several times: the same bytes)
+  static constexpr int STAGE_BYTES = PIECES * 1024, LDS_BYTES = NST * STAGE_BYTES;
+  static_assert(NST >= 3 && LDS_BYTES <= 160 * 1024, "");
+  static constexpr int WGS = WAVES <= 4 && 2 * LDS_BYTES <= 160 * 1024 ? 2 : 1;     // workgroups per CU
+
+  struct Operands {
+    const char* at[PPW];        // each piece of the next stage to be requested (activations: without the row)
+    uint32_t lane[PPW];         // byte offset of this lane
+    uint32_t step[PPW];         // bytes from one stage to the next
+    int left;                   // stages not yet requested
+  };
+  __device__ static __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+  // x_row(r): row of X (clamped by the caller) for row r of the workgroup's tile; w_at(t): byte offset of the packed row tile at
+  // position t of the workgroup's CT weight tiles (wave wn multiplies positions wn * NW .. wn * NW + NW - 1); w_lane: byte offset of a
+  // lane inside a fragment (16 * lane, unless a tile is put together from two).  s0: first stage (32 of K).
+  template <typename XRow, typename WAt>
+  __device__ static __forceinline__ void make_operands(Operands& op, const f16* X, int ld, XRow x_row, const f16* Wp, WAt w_at,
+                                                       uint32_t w_lane, int s0) {
+    const int wave = wave_id(), lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < PPW; ++j) {
+      const int p = min(wave * PPW + j, PIECES - 1), t = p >> 1, half = p & 1;
+      if (p < 2 * RT) {
+        op.at[j] = (const char*)X + ((size_t)s0 * 4 + half * 2) * ld * 16;
+        op.lane[j] = (uint32_t)(lg * ld + x_row(t * 32 + ln)) * 16u;
+        op.step[j] = 64u * ld;
+      } else {
+        op.at[j] = (const char*)Wp + w_at(t - RT) + (size_t)s0 * 2048 + half * 1024;
+        op.lane[j] = w_lane;
+        op.step[j] = 2048u;
+      }
+    }
+  }
+  // Requests piece j of the next stage into a slot.  Past the last stage of the last tile that one is requested again, into slots
+  // nobody reads: unconditional, so that the wait counts hold.
+  __device__ static __forceinline__ void request(Operands& op, char* slot, int j) {
+    char* dst = slot + (PIECES % WAVES == 0 ? wave_id() * PPW + j : min(wave_id() * PPW + j, PIECES - 1)) * 1024;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(wt_buffer(op.at[j]), (__attribute__((address_space(3))) void*)dst, 16, op.lane[j], 0, 0, 0);
+    op.at[j] += op.left > 1 ? op.step[j] : 0u;
+  }
+  // Waits until at most N of this wave's requests are in flight, then for the other waves.
+  template <int N> __device__ static __forceinline__ void wait_stage() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+#endif
+  }
+
+  // Computes the tiles id, id + stride, .. below n, ns stages of 32 of K each (the same for all).  operands(op, id) sets up a tile's
+  // requests, finish(acc, id) stores it: C^T tiles, accumulator rows = weight rows, lane = activation row.  The tiles are one
+  // stream of stages: while a tile is finished, the first stages of the next one are in flight or have arrived.  finish() must
+  // not use LDS unless there is one tile only (it then needs a barrier first).  All threads must call it.
+  template <typename Ops, typename Finish>
+  __device__ static __forceinline__ void run(int id, int stride, int n, int ns, char* lds, Ops operands, Finish finish) {
+    const int wave = wave_id(), lane16 = (threadIdx.x & 63) * 16, wm = wave / WN, wn = wave % WN;
+    Operands op;
+    int rid = id;                                         // tile of the requests
+    operands(op, rid);
+    op.left = ns;
+    auto advance = [&]() {
+      if (--op.left == 0) {
+        rid += stride;
+        if (rid < n) { operands(op, rid); op.left = ns; }
+      }
+    };
+#pragma unroll
+    for (int st = 0; st < NST - 1; ++st) {
+#pragma unroll
+      for (int j = 0; j < PPW; ++j) request(op, lds + st * STAGE_BYTES, j);
+      advance();
+    }
+    const char* xb = lds + wm * MW * 2048 + lane16;
+    const char* wb = lds + (RT + wn * NW) * 2048 + lane16;
+    u32x4 xf[2][MW], wf[2][NW];
+    wait_stage<PPW * (NST - 2)>();
+#pragma unroll
+    for (int b = 0; b < NW; ++b) wf[0][b] = *(const u32x4*)(wb + b * 2048);
+#pragma unroll
+    for (int a = 0; a < MW; ++a) xf[0][a] = *(const u32x4*)(xb + a * 2048);
+    // fragment reads go out in the first half of a step, one or two per MFMA, so that they have arrived when it ends
+    constexpr int NM = MW * NW, NR = MW + NW, RPM = (2 * NR + NM - 1) / NM;
+    int slot = 0;
+    for (; id < n; id += stride) {
+      f32x16 acc[MW][NW];
+#pragma unroll
+      for (int a = 0; a < MW; ++a)
+#pragma unroll
+        for (int b = 0; b < NW; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+      for (int i = 0; i < ns; ++i) {
+        const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const char* xs = s == 0 ? xb + slot * STAGE_BYTES + 1024 : xb + next * STAGE_BYTES;
+          const char* ws = s == 0 ? wb + slot * STAGE_BYTES + 1024 : wb + next * STAGE_BYTES;
+          if (s == 1) {
+            wait_stage<PPW * (NST - 3)>();                // the next stage is complete, the previous one no longer read
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int m = 0; m < NM; ++m) {
+            const int a = m / NW, b = m % NW;
+#pragma unroll
+            for (int r = m * RPM; r < (m + 1) * RPM && r < NR; ++r) {
+              if (r < NW) wf[1 - s][r] = *(const u32x4*)(ws + r * 2048);
+              else xf[1 - s][r - NW] = *(const u32x4*)(xs + (r - NW) * 2048);
+            }
+            if (s == 1) {
+#pragma unroll
+              for (int j = m * PPW / NM; j < (m + 1) * PPW / NM; ++j) request(op, lds + prev * STAGE_BYTES, j);
+            }
+            acc[a][b] = mfma_f16(wf[s][b], xf[s][a], acc[a][b]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        slot = next;
+        advance();
+      }
+      if (id + stride >= n) {
+        // LDS must not be given away, nor reused, while a request may still write it
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+      }
+      finish(acc, id);
+    }
+  }
+};
+
+// The same with the weights in registers: all rows of the tile in every wave (WM = 1), so a weight fragment has one reader and LDS
+// would only be a buffer; LDS then carries the activations alone, and short stages leave room for two workgroups per CU.  RW stages
+// of weights are in registers or in flight, as many stages of activations in LDS, one tile per workgroup.
+template <int MW_, int NW_, int WN_, int RW_, int KS_ = 4>
+struct StreamGemm {
+  static constexpr int MW = MW_, NW = NW_, WM = 1, WN = WN_, RW = RW_, NSX = RW + 1, KS = KS_;   // KS: MFMA steps (16 of K) of a stage
+  static constexpr int RT = MW, CT = NW * WN, BM = 32 * RT, WAVES = WN, THREADS = 64 * WAVES;
+  static constexpr int PIECES = KS * MW, PX = (PIECES + WAVES - 1) / WAVES;
+  static constexpr int STAGE_BYTES = PIECES * 1024, LDS_BYTES = NSX * STAGE_BYTES;
+  // workgroups per CU: accumulators, weights and fragments in a SIMD's registers divided by its waves, LDS in half of a CU's
+  static constexpr int WGS = WAVES <= 4 && 16 * MW * NW + 4 * RW * NW * KS + 8 * MW <= 232 && 2 * LDS_BYTES <= 160 * 1024 ? 2 : 1;
+  static_assert(RW >= 2 && LDS_BYTES <= 160 * 1024, "");
+
+  struct Operands {
+    const char *x, *w[NW];      // next stage to be requested
+    uint32_t x_lane[PX], x_step, w_lane;
+    int left_x, left_w;
+  };
+  __device__ static __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+  template <typename XRow, typename WAt>
+  __device__ static __forceinline__ void make_operands(Operands& op, const f16* X, int ld, XRow x_row, const f16* Wp, WAt w_at,
+                                                       uint32_t w_lane, int s0) {
+    const int wave = wave_id(), lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+    op.x = (const char*)X + (size_t)s0 * 64 * ld;
+    op.x_step = 32u * KS * ld;
+#pragma unroll
+    for (int j = 0; j < PX; ++j) {
+      const int p = min(wave * PX + j, PIECES - 1);
+      op.x_lane[j] = (uint32_t)((p % KS * 2 + lg) * ld + x_row(p / KS * 32 + ln)) * 16u;
+    }
+#pragma unroll
+    for (int b = 0; b < NW; ++b) op.w[b] = (const char*)Wp + w_at(wave * NW + b) + (size_t)s0 * 2048;
+    op.w_lane = w_lane;
+  }
+  __device__ static __forceinline__ void request_x(Operands& op, char* slot, int j) {
+    char* dst = slot + (PIECES % WAVES == 0 ? wave_id() * PX + j : min(wave_id() * PX + j, PIECES - 1)) * 1024;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(wt_buffer(op.x), (__attribute__((address_space(3))) void*)dst, 16, op.x_lane[j], 0, 0, 0);
+    if (j == PX - 1) op.x += op.left_x-- > 1 ? op.x_step : 0u;
+  }
+  __device__ static __forceinline__ void load_w(Operands& op, u32x4 (&w)[NW][KS], int s) {
+#pragma unroll
+    for (int b = 0; b < NW; ++b) {
+      w[b][s] = __builtin_amdgcn_raw_buffer_load_b128(wt_buffer(op.w[b]), (int)op.w_lane + s * 1024, 0, 0);
+      if (s == KS - 1) op.w[b] += op.left_w > 1 ? 1024 * KS : 0;
+    }
+    if (s == KS - 1) --op.left_w;
+  }
+  template <int N> __device__ static __forceinline__ void wait_stage() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
+#endif
+  }
+  // One stage, its weights in w; the fragments of a step are requested for the stage RW further as soon as the step is issued.
+  __device__ static __forceinline__ void stage(f32x16 (&acc)[MW][NW], u32x4 (&w)[NW][KS], u32x4 (&xf)[2][MW], Operands& op, int& slot,
+                                               char* lds, const char* xb) {
+    constexpr int NM = MW * NW;
+    const int next = slot + 1 == NSX ? 0 : slot + 1, prev = slot == 0 ? NSX - 1 : slot - 1;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if (s == KS - 1) {
+        wait_stage<KS * NW + (NSX - 3) * (PX + KS * NW)>();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const char* xs = s < KS - 1 ? xb + slot * STAGE_BYTES + (s + 1) * 1024 : xb + next * STAGE_BYTES;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        const int a = m / NW, b = m % NW;
+        if (b == 0) xf[(s + 1) & 1][a] = *(const u32x4*)(xs + a * KS * 1024);
+        if (s == KS - 1) {
+#pragma unroll
+          for (int j = m * PX / NM; j < (m + 1) * PX / NM; ++j) request_x(op, lds + prev * STAGE_BYTES, j);
+        }
+        acc[a][b] = mfma_f16(w[b][s], xf[s & 1][a], acc[a][b]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      load_w(op, w, s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    slot = next;
+  }
+  // One tile (id): the arguments are those of DmaGemm::run.
+  template <typename Ops, typename Finish>
+  __device__ static __forceinline__ void run(int id, int, int, int n32, char* lds, Ops operands, Finish finish) {
+    const int ns = n32 / (KS / 2);                        // n32: 32s of K (KS = 4: an even number)
+    Operands op;
+    operands(op, id);
+    op.left_x = op.left_w = ns;
+    u32x4 w[RW][NW][KS], xf[2][MW];
+    // in the order of the loop: the wait counts hold from the first stage on
+#pragma unroll
+    for (int st = 0; st < RW; ++st) {
+#pragma unroll
+      for (int j = 0; j < PX; ++j) request_x(op, lds + st * STAGE_BYTES, j);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) load_w(op, w[st], s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    f32x16 acc[MW][NW];
+#pragma unroll
+    for (int a = 0; a < MW; ++a)
+#pragma unroll
+      for (int b = 0; b < NW; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+    const char* xb = lds + (threadIdx.x & 63) * 16;
+    wait_stage<RW * KS * NW + (RW - 1) * PX>();
+#pragma unroll
+    for (int a = 0; a < MW; ++a) xf[0][a] = *(const u32x4*)(xb + a * KS * 1024);
+    int slot = 0, i = 0;
+    for (; i + RW <= ns; i += RW) {
+#pragma unroll
+      for (int r = 0; r < RW; ++r) stage(acc, w[r], xf, op, slot, lds, xb);
+    }
+#pragma unroll
+    for (int r = 0; r < RW - 1; ++r)
+      if (i + r < ns) stage(acc, w[r], xf, op, slot, lds, xb);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // LDS must not be given away, nor reused, while a request may still write it
+    // The wait counts hold only if every load of weights is issued where it is written.  A use of the whole ring on every path
+    // keeps the compiler from dropping those of stages past the last one and from sinking those of the first stages into the loop.
+#pragma unroll
+    for (int r = 0; r < RW; ++r)
+#pragma unroll
+      for (int b = 0; b < NW; ++b)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(w[r][b][s]));
+#endif
+    finish(acc, id);
+  }
+};

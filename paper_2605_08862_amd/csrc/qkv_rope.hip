@@ -4,148 +4,208 @@
 //   (pairs (j, j + 64)), q stored as float16 rows (attention operand), k and v rounded to bf16 and written
 //   into the slot's KV page in the page layout.
 //
-// One workgroup = 32*MT rows x one head: its four waves hold 32 columns each, so the 128 columns of the
-// tile are exactly the head and the partner of column j (< 64) sits in the wave two places further.  After
-// the main loop (full K, no split) the waves exchange their accumulators through LDS once, rotate with the
-// step's cos / sin table and store the final values: the float32 projection never goes to memory and q, k,
-// v are still rounded exactly once, after the rotation.  Replaces a split-K GEMM + a separate rotary kernel
-// that had to sum the float32 slabs (13.5 + 8 us at M = 576, d = 1536 against about 15 us fused).
-#include "gemm_mfma.h"
+// One workgroup = rows x one head.  The partner of column j (< 64) of a head is two weight tiles further:
+//   two columns of waves (many rows)  wave column w multiplies tiles w and w + 2, so that both halves of a rotation are in one
+//                                     lane and the epilogue needs no exchange;
+//   four columns of waves (fewer rows) one tile each; the waves exchange their accumulators through LDS once.
+// The float32 projection never goes to memory and q, k, v are rounded exactly once, after the rotation.
+#include "gemm_dma.h"
+#include <type_traits>
 
 namespace {
 constexpr int kD = 128;
+constexpr int kLdx = kD + 4;                            // padded row (floats) of the exchange buffer
 
-template <int MT>
-__global__ void __launch_bounds__(256, (MT <= 2 ? 2 : 1))
-qkv_rope_kernel(Plan p, KvView kv, int M_max, int K, int Hq, int Hkv, const f16* __restrict__ A,
-                const f16* __restrict__ Wp, const float* __restrict__ cos_t, const float* __restrict__ sin_t,
-                f16* __restrict__ q_out, f16* __restrict__ k_pages, f16* __restrict__ v_pages, int m_blocks,
-                int defer_rows) {
-  using G = MfmaGemm<MT, 1, true>;
-  extern __shared__ __align__(16) char lds[];
-  // a one-round launch does not wait for the row count before its first loads: it multiplies all M_max rows (those
-  // beyond the count are stale rows, each affecting only its own output) and applies the count to the stores
-  int M = defer_rows ? M_max : min(p.n_rows[0], M_max);
-  // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2): every XCD takes a contiguous range
-  // of (head, M block) tiles, M block fastest, so a head's weights are fetched by one L2 only.
-  const int total = m_blocks * (Hq + 2 * Hkv), per_xcd = (total + 7) / 8;
-  const int tile = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (blockIdx.x / 8 >= per_xcd || tile >= total) return;
-  const int mb = tile % m_blocks, head = tile / m_blocks;
-  const int m0 = mb * G::BM;
-  if (m0 >= M) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ln = lane & 31, lg = lane >> 5;
-  const int nk = K / kBK;
+struct QkvArgs {
+  int M_max, K, Hq, Hkv, max_pages;
+  const f16 *A, *Wp;
+  const float *cos_t, *sin_t;
+  f16 *q_out, *k_pages, *v_pages;
+  const int32_t* block_table;
+};
 
-  typename G::Operands op;
+template <typename G>
+__device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0, int head, char* lds) {
+  constexpr bool PAIR = G::NW == 2;
+  static_assert(G::CT == 4 && (PAIR ? G::WN == 2 : G::WN == 4), "a workgroup's columns are one head");
+  const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
+  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const size_t tile_bytes = (size_t)(g.K / kBK) * 4096;
+  // position t = wn * NW + b of the LDS tiles holds tile wn + 2 b of the head (PAIR), or tile t
+  auto operands = [&](typename G::Operands& op, int) {
+    G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp,
+                     [&](int t) { return (size_t)(head * 4 + (PAIR ? (t >> 1) + 2 * (t & 1) : t)) * tile_bytes; }, lane * 16u, 0);
+  };
+  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int) {
+  const int M = min(p.n_rows[0], g.M_max);
+  // Accumulator register i of lane (ln, lg): row m0 + 32 (wm MW + a) + ln, column 32 tile + 8 (i / 4) + 4 lg + (i % 4) of the head.
+  const bool is_v = head >= g.Hq + g.Hkv;
+  float* s_x = (float*)lds;                             // [BM][kLdx]
+  if constexpr (!PAIR) {
+    if (!is_v) {
+      __syncthreads();                                  // every wave is done reading the loop's LDS stages
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    int row, g, s;
-    G::chunk_of(i, row, g, s);
-    const int r = min(m0 + row, M - 1);
-    op.x_rows[i] = A + (size_t)r * K + g * 32 + s * 8;
-    op.x_lds[i] = G::chunk_lds_offset(row, g, s);
+      for (int a = 0; a < G::MW; ++a)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+          *(f32x4*)(s_x + ((wm * G::MW + a) * 32 + ln) * kLdx + 32 * wn + 8 * i4 + 4 * lg) =
+              f32x4{acc[a][0][4 * i4], acc[a][0][4 * i4 + 1], acc[a][0][4 * i4 + 2], acc[a][0][4 * i4 + 3]};
+      __syncthreads();
+    }
   }
-  op.w_tiles[0] = Wp + (size_t)(head * 4 + wave) * nk * kWBlock + lane * 8;
-  f32x16 acc[MT][1];
 #pragma unroll
-  for (int mi = 0; mi < MT; ++mi)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[mi][0][i] = 0.f;
-  G::run(acc, op, 0, nk, lds);
-  if (defer_rows) M = min(p.n_rows[0], M_max);
-
-  // ---- epilogue.  Accumulator register i of lane (ln, lg) in tile mi: row m0 + 32 mi + ln,
-  // head column d = 32 wave + 8 (i / 4) + 4 lg + (i % 4).
-  const bool is_v = head >= Hq + Hkv;
-  constexpr int LDX = kD + 4;                         // padded row (floats) of the exchange buffer
-  float* s_x = (float*)lds;                           // [32 MT][LDX]; the loop's last barrier has been passed
-  if (!is_v) {
-    __syncthreads();                                  // every wave is done reading the loop's LDS stages
-#pragma unroll
-    for (int mi = 0; mi < MT; ++mi)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
-        *(f32x4*)(s_x + (mi * 32 + ln) * LDX + 32 * wave + 8 * i4 + 4 * lg) =
-            f32x4{acc[mi][0][4 * i4], acc[mi][0][4 * i4 + 1], acc[mi][0][4 * i4 + 2], acc[mi][0][4 * i4 + 3]};
-    __syncthreads();
-  }
-  const float sign = (wave < 2) ? -1.0f : 1.0f;       // y1 = x1 c - x2 s (columns < 64), y2 = x2 c + x1 s
-  const int partner = (wave < 2) ? 64 : -64;
-#pragma unroll
-  for (int mi = 0; mi < MT; ++mi) {
-    const int m = m0 + mi * 32 + ln;
+  for (int a = 0; a < G::MW; ++a) {
+    const int m = m0 + (wm * G::MW + a) * 32 + ln;
     if (m >= M) continue;
     size_t pbase = 0;
     int tok = 0;
-    if (head >= Hq) {                                 // k or v head: locate the row's cache slot
-      const int b = p.row_seq[m];
-      const int pos = p.seq_c[b] + p.row_pos[m];
-      const int page = kv.block_table[(size_t)p.seq_slot[b] * kv.max_pages + pos / kPage];
+    if (head >= g.Hq) {                                 // k or v head: locate the row's cache slot
+      const int b = p.row_seq[m], pos = p.seq_c[b] + p.row_pos[m];
       tok = pos % kPage;
-      pbase = (size_t)page * kv_page_elems(Hkv, kD);
+      pbase = (size_t)g.block_table[(size_t)p.seq_slot[b] * g.max_pages + pos / kPage] * kv_page_elems(g.Hkv, kD);
     }
+    // four consecutive columns d .. d + 3 of the head
+    auto store = [&](int d, const float (&y)[4]) {
+      if (head < g.Hq) {
+        *(f16x4*)(g.q_out + ((size_t)m * g.Hq + head) * kD + d) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
+        return;
+      }
+      // bf16-rounded values in float16 encoding (page format)
+      const f16x4 v = to_f16x4_guarded((float)(bf16)y[0], (float)(bf16)y[1], (float)(bf16)y[2], (float)(bf16)y[3], p.status);
+      if (!is_v) {
+        *(f16x4*)(g.k_pages + pbase + k_index_bf16(kD, head - g.Hq, tok, d)) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g.v_pages[pbase + v_index_bf16(kD, head - g.Hq - g.Hkv, tok, d + e)] = v[e];
+      }
+    };
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
-      const int d = 32 * wave + 8 * i4 + 4 * lg;      // four consecutive head columns d .. d + 3
-      float y[4];
-      if (is_v) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = acc[mi][0][4 * i4 + e];
-      } else {
-        const int j = d & 63;
-        const f32x4 c = *(const f32x4*)(cos_t + (size_t)m * 64 + j), sn = *(const f32x4*)(sin_t + (size_t)m * 64 + j);
-        const f32x4 other = *(const f32x4*)(s_x + (mi * 32 + ln) * LDX + d + partner);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = acc[mi][0][4 * i4 + e] * c[e] + sign * other[e] * sn[e];
+      const int d = 32 * wn + 8 * i4 + 4 * lg;
+      f32x4 c = f32x4{1.f, 1.f, 1.f, 1.f}, sn = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (!is_v) {
+        c = *(const f32x4*)(g.cos_t + (size_t)m * 64 + (d & 63));
+        sn = *(const f32x4*)(g.sin_t + (size_t)m * 64 + (d & 63));
       }
-      if (head < Hq) {
-        *(f16x4*)(q_out + ((size_t)m * Hq + head) * kD + d) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
-      } else {
-        // bf16-rounded values in float16 encoding (page format)
-        const f16x4 v = to_f16x4_guarded((float)(bf16)y[0], (float)(bf16)y[1], (float)(bf16)y[2], (float)(bf16)y[3], p.status);
-        if (!is_v) {
-          *(f16x4*)(k_pages + pbase + k_index_bf16(kD, head - Hq, tok, d)) = v;
-        } else {
+      float y[4];
+      if constexpr (PAIR) {
+        float y2[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v_pages[pbase + v_index_bf16(kD, head - Hq - Hkv, tok, d + e)] = v[e];
+        for (int e = 0; e < 4; ++e) {
+          const float x1 = acc[a][0][4 * i4 + e], x2 = acc[a][1][4 * i4 + e];
+          y[e] = is_v ? x1 : x1 * c[e] - x2 * sn[e];
+          y2[e] = is_v ? x2 : x2 * c[e] + x1 * sn[e];
         }
+        store(d, y);
+        store(d + 64, y2);
+      } else {
+        if (is_v) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = acc[a][0][4 * i4 + e];
+        } else {
+          const f32x4 other = *(const f32x4*)(s_x + ((wm * G::MW + a) * 32 + ln) * kLdx + (d ^ 64));
+          const float sign = d < 64 ? -1.0f : 1.0f;     // y1 = x1 c - x2 s (columns < 64), y2 = x2 c + x1 s
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = acc[a][0][4 * i4 + e] * c[e] + sign * other[e] * sn[e];
+        }
+        store(d, y);
       }
     }
   }
+  };
+  G::run(0, 1, 1, g.K / 32, lds, operands, finish);
 }
 
-template <int MT>
-void launch_t(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
-              const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
-  using G = MfmaGemm<MT, 1, true>;
-  const int m_blocks = (M_max + G::BM - 1) / G::BM, heads = s.Hq + 2 * s.Hkv;
-  size_t lds = G::LDS_BYTES;
-  const size_t lds_x = (size_t)32 * MT * (kD + 4) * 4;
-  if (lds < lds_x) lds = lds_x;
-  static bool attr_set = false;
-  if (!attr_set) { (void)hipFuncSetAttribute((const void*)qkv_rope_kernel<MT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); attr_set = true; }
-  const int grid = 8 * ((m_blocks * heads + 7) / 8);
-  hipLaunchKernelGGL((qkv_rope_kernel<MT>), dim3(grid), dim3(256), lds, st, p, kv, M_max, s.d, s.Hq, s.Hkv,
-                     (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, m_blocks,
-                     m_blocks * heads <= 512 ? 1 : 0);
+// The row count is only needed for the stores (rows beyond it are stale rows, each affecting only its own output).
+template <typename G>
+__global__ void __launch_bounds__(G::THREADS) qkv_kernel(Plan p, QkvArgs g, int m_blocks) {
+  extern __shared__ __align__(16) char lds[];
+  const int id = xcd_flat(m_blocks * (g.Hq + 2 * g.Hkv));
+  if (id >= 0) qkv_tile<G>(p, g, id % m_blocks * G::BM, id / m_blocks, lds);
+}
+// Rows of a workgroup's tile, with the time of one K tile in 0.01 us when a launch fills the CUs once.  The first stages, the epilogue
+// and the launch's ragged start take as long as about 8 K tiles.  Measured, 16 heads, K 1536 / 36 heads, K 3584:
+//   432 rows  32: 11.8 us, 64: 14.6, 128: 18.9     576 rows  32: 15.8, 64: 15.0, 128: 18.0
+//   1024 rows 64: 15.5, 128: 18.5, 192: 22         2048 rows 64: 26.3, 128: 20.2, 192: 24     3700 rows 64: 48, 128: 33.5, 192: 46
+//   64 rows   32: 24, 64: 28.5     288 rows 32: 35, 64: 26.6     816 rows 64: 50, 128: 36, 192: 41
+//   1185 rows 64: 73, 128: 57, 192: 49             2048 rows 64: 119, 128: 86, 192: 90
+// 128 and 192 rows are eight and twelve waves of two accumulator tiles and 80 KB, so that two workgroups share a CU and one's epilogue
+// runs beside the other's loop.  In four waves of six tiles 192 rows take 54 us at 1185 rows, 57 at 3700; 256 rows in one workgroup
+// per CU take 51 and 33, but a kernel that offers them has one workgroup per CU for every tile (128 rows: 62 and 39).
+// Up to 640 rows the weights of the small tiles are in registers (StreamGemm).  Beyond, the tile is chosen on the device: a workgroup
+// has twelve waves, of which four leave at once where the tile has eight.
+typedef StreamGemm<1, 1, 4, 6> Few32;
+typedef StreamGemm<2, 1, 4, 4> Few64;
+typedef DmaGemm<1, 1, 2, 4, 6> Rows64;
+typedef DmaGemm<1, 2, 4, 2, 5> Rows128;
+typedef DmaGemm<1, 2, 6, 2, 4> Rows192;
+__host__ __device__ inline int rows_cost(int M, int bm, int heads, int nk, int t) { return ((M + bm - 1) / bm * heads + kCUs - 1) / kCUs * (nk + 8) * t; }
+__host__ __device__ inline int pick_rows(int M, int heads, int nk, bool few, int& cost) {
+  int bm = 128;
+  cost = rows_cost(M, 128, heads, nk, 48);
+  int c = rows_cost(M, 64, heads, nk, 37);
+  if (c < cost) { bm = 64; cost = c; }
+  c = few ? rows_cost(M, 32, heads, nk, 31) : rows_cost(M, 192, heads, nk, 72);
+  if (c < cost) { bm = few ? 32 : 192; cost = c; }
+  return bm;
+}
+constexpr int kFewRows = 640;
+template <typename G> constexpr int qkv_lds() {
+  constexpr int x = G::NW == 2 ? 0 : G::BM * kLdx * 4;  // exchange buffer
+  return G::LDS_BYTES > x ? G::LDS_BYTES : x;
+}
+// Many rows: the rows of a tile from the step's row count.
+__global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, QkvArgs g) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(p.n_rows[0], g.M_max), heads = g.Hq + 2 * g.Hkv;
+  int cost;
+  const int bm = pick_rows(M, heads, g.K / kBK, false, cost), m_blocks = (M + bm - 1) / bm;
+  const int id = xcd_flat(m_blocks * heads);
+  if (id < 0) return;
+  const int m0 = id % m_blocks * bm, head = id / m_blocks;
+  if (bm == 192) {
+    qkv_tile<Rows192>(p, g, m0, head, lds);
+    return;
+  }
+  if (threadIdx.x >= 512) return;
+  if (bm == 64) qkv_tile<Rows64>(p, g, m0, head, lds);
+  else qkv_tile<Rows128>(p, g, m0, head, lds);
+}
+template <auto KERN, typename... Args>
+void launch_one(int blocks, int threads, int lds, hipStream_t st, const Args&... args) {
+  static bool done = false;                              // one per kernel
+  if (!done) { (void)hipFuncSetAttribute((const void*)KERN, hipFuncAttributeMaxDynamicSharedMemorySize, lds); done = true; }
+  hipLaunchKernelGGL(KERN, dim3((blocks + 7) / 8 * 8), dim3(threads), lds, st, args...);
 }
 }  // namespace
 
-bool qkv_rope_supported(const Shape& s) { return s.dtype == BS_BF16 && s.D == kD; }
+// Few rows have too few (rows, head) tiles for 256 CUs: the GEMM split over K and the rotary kernel behind it (6 us; both have 11 us of
+// launches and latency, the fused kernel 3) are then faster.  Measured, 7B shape: 64 rows 13 + 6 us, 24 fused; 136 rows 14 + 6, 22.
+// 1.5B shape: 432 rows 12 + 7, 12 fused; 576 rows 13 + 7.6, 15.
+bool qkv_rope_applies(const Shape& s, int M_max) {
+  if (s.dtype != BS_BF16 || s.D != kD) return false;
+  if (M_max > kFewRows) return true;
+  int cost;
+  pick_rows(M_max, s.Hq + 2 * s.Hkv, s.d / kBK, true, cost);
+  return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 1100;
+}
 
 void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
-  // 32-row tiles while that gives at most two workgroups per CU (measured at M = 576, 16 heads: 13.5 us
-  // against 15.3 us with 64-row tiles); larger tiles re-read the weights less often when there are many rows
-  const int tiles1 = (M_max + 31) / 32 * (s.Hq + 2 * s.Hkv);
-  int mt = tiles1 <= 512 ? 1 : (tiles1 <= 2048 ? 2 : 4);
-  // between one and two 32-row workgroups per CU with a long contraction, 64-row tiles (at most one workgroup per
-  // CU, half the weight re-reads) are faster: 7B shape, 288 rows x 36 heads, 42.5 -> 33.4 us; with the short
-  // contraction of the 1.5B shape (576 rows x 16 heads) they are not: 20.3 -> 21.8 us
-  if (tiles1 > 256 && tiles1 <= 512 && s.d >= 2048) mt = 2;
-  if (mt <= 1) launch_t<1>(s, p, kv, M_max, A, Wp, cos_t, sin_t, q_out, k_pages, v_pages, st);
-  else if (mt == 2) launch_t<2>(s, p, kv, M_max, A, Wp, cos_t, sin_t, q_out, k_pages, v_pages, st);
-  else launch_t<4>(s, p, kv, M_max, A, Wp, cos_t, sin_t, q_out, k_pages, v_pages, st);
+  const int heads = s.Hq + 2 * s.Hkv;
+  const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, kv.max_pages, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, kv.block_table};
+  if (M_max > kFewRows) {
+    constexpr int a = qkv_lds<Rows64>(), b = qkv_lds<Rows128>(), c = qkv_lds<Rows192>(), ab = a > b ? a : b, lds = ab > c ? ab : c;
+    static_assert(Rows64::THREADS == 512 && Rows128::THREADS == 512 && 2 * lds <= 160 * 1024, "two workgroups per CU");
+    launch_one<qkv_rows_kernel>((M_max + 63) / 64 * heads, Rows192::THREADS, lds, st, p, g);
+    return;
+  }
+  int cost;
+#define BS_QKV(G_) do { const int mb = (M_max + G_::BM - 1) / G_::BM; launch_one<qkv_kernel<G_>>(mb * heads, G_::THREADS, qkv_lds<G_>(), st, p, g, mb); } while (0)
+  switch (pick_rows(M_max, heads, s.d / kBK, true, cost)) {
+    case 32: BS_QKV(Few32); break;
+    case 64: BS_QKV(Few64); break;
+    default: BS_QKV(Rows128);
+  }
+#undef BS_QKV
 }

@@ -7,7 +7,7 @@
 //   phase 2  the one row per sequence that is sampled from (recovered, bonus or plain token) is read back, or
 //            recomputed by the same MFMA loop (bit-identical logits), and sampled by inverse CDF in
 //            vocabulary order with float64 running sums (Eq. 3 / max(0, p - q)).
-#include "gemm_mfma.h"
+#include "gemm_dma.h"
 
 enum { MODE_NONE = 0, MODE_PLAIN = 1, MODE_RESID_ONEHOT = 2, MODE_RESID_DENSE = 3 };
 
@@ -36,56 +36,33 @@ int lmhead_logit_rows(const Shape& s) { return s.dtype == BS_BF16 ? s.d / 4 : 0;
 
 // ------------------------------------------------------------------ phase 1 / phase 2 GEMM (bf16)
 // STATS = true : rows are the packed query rows; epilogue writes statistics (+ optional debug logits).
-// STATS = false: rows are gathered through sel_row (one per sequence); epilogue stores float32 logits
-//                to sel_logits [B, V].
-template <int kLmMT, bool STATS>
-__global__ void __launch_bounds__(256, (kLmMT <= 3 ? 2 : 1)) lmhead_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int V, int K,
-                                                     const f16* __restrict__ X, const int32_t* __restrict__ x_rows,
-                                                     const f16* __restrict__ W, float inv_temp,
+// STATS = false: rows are the gathered ones (one per sequence); epilogue stores float32 logits to sel_logits [B, V].
+template <typename G, bool STATS>
+__global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhead_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int V, int K,
+                                                     const f16* __restrict__ X, int ld, const f16* __restrict__ W, float inv_temp,
                                                      const int32_t* __restrict__ row_target, SamplerBufs sb,
-                                                     float* __restrict__ store, int m_blocks, int n_blocks) {
-  using G = MfmaGemm<kLmMT, kLmNT, true>;
+                                                     float* __restrict__ store, int n_blocks) {
+  constexpr int kLmMT = G::MW;
+  static_assert(G::NW == kLmNT, "a wave's columns are one statistics tile");
   extern __shared__ __align__(16) char lds[];
   const int M = n_rows_dev ? min(*n_rows_dev, M_max) : M_max;
-  const int total = m_blocks * n_blocks;
-  const int per_xcd = (total + 7) / 8;
-  const int id = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (id >= total) return;
-  const int mb = id % m_blocks, nb = id / m_blocks;
-  const int m0 = mb * G::BM;
-  if (m0 >= M) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int vt = nb * 4 + wave;                       // statistics tile of this wave
+  const int m_blocks = (M + G::BM - 1) / G::BM;
+  const int id0 = xcd_flat(m_blocks * n_blocks);
+  if (id0 < 0) return;
+  const int wave = G::wave_id(), lane = threadIdx.x & 63;
+  const size_t tile_bytes = (size_t)(K / kBK) * 4096;
+  const int t_last = (V + 31) / 32 - 1;
+  auto operands = [&](typename G::Operands& op, int id) {
+    const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT;
+    G::make_operands(op, X, ld, [&](int r) { return min(m0 + r, M - 1); }, W, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, lane * 16u, 0);
+  };
+  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int id) {
+  const int m0 = id % m_blocks * G::BM + wave / G::WN * kLmMT * 32;      // first row of this wave
+  const int vt = id / m_blocks * G::WN + wave % G::WN;           // statistics tile of this wave
   const int n_wave0 = vt * kLmVtile;
-
-  typename G::Operands op;
-#pragma unroll
-  for (int i = 0; i < kLmMT; ++i) {
-    int row, g, s;
-    G::chunk_of(i, row, g, s);
-    int r = min(m0 + row, M - 1);
-    if (x_rows) r = x_rows[r];
-    op.x_rows[i] = X + (size_t)r * K + g * 32 + s * 8;
-    op.x_lds[i] = G::chunk_lds_offset(row, g, s);
-  }
-  const int nk = K / kBK;
-  const int n_tiles = (V + 31) / 32;
-#pragma unroll
-  for (int ni = 0; ni < kLmNT; ++ni) {
-    const int nt = min(n_wave0 / 32 + ni, n_tiles - 1);
-    op.w_tiles[ni] = W + (size_t)nt * nk * kWBlock + lane * 8;
-  }
-  f32x16 acc[kLmMT][kLmNT];
-#pragma unroll
-  for (int mi = 0; mi < kLmMT; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < kLmNT; ++ni)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
-  G::run(acc, op, 0, nk, lds);
   if (n_wave0 >= V) return;
 
-  // accumulator (SWAP): rows = vocabulary entries n_wave0 + ni*32 + acc_row, lane column = token
+  // accumulator: rows = vocabulary entries n_wave0 + ni*32 + acc_row, lane column = token
   const bool store_vec = (V & 3) == 0 && ((uintptr_t)store & 15) == 0;   // V % 4 == 0: groups of four never straddle V
 #pragma unroll
   for (int mi = 0; mi < kLmMT; ++mi) {
@@ -170,6 +147,8 @@ __global__ void __launch_bounds__(256, (kLmMT <= 3 ? 2 : 1)) lmhead_kernel(const
         }
     }
   }
+  };
+  G::run(id0, 1, id0 + 1, K / 32, lds, operands, finish);
 }
 
 // ------------------------------------------------------------------ statistics of given float32 logits
@@ -733,43 +712,49 @@ __global__ void __launch_bounds__(kPickThreads) sample_pick_kernel(int V, const 
 }
 
 // ------------------------------------------------------------------ launchers
-template <int MT, bool STATS>
-static void launch_lmhead_t(const Shape& s, const int32_t* n_rows_dev, int M_max, const void* hf, const int32_t* x_rows,
+template <typename G, bool STATS>
+static void launch_lmhead_t(const Shape& s, const int32_t* n_rows_dev, int M_max, const void* hf, int ld,
                             const void* lm_head, float inv_temp, const int32_t* row_target, const SamplerBufs& sb,
                             float* store, hipStream_t st) {
-  using G = MfmaGemm<MT, kLmNT, true>;
-  int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (s.V + 4 * kLmVtile - 1) / (4 * kLmVtile);
-  int grid = ((m_blocks * n_blocks + 7) / 8) * 8;
-  static bool attr_set = false;              // more than 64 KiB of dynamic LDS needs an opt-in (192-row tiles)
-  if (!attr_set) { (void)hipFuncSetAttribute((const void*)lmhead_kernel<MT, STATS>, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES); attr_set = true; }
-  hipLaunchKernelGGL((lmhead_kernel<MT, STATS>), dim3(grid), dim3(256), G::LDS_BYTES, st, n_rows_dev, M_max, s.V, s.d,
-                     (const f16*)hf, x_rows, (const f16*)lm_head, inv_temp, row_target, sb, store, m_blocks, n_blocks);
+  const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (s.V + G::WN * kLmVtile - 1) / (G::WN * kLmVtile);
+  const int grid = ((m_blocks * n_blocks + 7) / 8) * 8;
+  static bool attr_set = false;              // more than 64 KiB of dynamic LDS needs an opt-in
+  if (!attr_set) { (void)hipFuncSetAttribute((const void*)lmhead_kernel<G, STATS>, hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS_BYTES); attr_set = true; }
+  hipLaunchKernelGGL((lmhead_kernel<G, STATS>), dim3(grid), dim3(G::THREADS), G::LDS_BYTES, st, n_rows_dev, M_max, s.V, s.d,
+                     (const f16*)hf, ld, (const f16*)lm_head, inv_temp, row_target, sb, store, n_blocks);
 }
 template <bool STATS>
-static void launch_lmhead_any(const Shape& s, const int32_t* n_rows_dev, int M_max, const void* hf, const int32_t* x_rows,
+static void launch_lmhead_any(const Shape& s, const int32_t* n_rows_dev, int M_max, const void* hf, int ld,
                               const void* lm_head, float inv_temp, const int32_t* row_target, const SamplerBufs& sb,
                               float* store, hipStream_t st) {
-  // Row tiling.  The vocabulary gives thousands of workgroups (many rounds per CU), so above 128 rows the
-  // 96-row tile is used: it fits two workgroups per CU, and the statistics epilogue and the pipeline fill of
-  // one overlap the matrix products of the other (measured at M = 576, V = 151936: 308 us against 372 us with
-  // 192-row tiles, one workgroup per CU).
-  const int mt = M_max <= 32 ? 1 : M_max <= 64 ? 2 : M_max <= 128 ? 4 : 3;
-#define BS_LM(MT_) launch_lmhead_t<MT_, STATS>(s, n_rows_dev, M_max, hf, x_rows, lm_head, inv_temp, row_target, sb, store, st)
-  switch (mt) {
-    case 1: BS_LM(1); break;
-    case 2: BS_LM(2); break;
-    case 4: BS_LM(4); break;
-    default: BS_LM(3);
-  }
+  // The vocabulary gives hundreds of workgroups, several rounds of the CUs.  Up to 96 rows one row block and 320 entries per
+  // workgroup (one round of 475 workgroups, two per CU: 96 rows 114 us on the 1.5B shape, 124 with 256 entries).  Above, 96 or 128 rows, two
+  // workgroups per CU so that one's epilogue overlaps the other's products: the larger tile does 9 % more work per unit of time,
+  // against the rows it pads.  Measured, 1.5B / 7B shape, before in brackets: 64 rows 104 / 213 us (115 / 225), 288 rows 212 / 401
+  // (211 / 397), 576 rows 266 / 614 (275 / 623), 1185 rows 534 / 1171 (583 / 1304), 3480 rows 1497 (1659).
+  const int p96 = (M_max + 95) / 96 * 96, p128 = (M_max + 127) / 128 * 128;
+#define BS_LM(...) launch_lmhead_t<StreamGemm<__VA_ARGS__>, STATS>(s, n_rows_dev, M_max, hf, ld, lm_head, inv_temp, row_target, sb, store, st)
+  if (M_max <= 32) BS_LM(1, 2, 5, 4);
+  else if (M_max <= 64) BS_LM(2, 2, 5, 3);
+  else if (M_max <= 96) BS_LM(3, 2, 5, 3);
+  else if (109 * p96 < 100 * p128) BS_LM(3, 2, 4, 2);
+  else BS_LM(4, 2, 4, 2);
 #undef BS_LM
 }
 void launch_lmhead_stats(const Shape& s, const Plan& p, int M_max, const void* hf, const void* lm_head, float inv_temp,
                          const SamplerBufs& sb, float* logits_debug, hipStream_t st) {
-  launch_lmhead_any<true>(s, p.n_rows, M_max, hf, nullptr, lm_head, inv_temp, p.row_target, sb, logits_debug, st);
+  launch_lmhead_any<true>(s, p.n_rows, M_max, hf, M_max, lm_head, inv_temp, p.row_target, sb, logits_debug, st);
 }
-void launch_lmhead_rows(const Shape& s, int B, const void* hf, const void* lm_head, const SamplerBufs& sb,
+// Final rows sel_row[b] -> rows 0 .. B - 1 of a compact matrix (both in chunk order).
+__global__ void __launch_bounds__(256) gather_rows_kernel(int B, int d, const f16* __restrict__ hf, int ld, const int32_t* __restrict__ sel_row,
+                                                          f16* __restrict__ out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;          // one chunk of eight elements; consecutive threads: consecutive sequences
+  if (i < d / 8 * B) *(f16x8*)(out + (size_t)i * 8) = *(const f16x8*)(hf + ((size_t)(i / B) * ld + sel_row[i % B]) * 8);
+}
+void launch_lmhead_rows(const Shape& s, int B, int M_max, const void* hf, void* rows, const void* lm_head, const SamplerBufs& sb,
                         hipStream_t st) {
-  launch_lmhead_any<false>(s, nullptr, B, hf, sb.sel_row, lm_head, 1.0f, nullptr, sb, sb.sel_logits, st);
+  hipLaunchKernelGGL(gather_rows_kernel, dim3((s.d / 8 * B + 255) / 256), dim3(256), 0, st, B, s.d, (const f16*)hf, M_max, sb.sel_row, (f16*)rows);
+  launch_lmhead_any<false>(s, nullptr, B, rows, B, lm_head, 1.0f, nullptr, sb, sb.sel_logits, st);
 }
 void launch_logit_stats(const Plan& p, int M_max, int V, const float* logits, float inv_temp, const SamplerBufs& sb,
                         hipStream_t st) {

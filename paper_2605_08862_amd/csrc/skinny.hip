@@ -8,7 +8,7 @@
 //     the packed weights HBM -> registers, one contiguous KiB per load, and the partial tiles meet in LDS at the end.
 //     Where that gives fewer workgroups than CUs, K is also split across workgroups and the last one to arrive adds the
 //     partial tiles (publish_arrival: no slabs for another kernel to sum);
-//   * activations are kept in MFMA fragment order too (act_frag_index, h_frag_index), so a fragment is one contiguous
+//   * activations are kept in MFMA fragment order too (act_index, h_frag_index), so a fragment is one contiguous
 //     KiB from L2 straight into operand registers: no LDS staging, no swizzle, no barrier in the main loop;
 //   * O and down add their result to the residual themselves and write the sum of squares of their 32 columns per row.  QKV
 //     adds those up and normalises the residual as it reads it; in front of gate/up the normalisation is one small
@@ -343,7 +343,7 @@ skinny_glu_kernel(Plan p, int K, const f16* __restrict__ X, const f16* __restric
     float y[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) y[j] = silu_fast(acc[0][4 * i4 + j]) * acc[1][4 * i4 + j];
-    *(f16x4*)(act + act_frag_index(ln, unit * 32 + 8 * i4 + 4 * lg, units / 2)) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
+    *(f16x4*)(act + act_index(ln, unit * 32 + 8 * i4 + 4 * lg, kSkinnyRows)) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
   }
 }
 
@@ -404,10 +404,10 @@ __global__ void __launch_bounds__(256) embed_frag_kernel(Plan p, int d, const bf
   if (threadIdx.x == 0) ssq[r] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Final RMSNorm: fragment-ordered residual -> row-major float16 rows (operand of the LM head).
+// Final RMSNorm: fragment-ordered residual -> float16 rows in chunk order (operand of the LM head).
 __global__ void __launch_bounds__(256) final_norm_frag_kernel(Plan p, int d, float eps, const float* __restrict__ h,
                                                               const float* __restrict__ ssq, int ssq_parts,
-                                                              const float* __restrict__ gain, f16* __restrict__ out) {
+                                                              const float* __restrict__ gain, f16* __restrict__ out, int ld) {
   __shared__ float red[4];
   const int r = blockIdx.x;
   if (r >= p.n_rows[0]) return;
@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(256) final_norm_frag_kernel(Plan p, int d, flo
   const float inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + eps);
   for (int i = threadIdx.x * 4; i < d; i += 1024) {
     const f32x4 v = *(const f32x4*)(h + h_frag_index(r, i, d / kBK)), g = *(const f32x4_u*)(gain + i);
-    *(f16x4*)(out + (size_t)r * d + i) = to_f16x4_guarded(v[0] * inv * g[0], v[1] * inv * g[1], v[2] * inv * g[2], v[3] * inv * g[3], p.status);
+    *(f16x4*)(out + act_index(r, i, ld)) = to_f16x4_guarded(v[0] * inv * g[0], v[1] * inv * g[1], v[2] * inv * g[2], v[3] * inv * g[3], p.status);
   }
 }
 }  // namespace
@@ -433,7 +433,7 @@ void launch_skinny_embed(const Shape& s, const Plan& p, const void* embed, float
 }
 void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, const float* gain,
                               void* out, hipStream_t st) {
-  hipLaunchKernelGGL(final_norm_frag_kernel, dim3(M_max), dim3(256), 0, st, p, s.d, s.eps, h, ssq, s.d / 32, gain, (f16*)out);
+  hipLaunchKernelGGL(final_norm_frag_kernel, dim3(M_max), dim3(256), 0, st, p, s.d, s.eps, h, ssq, s.d / 32, gain, (f16*)out, M_max);
 }
 void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, const float* h, const float* ssq, int ssq_parts,
                        const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, const SkinnyBufs& sk, hipStream_t st) {

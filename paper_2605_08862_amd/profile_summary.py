@@ -51,15 +51,14 @@ def classify(names):
         cls = None
         if "attn_mfma_kernel" in n or "attn_wide_kernel" in n:
             cls, marker = "attention", "attention"
-        elif "qkv_rope_kernel" in n or "skinny_kernelILi0E" in n:
+        elif "qkv_kernel" in n or "qkv_rows_kernel" in n or "skinny_kernelILi0E" in n:
             cls = "gemm_qkv"
-        elif "gemm8_kernel" in n or "skinny_glu_kernel" in n or "gemm_ring2_swiglu_kernel" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi2E", n):
+        elif re.search(r"glu_(rows_)?kernel", n):
             cls, marker = "gemm_gate_up", "gate_up"
-        elif "gemm_resid_kernel" in n or "skinny_kernelILi1E" in n or re.search(r"gemm_mfma_kernelILi\dELi\dELi1E", n):
-            cls = "gemm_down" if marker == "gate_up" else "gemm_o"
-        elif re.search(r"gemm_mfma_kernelILi\dELi\dELi3E", n):
-            cls = "gemm_qkv"                                   # unfused QKV projection (head sizes other than 128)
-        elif re.search(r"lmhead_kernelILi\dELb1E", n):
+        elif re.search(r"slab_(alt_)?kernel", n) or "skinny_kernelILi1E" in n:
+            # a layer's order: QKV (where it is not the fused kernel), attention, O, gate/up, down
+            cls, marker = {"gate_up": "gemm_down", "attention": "gemm_o"}.get(marker, "gemm_qkv"), None
+        elif re.search(r"lmhead_kernel.*(ELb1E|, true>)", n):
             cls = "lmhead"
         out.append(cls)
     return out

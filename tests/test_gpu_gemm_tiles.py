@@ -1,0 +1,22 @@
+"""GPU parity at the edges of the bf16 GEMM launches: the launchers choose row tiles, columns per workgroup and K splits by the row
+limit and the widths.  One layer; K tiles that no ring length divides (5 and 7), widths that no column tile divides (320, 448, 12352 features,
+the last wide enough for the weight-stationary gate/up tiles)."""
+import numpy as np
+import pytest
+
+from paper_2605_08862_amd import workloads as W
+from tests.test_gpu_bf16 import _run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_ffn,n_seq,k_max", [(448, 11, 2), (448, 16, 3), (448, 13, 4), (448, 32, 4), (448, 23, 6), (448, 39, 4), (448, 64, 4),
+                                               (448, 107, 2), (448, 128, 4), (448, 43, 14), (448, 69, 16), (12352, 11, 2), (12352, 13, 4),
+                                               (12352, 49, 1), (12352, 43, 2), (12352, 27, 6), (12352, 36, 6), (12352, 64, 4), (12352, 107, 2)])
+def test_gemm_launches_at_row_limit(d_ffn, n_seq, k_max):
+    """Row limits 33, 64, 65, 160, 161, 195, 320, 321, 640, 645 and 1173 (narrow), 33, 65, 98, 129, 189, 252, 320 and 321 (wide); full
+    draft blocks, so every row of every tile is live, with two short ones at the end, so that the last tile is not full."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=320, n_q_heads=14, n_kv_heads=2, d_ffn=d_ffn, vocab=777)
+    rng = np.random.default_rng(n_seq)
+    ctx = [int(x) for x in rng.integers(0, 70, n_seq)]
+    _run_case(desc, ctx_lens=ctx, k_b=[k_max] * (n_seq - 2) + [k_max - 1, 0], k_max=k_max, seed=70 + k_max, q_mode="onehot", check_kv=(n_seq < 20))

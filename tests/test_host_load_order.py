@@ -1,0 +1,51 @@
+"""CPU check of the compiled GEMM loops: spills, and the order in which loads are issued.  (hipcc cross-compiles; no GPU needed.)"""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2605_08862_amd import build as BLD
+
+
+def stream_events(mw, nw, wn, rw, ks):
+    """Loads of activations into LDS (X), of weights into registers (w) and barriers (|) of a StreamGemm loop, in the order that its
+    wait counts assume: the ring's stages, then per stage (a loop of rw of them, up to rw - 1 more behind it) all steps' weights but
+    the last, the barrier, the activations, the last step's weights."""
+    x = "X" * -(-ks * mw // wn)
+    return (x + "w" * (ks * nw)) * rw + "|" + ("w" * ((ks - 1) * nw) + "|" + x + "w" * nw) * (2 * rw - 1)
+
+
+@pytest.mark.parametrize("source, kernels", [("gemm.hip", 15), ("qkv_rope.hip", 2), ("sampler.hip", 10)])
+def test_weight_ring_loads_are_issued_where_they_are_written(tmp_path, source, kernels):
+    """A wait for "at most N requests in flight" is right only if every request is issued where the source has it: a load that the
+    compiler drops or moves past a wait would let a stage be multiplied before it has arrived."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "kernels.s"
+    r = subprocess.run([hipcc, *BLD.FLAGS, "--offload-device-only", "-S", "-Rpass-analysis=kernel-resource-usage",
+                        os.path.join(BLD.CSRC, source), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    spills = {n: int(s) for n, s in re.findall(r"Function Name: (\S+).*?VGPRs Spill: (\d+)", r.stderr, re.S)}
+    checked = 0
+    for name, body in re.findall(r"\n(_Z\S+):\s*; @.*?\n(.*?)\n\.Lfunc_end", out.read_text(), re.S):
+        if not re.search(r"StreamGemmI|DmaGemmI|_rows_kernel", name):
+            continue
+        assert spills[name] == 0, name
+        events = ""
+        for line in body.split("\n"):
+            line = line.strip()
+            if line.startswith("buffer_load") and line.endswith(" lds"):
+                events += "X"
+            elif line.startswith("buffer_load_dwordx4"):
+                events += "w"
+            elif line.startswith("s_barrier"):
+                events += "|"
+        tiles = [tuple(map(int, t)) for t in re.findall(r"(?:StreamGemm|S\d*_)ILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)]
+        if len(tiles) == 1 or len(tiles) == 2:                # a kernel with two tiles has their loops one after the other
+            orders = [tiles, tiles[::-1]]
+            assert any(events.startswith("".join(stream_events(*t) for t in o)) for o in orders), (name, events)
+            checked += 1
+    assert checked >= kernels, checked
