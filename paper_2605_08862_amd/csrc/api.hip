@@ -437,16 +437,16 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
     { ProfScope ps(c, BS_PROF_EMPTY, st); }
     if (skinny) {
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-        launch_skinny_qkv(s, p, c->kv, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
+        launch_skinny_qkv(s, p, c->kv, M_max, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
                           c->q, c->k_pages[l], c->v_pages[l], c->sk, st); }
       launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, kSkinnyRows,
                        c->attn_scratch, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
       { ProfScope ps(c, BS_PROF_GEMM_O, st);
-        launch_skinny_resid(s, p, s.Hq * s.D, c->attn_out, c->wo[l], c->h, c->ssq, c->sk, st); }
+        launch_skinny_resid(s, p, M_max, s.Hq * s.D, c->attn_out, c->wo[l], c->h, c->ssq, c->sk, st); }
       { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
-        launch_skinny_gate_up(s, p, c->h, c->ssq, s.d / 32, c->mlp_norm[l], c->a, c->w_gate_up[l], c->act, st); }
+        launch_skinny_gate_up(s, p, M_max, c->h, c->ssq, s.d / 32, c->mlp_norm[l], c->a, c->w_gate_up[l], c->act, st); }
       { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
-        launch_skinny_resid(s, p, s.F, c->act, c->w_down[l], c->h, c->ssq, c->sk, st); }
+        launch_skinny_resid(s, p, M_max, s.F, c->act, c->w_down[l], c->h, c->ssq, c->sk, st); }
       continue;
     }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->attn_norm[l], c->a, st);

@@ -376,12 +376,12 @@ void launch_skinny_embed(const Shape& s, const Plan& p, const void* embed, float
                          float* cos_t, float* sin_t, hipStream_t st);
 void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, const float* gain,
                               void* out, hipStream_t st);
-void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, const float* h, const float* ssq, int ssq_parts,
+void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* h, const float* ssq, int ssq_parts,
                        const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages,
                        void* v_pages, const SkinnyBufs& sk, hipStream_t st);
-void launch_skinny_gate_up(const Shape& s, const Plan& p, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
+void launch_skinny_gate_up(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
                            const void* W, void* act, hipStream_t st);      // a: scratch for the normalised rows
-void launch_skinny_resid(const Shape& s, const Plan& p, int K, const void* X, const void* W, float* h, float* ssq,
+void launch_skinny_resid(const Shape& s, const Plan& p, int M_max, int K, const void* X, const void* W, float* h, float* ssq,
                          const SkinnyBufs& sk, hipStream_t st);
 // attention.hip
 // out_ld: ld of the output rows (bf16 models: chunk order, act_index).

@@ -16,6 +16,9 @@
 //     launch subtracted: 8.1 us against 6.1 + 4.0.  Gate/up has a wave per tile and every wave would convert the whole residual: 7B shape, staged
 //     in LDS once per workgroup, 56 us against 45 + 4.)
 // Loads are issued in the order in which they are waited for (the memory counter is in order).
+// A CU draws about 54 GB/s, so what it reads is what it costs, and a fragment of 32 rows is as many bytes as one of the weights: lanes
+// of rows beyond the row limit read the last row again, which costs no line of its own (9 rows: half of the
+// bytes; 1.5B shape, gate/up 14.9 -> 14.0 us, O and down 9.3 -> 8.6 on average; cutting K over more waves than now takes gate/up to 16).
 #include "gemm_mfma.h"
 #include <type_traits>
 
@@ -96,7 +99,7 @@ __device__ __forceinline__ int xcd_range(int n) {
 // SK_QKV takes the float32 residual and normalises it, SK_RESID float16 rows in fragment order.
 template <int KIND>
 __global__ void __launch_bounds__(512, 2)
-skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* __restrict__ Wp, float* h, float* __restrict__ ssq_out, int d,
+skinny_kernel(Plan p, int rows, int K, const f16* __restrict__ X, NormIn nin, const f16* __restrict__ Wp, float* h, float* __restrict__ ssq_out, int d,
               QkvOut qo, int units, int n_split, float* __restrict__ part, int32_t* __restrict__ counters) {
   constexpr int WS = 8;
   using R = WaveSum<WS>;
@@ -135,11 +138,12 @@ skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* _
   // condition the compiler would have to wait for all outstanding loads); beyond the wave's range its last tile is read again.
   const wt_buf wr = wt_buffer(Wp + (size_t)tile0 * nk * kWBlock), xr = wt_buffer(NORM ? (const void*)nin.h : (const void*)X);
   const int kl = max(kt1 - 1, 0);
+  const uint32_t x_lane = (lg * 32 + min(ln, rows - 1)) * 16;
   auto load_x = [&](auto stage_tag, int kt) {
     constexpr int ST = decltype(stage_tag)::value, N = NORM ? 8 : 4;
     const int so = min(kt, kl) * (N * 1024);
 #pragma unroll
-    for (int s = 0; s < N; ++s) x[ST][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, lane * 16 + (s & 3) * 1024, so + (s >> 2) * 4096, 0);
+    for (int s = 0; s < N; ++s) x[ST][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)x_lane + (s & 3) * 1024, so + (s >> 2) * 4096, 0);
   };
   auto load_w = [&](auto stage_tag, int kt) {
     constexpr int ST = decltype(stage_tag)::value;
@@ -162,7 +166,12 @@ skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* _
   float inv = 0.f;
   f32x4 h_old = f32x4{0.f, 0.f, 0.f, 0.f};              // SK_RESID: the residual this wave will add to
   f32x4* h_at = nullptr;
+  f32x4 rot_c = f32x4{0.f, 0.f, 0.f, 0.f}, rot_s = rot_c;   // SK_QKV: the rotation
+  // SK_QKV: the four columns dc .. dc + 3 (and their partners dc + 64 ..) that this wave stores, if it stores any
+  const int dc = 32 * ((unit >> 1) & 1) + half * 16 + 8 * (wave & 1) + 4 * lg;
   if constexpr (NORM) {
+    rot_c = *(const f32x4*)(qo.cos_t + (size_t)min(ln, rows - 1) * 64 + dc);
+    rot_s = *(const f32x4*)(qo.sin_t + (size_t)min(ln, rows - 1) * 64 + dc);
     if ((unit >> 2) >= qo.Hq && ln < M) {
       const int b = p.row_seq[ln], pos = p.seq_c[b] + p.row_pos[ln];
       tok = pos % kPage;
@@ -257,12 +266,11 @@ skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* _
     constexpr int D = 128;
     const f32x4 a = total(wave), b = total(wave + 2);
     if (m >= M) return;
-    const int head = unit >> 2, dc = 32 * ((unit >> 1) & 1) + half * 16 + 8 * wave + 4 * lg;      // columns dc .. dc + 3, dc + 64 ..
+    const int head = unit >> 2;
     f32x4 y1 = a, y2 = b;
     if (head < qo.Hq + qo.Hkv) {
-      const f32x4 c = *(const f32x4*)(qo.cos_t + (size_t)m * 64 + dc), sn = *(const f32x4*)(qo.sin_t + (size_t)m * 64 + dc);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { y1[e] = a[e] * c[e] - b[e] * sn[e]; y2[e] = b[e] * c[e] + a[e] * sn[e]; }
+      for (int e = 0; e < 4; ++e) { y1[e] = a[e] * rot_c[e] - b[e] * rot_s[e]; y2[e] = b[e] * rot_c[e] + a[e] * rot_s[e]; }
     }
     if (head < qo.Hq) {
       f16* dst = qo.q + ((size_t)m * qo.Hq + head) * D + dc;
@@ -290,7 +298,7 @@ skinny_kernel(Plan p, int K, const f16* __restrict__ X, NormIn nin, const f16* _
 // whole K, three K tiles (24 KiB of weights) ahead: no sum over waves, no LDS, no barrier, and because every unit of the
 // launch is resident at once and draws the same share of the memory bandwidth, no tail.
 __global__ void __launch_bounds__(256, 2)
-skinny_glu_kernel(Plan p, int K, const f16* __restrict__ X, const f16* __restrict__ Wp, int units, f16* __restrict__ act) {
+skinny_glu_kernel(Plan p, int rows, int K, const f16* __restrict__ X, const f16* __restrict__ Wp, int units, f16* __restrict__ act) {
   constexpr int RING = 3;
   const int waves = blockDim.x >> 6;
   const int wg = xcd_range((units + waves - 1) / waves);
@@ -300,12 +308,13 @@ skinny_glu_kernel(Plan p, int K, const f16* __restrict__ X, const f16* __restric
   const int unit = wg * waves + wave, nk = K / kBK;
   if (unit >= units) return;
   const wt_buf xr = wt_buffer(X), w_gate = wt_buffer(Wp + (size_t)unit * nk * kWBlock), w_up = wt_buffer(Wp + (size_t)(unit + units) * nk * kWBlock);
+  const uint32_t x_lane = (lg * 32 + min(ln, rows - 1)) * 16;
   u32x4 w[RING][2][4], x[RING][4];
   auto load = [&](auto stage_tag, int kt) {
     constexpr int ST = decltype(stage_tag)::value;
     const int so = min(kt, nk - 1) * (kWBlock * 2);     // unconditional, as above
 #pragma unroll
-    for (int s = 0; s < 4; ++s) x[ST][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, lane * 16 + s * 1024, so, 0);
+    for (int s = 0; s < 4; ++s) x[ST][s] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)x_lane + s * 1024, so, 0);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       w[ST][0][s] = __builtin_amdgcn_raw_buffer_load_b128(w_gate, lane * 16 + s * 1024, so, 0);
@@ -370,10 +379,10 @@ __global__ void __launch_bounds__(256) norm_frag_kernel(Plan p, int K, float eps
 }
 
 template <int KIND>
-void launch_t(int units, int n_split, int K, const Shape& s, const Plan& p, const void* X, const NormIn& nin, const void* W, float* h, float* ssq,
+void launch_t(int rows, int units, int n_split, int K, const Shape& s, const Plan& p, const void* X, const NormIn& nin, const void* W, float* h, float* ssq,
               const QkvOut& qo, const SkinnyBufs& sk, hipStream_t st) {
   const int lds = WaveSum<8>::LDS_BYTES + (KIND == SK_QKV ? K * 4 : 0);
-  hipLaunchKernelGGL((skinny_kernel<KIND>), dim3((units * n_split + 7) / 8 * 8), dim3(512), lds, st, p, K, (const f16*)X, nin, (const f16*)W, h, ssq, s.d, qo, units, n_split, sk.part, sk.counters);
+  hipLaunchKernelGGL((skinny_kernel<KIND>), dim3((units * n_split + 7) / 8 * 8), dim3(512), lds, st, p, rows, K, (const f16*)X, nin, (const f16*)W, h, ssq, s.d, qo, units, n_split, sk.part, sk.counters);
 }
 
 // Token embedding into the fragment-ordered residual; rows beyond the step's count become zero rows.  Also the row's sum
@@ -435,21 +444,21 @@ void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const fl
                               void* out, hipStream_t st) {
   hipLaunchKernelGGL(final_norm_frag_kernel, dim3(M_max), dim3(256), 0, st, p, s.d, s.eps, h, ssq, s.d / 32, gain, (f16*)out, M_max);
 }
-void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, const float* h, const float* ssq, int ssq_parts,
+void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* h, const float* ssq, int ssq_parts,
                        const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, const SkinnyBufs& sk, hipStream_t st) {
   const QkvOut qo{s.Hq, s.Hkv, kv.max_pages, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, kv.block_table};
-  launch_t<SK_QKV>(4 * (s.Hq + 2 * s.Hkv), 1, s.d, s, p, nullptr, NormIn{h, ssq, gain, ssq_parts, s.eps}, W, nullptr, nullptr, qo, sk, st);
+  launch_t<SK_QKV>(M_max, 4 * (s.Hq + 2 * s.Hkv), 1, s.d, s, p, nullptr, NormIn{h, ssq, gain, ssq_parts, s.eps}, W, nullptr, nullptr, qo, sk, st);
 }
-void launch_skinny_gate_up(const Shape& s, const Plan& p, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
+void launch_skinny_gate_up(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
                            const void* W, void* act, hipStream_t st) {
   hipLaunchKernelGGL(norm_frag_kernel, dim3(s.d / kBK), dim3(256), 0, st, p, s.d, s.eps, h, ssq, ssq_parts, gain, (f16*)a);
   const int units = s.F / 32;
   int waves = (units + 255) / 256;                       // one workgroup per CU while the units last
   if (waves > 4) waves = 4;
-  hipLaunchKernelGGL(skinny_glu_kernel, dim3(((units + waves - 1) / waves + 7) / 8 * 8), dim3(64 * waves), 0, st, p, s.d, (const f16*)a,
+  hipLaunchKernelGGL(skinny_glu_kernel, dim3(((units + waves - 1) / waves + 7) / 8 * 8), dim3(64 * waves), 0, st, p, M_max, s.d, (const f16*)a,
                      (const f16*)W, units, (f16*)act);
 }
-void launch_skinny_resid(const Shape& s, const Plan& p, int K, const void* X, const void* W, float* h, float* ssq,
+void launch_skinny_resid(const Shape& s, const Plan& p, int M_max, int K, const void* X, const void* W, float* h, float* ssq,
                          const SkinnyBufs& sk, hipStream_t st) {
   // A CU draws at most ~54 GB/s from HBM (measured: 48 streaming workgroups reach 2.6 TB/s, 128 reach 5.5), so K is also
   // split across workgroups where few column tiles meet a long K (1.5B shape, down projection: 48 tiles of 573 KB); the
@@ -458,5 +467,5 @@ void launch_skinny_resid(const Shape& s, const Plan& p, int K, const void* X, co
   int n_split = nk >= 96 ? (192 + units / 2) / units : 1;
   if (n_split > kMaxGemmSplit) n_split = kMaxGemmSplit;
   if (n_split < 1) n_split = 1;
-  launch_t<SK_RESID>(units, n_split, K, s, p, X, NormIn{}, W, h, ssq, QkvOut{}, sk, st);
+  launch_t<SK_RESID>(M_max, units, n_split, K, s, p, X, NormIn{}, W, h, ssq, QkvOut{}, sk, st);
 }
