@@ -75,6 +75,44 @@ def test_kept_set_of_every_row_matches_the_oracle(eng, V, T, top_k, top_p):
     assert eng.poll_status() == 0
 
 
+@pytest.mark.parametrize("top_k,top_p", [(1, 1.0), (50, 0.913), (127, 1.0), (128, 0.999), (129, 0.913), (0, 0.913), (0, 0.417)])
+def test_small_top_k_at_group_and_list_edges(eng, top_k, top_p):
+    """Kept sets around the limit of the counting path (128), for rows shorter than one vector up to two reads of all threads, lengths
+    that are no multiple of four (unaligned rows), the largest tokens at either end of the row, ties that overflow the list of
+    512, rows that the 256 threads see in order, and rows with fewer finite logits than the set has tokens; rows whose first token
+    reaches top_p alone, by little and by far, at logits around zero and around 3e4.  (top_p times a number of equal tokens is nowhere within 1e-2 of a whole
+    number: it would make the cut a tie, which float32 and float64 values of top_p decide differently.)"""
+    rng = np.random.default_rng(top_k)
+    for V in (3, 131, 514, 1025, 2050, 4093, 4096):
+        if top_k >= V:
+            continue
+        Bn, M = 18, 18
+        logits = rng.normal(0, 2.0, (M, V)).astype(np.float32)
+        logits[1] = np.round(logits[1])
+        logits[2] = -3.5
+        logits[3, rng.permutation(V)[:V - min(V // 2, 20)]] = -np.inf
+        logits[4] = np.sort(logits[4])
+        logits[5] = -np.sort(-logits[5])
+        logits[6, -3:] += 20.0
+        logits[7, :4] += 20.0
+        logits[8, ::4] += 5.0                              # one token of every vector
+        logits[9, :min(V, 512)] = 9.0                      # exactly as many equal tokens as the list holds
+        logits[10, :min(V, 513)] = 9.0
+        for r, (f, shift) in enumerate([(0.9995, 0), (1.0005, 0), (1.002, 0), (1.05, 3e4), (1.2, 0)], 12):
+            p1 = min(f * top_p, 0.9995)                    # probability of the first token in the whole row, nowhere top_p itself
+            rest = np.log(np.exp(np.delete(logits[r], V // 3).astype(np.float64) / 0.8).sum())
+            logits[r, V // 3] = 0.8 * (rest + np.log(p1 / (1 - p1)))
+            logits[r] += shift
+        drafts = np.zeros((Bn, 1), np.int32)
+        k_b = np.zeros(Bn, np.int32)
+        ua, us = W.uniforms(V, Bn, 1)
+        eng.set_filter(top_k, top_p)
+        out = _call(eng, logits, drafts, k_b, ua, us, temperature=0.8)
+        assert _check_thresholds(eng, logits, 0.8, top_k, top_p) == 0
+        H.compare_sampler(out, logits, drafts, k_b, ua, us, None, 0.8, top_k=top_k, top_p=top_p)
+    assert eng.poll_status() == 0
+
+
 def test_filtered_accept_and_resample_integers_match_the_oracle(eng):
     """Ragged blocks, dense and one-hot proposals, greedy drafts so that many are accepted, EOS and no-bonus."""
     rng = np.random.default_rng(77)
