@@ -330,10 +330,12 @@ __global__ void __launch_bounds__(256) filter_kernel(Plan p, int M_max, int V, c
   bool finished = false;
 
   // ================= the first token of the ranking alone reaches top_p: most rows of a confident model.  Its probability comes from
-  // the row statistics; what they are off by (float32 sums and a float32 log, whose rounding grows with its value) is far below
-  // the margin, and rows inside it take the ways below.  With top-k the mass of what is left is no larger, so the same holds.
+  // the row statistics, whose log-sum is off by up to three float32 roundings of its terms (1 / T, the scaled maximum, the sum; one is
+  // 6e-8 of the value) and by the rounding of the float32 sum: the probability must reach top_p with all of that against it.  Rows
+  // inside the margin, and NaN or infinite statistics, take the ways below.  With top-k the mass of what is left is no larger, so the same holds.
   // Nothing of the row is read (432 peaked rows of 151936 tokens, accept and resample together: 237 .. 270 us before, 79 here).
-  if (use_p && exp(mxp - (double)sb.row_lse[m]) >= (double)top_p * (1.001 + 1e-6 * fabs((double)sb.row_lse[m]))) {
+  const double lse = (double)sb.row_lse[m];
+  if (use_p && exp(mxp - lse - 4e-7 * (fabs(mxp) + fabs(lse))) >= 1.001 * (double)top_p) {
     if (tid == 0) store(filter_key(sb.row_max[m]), sb.row_arg[m], (u64)kScale);
     return;
   }

@@ -113,6 +113,20 @@ def test_small_top_k_at_group_and_list_edges(eng, top_k, top_p):
     assert eng.poll_status() == 0
 
 
+@pytest.mark.parametrize("T", [0.55, 0.61, 0.7, 0.9, 1.1, 1.3])
+def test_tied_tokens_at_large_logits_are_both_kept(eng, T):
+    """Two equal largest tokens share the mass, so top_p = 0.9 needs both, whatever their size: float32 row statistics of logits of
+    1e8 are off by tens, which must not let the first of the two look certain.  (Half of the mass is nowhere near 0.9: no cut can be a tie.)"""
+    z = np.zeros((40, 4096), np.float32)
+    for r in range(40):
+        z[r, [5, 900]] = np.float32((-1) ** (r % 2) * 10.0 ** (6 + r / 10))
+        if r % 2:
+            z[r] = np.where(z[r] == 0, np.float32(-3e38), z[r])
+    eng.set_filter(0, 0.9)
+    _call(eng, z, np.zeros((40, 0), np.int32), np.zeros(40, np.int32), np.zeros((40, 1), np.float32), np.full(40, 0.9, np.float32), temperature=T)
+    assert _check_thresholds(eng, z, T, 0, 0.9) == 0
+
+
 def test_filtered_accept_and_resample_integers_match_the_oracle(eng):
     """Ragged blocks, dense and one-hot proposals, greedy drafts so that many are accepted, EOS and no-bonus."""
     rng = np.random.default_rng(77)
