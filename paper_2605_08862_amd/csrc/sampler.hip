@@ -356,7 +356,16 @@ __global__ void __launch_bounds__(256) q_stats_kernel(Plan p, int V, const Q* __
 #pragma unroll
       for (int j = 0; j < N; ++j) vm = fmaxf(vm, x[u][j]);
     }
-    if (vm == -INFINITY) return;
+    if (vm == -INFINITY) {                                    // masked tokens; a vector of NaN alone is none and makes the sum NaN
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        bool number = false;
+#pragma unroll
+        for (int j = 0; j < N; ++j) number |= x[u][j] == x[u][j];
+        if (!number) sum = __builtin_nanf("");
+      }
+      return;
+    }
     if (vm > m) { sum *= __expf(m - vm); m = vm; }
 #pragma unroll
     for (int u = 0; u < U; ++u)

@@ -8,6 +8,7 @@ from scipy import stats
 from scipy.special import softmax
 
 from oracle import accept as OA
+from paper_2605_08862_amd import binding as B
 from paper_2605_08862_amd import workloads as W
 from paper_2605_08862_amd.runtime import Engine, fuse_weights
 from tests import helpers as H
@@ -88,3 +89,24 @@ def test_ragged_blocks_options_and_dtypes(eng):
         assert near <= 3, (V, exact, near)
         n_emit = out["n_emitted"].cpu().numpy()
         assert sum(len(r.tokens) for r in res) == n_emit.sum() or near > 0
+
+
+@pytest.mark.parametrize("dtype,n_nan", [(torch.float32, 1), (torch.float32, 4096), (torch.float32, 12288), (torch.bfloat16, 1),
+                                         (torch.bfloat16, 8192)])
+def test_nan_block_in_a_proposal_row_is_not_read_as_masked(dtype, n_nan):
+    """A proposal row with NaN has no probabilities: its draft is accepted whatever the uniform, for one NaN as for a block of them as
+    long as everything a thread has in flight at once (a block of -inf instead is a mask, and the rule applies)."""
+    V, Bn = 20480, 8
+    rng = np.random.default_rng(n_nan)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device=DEV)
+    z = torch.tensor(rng.normal(0, 1, (2 * Bn, V)), dtype=torch.float32, device=DEV)
+    z[:, V - 1] = -30.0                                    # the target hardly has the draft: u = 0.5 rejects it
+    q = torch.tensor(rng.normal(0, 1, (Bn, V)), dtype=dtype, device=DEV)
+    for fill, accepted in ((float("nan"), 1), (-float("inf"), 0)):
+        q[:, :n_nan] = fill
+        new = lambda *s: torch.full(s, -7, dtype=torch.int32, device=DEV)
+        n_acc, toks, n_emit, tie = new(Bn), new(Bn, 2), new(Bn), new(Bn)
+        B.bs_accept_resample_logits_noalloc(Bn, V, z, i32(np.full((Bn, 1), V - 1)), i32(np.ones(Bn)), 1, q,
+                                            B.BS_BF16 if dtype == torch.bfloat16 else B.BS_F32, 1.0, -1, True,
+                                            torch.full((Bn, 1), 0.5, device=DEV), torch.full((Bn,), 0.5, device=DEV), n_acc, toks, n_emit, tie)
+        assert n_acc.tolist() == [accepted] * Bn, fill
