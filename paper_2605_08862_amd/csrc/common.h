@@ -144,7 +144,7 @@ template <> __host__ __device__ __forceinline__ int v_index<bf16>(int D, int h, 
 // ---------------------------------------------------------------------------------------------
 struct Plan {
   int32_t* status;      // [1]   BS_FAULT_* bits (sticky until polled)
-  int32_t* n_rows;      // [2]   M, T_d
+  int32_t* n_rows;      // [5]   M, T_d, choices of the slab GEMMs (SlabRule)
   int32_t* row_start;   // [B+1] first packed row of sequence b (k_b+1 rows each)
   int32_t* draft_start; // [B+1] first packed draft row of sequence b (k_b rows each)
   int32_t* seq_k;       // [B]   validated k_b (-1: sequence skipped)
@@ -264,19 +264,21 @@ void launch_clear_status(int32_t* status, hipStream_t st);
 void launch_kv_lengths(const KvView& kv, int B, const int32_t* seq_slot, int32_t* out, int32_t* status, hipStream_t st);
 // elementwise.hip
 // also fills the step's rotary tables cos_t / sin_t [M_max][D/2] (shared by all layers)
-void launch_embed(const Shape& s, const Plan& p, int M_max, const void* embed, float* h, const double* inv_freq,
+// rules: those of the step's GEMMs (gemm_slab_rules); their choices are left behind the row count.
+struct SlabRules;
+void launch_embed(const Shape& s, const Plan& p, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st);
 // h[r] += sum of n_slabs slabs [M_max, d] (n_slabs may be 0), then out[r] = RMSNorm(h[r]).
-struct SlabRule;
+struct SlabCount;
 // float32 models: out row-major; bf16 models: chunk order, ld = M_max
-void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabRule& n_slabs,
+void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabCount& n_slabs,
                     const float* gain, void* out, hipStream_t st);
-// qkv is the float32 projection, given as n_slabs >= 1 slabs [M_max, Nqkv] that are summed.
+// qkv is the float32 projection, given as slabs [M_max, Nqkv] that are summed.
 // inv_freq: [D/2] float64 table written by launch_rope_table.
 void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st);
 // cos_t / sin_t: [M_max][D/2] tables of the step's packed rows (filled by launch_embed, once per step).
 void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
-                        const float* qkv, const SlabRule& slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
+                        const float* qkv, const SlabCount& slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,
                     void* k_rows, void* v_rows, bool to_pages, int32_t* status, hipStream_t st);
 // qkv_rope.hip   QKV projection + rotary + KV append in one kernel (bf16 models with head size 128); A = normed
@@ -327,7 +329,10 @@ __host__ __device__ __forceinline__ int gemm_adaptive_split(int tiles, int nk, i
 }
 // Number of K-split slabs a float32-epilogue GEMM writes: fixed on the host (bm == 0), or decided on the DEVICE from
 // the step's row count M, which only the device knows (draft lengths may come straight from the lookup kernel): the
-// launch is sized for the row limit, the kernel and the consumer of the slabs both evaluate slabs(M).
+// launch is sized for the row limit.  The embedding kernel evaluates the rules of a step once, beside its rows, and leaves
+// choice(M) behind the row count (Plan::n_rows[at]), where the GEMM and the consumer of its slabs read it with the row count.
+// (Evaluated by every workgroup it was some 1500 instructions in front of a GEMM's first load, 650 in front of a normalisation's:
+// two layers of d = 256 with 646 .. 1836 rows took 121 .. 168 us where they now take 99 .. 140.)
 struct SlabRule {
   int fixed;                    // slab count when bm == 0 (0: the output was updated in place)
   int bm, n_blocks, nk, cap;    // device rule: row tile, column blocks, K tiles, resident workgroups
@@ -335,29 +340,39 @@ struct SlabRule {
   int n_blocks_alt = 0;         // its column blocks (0: the same)
   int t = 90, t_alt = 90;       // time of a K tile (gemm_split_cost)
   int slab_cols = 0;            // columns of the output (0: slabs cost nothing)
+  int at = 0;                   // device rule: where the choice is
   __host__ __device__ int slab_cost(int M) const { return gemm_slab_cost(M, slab_cols); }
   __host__ __device__ int blocks(int b) const { return b == bm_alt && n_blocks_alt > 0 ? n_blocks_alt : n_blocks; }
-  // Row tile of the step: with two candidates, the one whose launch is shorter.
-  __host__ __device__ int tile_rows(int M) const {
-    if (bm_alt == 0) return bm;
-    int cost[2];
-    for (int i = 0; i < 2; ++i) {
+  // Row tile and slabs of the step (device rule): with two candidates, the tile whose launch is shorter.
+  struct Choice { int rows, slabs; };
+  __host__ __device__ Choice choice(int M) const {
+    Choice best{bm, 1};
+    int least = 0;
+    for (int i = 0; i < (bm_alt ? 2 : 1); ++i) {
       const int b = i ? bm_alt : bm, tiles = ((M + b - 1) / b) * blocks(b), tt = i ? t_alt : t;
-      cost[i] = gemm_split_cost(tiles, nk, cap, gemm_adaptive_split(tiles, nk, cap, tt, slab_cost(M)), tt, slab_cost(M));
+      const int s = gemm_adaptive_split(tiles, nk, cap, tt, slab_cost(M)), cost = gemm_split_cost(tiles, nk, cap, s, tt, slab_cost(M));
+      if (i == 0 || cost < least) { best = Choice{b, s}; least = cost; }
     }
-    return cost[1] < cost[0] ? bm_alt : bm;
+    return best;
   }
-  __host__ __device__ int slabs(int M) const {
-    if (bm == 0) return fixed;
-    const int b = tile_rows(M);
-    return gemm_adaptive_split(((M + b - 1) / b) * blocks(b), nk, cap, bm_alt != 0 && b == bm_alt ? t_alt : t, slab_cost(M));
-  }
+  __host__ __device__ int tile_rows(int M) const { return choice(M).rows; }
+  __host__ __device__ int slabs(int M) const { return bm == 0 ? fixed : choice(M).slabs; }
 };
-// status: the step's device status word (float16-range faults of the float16 epilogues).  Returns the slabs written (bf16 models,
-// EPI_RESID_ADD / EPI_STORE_F32: `out` is the slab buffer [split][M_max][N] and the consumer sums them), none where `out` was
-// updated in place (float32 models).
-SlabRule launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                     int32_t* status, hipStream_t st);
+// A choice as one word, and the slab count of a launch as its consumer gets it.
+__host__ __device__ __forceinline__ int pack_choice(SlabRule::Choice c) { return c.rows << 4 | c.slabs; }
+struct SlabCount {
+  int fixed, at;                // at == 0: fixed (0: the output was updated in place)
+  __device__ int of(const int32_t* n_rows) const { return at ? n_rows[at] & 15 : fixed; }
+};
+// The GEMMs of a layer that write slabs.
+enum SlabGemm { SLAB_QKV = 0, SLAB_O = 1, SLAB_DOWN = 2 };
+struct SlabRules { SlabRule r[3]; };
+SlabRules gemm_slab_rules(const Shape& s, int M_max);
+// status: the step's device status word (float16-range faults of the float16 epilogues).  which: place of the GEMM's rule (SlabGemm;
+// EPI_RESID_ADD / EPI_STORE_F32 of bf16 models).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
+// and the consumer sums them), none where `out` was updated in place (float32 models).
+SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
+                      int32_t* status, hipStream_t st, int which = 0);
 // time (0.01 us, without the fixed part of a launch) of an EPI_STORE_F32 launch of at most 640 rows
 int gemm_slab_time(int M_max, int N, int K);
 size_t packed_weight_elems(int N, int K);

@@ -8,10 +8,16 @@
 // Token embedding of every packed row and, in the same launch, the row's rotary cos / sin table entries (the table
 // [M_max][D/2] is shared by all layers of the step).
 template <typename T>
-__global__ void __launch_bounds__(256) embed_kernel(Plan p, int d, const T* __restrict__ embed, float* __restrict__ h,
+__global__ void __launch_bounds__(256) embed_kernel(Plan p, int M_max, SlabRules rules, int d, const T* __restrict__ embed, float* __restrict__ h,
                                                     int D, const double* __restrict__ inv_freq,
                                                     float* __restrict__ cos_t, float* __restrict__ sin_t) {
   int r = blockIdx.x;
+  if (r >= M_max) {                                      // three more workgroups: one rule each
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (r == M_max + i && rules.r[i].at && threadIdx.x == 0) p.n_rows[rules.r[i].at] = pack_choice(rules.r[i].choice(p.n_rows[0]));
+    return;
+  }
   if (r >= p.n_rows[0]) return;
   const T* src = embed + (size_t)p.row_tok[r] * d;
   float* dst = h + (size_t)r * d;
@@ -40,7 +46,7 @@ template <> struct Vec4<f16> { typedef _Float16 type __attribute__((ext_vector_t
 
 template <typename T, int NV, int NT = 256>
 __global__ void __launch_bounds__(NT) rmsnorm_kernel(Plan p, int d, float eps, float* __restrict__ h,
-                                                      const float* __restrict__ slabs, SlabRule rule, size_t slab_stride,
+                                                      const float* __restrict__ slabs, SlabCount rule, size_t slab_stride,
                                                       const float* __restrict__ gain, T* __restrict__ out, int ld) {
   constexpr bool CHUNKS = std::is_same<T, f16>::value;
   __shared__ float red[NT / 64];
@@ -52,8 +58,8 @@ __global__ void __launch_bounds__(NT) rmsnorm_kernel(Plan p, int d, float eps, f
   // With the device rule the slab count needs the row count before the first slab load anyway, so the rows beyond
   // the count leave here instead of loading what they never store (a step with 1185 of at most 2176 rows fetched
   // 123 MB per launch for 68 MB of live operands).
-  if (rule.bm != 0 && r >= n_rows) return;
-  const int n_slabs = rule.slabs(n_rows);
+  if (rule.at != 0 && r >= n_rows) return;
+  const int n_slabs = rule.of(p.n_rows);
   typedef float f4 __attribute__((ext_vector_type(4)));
   float* x = h + (size_t)r * d;
   const float* sl = slabs + (size_t)r * d;
@@ -126,7 +132,7 @@ __global__ void __launch_bounds__(NT) rmsnorm_kernel(Plan p, int d, float eps, f
 // rows' chunks of 16 k as runs of 64 bytes; two groups of four (a 128-byte line) go to one XCD.  Row per workgroup, 16-byte
 // pieces: 23.2 us at 3700 rows of 1536 and one slab, 18.6 here.
 __global__ void __launch_bounds__(512) rmsnorm_rows_kernel(Plan p, int d, float eps, float* __restrict__ h, const float* __restrict__ slabs,
-                                                           SlabRule rule, size_t slab_stride, const float* __restrict__ gain,
+                                                           SlabCount rule, size_t slab_stride, const float* __restrict__ gain,
                                                            f16* __restrict__ out, int ld) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   extern __shared__ __align__(16) char lds[];            // [4][d] float16, rows 32 bytes apart in the banks
@@ -134,7 +140,7 @@ __global__ void __launch_bounds__(512) rmsnorm_rows_kernel(Plan p, int d, float 
   const int id = blockIdx.x, r0 = ((id & ~15) + (id & 7) * 2 + ((id >> 3) & 1)) * 4;
   const int n_rows = min(p.n_rows[0], ld);
   if (r0 >= n_rows) return;
-  const int n_slabs = rule.slabs(n_rows);
+  const int n_slabs = rule.of(p.n_rows);
   const int wave = threadIdx.x >> 6, rr = wave >> 1, t128 = threadIdx.x & 127, lds_row = 2 * d + 32;
   const int r = min(r0 + rr, n_rows - 1);                // a row past the end is computed again and stored by nobody
   float* x = h + (size_t)r * d;
@@ -214,14 +220,14 @@ __global__ void rope_table_kernel(int D, float theta, double* __restrict__ inv_f
 template <typename T, typename TQ, typename TP>
 __global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int Hq, int Hkv, int D,
                                                           const float* __restrict__ cos_t, const float* __restrict__ sin_t,
-                                                          const float* __restrict__ qkv, SlabRule rule, size_t slab_stride,
+                                                          const float* __restrict__ qkv, SlabCount rule, size_t slab_stride,
                                                           TQ* __restrict__ q_out, TP* __restrict__ k_pages,
                                                           TP* __restrict__ v_pages) {
   typedef float f4 __attribute__((ext_vector_type(4)));
   const int r = blockIdx.x, idx = blockIdx.y * 256 + threadIdx.x;
   const int n_rows = p.n_rows[0];
-  if (rule.bm != 0 && r >= n_rows) return;               // the device rule needs the row count before the first slab load anyway
-  const int n_slabs = max(rule.slabs(n_rows), 1);
+  if (rule.at != 0 && r >= n_rows) return;               // the device rule needs the row count before the first slab load anyway
+  const int n_slabs = max(rule.of(p.n_rows), 1);
   const int half = D / 2, groups = half / 4;
   const int n_rot = (Hq + Hkv) * groups, n_items = n_rot + Hkv * D / 4;
   if (idx >= n_items) return;
@@ -394,14 +400,15 @@ __global__ void __launch_bounds__(256) kv_copy_f16_kernel(KvView kv, int Hkv, in
   if (out_of_range) atomicOr(status, BS_FAULT_RANGE);
 }
 
-void launch_embed(const Shape& s, const Plan& p, int M_max, const void* embed, float* h, const double* inv_freq,
+void launch_embed(const Shape& s, const Plan& p, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st) {
+  const int grid = M_max + (rules.r[0].at ? 3 : 0);
   if (s.dtype == BS_F32)
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(M_max), dim3(256), 0, st, p, s.d, (const float*)embed, h, s.D, inv_freq, cos_t, sin_t);
+    hipLaunchKernelGGL(embed_kernel<float>, dim3(grid), dim3(256), 0, st, p, M_max, rules, s.d, (const float*)embed, h, s.D, inv_freq, cos_t, sin_t);
   else
-    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(M_max), dim3(256), 0, st, p, s.d, (const bf16*)embed, h, s.D, inv_freq, cos_t, sin_t);
+    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(grid), dim3(256), 0, st, p, M_max, rules, s.d, (const bf16*)embed, h, s.D, inv_freq, cos_t, sin_t);
 }
-void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabRule& n_slabs,
+void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabCount& n_slabs,
                     const float* gain, void* out, hipStream_t st) {
   const size_t stride = (size_t)M_max * s.d;
 #define BS_RMS(T_, NV_, NT_) hipLaunchKernelGGL((rmsnorm_kernel<T_, NV_, NT_>), dim3(s.dtype == BS_F32 ? M_max : (M_max + 63) / 64 * 64), dim3(NT_), 0, st, p, s.d, s.eps, h, slabs, n_slabs, stride, gain, (T_*)out, M_max)
@@ -420,7 +427,7 @@ void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st) {
   hipLaunchKernelGGL(rope_table_kernel, dim3(1), dim3(64), 0, st, s.D, s.theta, inv_freq);
 }
 void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
-                        const float* qkv, const SlabRule& n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
+                        const float* qkv, const SlabCount& n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const size_t stride = (size_t)M_max * s.Nqkv();
   const int y = ((s.Hq + s.Hkv) * s.D / 8 + s.Hkv * s.D / 4 + 255) / 256;
   if (s.dtype == BS_F32)

@@ -207,7 +207,7 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
   const size_t tile_bytes = (size_t)(K / kBK) * 4096;
   const int t0 = nb * G::CT, t_last = N / 32 - 1;
-  const int nk = K / kBK, s0 = 2 * (int)((long)nk * split / n_split), s1 = 2 * (int)((long)nk * (split + 1) / n_split);
+  const int nk = K / kBK, s0 = 2 * (nk * split / n_split), s1 = 2 * (nk * (split + 1) / n_split);
   auto operands = [&](typename G::Operands& op, int) {
     G::make_operands(op, A, M_max, [&](int r) { return min(m0 + r, M_max - 1); }, Wp, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, lane * 16u, s0);
   };
@@ -230,29 +230,29 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
   };
   G::run(0, 1, 1, s1 - s0, lds, operands, finish);
 }
-// Tile and number of splits fixed by the launch (rule.bm == 0: see glu_kernel), or the splits from the step's row count.
+// Tile and number of splits fixed by the launch (see glu_kernel), or the splits from the step's row count (SlabRule).
 template <typename G>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) slab_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
-                                                          const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, SlabRule rule) {
+                                                          const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, SlabCount count) {
   extern __shared__ __align__(16) char lds[];
-  const int M = rule.bm ? min(*n_rows_dev, M_max) : M_max;
-  const int m_blocks = (M + G::BM - 1) / G::BM, tiles = m_blocks * n_blocks, n_split = __builtin_amdgcn_readfirstlane(rule.slabs(M));
+  const int M = count.at ? min(*n_rows_dev, M_max) : M_max;
+  const int m_blocks = (M + G::BM - 1) / G::BM, tiles = m_blocks * n_blocks, n_split = count.of(n_rows_dev);
   const int id = xcd_flat(tiles * n_split);
   if (id < 0) return;
   slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, id % tiles % m_blocks * G::BM, id % tiles / m_blocks, id / tiles, n_split, lds);
 }
-// Two tiles to choose from: tile and splits both from the step's row count (SlabRule::tile_rows).
+// Two tiles to choose from: tile and splits both from the step's row count (SlabRule).
 template <typename G, typename GA>
 __global__ void __launch_bounds__(256, 2) slab_alt_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
-                                                          const f16* __restrict__ Wp, float* __restrict__ out, SlabRule rule) {
+                                                          const f16* __restrict__ Wp, float* __restrict__ out, int nb_g, int nb_ga, int at) {
   extern __shared__ __align__(16) char lds[];
-  // (what comes out of the float arithmetic of the rule is made scalar: everything is derived from it)
-  const int M = min(*n_rows_dev, M_max), bm = __builtin_amdgcn_readfirstlane(rule.tile_rows(M));
-  const int m_blocks = (M + bm - 1) / bm, tiles = m_blocks * rule.blocks(bm), n_split = __builtin_amdgcn_readfirstlane(rule.slabs(M));
+  const int M = min(*n_rows_dev, M_max), choice = n_rows_dev[at], n_split = choice & 15;
+  const bool first = choice >> 4 == G::BM;
+  const int bm = first ? G::BM : GA::BM, m_blocks = first ? (M + G::BM - 1) / G::BM : (M + GA::BM - 1) / GA::BM, tiles = m_blocks * (first ? nb_g : nb_ga);
   const int id = xcd_flat(tiles * n_split);
   if (id < 0) return;
   const int split = id / tiles, tile = id % tiles, m0 = tile % m_blocks * bm, nb = tile / m_blocks;
-  if (bm == G::BM) slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, m0, nb, split, n_split, lds);
+  if (first) slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, m0, nb, split, n_split, lds);
   else slab_tile<GA>(n_rows_dev, M_max, N, K, A, Wp, out, m0, nb, split, n_split, lds);
 }
 
@@ -324,29 +324,26 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
 }
 
 template <typename G>
-static SlabRule launch_slab(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule,
-                            hipStream_t st) {
+static void launch_slab(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule,
+                        hipStream_t st) {
   const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + G::CT * 32 - 1) / (G::CT * 32), tiles = m_blocks * n_blocks;
   // with the device rule tiles(M) * splits(M) never exceeds max(tiles(M_max), cap)
   const int n = rule.bm ? (tiles > rule.cap ? tiles : rule.cap) : tiles * rule.fixed;
   static bool done = false;
   allow_lds(slab_kernel<G>, G::LDS_BYTES, done);
   hipLaunchKernelGGL(slab_kernel<G>, dim3(grid8(n)), dim3(G::THREADS), G::LDS_BYTES, st, n_rows_dev, M_max, N, K, (const f16*)A, (const f16*)W,
-                     (float*)out, n_blocks, rule);
-  return rule;
+                     (float*)out, n_blocks, SlabCount{rule.fixed, rule.at});
 }
 template <typename G, typename GA>
-static SlabRule launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, int t, int t_alt, hipStream_t st) {
+static void launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule, hipStream_t st) {
   const int nb = (N + G::CT * 32 - 1) / (G::CT * 32), nba = (N + GA::CT * 32 - 1) / (GA::CT * 32);
-  const SlabRule rule{0, G::BM, nb, K / kBK, 2 * kCUs, GA::BM, nba, t, t_alt, N};
   const int ta = (M_max + G::BM - 1) / G::BM * nb, tb = (M_max + GA::BM - 1) / GA::BM * nba, tiles = ta > tb ? ta : tb;
   constexpr int lds = G::LDS_BYTES > GA::LDS_BYTES ? G::LDS_BYTES : GA::LDS_BYTES;
   static bool done = false;
   allow_lds(slab_alt_kernel<G, GA>, lds, done);
   // tiles(M) * splits(M) never exceeds max(tiles(M_max), cap)
   hipLaunchKernelGGL((slab_alt_kernel<G, GA>), dim3(grid8(tiles > rule.cap ? tiles : rule.cap)), dim3(256), lds, st, n_rows_dev, M_max, N, K, (const f16*)A,
-                     (const f16*)W, (float*)out, rule);
-  return rule;
+                     (const f16*)W, (float*)out, nb, nba, rule.at);
 }
 // Tile and split of a float32-result GEMM: the cheapest of the tiles below by gemm_split_cost, whose times of a K tile are those of
 // launches that fill the CUs once (a tile of 32 MW rows x 128 NW columns).  Measured in us, down projection of the 1.5B and the 7B
@@ -375,35 +372,58 @@ static SlabPick pick_slab(int M_max, int N, int nk) {
   return best;
 }
 int gemm_slab_time(int M_max, int N, int K) { return pick_slab(M_max, N, K / kBK).cost; }
-static SlabRule launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, hipStream_t st) {
-  const int nk = K / kBK;
-  if (M_max <= 640) {
-    const SlabPick pick = pick_slab(M_max, N, nk);
-    const SlabRule r{pick.split, 0, 0, 0, 0, 0};
-#define BS_SLAB(T_) return launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
-    switch (pick.tile) {
-      case 0: BS_SLAB(T64x64);
-      case 1: BS_SLAB(T64x128);
-      case 2: BS_SLAB(T96x128);
-      case 3: BS_SLAB(T128x128);
-      case 4: BS_SLAB(T160x128);
-      case 5: BS_SLAB(T96x256);
-      case 6: BS_SLAB(T128x256);
-      default: BS_SLAB(T160x256);
-    }
-#undef BS_SLAB
-  }
+static SlabRule slab_rule(int M_max, int N, int nk, int at) {
+  if (M_max <= 640) return SlabRule{pick_slab(M_max, N, nk).split, 0, 0, 0, 0, 0};
   const int nb128 = (N + 127) / 128, nb256 = (N + 255) / 256;
+  SlabRule r{0, T96x256::BM, nb256, nk, 2 * kCUs, 0, 0, 83, 0, N, at};
   if (nk < 96) {                                         // the second tile: the better one at the row limit
     auto cost = [&](int bm, int t) {
       const int tiles = (M_max + bm - 1) / bm * nb128, tsl = gemm_slab_cost(M_max, N);
       return gemm_split_cost(tiles, nk, 2 * kCUs, gemm_adaptive_split(tiles, nk, 2 * kCUs, t, tsl), t, tsl);
     };
-    if (cost(128, 51) < cost(160, 68)) return launch_slab_alt<T96x256, T128x128>(n_rows_dev, M_max, N, K, A, W, out, 83, 51, st);
-    return launch_slab_alt<T96x256, T160x128>(n_rows_dev, M_max, N, K, A, W, out, 83, 68, st);
+    const bool rows128 = cost(128, 51) < cost(160, 68);
+    r.bm_alt = rows128 ? T128x128::BM : T160x128::BM;
+    r.n_blocks_alt = nb128;
+    r.t_alt = rows128 ? 51 : 68;
+  } else if ((M_max + 95) / 96 * nb256 >= 128) {
+    r.bm_alt = T128x256::BM;
+    r.n_blocks_alt = nb256;
+    r.t_alt = 92;
+  } else {
+    r.bm = T128x128::BM;
+    r.n_blocks = nb128;
+    r.t = 51;
   }
-  if ((M_max + 95) / 96 * nb256 >= 128) return launch_slab_alt<T96x256, T128x256>(n_rows_dev, M_max, N, K, A, W, out, 83, 92, st);
-  return launch_slab<T128x128>(n_rows_dev, M_max, N, K, A, W, out, SlabRule{0, T128x128::BM, nb128, nk, 2 * kCUs, 0, 0, 51, 51, N}, st);
+  return r;
+}
+constexpr int kChoiceAt = 2;                             // Plan::n_rows: rows, drafts, then a choice per SlabGemm
+SlabRules gemm_slab_rules(const Shape& s, int M_max) {
+  if (s.dtype != BS_BF16) return SlabRules{};
+  return SlabRules{{slab_rule(M_max, s.Nqkv(), s.d / kBK, kChoiceAt + SLAB_QKV), slab_rule(M_max, s.d, s.Hq * s.D / kBK, kChoiceAt + SLAB_O),
+                    slab_rule(M_max, s.d, s.F / kBK, kChoiceAt + SLAB_DOWN)}};
+}
+static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, int which, hipStream_t st) {
+  const SlabRule r = slab_rule(M_max, N, K / kBK, kChoiceAt + which);
+#define BS_SLAB(T_) launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
+#define BS_SLAB_ALT(T_) launch_slab_alt<T96x256, T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
+  if (r.at == 0) {
+    switch (pick_slab(M_max, N, K / kBK).tile) {
+      case 0: BS_SLAB(T64x64); break;
+      case 1: BS_SLAB(T64x128); break;
+      case 2: BS_SLAB(T96x128); break;
+      case 3: BS_SLAB(T128x128); break;
+      case 4: BS_SLAB(T160x128); break;
+      case 5: BS_SLAB(T96x256); break;
+      case 6: BS_SLAB(T128x256); break;
+      default: BS_SLAB(T160x256);
+    }
+  } else if (r.bm_alt == 0) BS_SLAB(T128x128);
+  else if (r.nk >= 96) BS_SLAB_ALT(T128x256);
+  else if (r.bm_alt == T128x128::BM) BS_SLAB_ALT(T128x128);
+  else BS_SLAB_ALT(T160x128);
+#undef BS_SLAB
+#undef BS_SLAB_ALT
+  return SlabCount{r.fixed, r.at};
 }
 
 template <int EPI>
@@ -412,16 +432,16 @@ static void launch_f32(const int32_t* n_rows_dev, int M_max, int N, int K, const
                      (const float*)A, (const float*)W, (float*)out);
 }
 
-SlabRule launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                     int32_t* status, hipStream_t st) {
-  const SlabRule none{0, 0, 0, 0, 0, 0};
+SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
+                      int32_t* status, hipStream_t st, int which) {
+  const SlabCount none{0, 0};
   if (dtype == BS_F32) {
     if (epi == EPI_SWIGLU) launch_f32<EPI_SWIGLU>(n_rows_dev, M_max, N, K, A, W, out, st);
     else if (epi == EPI_RESID_ADD) launch_f32<EPI_RESID_ADD>(n_rows_dev, M_max, N, K, A, W, out, st);
     else launch_f32<EPI_STORE_F32>(n_rows_dev, M_max, N, K, A, W, out, st);
     return none;
   }
-  if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, st);
+  if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, which, st);
   launch_glu(n_rows_dev, M_max, N, K, A, W, out, status, st);
   return none;
 }

@@ -20,3 +20,15 @@ def test_gemm_launches_at_row_limit(d_ffn, n_seq, k_max):
     rng = np.random.default_rng(n_seq)
     ctx = [int(x) for x in rng.integers(0, 70, n_seq)]
     _run_case(desc, ctx_lens=ctx, k_b=[k_max] * (n_seq - 2) + [k_max - 1, 0], k_max=k_max, seed=70 + k_max, q_mode="onehot", check_kv=(n_seq < 20))
+
+
+@pytest.mark.parametrize("d_ffn", [448, 6400])
+@pytest.mark.parametrize("fill", ["full", "mixed", "plain"])
+def test_splits_from_the_row_count(d_ffn, fill):
+    """Row limit 645: the K splits of O and down follow from the step's row count (645, about 330 and 43 rows), which the GEMM and
+    the normalisation behind it read in one place; 7 K tiles of down take the kernel with two row tiles, 100 the one with a single tile."""
+    desc = W.shape("mini_bf16", n_layers=2, d_model=320, n_q_heads=14, n_kv_heads=2, d_ffn=d_ffn, vocab=777)
+    rng = np.random.default_rng(d_ffn)
+    ctx = [int(x) for x in rng.integers(0, 70, 43)]
+    k_b = {"full": [14] * 43, "mixed": [int(x) for x in rng.integers(0, 15, 43)], "plain": [0] * 43}[fill]
+    _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=14, seed=91, q_mode="onehot", check_kv=fill == "mixed")

@@ -1,10 +1,13 @@
 """CPU check of host/device-shared launch rules: a small C++ program compiled against the library's own header
 (no GPU needed; hipcc compiles it like any other translation unit of the library)."""
 import os
+import re
 import shutil
 import subprocess
 
 import pytest
+
+from paper_2605_08862_amd import build as BLD
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -33,3 +36,23 @@ def test_attention_chunk_rule_compares_times_and_avoids_second_rounds(tmp_path):
     assert r.returncode == 0, r.stderr[-2000:]
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("source, kernel, limit", [("gemm.hip", r"slab_(alt_)?kernel", 300), ("elementwise.hip", r"rmsnorm_(rows_)?kernel|rope_append_kernel", 200)])
+def test_launch_rules_are_not_evaluated_in_front_of_the_loads(tmp_path, source, kernel, limit):
+    """The K splits of a step are decided once, by the embedding kernel: a GEMM or a consumer of its slabs that evaluates the rule
+    itself has 650 .. 1500 instructions in front of its first operand load, one that reads the choice at most 260."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "kernels.s"
+    r = subprocess.run([hipcc, *BLD.FLAGS, "--offload-device-only", "-S", os.path.join(BLD.CSRC, source), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    seen = 0
+    for name, body in re.findall(r"\n(_Z\S+):\s*; @.*?\n(.*?)\n\.Lfunc_end", out.read_text(), re.S):
+        if re.search(kernel, name):
+            ops = [line.strip() for line in body.split("\n") if line.startswith("\t") and not line.strip().startswith((".", ";"))]
+            first = next(i for i, op in enumerate(ops) if re.match(r"buffer_load_dwordx4|global_load_dwordx4|buffer_load.* lds$", op))
+            assert first <= limit, (name, first)
+            seen += 1
+    assert seen >= 8, seen
