@@ -134,8 +134,8 @@ struct GluArgs {
   f16* out;
   int32_t* status;
 };
-// Tiles id, id + stride, .. of m_blocks x n_blocks, M block fastest.
-template <typename G>
+// Tiles id, id + stride, .. of m_blocks x n_blocks, M block fastest, BM rows apart.
+template <typename G, int BM = G::BM>
 __device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_blocks, int id0, int stride, int n, char* lds) {
   constexpr bool MIX = G::NW == 1;
   const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
@@ -144,13 +144,13 @@ __device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_
   const int t_last = g.F / 32 - 1;
   const uint32_t w_lane = MIX ? (lg * 32 + (ln & 15)) * 16u + (ln >= 16 ? (uint32_t)half : 0u) : lane * 16u;
   auto operands = [&](typename G::Operands& op, int id) {
-    const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT;
+    const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT;
     // position t: features 16 (t0 + t) .. (mixed), or the gate (t even) / up (t odd) rows of features 32 ((t0 + t) / 2) ..
     auto w_at = [&](int t) -> size_t { return min((t0 + t) >> 1, t_last) * tile_bytes + (((t0 + t) & 1) ? (MIX ? 256 : half) : 0); };
     G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp, w_at, w_lane, 0);
   };
   auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int id) {
-    const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT, M = min(*g.n_rows_dev, g.M_max);
+    const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT, M = min(*g.n_rows_dev, g.M_max);
 #pragma unroll
     for (int a = 0; a < G::MW; ++a) {
       const int m = m0 + (wm * G::MW + a) * 32 + ln;
@@ -174,17 +174,31 @@ __device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_
   };
   G::run(id0, stride, n, g.K / 32, lds, operands, finish);
 }
-// One tile per workgroup.  A launch of one round does not wait for the row count before its first loads (rows beyond it are stale
-// rows of the same buffer, each affecting only its own output row); one of several rounds leaves the row blocks beyond it out.
+// One tile per workgroup.  A launch with a CU for every workgroup does not wait for the row count before its first loads (rows beyond
+// it are stale rows of the same buffer, each affecting only its own output row).  Where workgroups share a CU, or wait for one, the
+// row blocks beyond the count are left out (1.5B shape, 80 of 720 rows, 420 workgroups, two to a CU: 40.7 us, 25.0 without them).
 constexpr int kFewRows = 320;
 template <typename G>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_kernel(GluArgs g, int m_blocks, int n_blocks) {
   extern __shared__ __align__(16) char lds[];
-  if (m_blocks * n_blocks > G::WGS * kCUs) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
+  if (m_blocks * n_blocks > kCUs) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
   const int id = xcd_flat(m_blocks * n_blocks);
   if (id >= 0) glu_tiles<G>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
 }
+// The same with a last row block of at most 64 live rows as one of 64 (1.5B shape, 390 of 702 rows: 43 us with the blocks beyond the count and a
+// whole last one, 40.6 here).
+template <typename G, typename GT>
+__global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_tail_kernel(GluArgs g, int n_blocks) {
+  static_assert(GT::CT == G::CT && GT::THREADS == G::THREADS && GT::LDS_BYTES <= G::LDS_BYTES && G::LDS_BYTES <= 64 * 1024, "");
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(*g.n_rows_dev, g.M_max), m_blocks = (M + G::BM - 1) / G::BM;
+  const int id = xcd_flat(m_blocks * n_blocks);
+  if (id < 0) return;
+  if (M - id % m_blocks * G::BM <= GT::BM) glu_tiles<GT, G::BM>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
+  else glu_tiles<G>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
+}
 // More rows: 192 or 256 rows x 128 features per tile, persistent workgroups, one per CU (rows_by_rounds).
+typedef DmaGemm<2, 2, 2, 4, 6> GemmRows128;
 typedef DmaGemm<3, 2, 2, 4, 5> GemmRows192;
 typedef DmaGemm<4, 2, 2, 4, 4> GemmRows256;
 __global__ void __launch_bounds__(512) glu_rows_kernel(GluArgs g, int n_blocks) {
@@ -193,7 +207,8 @@ __global__ void __launch_bounds__(512) glu_rows_kernel(GluArgs g, int n_blocks) 
   int stride, end;
   const int id = xcd_first(m_blocks * n_blocks, stride, end);
   if (id >= end) return;
-  if (bm == 256) glu_tiles<GemmRows256>(g, m_blocks, n_blocks, id, stride, end, lds);
+  if (bm == 128) glu_tiles<GemmRows128>(g, m_blocks, n_blocks, id, stride, end, lds);
+  else if (bm == 256) glu_tiles<GemmRows256>(g, m_blocks, n_blocks, id, stride, end, lds);
   else glu_tiles<GemmRows192>(g, m_blocks, n_blocks, id, stride, end, lds);
 }
 
@@ -315,11 +330,16 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
   // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows: 283 us, 290 with 128-row tiles), 128-row
   // tiles, two workgroups per CU, for a short one, where filling and storing a tile is a larger part (1.5B shape, 1037 rows: 63 us
   // against 67; 3480 rows: 169.5 against 171).
-  if (K / kBK < 32) { launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st); return; }
-  constexpr int lds = GemmRows192::LDS_BYTES > GemmRows256::LDS_BYTES ? GemmRows192::LDS_BYTES : GemmRows256::LDS_BYTES;
   static bool done = false;
+  if (K / kBK < 32) {
+    typedef StreamGemm<4, 2, 4, 2> G;
+    hipLaunchKernelGGL((glu_tail_kernel<G, StreamGemm<2, 2, 4, 2>>), dim3(grid8((M_max + G::BM - 1) / G::BM * n128)), dim3(G::THREADS), G::LDS_BYTES, st, g, n128);
+    return;
+  }
+  constexpr int lds = GemmRows128::LDS_BYTES;
+  static_assert(GemmRows192::LDS_BYTES <= lds && GemmRows256::LDS_BYTES <= lds, "");
   allow_lds(glu_rows_kernel, lds, done);
-  const int tiles = (M_max + 191) / 192 * n128;
+  const int tiles = (M_max + 127) / 128 * n128;
   hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
 }
 

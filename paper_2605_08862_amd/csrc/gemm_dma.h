@@ -35,8 +35,10 @@ __device__ __forceinline__ int xcd_first(int total, int& stride, int& end) {
 }
 constexpr int kCUs = 256;
 
-// Many rows, one workgroup per CU: 192 or 256 rows per workgroup, whichever takes fewer rows x rounds of the CUs.
+// Many rows, one workgroup per CU: 192 or 256 rows per workgroup, whichever takes fewer rows x rounds of the CUs; 128 where they are
+// all there is (a step of plain decodes in a batch that may verify drafts).
 __host__ __device__ inline int rows_by_rounds(int M, int n_blocks) {
+  if (M <= 128) return 128;
   const int r192 = ((M + 191) / 192 * n_blocks + kCUs - 1) / kCUs, r256 = ((M + 255) / 256 * n_blocks + kCUs - 1) / kCUs;
   return 4 * r256 <= 3 * r192 ? 256 : 192;
 }

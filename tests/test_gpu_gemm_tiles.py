@@ -32,3 +32,12 @@ def test_splits_from_the_row_count(d_ffn, fill):
     ctx = [int(x) for x in rng.integers(0, 70, 43)]
     k_b = {"full": [14] * 43, "mixed": [int(x) for x in rng.integers(0, 15, 43)], "plain": [0] * 43}[fill]
     _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=14, seed=91, q_mode="onehot", check_kv=fill == "mixed")
+
+
+@pytest.mark.parametrize("d_model,k_b", [(320, [14] * 11 + [3] + [0] * 31), (320, [14] * 8 + [0] * 35), (2048, [0] * 43), (2048, [14] * 8 + [1] + [0] * 34),
+                                         (2048, [14] * 8 + [0] * 35)])
+def test_gate_up_row_blocks_with_few_live_rows(d_model, k_b):
+    """Row limit 645.  Short K: a last row block of 72 live rows, whose workgroups compute 128, and one of 27, where they compute 64, with the blocks
+    behind it left out.  Long K: all rows in one block of 128 (43 rows), and 156 and 155 rows in one of 192."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=14, n_kv_heads=2, d_ffn=6400, vocab=333)
+    _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(5).integers(0, 70, 43)], k_b=k_b, k_max=14, seed=92, q_mode="onehot", check_kv=False)
