@@ -133,20 +133,24 @@ __global__ void __launch_bounds__(G::THREADS) qkv_kernel(Plan p, QkvArgs g, int 
 // runs beside the other's loop.  In four waves of six tiles 192 rows take 54 us at 1185 rows, 57 at 3700; 256 rows in one workgroup
 // per CU take 51 and 33, but a kernel that offers them has one workgroup per CU for every tile (128 rows: 62 and 39).
 // Up to 640 rows the weights of the small tiles are in registers (StreamGemm).  Beyond, the tile is chosen on the device: a workgroup
-// has twelve waves, of which four leave at once where the tile has eight.
+// has twelve waves, of which four or eight leave at once where the tile has eight or four.  32 rows are for steps with few live rows.
 typedef StreamGemm<1, 1, 4, 6> Few32;
 typedef StreamGemm<2, 1, 4, 4> Few64;
+typedef DmaGemm<1, 1, 1, 4, 8> Rows32;
 typedef DmaGemm<1, 1, 2, 4, 6> Rows64;
 typedef DmaGemm<1, 2, 4, 2, 5> Rows128;
 typedef DmaGemm<1, 2, 6, 2, 4> Rows192;
 __host__ __device__ inline int rows_cost(int M, int bm, int heads, int nk, int t) { return ((M + bm - 1) / bm * heads + kCUs - 1) / kCUs * (nk + 8) * t; }
+constexpr int kRows32Tiles = 2 * kCUs;                   // most 32-row tiles that the launch of the device's choice is sized for
 __host__ __device__ inline int pick_rows(int M, int heads, int nk, bool few, int& cost) {
   int bm = 128;
   cost = rows_cost(M, 128, heads, nk, 48);
   int c = rows_cost(M, 64, heads, nk, 37);
   if (c < cost) { bm = 64; cost = c; }
-  c = few ? rows_cost(M, 32, heads, nk, 31) : rows_cost(M, 192, heads, nk, 72);
-  if (c < cost) { bm = few ? 32 : 192; cost = c; }
+  c = rows_cost(M, 32, heads, nk, 31);
+  if ((few || (M + 31) / 32 * heads <= kRows32Tiles) && c < cost) { bm = 32; cost = c; }
+  c = rows_cost(M, 192, heads, nk, 72);
+  if (!few && c < cost) { bm = 192; cost = c; }
   return bm;
 }
 constexpr int kFewRows = 640;
@@ -165,6 +169,10 @@ __global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, Q
   const int m0 = id % m_blocks * bm, head = id / m_blocks;
   if (bm == 192) {
     qkv_tile<Rows192>(p, g, m0, head, lds);
+    return;
+  }
+  if (bm == 32) {
+    if (threadIdx.x < Rows32::THREADS) qkv_tile<Rows32>(p, g, m0, head, lds);
     return;
   }
   if (threadIdx.x >= 512) return;
@@ -195,9 +203,10 @@ void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max,
   const int heads = s.Hq + 2 * s.Hkv;
   const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, kv.max_pages, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, kv.block_table};
   if (M_max > kFewRows) {
-    constexpr int a = qkv_lds<Rows64>(), b = qkv_lds<Rows128>(), c = qkv_lds<Rows192>(), ab = a > b ? a : b, lds = ab > c ? ab : c;
+    constexpr int a = qkv_lds<Rows64>(), b = qkv_lds<Rows128>(), c = qkv_lds<Rows192>(), d = qkv_lds<Rows32>(), ab = a > b ? a : b, cd = c > d ? c : d, lds = ab > cd ? ab : cd;
     static_assert(Rows64::THREADS == 512 && Rows128::THREADS == 512 && 2 * lds <= 160 * 1024, "two workgroups per CU");
-    launch_one<qkv_rows_kernel>((M_max + 63) / 64 * heads, Rows192::THREADS, lds, st, p, g);
+    const int tiles = (M_max + 63) / 64 * heads;
+    launch_one<qkv_rows_kernel>(tiles > kRows32Tiles ? tiles : kRows32Tiles, Rows192::THREADS, lds, st, p, g);
     return;
   }
   int cost;
