@@ -797,17 +797,29 @@ template <bool STATS>
 static void launch_lmhead_any(const Shape& s, const int32_t* n_rows_dev, int M_max, const void* hf, int ld,
                               const void* lm_head, float inv_temp, const int32_t* row_target, const SamplerBufs& sb,
                               float* store, hipStream_t st) {
-  // The vocabulary gives hundreds of workgroups, several rounds of the CUs.  Up to 96 rows one row block and 320 entries per
-  // workgroup (one round of 475 workgroups, two per CU: 96 rows 114 us on the 1.5B shape, 124 with 256 entries).  Above, 96 or 128 rows, two
-  // workgroups per CU so that one's epilogue overlaps the other's products: the larger tile does 9 % more work per unit of time,
-  // against the rows it pads.  Measured, 1.5B / 7B shape, before in brackets: 64 rows 104 / 213 us (115 / 225), 288 rows 212 / 401
-  // (211 / 397), 576 rows 266 / 614 (275 / 623), 1185 rows 534 / 1171 (583 / 1304), 3480 rows 1497 (1659).
-  const int p96 = (M_max + 95) / 96 * 96, p128 = (M_max + 127) / 128 * 128;
+  // Up to 96 rows one row block.  256 entries per workgroup as long as that is one round (two workgroups per CU), 320 where it is not: V = 151936,
+  // 96 rows, 1.5B / 7B shape 111 / 223 us against 115 / 238; V = 128256 102 / 200 against 90 / 190, V = 32000 34 / 56 against 28 / 45, 1 row of
+  // V = 1000, d = 256 9.0 against 7.6.
+  // Above, 96 or 128 rows, two workgroups per CU so that one's epilogue overlaps the other's products: by tiles per CU x time of a tile.  A 128-row
+  // tile takes 1.19 times as long with the short K of the 1.5B shape (V = 151936, 576 rows 256 us with 96, 259 with 128; 432 rows 221, 216) and
+  // 1.13 times with that of the 7B shape (576 rows 677 us with 96, 639 with 128; 280 rows 384, 392; V = 32000, 576 rows, 3 tiles per CU either
+  // way, 150 and 160).  One block of 128 reads the weights once (V = 32000, 128 rows, 1.5B / 7B shape 33 / 52 us, with two of 96 37 / 62).
 #define BS_LM(...) launch_lmhead_t<StreamGemm<__VA_ARGS__>, STATS>(s, n_rows_dev, M_max, hf, ld, lm_head, inv_temp, row_target, sb, store, st)
-  if (M_max <= 32) BS_LM(1, 2, 5, 4);
-  else if (M_max <= 64) BS_LM(2, 2, 5, 3);
-  else if (M_max <= 96) BS_LM(3, 2, 5, 3);
-  else if (109 * p96 < 100 * p128) BS_LM(3, 2, 4, 2);
+  const int n256 = (s.V + 255) / 256;
+  if (M_max <= 96) {
+    if (n256 > 2 * kCUs) {
+      if (M_max <= 32) BS_LM(1, 2, 5, 4);
+      else if (M_max <= 64) BS_LM(2, 2, 5, 3);
+      else BS_LM(3, 2, 5, 3);
+    } else {
+      if (M_max <= 32) BS_LM(1, 2, 4, 3);
+      else if (M_max <= 64) BS_LM(2, 2, 4, 2);
+      else BS_LM(3, 2, 4, 2);
+    }
+    return;
+  }
+  auto cost = [&](int bm, int t) { return ((M_max + bm - 1) / bm * n256 + kCUs - 1) / kCUs * t; };
+  if (M_max > 128 && cost(96, 100) < cost(128, s.d / kBK < 32 ? 119 : 113)) BS_LM(3, 2, 4, 2);
   else BS_LM(4, 2, 4, 2);
 #undef BS_LM
 }

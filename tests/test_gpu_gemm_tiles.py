@@ -41,3 +41,13 @@ def test_gate_up_row_blocks_with_few_live_rows(d_model, k_b):
     behind it left out.  Long K: all rows in one block of 128 (43 rows), and 156 and 155 rows in one of 192."""
     desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=14, n_kv_heads=2, d_ffn=6400, vocab=333)
     _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(5).integers(0, 70, 43)], k_b=k_b, k_max=14, seed=92, q_mode="onehot", check_kv=False)
+
+
+@pytest.mark.parametrize("vocab", [131072, 131401])
+@pytest.mark.parametrize("n_seq,k_max", [(7, 2), (13, 4), (19, 4), (33, 3)])
+def test_lm_head_columns_per_workgroup(vocab, n_seq, k_max):
+    """Up to 96 rows a workgroup of the LM head takes 256 vocabulary entries while 512 workgroups hold all of them, then 320; row limits 21, 65 and 95, and
+    132 (two tiles of 96, or 128, by tiles per CU).  Above 64 rows the sampled rows are computed a second time from the gathered ones."""
+    desc = W.shape("mini_bf16", n_layers=1, vocab=vocab)
+    ctx = [int(x) for x in np.random.default_rng(n_seq).integers(0, 70, n_seq)]
+    _run_case(desc, ctx_lens=ctx, k_b=[k_max] * (n_seq - 1) + [0], k_max=k_max, seed=93, q_mode="onehot", check_kv=False)
