@@ -285,6 +285,14 @@ static void launch_glu_t(const GluArgs& g, hipStream_t st) {
   allow_lds(glu_kernel<G>, G::LDS_BYTES, done);
   hipLaunchKernelGGL(glu_kernel<G>, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
 }
+static void launch_glu_rows(const GluArgs& g, int n128, hipStream_t st) {
+  constexpr int lds = GemmRows128::LDS_BYTES;
+  static_assert(GemmRows192::LDS_BYTES <= lds && GemmRows256::LDS_BYTES <= lds, "");
+  static bool done = false;
+  allow_lds(glu_rows_kernel, lds, done);
+  const int tiles = (g.M_max + 127) / 128 * n128;
+  hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
+}
 // Measured in us (gate/up of the 1.5B shape, 8960 features, and of the 7B shape, 18944; the loops with weights in registers and
 // activations staged through registers that were here before in brackets):
 //   64 rows 13.3 (22.3) / 48.4 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 87.3 (104)
@@ -321,8 +329,11 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     // 128 features per workgroup; rows by time of a K tile (0.01 us) x rounds of the CUs
     auto cost = [&](int bm, int t) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * t; };
     const int c96 = cost(96, 83), c128 = cost(128, 92), c160 = cost(160, 113), c192 = cost(192, 128);
-    if (c192 < c96 && c192 < c128 && c192 < c160) launch_glu_t<GemmRows192>(g, st);
-    else if (c160 < c96 && c160 < c128) launch_glu_t<StreamGemm<5, 2, 4, 2>>(g, st);
+    if (c192 < c96 && c192 < c128 && c192 < c160) {
+      // more than one round of the CUs: the tile from the step's row count (7B shape, 504 rows, 252 of them live: 140 us with 192 rows, 112 with 128)
+      if ((M_max + 191) / 192 * n128 > kCUs) launch_glu_rows(g, n128, st);
+      else launch_glu_t<GemmRows192>(g, st);
+    } else if (c160 < c96 && c160 < c128) launch_glu_t<StreamGemm<5, 2, 4, 2>>(g, st);
     else if (c128 < c96) launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st);
     else launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
     return;
@@ -330,17 +341,12 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
   // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows: 283 us, 290 with 128-row tiles), 128-row
   // tiles, two workgroups per CU, for a short one, where filling and storing a tile is a larger part (1.5B shape, 1037 rows: 63 us
   // against 67; 3480 rows: 169.5 against 171).
-  static bool done = false;
   if (K / kBK < 32) {
     typedef StreamGemm<4, 2, 4, 2> G;
     hipLaunchKernelGGL((glu_tail_kernel<G, StreamGemm<2, 2, 4, 2>>), dim3(grid8((M_max + G::BM - 1) / G::BM * n128)), dim3(G::THREADS), G::LDS_BYTES, st, g, n128);
     return;
   }
-  constexpr int lds = GemmRows128::LDS_BYTES;
-  static_assert(GemmRows192::LDS_BYTES <= lds && GemmRows256::LDS_BYTES <= lds, "");
-  allow_lds(glu_rows_kernel, lds, done);
-  const int tiles = (M_max + 127) / 128 * n128;
-  hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
+  launch_glu_rows(g, n128, st);
 }
 
 template <typename G>

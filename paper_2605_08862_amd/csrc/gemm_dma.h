@@ -35,12 +35,11 @@ __device__ __forceinline__ int xcd_first(int total, int& stride, int& end) {
 }
 constexpr int kCUs = 256;
 
-// Many rows, one workgroup per CU: 192 or 256 rows per workgroup, whichever takes fewer rows x rounds of the CUs; 128 where they are
-// all there is (a step of plain decodes in a batch that may verify drafts).
+// Many rows, one workgroup per CU: the rows per workgroup with the least rounds of the CUs x time of a K tile (0.01 us).
 __host__ __device__ inline int rows_by_rounds(int M, int n_blocks) {
-  if (M <= 128) return 128;
-  const int r192 = ((M + 191) / 192 * n_blocks + kCUs - 1) / kCUs, r256 = ((M + 255) / 256 * n_blocks + kCUs - 1) / kCUs;
-  return 4 * r256 <= 3 * r192 ? 256 : 192;
+  auto cost = [&](int bm, int t) { return ((M + bm - 1) / bm * n_blocks + kCUs - 1) / kCUs * t; };
+  const int c128 = cost(128, 100), c192 = cost(192, 128), c256 = cost(256, 170);
+  return c256 <= c192 && c256 <= c128 ? 256 : c192 <= c128 ? 192 : 128;
 }
 
 template <int MW_, int NW_, int WM_, int WN_, int NST_>

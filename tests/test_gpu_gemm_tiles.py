@@ -51,3 +51,11 @@ def test_lm_head_columns_per_workgroup(vocab, n_seq, k_max):
     desc = W.shape("mini_bf16", n_layers=1, vocab=vocab)
     ctx = [int(x) for x in np.random.default_rng(n_seq).integers(0, 70, n_seq)]
     _run_case(desc, ctx_lens=ctx, k_b=[k_max] * (n_seq - 1) + [0], k_max=k_max, seed=93, q_mode="onehot", check_kv=False)
+
+
+@pytest.mark.parametrize("n_draft", [8, 4, 2])
+def test_gate_up_rows_from_the_row_count_below_640(n_draft):
+    """Row limit 504, 148 column blocks: 192-row tiles are two rounds of the CUs at the limit, so the tile follows from the row count:
+    192 rows of 504 (three blocks) and of 168 (one), 128 of 280."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=192, n_q_heads=6, n_kv_heads=2, d_ffn=18944, vocab=333)
+    _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(6).integers(0, 70, 56)], k_b=[n_draft] * 56, k_max=8, seed=94, q_mode="onehot", check_kv=False)
