@@ -428,8 +428,9 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attention_plan_params(s, B, k_max),
               s.L, st);
   const bool skinny = c->fragments && skinny_applies(s, M_max) && !c->unfused_qkv;
+  const SlabRules rules = skinny ? SlabRules{} : gemm_slab_rules(s, M_max);
   if (skinny) launch_skinny_embed(s, p, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
-  else launch_embed(s, p, M_max, gemm_slab_rules(s, M_max), c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  else launch_embed(s, p, M_max, rules, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool fused_qkv = qkv_rope_applies(s, M_max) && !c->unfused_qkv;
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
   SlabCount pending{0, 0};                      // slabs of the last residual projection not yet added to h
@@ -457,7 +458,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       SlabCount nq;
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
         nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
-                         slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, SLAB_QKV); }
+                         slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.r[SLAB_QKV]); }
       launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
@@ -465,13 +466,13 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
                      c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
     { ProfScope ps(c, BS_PROF_GEMM_O, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],
-                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, SLAB_O); }
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.r[SLAB_O]); }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->mlp_norm[l], c->a, st);
     { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
       launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, c->w_gate_up[l], c->act, p.status, st); }
     { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
-                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, SLAB_DOWN); }
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.r[SLAB_DOWN]); }
   }
   if (skinny) launch_skinny_final_norm(s, p, M_max, c->h, c->ssq, c->final_norm, c->hf, st);
   else launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->final_norm, c->hf, st);

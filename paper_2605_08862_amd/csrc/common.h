@@ -341,6 +341,7 @@ struct SlabRule {
   int t = 90, t_alt = 90;       // time of a K tile (gemm_split_cost)
   int slab_cols = 0;            // columns of the output (0: slabs cost nothing)
   int at = 0;                   // device rule: where the choice is
+  int tile = 0;                 // gemm.hip: the kernel
   __host__ __device__ int slab_cost(int M) const { return gemm_slab_cost(M, slab_cols); }
   __host__ __device__ int blocks(int b) const { return b == bm_alt && n_blocks_alt > 0 ? n_blocks_alt : n_blocks; }
   // Row tile and slabs of the step (device rule): with two candidates, the tile whose launch is shorter.
@@ -368,11 +369,11 @@ struct SlabCount {
 enum SlabGemm { SLAB_QKV = 0, SLAB_O = 1, SLAB_DOWN = 2 };
 struct SlabRules { SlabRule r[3]; };
 SlabRules gemm_slab_rules(const Shape& s, int M_max);
-// status: the step's device status word (float16-range faults of the float16 epilogues).  which: place of the GEMM's rule (SlabGemm;
-// EPI_RESID_ADD / EPI_STORE_F32 of bf16 models).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
+// status: the step's device status word (float16-range faults of the float16 epilogues).  rule: gemm_slab_rules, made once per step
+// (EPI_RESID_ADD / EPI_STORE_F32 of bf16 models; made in each launch it kept steps of small models waiting for the host).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
 // and the consumer sums them), none where `out` was updated in place (float32 models).
 SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                      int32_t* status, hipStream_t st, int which = 0);
+                      int32_t* status, hipStream_t st, const SlabRule& rule = SlabRule{});
 // time (0.01 us, without the fixed part of a launch) of an EPI_STORE_F32 launch of at most 640 rows
 int gemm_slab_time(int M_max, int N, int K);
 size_t packed_weight_elems(int N, int K);

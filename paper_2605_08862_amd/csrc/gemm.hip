@@ -245,13 +245,12 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
   };
   G::run(0, 1, 1, s1 - s0, lds, operands, finish);
 }
-// Tile and number of splits fixed by the launch (see glu_kernel), or the splits from the step's row count (SlabRule).
+// Tile and number of splits fixed by the launch (see glu_kernel).
 template <typename G>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) slab_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
-                                                          const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, SlabCount count) {
+                                                          const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, int n_split) {
   extern __shared__ __align__(16) char lds[];
-  const int M = count.at ? min(*n_rows_dev, M_max) : M_max;
-  const int m_blocks = (M + G::BM - 1) / G::BM, tiles = m_blocks * n_blocks, n_split = count.of(n_rows_dev);
+  const int m_blocks = (M_max + G::BM - 1) / G::BM, tiles = m_blocks * n_blocks;
   const int id = xcd_flat(tiles * n_split);
   if (id < 0) return;
   slab_tile<G>(n_rows_dev, M_max, N, K, A, Wp, out, id % tiles % m_blocks * G::BM, id % tiles / m_blocks, id / tiles, n_split, lds);
@@ -350,15 +349,13 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
 }
 
 template <typename G>
-static void launch_slab(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule,
+static void launch_slab(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, int n_split,
                         hipStream_t st) {
   const int m_blocks = (M_max + G::BM - 1) / G::BM, n_blocks = (N + G::CT * 32 - 1) / (G::CT * 32), tiles = m_blocks * n_blocks;
-  // with the device rule tiles(M) * splits(M) never exceeds max(tiles(M_max), cap)
-  const int n = rule.bm ? (tiles > rule.cap ? tiles : rule.cap) : tiles * rule.fixed;
   static bool done = false;
   allow_lds(slab_kernel<G>, G::LDS_BYTES, done);
-  hipLaunchKernelGGL(slab_kernel<G>, dim3(grid8(n)), dim3(G::THREADS), G::LDS_BYTES, st, n_rows_dev, M_max, N, K, (const f16*)A, (const f16*)W,
-                     (float*)out, n_blocks, SlabCount{rule.fixed, rule.at});
+  hipLaunchKernelGGL(slab_kernel<G>, dim3(grid8(tiles * n_split)), dim3(G::THREADS), G::LDS_BYTES, st, n_rows_dev, M_max, N, K, (const f16*)A, (const f16*)W,
+                     (float*)out, n_blocks, n_split);
 }
 template <typename G, typename GA>
 static void launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& rule, hipStream_t st) {
@@ -398,27 +395,35 @@ static SlabPick pick_slab(int M_max, int N, int nk) {
   return best;
 }
 int gemm_slab_time(int M_max, int N, int K) { return pick_slab(M_max, N, K / kBK).cost; }
+enum SlabTile { T_96x256_128x128 = 8, T_96x256_160x128, T_96x256_128x256, T_96x128_128x128, T_96x128_160x128 };   // up to 7: place in pick_slab's list
 static SlabRule slab_rule(int M_max, int N, int nk, int at) {
-  if (M_max <= 640) return SlabRule{pick_slab(M_max, N, nk).split, 0, 0, 0, 0, 0};
+  if (M_max <= 640) {
+    const SlabPick pick = pick_slab(M_max, N, nk);
+    SlabRule r{pick.split, 0, 0, 0, 0, 0};
+    r.tile = pick.tile;
+    return r;
+  }
   const int nb128 = (N + 127) / 128, nb256 = (N + 255) / 256;
-  SlabRule r{0, T96x256::BM, nb256, nk, 2 * kCUs, 0, 0, 83, 0, N, at};
-  if (nk < 96) {                                         // the second tile: the better one at the row limit
+  // The first tile: 96 rows x 256 columns, 128 where the row limit has too few of those to fill the CUs (two layers of d = 256, 390 of
+  // 702 rows: O and down 6.6 us with 256 columns or 128 rows, 5.6 here; 1.5B shape 10.1 and 22.9, 9.7 and 23.3).  96 x 128 takes 43 per K tile where it is
+  // the better one.
+  const bool few = (M_max + 95) / 96 * nb256 < 128;
+  SlabRule r{0, T96x256::BM, few ? nb128 : nb256, nk, 2 * kCUs, 0, 0, few ? 43 : 83, 0, N, at};
+  if (few || nk < 96) {                                  // the second tile: the better one at the row limit
     auto cost = [&](int bm, int t) {
       const int tiles = (M_max + bm - 1) / bm * nb128, tsl = gemm_slab_cost(M_max, N);
       return gemm_split_cost(tiles, nk, 2 * kCUs, gemm_adaptive_split(tiles, nk, 2 * kCUs, t, tsl), t, tsl);
     };
-    const bool rows128 = cost(128, 51) < cost(160, 68);
+    const bool rows128 = nk >= 96 || cost(128, 51) < cost(160, 68);
     r.bm_alt = rows128 ? T128x128::BM : T160x128::BM;
     r.n_blocks_alt = nb128;
     r.t_alt = rows128 ? 51 : 68;
-  } else if ((M_max + 95) / 96 * nb256 >= 128) {
+    r.tile = few ? (rows128 ? T_96x128_128x128 : T_96x128_160x128) : rows128 ? T_96x256_128x128 : T_96x256_160x128;
+  } else {
     r.bm_alt = T128x256::BM;
     r.n_blocks_alt = nb256;
     r.t_alt = 92;
-  } else {
-    r.bm = T128x128::BM;
-    r.n_blocks = nb128;
-    r.t = 51;
+    r.tile = T_96x256_128x256;
   }
   return r;
 }
@@ -428,25 +433,24 @@ SlabRules gemm_slab_rules(const Shape& s, int M_max) {
   return SlabRules{{slab_rule(M_max, s.Nqkv(), s.d / kBK, kChoiceAt + SLAB_QKV), slab_rule(M_max, s.d, s.Hq * s.D / kBK, kChoiceAt + SLAB_O),
                     slab_rule(M_max, s.d, s.F / kBK, kChoiceAt + SLAB_DOWN)}};
 }
-static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, int which, hipStream_t st) {
-  const SlabRule r = slab_rule(M_max, N, K / kBK, kChoiceAt + which);
-#define BS_SLAB(T_) launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
-#define BS_SLAB_ALT(T_) launch_slab_alt<T96x256, T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
-  if (r.at == 0) {
-    switch (pick_slab(M_max, N, K / kBK).tile) {
-      case 0: BS_SLAB(T64x64); break;
-      case 1: BS_SLAB(T64x128); break;
-      case 2: BS_SLAB(T96x128); break;
-      case 3: BS_SLAB(T128x128); break;
-      case 4: BS_SLAB(T160x128); break;
-      case 5: BS_SLAB(T96x256); break;
-      case 6: BS_SLAB(T128x256); break;
-      default: BS_SLAB(T160x256);
-    }
-  } else if (r.bm_alt == 0) BS_SLAB(T128x128);
-  else if (r.nk >= 96) BS_SLAB_ALT(T128x256);
-  else if (r.bm_alt == T128x128::BM) BS_SLAB_ALT(T128x128);
-  else BS_SLAB_ALT(T160x128);
+static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& r, hipStream_t st) {
+#define BS_SLAB(T_) launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r.fixed, st)
+#define BS_SLAB_ALT(G_, T_) launch_slab_alt<G_, T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
+  switch (r.tile) {
+    case 0: BS_SLAB(T64x64); break;
+    case 1: BS_SLAB(T64x128); break;
+    case 2: BS_SLAB(T96x128); break;
+    case 3: BS_SLAB(T128x128); break;
+    case 4: BS_SLAB(T160x128); break;
+    case 5: BS_SLAB(T96x256); break;
+    case 6: BS_SLAB(T128x256); break;
+    case 7: BS_SLAB(T160x256); break;
+    case T_96x256_128x128: BS_SLAB_ALT(T96x256, T128x128); break;
+    case T_96x256_160x128: BS_SLAB_ALT(T96x256, T160x128); break;
+    case T_96x256_128x256: BS_SLAB_ALT(T96x256, T128x256); break;
+    case T_96x128_128x128: BS_SLAB_ALT(T96x128, T128x128); break;
+    default: BS_SLAB_ALT(T96x128, T160x128);
+  }
 #undef BS_SLAB
 #undef BS_SLAB_ALT
   return SlabCount{r.fixed, r.at};
@@ -459,7 +463,7 @@ static void launch_f32(const int32_t* n_rows_dev, int M_max, int N, int K, const
 }
 
 SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                      int32_t* status, hipStream_t st, int which) {
+                      int32_t* status, hipStream_t st, const SlabRule& rule) {
   const SlabCount none{0, 0};
   if (dtype == BS_F32) {
     if (epi == EPI_SWIGLU) launch_f32<EPI_SWIGLU>(n_rows_dev, M_max, N, K, A, W, out, st);
@@ -467,7 +471,7 @@ SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, in
     else launch_f32<EPI_STORE_F32>(n_rows_dev, M_max, N, K, A, W, out, st);
     return none;
   }
-  if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, which, st);
+  if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, rule, st);
   launch_glu(n_rows_dev, M_max, N, K, A, W, out, status, st);
   return none;
 }
