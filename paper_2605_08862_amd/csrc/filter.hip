@@ -182,7 +182,10 @@ __device__ u64 list_select(Shared& sh, int n, u64 floor_c, u64 target, Wt weight
 // What bounds it: one read of the row by one workgroup.  The histogram passes are bound by LDS atomics, of which the lanes of a
 // wave hit some ten bins.  432 rows of 151936 tokens, accept and resample together: top_k = 50 190 .. 246 us before, 131 here;
 // 128 203 .. 243, 138.
-// False (the list overflows: many equal logits; no mass): nothing is decided, the general way follows.
+// Where the bound itself is the logit of many tokens (a row masked down to fewer tokens than k, a constant row), only the tokens above it are
+// listed; the set is filled up with the first tokens of that logit, and one more pass finds the last of them.  40 tokens of 151936 left, top_k = 50,
+// one row, accept and resample together: 151 us, with top-p 64; 588 and 652 with the general way behind this one.
+// False (the list overflows all the same; no mass): nothing is decided, the general way follows.
 constexpr int kShortK = 128;                                 // at 128 the bound lets about 180 tokens pass, at 200 already 400
 constexpr int kShortList = 512;                              // ranked by counting: n^2 / 256 LDS reads per thread
 template <typename Mass, typename ValueOf, typename Store>
@@ -231,36 +234,42 @@ __device__ __forceinline__ bool short_top_k(const float* __restrict__ z, int V, 
   if (rank == k - 1) sh.bin = (int)top;
   __syncthreads();
   const uint32_t bound = (uint32_t)sh.bin;
-  for (int it = 0; it < n_it; ++it)
-    if (s_group[it * 256 + tid] >= bound) {
-      const int q = atomicAdd(&sh.cand_n, 1);
-      if (q < kShortList) s_u32[q] = (uint32_t)(it * 256 + tid);
-    }
-  __syncthreads();
-  const int n_q = sh.cand_n;
-  __syncthreads();
-  if (n_q > kShortList) return false;
-  if (tid == 0) sh.cand_n = 0;
-  __syncthreads();
-  auto offer = [&](int j, float zj) {
-    const uint32_t key = filter_key(zj);
-    if (key < bound) return;
-    const int slot = atomicAdd(&sh.cand_n, 1);
-    if (slot < kShortList) sh.cand[slot] = ((u64)key << kIdxBits) | (kIdxMask - (u64)j);
-  };
-  for (int i = tid; i < n_q * 8; i += 256) {
-    const int g = (int)s_u32[i >> 3], vec = (g >> 8) * 2048 + (i & 7) * 256 + (g & 255);
-    if (vec >= nvec) continue;
-    const f4 v = *(const f4_u*)(z + 4 * (size_t)vec);
+  int n = kShortList + 1;
+  for (int above = 0; n > kShortList; ++above) {             // the keys from the bound up, then those above it
+    const uint32_t least = bound + (uint32_t)above;
+    if (above > 1 || least < bound) return false;
+    for (int it = 0; it < n_it; ++it)
+      if (s_group[it * 256 + tid] >= least) {
+        const int q = atomicAdd(&sh.cand_n, 1);
+        if (q < kShortList) s_u32[q] = (uint32_t)(it * 256 + tid);
+      }
+    __syncthreads();
+    const int n_q = sh.cand_n;
+    __syncthreads();
+    if (tid == 0) sh.cand_n = 0;
+    __syncthreads();
+    if (n_q > kShortList) continue;
+    auto offer = [&](int j, float zj) {
+      const uint32_t key = filter_key(zj);
+      if (key < least) return;
+      const int slot = atomicAdd(&sh.cand_n, 1);
+      if (slot < kShortList) sh.cand[slot] = ((u64)key << kIdxBits) | (kIdxMask - (u64)j);
+    };
+    for (int i = tid; i < n_q * 8; i += 256) {
+      const int g = (int)s_u32[i >> 3], vec = (g >> 8) * 2048 + (i & 7) * 256 + (g & 255);
+      if (vec >= nvec) continue;
+      const f4 v = *(const f4_u*)(z + 4 * (size_t)vec);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) offer(4 * vec + e, v[e]);
+      for (int e = 0; e < 4; ++e) offer(4 * vec + e, v[e]);
+    }
+    if (tid < (V & 3)) offer(nvec * 4 + tid, z[nvec * 4 + tid]);
+    __syncthreads();
+    n = sh.cand_n;
+    __syncthreads();
+    if (tid == 0) sh.cand_n = 0;
+    __syncthreads();
   }
-  if (tid < (V & 3)) offer(nvec * 4 + tid, z[nvec * 4 + tid]);
-  __syncthreads();
-  const int n = sh.cand_n;
-  __syncthreads();
-  if (n > kShortList) return false;
-  u64* s_top = sh.hist_m;                                    // the top-k set in order; n >= k, so that all are written
+  u64* s_top = sh.hist_m;                                    // the top-k set in order; entries n .. k - 1 are tokens of the bound
   for (int i = tid; i < n; i += 256) {
     const u64 c = sh.cand[i];
     int r = 0;
@@ -268,7 +277,7 @@ __device__ __forceinline__ bool short_top_k(const float* __restrict__ z, int V, 
     if (r < k) s_top[r] = c;
   }
   __syncthreads();
-  const u64 mine = tid < k ? mass(value_of((uint32_t)(s_top[tid] >> kIdxBits))) : 0;
+  const u64 mine = tid < k ? mass(value_of(tid < n ? (uint32_t)(s_top[tid] >> kIdxBits) : bound)) : 0;
   u64 incl = mine;
   sh.scan[tid] = incl;
   __syncthreads();
@@ -292,9 +301,14 @@ __device__ __forceinline__ bool short_top_k(const float* __restrict__ z, int V, 
     if (tid < k && incl - mine < target && incl >= target) { sh.bin = tid; sh.above = incl; }
   }
   __syncthreads();
-  if (tid == 0) {
-    const u64 last = s_top[sh.bin];
-    store((uint32_t)(last >> kIdxBits), (int)(kIdxMask - (last & kIdxMask)), sh.above);
+  const int pos = sh.bin;
+  const u64 kept = sh.above;
+  if (pos >= n) {
+    const int cut = nth_match(z, V, pos - n + 1, [bound](int, float zj) { return filter_key(zj) == bound; }, sh);
+    if (tid == 0) store(bound, cut, kept);
+  } else if (tid == 0) {
+    const u64 last = s_top[pos];
+    store((uint32_t)(last >> kIdxBits), (int)(kIdxMask - (last & kIdxMask)), kept);
   }
   return true;
 }

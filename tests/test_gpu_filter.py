@@ -113,6 +113,31 @@ def test_small_top_k_at_group_and_list_edges(eng, top_k, top_p):
     assert eng.poll_status() == 0
 
 
+@pytest.mark.parametrize("top_k,top_p", [(1, 1.0), (50, 1.0), (50, 0.913), (50, 0.417), (128, 0.913), (128, 1.0)])
+def test_small_top_k_where_many_tokens_share_its_threshold(eng, top_k, top_p):
+    """Rows masked down to fewer tokens than top_k (-inf and the lowest float32), and rows whose threshold logit is shared by hundreds of tokens with
+    some above it, none, or exactly top_k: the set is filled up with the first tokens of that logit, and the top-p cut falls above them or
+    among them.  (top_p times a number of equal tokens is nowhere within 1e-2 of a whole number.)"""
+    rng = np.random.default_rng(top_k)
+    for V in (2050, 4093):
+        rows = []
+        for low in (-np.inf, np.finfo(np.float32).min, -2.0, 3.0):
+            for n_above in (0, 1, 20, 49, 50, 51, 127, 300):
+                z = np.full(V, low, np.float32)
+                z[rng.permutation(V)[:n_above]] = 3.5 + rng.normal(0, 0.5, n_above) ** 2
+                if n_above or low > -1e30:                     # (a row of the lowest float32 alone has a log-sum beyond float32)
+                    rows.append(z)
+        logits = np.array(rows, np.float32)
+        Bn = len(rows)
+        drafts, k_b = np.zeros((Bn, 1), np.int32), np.zeros(Bn, np.int32)
+        ua, us = W.uniforms(V, Bn, 1)
+        eng.set_filter(top_k, top_p)
+        out = _call(eng, logits, drafts, k_b, ua, us, temperature=0.8)
+        assert _check_thresholds(eng, logits, 0.8, top_k, top_p) == 0
+        H.compare_sampler(out, logits, drafts, k_b, ua, us, None, 0.8, top_k=top_k, top_p=top_p)
+    assert eng.poll_status() == 0
+
+
 @pytest.mark.parametrize("T", [0.55, 0.61, 0.7, 0.9, 1.1, 1.3])
 def test_tied_tokens_at_large_logits_are_both_kept(eng, T):
     """Two equal largest tokens share the mass, so top_p = 0.9 needs both, whatever their size: float32 row statistics of logits of
