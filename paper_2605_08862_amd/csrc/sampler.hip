@@ -592,7 +592,22 @@ __device__ __forceinline__ void for_each_token(const SampleRow<Q, FILT>& r, int 
         for (int e = 0; e < 4; ++e) f(j0 + 4 * i + e, z[u][e], to_f32<Q>(q[u][e]));
     }
   }
-  for (int j = j0 + 4 * n4 + threadIdx.x; j < j1; j += 256) f(j, r.z[j], r.q ? to_f32<Q>(r.q[j]) : 0.f);
+  // rows that do not start on sixteen bytes (an odd vocabulary), and the last tokens of the others: as many loads in flight
+  constexpr int US = 8;
+  for (int i0 = j0 + 4 * n4; i0 < j1; i0 += US * 256) {
+    float z[US], q[US];
+#pragma unroll
+    for (int u = 0; u < US; ++u) {
+      const int j = min(i0 + u * 256 + (int)threadIdx.x, j1 - 1);
+      z[u] = r.z[j];
+      q[u] = r.q ? to_f32<Q>(r.q[j]) : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < US; ++u) {
+      const int j = i0 + u * 256 + threadIdx.x;
+      if (j < j1) f(j, z[u], q[u]);
+    }
+  }
 }
 
 // Per chunk: sum of e_p, and the sum of e_q (dense residual) or of e_p without the rejected draft (one-hot residual).  Without a
