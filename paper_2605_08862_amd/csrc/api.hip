@@ -455,10 +455,9 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
       launch_qkv_rope(s, p, c->kv, M_max, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
     } else {
-      SlabCount nq;
-      { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-        nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
-                         slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.r[SLAB_QKV]); }
+      ProfScope ps(c, BS_PROF_GEMM_QKV, st);
+      const SlabCount nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
+                                       slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.r[SLAB_QKV]);
       launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }

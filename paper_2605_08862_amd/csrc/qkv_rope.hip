@@ -187,15 +187,17 @@ void launch_one(int blocks, int threads, int lds, hipStream_t st, const Args&...
 }
 }  // namespace
 
-// Few rows have too few (rows, head) tiles for 256 CUs: the GEMM split over K and the rotary kernel behind it (6 us; both have 11 us of
-// launches and latency, the fused kernel 3) are then faster.  Measured, 7B shape: 64 rows 13 + 6 us, 24 fused; 136 rows 14 + 6, 22.
-// 1.5B shape: 432 rows 12 + 7, 12 fused; 576 rows 13 + 7.6, 15.
+// Few rows have too few (rows, head) tiles for 256 CUs: the GEMM split over K and the rotary kernel behind it are then faster, although both
+// together have more launches and latency (the 300 and the 940, in 0.01 us) and the rotary kernel reads the slabs and scatters K and V: 6 us at 64 rows of
+// 4608 columns, 9 at 288 with 2048 cached tokens, 16 with 8192, when the pages are cold.  Steps measured with either route, us per layer, two kernels / fused:
+//   7B shape    72 rows 141 / 145   189 rows 196.7 / 197.3   243 rows 217.3 / 219.9   288 rows 228.9 / 228.7, with 8192 cached tokens 319.2 / 315.3   387 rows 300 / 294
+//   1.5B shape  63 rows 67.0 / 68.3   99 rows 75.2 / 75.8   135 rows 79.7 / 78.4   288 rows 99.1 / 95.3   576 rows 133.6 / 129.0
 bool qkv_rope_applies(const Shape& s, int M_max) {
   if (s.dtype != BS_BF16 || s.D != kD) return false;
   if (M_max > kFewRows) return true;
   int cost;
   pick_rows(M_max, s.Hq + 2 * s.Hkv, s.d / kBK, true, cost);
-  return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 1100;
+  return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 940 + M_max * s.Nqkv() / 5760;
 }
 
 void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
