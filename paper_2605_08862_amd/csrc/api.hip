@@ -730,7 +730,8 @@ void bs_debug_unfused_qkv(bs_ctx* c, int on) { if (c) c->unfused_qkv = on != 0; 
 // normed rows, 2 qkv (float32 models), 3 q, 4 attention out, 5 mlp act, 6 final rows; 1 .. 5 hold until the next accept call
 // (bf16 models: it writes logits there).  bf16 models: 1, 4, 5 and 6 are in chunk order (act_index), ld = row limit of the step; steps of at
 // most 32 rows (skinny.hip): 0 is in fragment order (h_frag_index), 1, 4 and 5 have ld = 32, and 1 holds the rows in front of gate/up only.  Of the last accept step:
-// 7, 8, 9 per-row filter threshold key, index cut, log of the kept mass.
+// 7, 8, 9 per-row filter threshold key, index cut, log of the kept mass.  10: int32 rows and drafts of the last verify step, then the choices for its QKV, O and
+// down projections where they follow from the row count (rows of a tile << 4 | slabs).
 void* bs_debug_buffer(bs_ctx* c, int which) {
   if (!c) return nullptr;
   switch (which) {
@@ -744,6 +745,7 @@ void* bs_debug_buffer(bs_ctx* c, int which) {
     case 7: return c->sb.f_key;
     case 8: return c->sb.f_idx;
     case 9: return c->sb.f_lse;
+    case 10: return c->plan.n_rows;
     default: return nullptr;
   }
 }

@@ -26,7 +26,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kBK = 64;                    // K tile (elements)
 constexpr int kWBlock = 32 * kBK;          // elements of one packed (row tile, K tile) block
 
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
 // (a function of its own: the host pass does not accept the builtin inside templates)
@@ -35,10 +34,3 @@ __device__ __forceinline__ f32x16 mfma_f16(u32x4 a, u32x4 b, f32x16 c) { return 
 // Accumulator element i of lane `lane` in a 32x32 MFMA tile: row, col inside the tile.
 __device__ __forceinline__ int acc_row(int lane, int i) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
 __device__ __forceinline__ int acc_col(int lane) { return lane & 31; }
-
-// Offset (elements) of weight element (n, k) in the packed layout of a matrix with nk K tiles.
-__host__ __device__ __forceinline__ size_t packed_w_index(int n, int k, int nk) {
-  int nt = n >> 5, nl = n & 31, kt = k >> 6, kk = k & 63;
-  int g = kk >> 5, s = (kk & 31) >> 3, j = kk & 7;
-  return ((size_t)nt * nk + kt) * kWBlock + (size_t)s * 512 + (g * 32 + nl) * 8 + j;
-}

@@ -39,6 +39,12 @@ def debug_buffer(eng, which, n):
     return out
 
 
+def slab_choice(eng, which):
+    """(rows of a tile, slabs) of the last verify step's QKV (0), O (1) or down projection (2), where the device chose them."""
+    v = int(debug_buffer(eng, 10, 3 + which).view(torch.int32)[2 + which].item())
+    return v >> 4, v & 15
+
+
 def pack_rows(last_token, draft_tokens, draft_len):
     """Token block [last, drafts...] per sequence."""
     return [np.concatenate([[last_token[b]], draft_tokens[b][:draft_len[b]]]).astype(np.int64)

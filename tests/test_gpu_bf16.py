@@ -22,7 +22,7 @@ def _f64_weights(wn):
 
 
 def _run_case(desc, ctx_lens, k_b, k_max, seed, temperature=1.0, q_mode="dense", q_scale=0.8, perm=3,
-              check_kv=True, unfused_qkv=False):
+              check_kv=True, unfused_qkv=False, after_step=None):
     """One verify step on random-filled contexts; returns stats after asserting all three tiers."""
     Bn = len(ctx_lens)
     rng = np.random.default_rng(seed)
@@ -69,6 +69,8 @@ def _run_case(desc, ctx_lens, k_b, k_max, seed, temperature=1.0, q_mode="dense",
     slots = H.dev_i32(np.arange(Bn))
     dt, dl = H.dev_i32(drafts), H.dev_i32(k_b)
     logits = eng.verify_step(slots, H.dev_i32(last), dt, dl, k_max, want_logits=True)
+    if after_step is not None:
+        after_step(eng)
     qdev = None if q_rows is None else q_t.to(DEV)
     out = eng.accept_resample(dt, dl, k_max, H.dev_f32(ua), H.dev_f32(us), q_logits=qdev, temperature=temperature)
     got = logits.cpu().numpy()[:M]
@@ -143,16 +145,26 @@ def test_mini_many_ragged_sequences():
 @pytest.mark.parametrize("fill", ["full", "mixed", "plain"])
 def test_wide_model_large_row_limit(fill):
     """Row limit 48 x 17 = 816 > 640 on a one-layer model that is wide enough (d = 3840) for the large-batch launch
-    paths at a size the oracle still finishes in seconds: the 128-row gate/up kernel, and the residual projections
-    whose row tile and K split are decided on the device from the step's row count.  With every draft block full (816
-    rows) the device rule takes 128-row tiles for the O projection (K = 2048), with mixed lengths (about 430 rows)
-    and with plain decodes only (48 rows) 96-row tiles; the down projection (K = 512) runs unsplit."""
+    paths at a size the oracle still finishes in seconds: the persistent gate/up kernel, and the residual projections
+    whose K split is decided on the device from the step's row count: for the O projection (K = 2048) one, two (mixed lengths, about
+    430 rows) and six slabs (plain decodes only, 48 rows) of 128-row tiles.  (Row tiles that change: test_row_tile_from_the_row_count.)"""
     desc = W.shape("mini_bf16", n_layers=1, d_model=3840, n_q_heads=16, n_kv_heads=4, d_ffn=512, vocab=640)
     rng = np.random.default_rng(61)
     Bn, k_max = 48, 16
     ctx = [int(x) for x in rng.integers(0, 150, Bn)]
     k_b = {"full": [16] * Bn, "mixed": [int(x) for x in rng.integers(0, 17, Bn)], "plain": [0] * Bn}[fill]
     _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=k_max, seed=61, check_kv=(fill == "mixed"))
+
+
+@pytest.mark.parametrize("k_b,choice", [([16] * 66, (160, 1)), ([15] * 42 + [0] * 24, (96, 2)), ([0] * 66, (160, 6))])
+def test_row_tile_from_the_row_count(k_b, choice):
+    """Row limit 66 x 17 = 1122: the O projection (K = 2048, 3840 columns) takes 160-row tiles of 128 columns when every block is full and when none has a
+    draft, 96-row tiles of 256 columns in two slabs for 696 rows, and the device says so."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=3840, n_q_heads=16, n_kv_heads=4, d_ffn=512, vocab=640)
+    ctx = [int(x) for x in np.random.default_rng(62).integers(0, 150, 66)]
+    seen = []
+    _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=16, seed=62, check_kv=False, q_mode="onehot", after_step=lambda eng: seen.append(H.slab_choice(eng, 1)))
+    assert seen == [choice]
 
 
 def test_mini_single_sequence_edges():

@@ -26,7 +26,7 @@ def test_gemm_launches_at_row_limit(d_ffn, n_seq, k_max):
 @pytest.mark.parametrize("fill", ["full", "mixed", "plain"])
 def test_splits_from_the_row_count(d_ffn, fill):
     """Row limit 645: the K splits of O and down follow from the step's row count (645, about 330 and 43 rows), which the GEMM and
-    the normalisation behind it read in one place; 7 K tiles of down take the kernel with two row tiles, 100 the one with a single tile."""
+    the normalisation behind it read in one place; down has 7 and 100 K tiles."""
     desc = W.shape("mini_bf16", n_layers=2, d_model=320, n_q_heads=14, n_kv_heads=2, d_ffn=d_ffn, vocab=777)
     rng = np.random.default_rng(d_ffn)
     ctx = [int(x) for x in rng.integers(0, 70, 43)]
@@ -59,3 +59,11 @@ def test_gate_up_rows_from_the_row_count_below_640(n_draft):
     192 rows of 504 (three blocks) and of 168 (one), 128 of 280."""
     desc = W.shape("mini_bf16", n_layers=1, d_model=192, n_q_heads=6, n_kv_heads=2, d_ffn=18944, vocab=333)
     _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(6).integers(0, 70, 56)], k_b=[n_draft] * 56, k_max=8, seed=94, q_mode="onehot", check_kv=False)
+
+
+@pytest.mark.parametrize("n_last", [0, 1, 2, 3])
+def test_normalisation_of_four_rows_per_workgroup(n_last):
+    """Row limit 2176 and d <= 2048: four rows per workgroup; 1600 to 1603 live rows."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=320, n_q_heads=6, n_kv_heads=2, d_ffn=448, vocab=333)
+    k_b = [16] * 92 + [n_last] + [0] * 35
+    _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(8).integers(0, 40, 128)], k_b=k_b, k_max=16, seed=95, q_mode="onehot", check_kv=False)

@@ -88,14 +88,15 @@ def test_step_replays_from_a_hip_graph(shape, q_mode):
     eng.close()
 
 
-def test_replay_with_changing_row_counts_on_the_large_batch_paths():
+@pytest.mark.parametrize("Bn,mixed", [(48, None), (66, [15] * 42 + [0] * 24)])
+def test_replay_with_changing_row_counts_on_the_large_batch_paths(Bn, mixed):
     """The captured step has fixed grids; the row count lives on the device.  On a model wide enough for the
-    large-batch launch paths (row limit 48 x 17 = 816 > 640: 128-row gate/up kernel, residual projections whose tile
-    and K split follow the row count, RMSNorm summing that many slabs) the draft lengths are rewritten between
-    replays - every block full (816 rows), mixed (about 430), no drafts at all (48) - and each replay must equal the
-    eager step on the same inputs bit for bit."""
+    large-batch launch paths (row limits 48 x 17 = 816 and 66 x 17 = 1122 > 640: persistent gate/up kernel whose row tile follows
+    the row count, residual projections whose K split does, RMSNorm summing that many slabs) the draft lengths are rewritten between
+    replays - every block full (816 and 1122 rows), mixed (about 430, and 696, where O takes another row tile than before and after), no
+    drafts at all (48 and 66) - and each replay must equal the eager step on the same inputs bit for bit."""
     desc = W.shape("mini_bf16", n_layers=1, d_model=3840, n_q_heads=16, n_kv_heads=4, d_ffn=512, vocab=640)
-    Bn, k_max, V = 48, 16, desc["vocab"]
+    k_max, V = 16, desc["vocab"]
     rng = np.random.default_rng(43)
     ctx_lens = [int(x) for x in rng.integers(0, 150, Bn)]
     eng = _setup(desc, Bn, k_max, ctx_lens, seed=43)
@@ -123,7 +124,8 @@ def test_replay_with_changing_row_counts_on_the_large_batch_paths():
             out_g = step()
     torch.cuda.current_stream().wait_stream(side)
     torch.cuda.synchronize()
-    lengths = [[16] * Bn, [int(x) for x in rng.integers(0, 17, Bn)], [0] * Bn, [16] * Bn, [int(x) for x in rng.integers(0, 17, Bn)]]
+    draw = lambda: mixed or [int(x) for x in rng.integers(0, 17, Bn)]
+    lengths, choices = [[16] * Bn, draw(), [0] * Bn, [16] * Bn, draw()], []
     for trial, k_b in enumerate(lengths):
         dl.copy_(H.dev_i32(k_b))
         drafts.copy_(H.dev_i32(rng.integers(0, V, (Bn, k_max))))
@@ -133,9 +135,12 @@ def test_replay_with_changing_row_counts_on_the_large_batch_paths():
         eng.ctx_len.fill_(-7)
         graph.replay()
         torch.cuda.synchronize()
+        choices.append(H.slab_choice(eng, 1))
         for k in ref:
             assert torch.equal(out_g[k], ref[k]), (trial, k)
         assert torch.equal(eng.ctx_len, ref_ctx), trial
         assert int(out_g["n_emitted"].sum().item()) >= Bn
+    assert len(set(choices)) == 3 and choices[0] == choices[3], choices       # K splits, and with 66 sequences the row tile
+    assert len({rows for rows, _ in choices}) == (2 if mixed else 1), choices
     assert eng.poll_status() == 0
     eng.close()

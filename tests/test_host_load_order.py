@@ -1,4 +1,4 @@
-"""CPU check of the compiled GEMM loops: spills, and the order in which loads are issued.  (hipcc cross-compiles; no GPU needed.)"""
+"""CPU check of the compiled main loops: spills, and the order in which loads are issued.  (hipcc cross-compiles; no GPU needed.)"""
 import os
 import re
 import shutil
@@ -48,4 +48,45 @@ def test_weight_ring_loads_are_issued_where_they_are_written(tmp_path, source, k
             orders = [tiles, tiles[::-1]]
             assert any(events.startswith("".join(stream_events(*t) for t in o)) for o in orders), (name, events)
             checked += 1
+    assert checked >= kernels, checked
+
+
+def dma_events(mw, nw, wm, wn, nst):
+    """Requests into LDS (X) and waits with a barrier of a DmaGemm loop: all stages but one, then a wait that leaves all but one of them in flight, and
+    per stage a wait that leaves all but two in flight, with the requests of the stage whose slot is free behind it."""
+    pieces, waves = 2 * (mw * wm + nw * wn), wm * wn
+    ppw = -(-pieces // waves)
+    return "X" * (ppw * (nst - 1)) + "<%d>" % (ppw * (nst - 2)) + "<%d>" % (ppw * (nst - 3)) + "X" * ppw
+
+
+# kernels whose loops are not all named in the symbol: those of the declarations next to them
+LOOPS = {"glu_rows_kernel": [(2, 2, 2, 4, 6), (3, 2, 2, 4, 5), (4, 2, 2, 4, 4)], "qkv_rows_kernel": [(1, 1, 1, 4, 8), (1, 1, 2, 4, 6), (1, 2, 4, 2, 5), (1, 2, 6, 2, 4)]}
+
+
+@pytest.mark.parametrize("source, kernels", [("gemm.hip", 6), ("qkv_rope.hip", 2), ("attention.hip", 2)])
+def test_lds_requests_are_issued_where_they_are_written(tmp_path, source, kernels):
+    """The same for the loops whose operands all go through LDS (two operands of a GEMM, K/V tiles of the attention with four query tiles): the
+    number of requests in front of each wait, and what the wait leaves in flight."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    out = tmp_path / "kernels.s"
+    r = subprocess.run([hipcc, *BLD.FLAGS, "--offload-device-only", "-S", os.path.join(BLD.CSRC, source), "-o", str(out)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    checked = 0
+    for name, body in re.findall(r"\n(_Z\S+):\s*; @.*?\n(.*?)\n\.Lfunc_end", out.read_text(), re.S):
+        loops = next((v for k, v in LOOPS.items() if k in name), None) or [tuple(map(int, t)) for t in re.findall(r"DmaGemmILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", name)]
+        head = re.search(r"attn_wide_kernelILi(\d+)E", name)
+        if not loops and not head:
+            continue
+        events = "".join("X" if a else "<%s>" % b for a, b in re.findall(r"(buffer_load\S* [^\n]* lds\b)|;#ASMSTART\s+s_waitcnt vmcnt\((\d+)\)\s+s_barrier", body))
+        if head:                                               # LPW = requests of a wave per tile; three tiles ahead, the waits of the last tiles in any order
+            lpw = int(head.group(1)) // 32
+            m = re.fullmatch("X{%d}((?:<\\d+>){3})X{%d}" % (3 * lpw, lpw), events)
+            assert m and sorted(re.findall(r"\d+", m.group(1)), key=int) == ["0", str(lpw), str(2 * lpw)], (name, events)
+        else:
+            for loop in loops:
+                assert events.count(dma_events(*loop)) == 1, (name, loop, events)
+            assert len(events) == sum(len(dma_events(*loop)) for loop in loops), (name, events)
+        checked += 1
     assert checked >= kernels, checked
