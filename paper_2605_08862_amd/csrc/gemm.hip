@@ -293,9 +293,9 @@ static void launch_glu_rows(const GluArgs& g, int n128, hipStream_t st) {
   hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
 }
 // Measured in us (gate/up of the 1.5B shape, 8960 features, and of the 7B shape, 18944; the loops with weights in registers and
-// activations staged through registers that were here before in brackets):
-//   64 rows 13.3 (22.3) / 48.4 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 87.3 (104)
-//   432 rows 29.1 (44.7)    576 rows 36.2 (41.4)    1037 rows 63.0 (73.0)    1185 rows - / 283 (324)    3480 rows 169.5 (190.9)
+// activations staged through registers that were here before in brackets; 7B at 64, 288 and 1185 rows and 1.5B from 432 rows in whole steps):
+//   64 rows 13.3 (22.3) / 48.7 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 80.1 (104)
+//   432 rows 28.9 (44.7)    576 rows 35.6 (41.4)    1037 rows 61.0 (73.0)    1185 rows - / 275 (324)    3480 rows 169.5 (190.9)
 static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const void* A, const void* W, void* out, int32_t* status, hipStream_t st) {
   const GluArgs g{n_rows_dev, M_max, F, K, (const f16*)A, (const f16*)W, (f16*)out, status};
   const int rt = (M_max + 31) / 32, n128 = (F + 127) / 128;
@@ -317,7 +317,7 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     return;
   }
   if (M_max <= kFewRows && wide && mix) {
-    // the same for two or three groups of waves side by side in the rows: 288 rows 87 us, 95 with 96-row tiles of 128 features
+    // the same for two or three groups of waves side by side in the rows: 288 rows, launches by themselves, 87 us, 95 with 96-row tiles of 128 features
     if (rt == 6) launch_glu_t<DmaGemm<3, 1, 2, 5, 7>>(g, st);
     else if (rt <= 8) launch_glu_t<DmaGemm<4, 1, 2, 5, 6>>(g, st);
     else if (rt == 9) launch_glu_t<DmaGemm<3, 1, 3, 5, 5>>(g, st);
@@ -329,7 +329,7 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     auto cost = [&](int bm, int t) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * t; };
     const int c96 = cost(96, 83), c128 = cost(128, 92), c160 = cost(160, 113), c192 = cost(192, 128);
     if (c192 < c96 && c192 < c128 && c192 < c160) {
-      // more than one round of the CUs: the tile from the step's row count (7B shape, 504 rows, 252 of them live: 140 us with 192 rows, 112 with 128)
+      // more than one round of the CUs: the tile from the step's row count (7B shape, 504 rows, 280 of them live: 140 us with 192 rows, 112 with 128)
       if ((M_max + 191) / 192 * n128 > kCUs) launch_glu_rows(g, n128, st);
       else launch_glu_t<GemmRows192>(g, st);
     } else if (c160 < c96 && c160 < c128) launch_glu_t<StreamGemm<5, 2, 4, 2>>(g, st);
@@ -337,7 +337,7 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     else launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
     return;
   }
-  // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows: 283 us, 290 with 128-row tiles), 128-row
+  // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows, in one run: 283 us, 290 with 128-row tiles), 128-row
   // tiles, two workgroups per CU, for a short one, where filling and storing a tile is a larger part (1.5B shape, 1037 rows: 63 us
   // against 67; 3480 rows: 169.5 against 171).
   if (K / kBK < 32) {
@@ -371,7 +371,7 @@ static void launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, 
 // Tile and split of a float32-result GEMM: the cheapest of the tiles below by gemm_split_cost, whose times of a K tile are those of
 // launches that fill the CUs once (a tile of 32 MW rows x 128 NW columns).  Measured in us, down projection of the 1.5B and the 7B
 // shape (before, with the loops that staged activations through registers):
-//   64 rows 10.0 (19.2) / 26.7 (38.8)    144 rows 12.8 (20.5) / 35.1 (44.1)    288 rows 16.7 (21.5) / 47.9 (66.3)
+//   64 rows 10.0 (19.2) / 26.7 (38.8)    144 rows 12.8 (20.5) / 35.1 (44.1)    288 rows 16.7 (21.5) / 47.9 (66.3; 57 in whole steps)
 //   576 rows 24.0 (24.6) / 82 (130)    1100 rows 36.0 (48.5) / 147 (159)
 typedef StreamGemm<2, 1, 2, 4> T64x64;
 typedef StreamGemm<2, 1, 4, 4> T64x128;

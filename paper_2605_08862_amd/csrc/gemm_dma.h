@@ -13,8 +13,8 @@
 //   * The tile (MW x NW accumulator tiles per wave, WM x WN waves) is a template parameter: few rows take all rows and few
 //     columns per workgroup, so that a weight is read once and as many CUs stream as columns allow; many rows take 192 x 256 or
 //     256 x 256, where LDS (128 bytes per clock) delivers what the matrix unit asks for.
-// What bounds it (MI355X, 7B shape, gate/up): 64 rows 55 -> 48 us, 5.7 TB/s of weights: memory.  1185 rows 321 -> 295 us: power; the
-// same launch takes 231 us when the activations are zeros and 270 us without its loads.
+// What bounds it (MI355X, 7B shape, gate/up in whole steps): 64 rows 55 -> 48.7 us, 5.6 TB/s of weights: memory.  1185 rows 324 -> 275 us: power (a build
+// that took 295 us took 231 when the activations were zeros and 270 without its loads).
 #pragma once
 #include "gemm_mfma.h"
 

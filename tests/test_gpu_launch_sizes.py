@@ -1,7 +1,7 @@
 """GPU parity at the launch sizes of the 7B-shape and pool-stress configurations.
 
 The launchers pick kernel instantiations by the row limit M_max = B (k_max + 1) and the shape (row tiling of the
-MFMA GEMMs, K splits, 96- or 192-row SwiGLU tiles, LM-head row tiling, query blocks and token chunks of the
+MFMA GEMMs, K splits, gate/up tiles of 64 to 256 rows, LM-head row tiling, query blocks and token chunks of the
 attention work list), so a variant is only checked if a test runs at the batch that selects it.  Each case here is a
 two-layer slice of the real per-layer shape with the full vocabulary at the REAL batch of the configuration, built
 by the same workload builder bench.py times:
