@@ -574,8 +574,8 @@ __device__ __forceinline__ void for_each_token(const SampleRow<Q, FILT>& r, int 
   typedef Q q4 __attribute__((ext_vector_type(4)));
   const bool vec = ((uintptr_t)(r.z + j0) & 15) == 0 && ((uintptr_t)(r.q + j0) & (4 * sizeof(Q) - 1)) == 0;
   const int n4 = vec ? (j1 - j0) / 4 : 0;
-  constexpr int U = 5;                                   // loads in flight: a chunk of a vocabulary of up to 163840 tokens at once
-  for (int i0 = 0; i0 < n4; i0 += U * 256) {
+  auto vectors = [&](auto count, int i0) {
+    constexpr int U = decltype(count)::value;
     f32x4 z[U];
     q4 q[U] = {};
 #pragma unroll
@@ -591,10 +591,16 @@ __device__ __forceinline__ void for_each_token(const SampleRow<Q, FILT>& r, int 
 #pragma unroll
         for (int e = 0; e < 4; ++e) f(j0 + 4 * i + e, z[u][e], to_f32<Q>(q[u][e]));
     }
+  };
+  // five loads in flight (a chunk of a vocabulary of up to 163840 tokens at once), one where a thread has no more (up to 32768)
+  constexpr int U = 5;
+  for (int v0 = 0; v0 < n4;) {
+    if (n4 - v0 > 256) { vectors(std::integral_constant<int, U>{}, v0); v0 += U * 256; }
+    else { vectors(std::integral_constant<int, 1>{}, v0); v0 += 256; }
   }
-  // rows that do not start on sixteen bytes (an odd vocabulary), and the last tokens of the others: as many loads in flight
-  constexpr int US = 8;
-  for (int i0 = j0 + 4 * n4; i0 < j1; i0 += US * 256) {
+  // rows that do not start on sixteen bytes (an odd vocabulary), and the last tokens of the others: eight tokens of a thread at once, then two
+  auto batch = [&](auto count, int i0) {
+    constexpr int US = decltype(count)::value;
     float z[US], q[US];
 #pragma unroll
     for (int u = 0; u < US; ++u) {
@@ -607,7 +613,10 @@ __device__ __forceinline__ void for_each_token(const SampleRow<Q, FILT>& r, int 
       const int j = i0 + u * 256 + threadIdx.x;
       if (j < j1) f(j, z[u], q[u]);
     }
-  }
+  };
+  int i0 = j0 + 4 * n4;
+  for (; i0 + 8 * 256 <= j1; i0 += 8 * 256) batch(std::integral_constant<int, 8>{}, i0);
+  for (; i0 < j1; i0 += 2 * 256) batch(std::integral_constant<int, 2>{}, i0);
 }
 
 // Per chunk: sum of e_p, and the sum of e_q (dense residual) or of e_p without the rejected draft (one-hot residual).  Without a
