@@ -125,8 +125,8 @@ void launch_pack_weight(const void* w_bf16, int N, int K, void* packed_f16, int3
 // ---- gate/up projection + SwiGLU.  F = features; the packed matrix holds the F gate rows, then the F up rows.  Both rows of a
 // feature land in the same lane:
 //   NW even  the wave's weight tiles alternate: gate tile, up tile of the same 32 features;
-//   NW == 1  ("mixed") a tile is 16 gate rows and their 16 up rows, put together by the lanes' addresses: accumulator registers i
-//            and i + 8.  16 features per wave instead of 32 fill 256 CUs in finer steps.
+//   NW == 1  ("mixed") a tile is 16 gate rows and their 16 up rows, put together by the addresses.  16 features per wave instead of
+//            32 fill 256 CUs in finer steps.
 struct GluArgs {
   const int32_t* n_rows_dev;
   int M_max, F, K;
@@ -138,37 +138,31 @@ struct GluArgs {
 template <typename G, int BM = G::BM>
 __device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_blocks, int id0, int stride, int n, char* lds) {
   constexpr bool MIX = G::NW == 1;
-  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int lane = threadIdx.x & 63;
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
   const size_t tile_bytes = (size_t)(g.K / kBK) * 4096, half = (size_t)(g.F / 32) * tile_bytes;    // up rows behind the gate rows
   const int t_last = g.F / 32 - 1;
-  const uint32_t w_lane = MIX ? (lg * 32 + (ln & 15)) * 16u + (ln >= 16 ? (uint32_t)half : 0u) : lane * 16u;
   auto operands = [&](typename G::Operands& op, int id) {
     const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT;
     // position t: features 16 (t0 + t) .. (mixed), or the gate (t even) / up (t odd) rows of features 32 ((t0 + t) / 2) ..
     auto w_at = [&](int t) -> size_t { return min((t0 + t) >> 1, t_last) * tile_bytes + (((t0 + t) & 1) ? (MIX ? 256 : half) : 0); };
-    G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp, w_at, w_lane, 0);
+    G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp, w_at, MIX ? (uint32_t)half : kWHalf, 0);
   };
-  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int id) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int id) {
     const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT, M = min(*g.n_rows_dev, g.M_max);
 #pragma unroll
-    for (int a = 0; a < G::MW; ++a) {
-      const int m = m0 + (wm * G::MW + a) * 32 + ln;
+    for (int a = 0; a < 2 * G::MW; ++a) {
+      const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
       if (m >= M) continue;
 #pragma unroll
-      for (int b = 0; b < (MIX ? 1 : G::NW / 2); ++b) {
-        const int f0 = (t0 + wn * G::NW + 2 * b) * 16;   // first feature of the tile, or pair of tiles
+      for (int b = 0; b < G::NW; ++b) {                  // 16 features each
+        const int f0 = (t0 + wn * G::NW + b) * 16;
         if (f0 >= g.F) continue;                         // F is a multiple of 64: whole tiles only
+        const int gate = MIX ? 0 : (b >> 1) * 4 + (b & 1), up = MIX ? 1 : gate + 2;
+        float y[4];
 #pragma unroll
-        for (int i4 = 0; i4 < (MIX ? 2 : 4); ++i4) {
-          float y[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int i = 4 * i4 + j;
-            y[j] = silu_fast(acc[a][MIX ? 0 : 2 * b][i]) * (MIX ? acc[a][0][(i + 8) & 15] : acc[a][(2 * b + 1) % G::NW][i]);
-          }
-          *(f16x4*)(g.out + act_index(m, f0 + 8 * i4 + 4 * lg, g.M_max)) = to_f16x4_guarded(y[0], y[1], y[2], y[3], g.status);
-        }
+        for (int e = 0; e < 4; ++e) y[e] = silu_fast(acc[a][gate][e]) * acc[a][up][e];
+        *(f16x4*)(g.out + act_index(m, f0 + acc_row(lane), g.M_max)) = to_f16x4_guarded(y[0], y[1], y[2], y[3], g.status);
       }
     }
   };
@@ -218,28 +212,26 @@ __global__ void __launch_bounds__(512) glu_rows_kernel(GluArgs g, int n_blocks) 
 template <typename G>
 __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
                                           const f16* __restrict__ Wp, float* __restrict__ out, int m0, int nb, int split, int n_split, char* lds) {
-  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int lane = threadIdx.x & 63;
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
   const size_t tile_bytes = (size_t)(K / kBK) * 4096;
   const int t0 = nb * G::CT, t_last = N / 32 - 1;
   const int nk = K / kBK, s0 = 2 * (nk * split / n_split), s1 = 2 * (nk * (split + 1) / n_split);
   auto operands = [&](typename G::Operands& op, int) {
-    G::make_operands(op, A, M_max, [&](int r) { return min(m0 + r, M_max - 1); }, Wp, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, lane * 16u, s0);
+    G::make_operands(op, A, M_max, [&](int r) { return min(m0 + r, M_max - 1); }, Wp, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, kWHalf, s0);
   };
-  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int) {
     const int M = min(*n_rows_dev, M_max);
     float* dst = out + (size_t)split * M_max * N;
 #pragma unroll
-    for (int a = 0; a < G::MW; ++a) {
-      const int m = m0 + (wm * G::MW + a) * 32 + ln;
+    for (int a = 0; a < 2 * G::MW; ++a) {
+      const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
       if (m >= M) continue;
 #pragma unroll
-      for (int b = 0; b < G::NW; ++b) {
-        const int n0 = (t0 + wn * G::NW + b) * 32;
+      for (int b = 0; b < 2 * G::NW; ++b) {
+        const int n0 = (t0 + wn * G::NW) * 32 + b * 16;
         if (n0 >= N) continue;                           // N is a multiple of 32: whole tiles only
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *(f32x4*)(dst + (size_t)m * N + n0 + 8 * i4 + 4 * lg) = f32x4{acc[a][b][4 * i4], acc[a][b][4 * i4 + 1], acc[a][b][4 * i4 + 2], acc[a][b][4 * i4 + 3]};
+        *(f32x4*)(dst + (size_t)m * N + n0 + acc_row(lane)) = acc[a][b];
       }
     }
   };

@@ -61,12 +61,13 @@ struct DmaGemm {
   __device__ static __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
   // x_row(r): row of X (clamped by the caller) for row r of the workgroup's tile; w_at(t): byte offset of the packed row tile at
-  // position t of the workgroup's CT weight tiles (wave wn multiplies positions wn * NW .. wn * NW + NW - 1); w_lane: byte offset of a
-  // lane inside a fragment (16 * lane, unless a tile is put together from two).  s0: first stage (32 of K).
+  // position t of the workgroup's CT weight tiles (wave wn multiplies positions wn * NW .. wn * NW + NW - 1); w_half: bytes from a
+  // tile's first 16 rows to its last 16 (kWHalf, unless a tile is put together from two).  s0: first stage (32 of K).
   template <typename XRow, typename WAt>
   __device__ static __forceinline__ void make_operands(Operands& op, const f16* X, int ld, XRow x_row, const f16* Wp, WAt w_at,
-                                                       uint32_t w_lane, int s0) {
+                                                       uint32_t w_half, int s0) {
     const int wave = wave_id(), lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+    const uint32_t w_lane = (lg * 32 + (ln & 15)) * 16u + (ln >= 16 ? w_half : 0u);
 #pragma unroll
     for (int j = 0; j < PPW; ++j) {
       const int p = min(wave * PPW + j, PIECES - 1), t = p >> 1, half = p & 1;
@@ -101,7 +102,7 @@ struct DmaGemm {
   // not use LDS unless there is one tile only (it then needs a barrier first).  All threads must call it.
   template <typename Ops, typename Finish>
   __device__ static __forceinline__ void run(int id, int stride, int n, int ns, char* lds, Ops operands, Finish finish) {
-    const int wave = wave_id(), lane16 = (threadIdx.x & 63) * 16, wm = wave / WN, wn = wave % WN;
+    const int wave = wave_id(), lane = frag_lane(), wm = wave / WN, wn = wave % WN;
     Operands op;
     int rid = id;                                         // tile of the requests
     operands(op, rid);
@@ -118,49 +119,49 @@ struct DmaGemm {
       for (int j = 0; j < PPW; ++j) request(op, lds + st * STAGE_BYTES, j);
       advance();
     }
-    const char* xb = lds + wm * MW * 2048 + lane16;
-    const char* wb = lds + (RT + wn * NW) * 2048 + lane16;
-    u32x4 xf[2][MW], wf[2][NW];
+    // The operand with more tiles per wave goes through the registers in two halves (16 of each tile's 32 rows), the fragments of the other
+    // one stay for the whole stage and are refilled in place, each after its last product.
+    constexpr bool XH = MW >= NW;                         // the activations in halves
+    constexpr int NH = XH ? MW : NW, NK = XH ? 2 * NW : 2 * MW, NM = NH * NK;
+    const char* hb = lds + (XH ? wm * MW : RT + wn * NW) * 2048 + lane;
+    const char* kb = lds + (XH ? RT + wn * NW : wm * MW) * 2048 + lane;
+    u32x4 half[2][NH], keep[NK];
     wait_stage<PPW * (NST - 2)>();
 #pragma unroll
-    for (int b = 0; b < NW; ++b) wf[0][b] = *(const u32x4*)(wb + b * 2048);
+    for (int i = 0; i < NH; ++i) half[0][i] = *(const u32x4*)(hb + i * 2048);
 #pragma unroll
-    for (int a = 0; a < MW; ++a) xf[0][a] = *(const u32x4*)(xb + a * 2048);
-    // fragment reads go out in the first half of a step, one or two per MFMA, so that they have arrived when it ends
-    constexpr int NM = MW * NW, NR = MW + NW, RPM = (2 * NR + NM - 1) / NM;
+    for (int i = 0; i < NK; ++i) keep[i] = *(const u32x4*)(kb + i * 1024 - (i & 1) * (1024 - kWHalf));
     int slot = 0;
     for (; id < n; id += stride) {
-      f32x16 acc[MW][NW];
+      f32x4 acc[2 * MW][2 * NW];
 #pragma unroll
-      for (int a = 0; a < MW; ++a)
+      for (int a = 0; a < 2 * MW; ++a)
 #pragma unroll
-        for (int b = 0; b < NW; ++b)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+        for (int b = 0; b < 2 * NW; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int i = 0; i < ns; ++i) {
         const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          const char* xs = s == 0 ? xb + slot * STAGE_BYTES + 1024 : xb + next * STAGE_BYTES;
-          const char* ws = s == 0 ? wb + slot * STAGE_BYTES + 1024 : wb + next * STAGE_BYTES;
           if (s == 1) {
             wait_stage<PPW * (NST - 3)>();                // the next stage is complete, the previous one no longer read
             __builtin_amdgcn_sched_barrier(0);
           }
+          const char* hs = s == 0 ? hb + slot * STAGE_BYTES + kWHalf : hb + next * STAGE_BYTES;
+          const char* ks = kb + next * STAGE_BYTES;
 #pragma unroll
           for (int m = 0; m < NM; ++m) {
-            const int a = m / NW, b = m % NW;
-#pragma unroll
-            for (int r = m * RPM; r < (m + 1) * RPM && r < NR; ++r) {
-              if (r < NW) wf[1 - s][r] = *(const u32x4*)(ws + r * 2048);
-              else xf[1 - s][r - NW] = *(const u32x4*)(xs + (r - NW) * 2048);
-            }
+            const int k = m / NH, h = m % NH, a = XH ? 2 * h + s : k, b = XH ? k : 2 * h + s;
+            if (m < NH) half[1 - s][m] = *(const u32x4*)(hs + m * 2048);
             if (s == 1) {
 #pragma unroll
               for (int j = m * PPW / NM; j < (m + 1) * PPW / NM; ++j) request(op, lds + prev * STAGE_BYTES, j);
             }
-            acc[a][b] = mfma_f16(wf[s][b], xf[s][a], acc[a][b]);
+            acc[a][b] = XH ? mfma_f16(keep[k], half[s][h], acc[a][b]) : mfma_f16(half[s][h], keep[k], acc[a][b]);
             __builtin_amdgcn_sched_barrier(0);
+            if (s == 1 && h == NH - 1) {
+              keep[k] = *(const u32x4*)(ks + k * 1024 - (k & 1) * (1024 - kWHalf));
+              __builtin_amdgcn_sched_barrier(0);
+            }
           }
         }
         slot = next;
@@ -192,13 +193,13 @@ struct StreamGemm {
 
   struct Operands {
     const char *x, *w[NW];      // next stage to be requested
-    uint32_t x_lane[PX], x_step, w_lane;
+    uint32_t x_lane[PX], x_step, w_half;
     int left_x, left_w;
   };
   __device__ static __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
   template <typename XRow, typename WAt>
   __device__ static __forceinline__ void make_operands(Operands& op, const f16* X, int ld, XRow x_row, const f16* Wp, WAt w_at,
-                                                       uint32_t w_lane, int s0) {
+                                                       uint32_t w_half, int s0) {
     const int wave = wave_id(), lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
     op.x = (const char*)X + (size_t)s0 * 64 * ld;
     op.x_step = 32u * KS * ld;
@@ -209,17 +210,18 @@ struct StreamGemm {
     }
 #pragma unroll
     for (int b = 0; b < NW; ++b) op.w[b] = (const char*)Wp + w_at(wave * NW + b) + (size_t)s0 * 2048;
-    op.w_lane = w_lane;
+    op.w_half = w_half;
   }
   __device__ static __forceinline__ void request_x(Operands& op, char* slot, int j) {
     char* dst = slot + (PIECES % WAVES == 0 ? wave_id() * PX + j : min(wave_id() * PX + j, PIECES - 1)) * 1024;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(wt_buffer(op.x), (__attribute__((address_space(3))) void*)dst, 16, op.x_lane[j], 0, 0, 0);
     if (j == PX - 1) op.x += op.left_x-- > 1 ? op.x_step : 0u;
   }
+  // w[b][s]: rows 16 (s & 1) .. of tile b, 32 of K from 32 (s >> 1) on
   __device__ static __forceinline__ void load_w(Operands& op, u32x4 (&w)[NW][KS], int s) {
 #pragma unroll
     for (int b = 0; b < NW; ++b) {
-      w[b][s] = __builtin_amdgcn_raw_buffer_load_b128(wt_buffer(op.w[b]), (int)op.w_lane + s * 1024, 0, 0);
+      w[b][s] = __builtin_amdgcn_raw_buffer_load_b128(wt_buffer(op.w[b]), frag_lane() + (s >> 1) * 2048, s & 1 ? (int)op.w_half : 0, 0);
       if (s == KS - 1) op.w[b] += op.left_w > 1 ? 1024 * KS : 0;
     }
     if (s == KS - 1) --op.left_w;
@@ -229,10 +231,11 @@ struct StreamGemm {
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 #endif
   }
-  // One stage, its weights in w; the fragments of a step are requested for the stage RW further as soon as the step is issued.
-  __device__ static __forceinline__ void stage(f32x16 (&acc)[MW][NW], u32x4 (&w)[NW][KS], u32x4 (&xf)[2][MW], Operands& op, int& slot,
+  // One stage, its weights in w: KS steps of 32 of K and 16 rows of each weight tile.  The weights of a step are requested for the stage RW
+  // further as soon as the step is issued; the activations stay for two steps and are refilled in place, each after its last product.
+  __device__ static __forceinline__ void stage(f32x4 (&acc)[2 * MW][2 * NW], u32x4 (&w)[NW][KS], u32x4 (&xf)[2 * MW], Operands& op, int& slot,
                                                char* lds, const char* xb) {
-    constexpr int NM = MW * NW;
+    constexpr int NM = 2 * MW * NW;
     const int next = slot + 1 == NSX ? 0 : slot + 1, prev = slot == 0 ? NSX - 1 : slot - 1;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
@@ -244,13 +247,16 @@ struct StreamGemm {
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
         const int a = m / NW, b = m % NW;
-        if (b == 0) xf[(s + 1) & 1][a] = *(const u32x4*)(xs + a * KS * 1024);
         if (s == KS - 1) {
 #pragma unroll
           for (int j = m * PX / NM; j < (m + 1) * PX / NM; ++j) request_x(op, lds + prev * STAGE_BYTES, j);
         }
-        acc[a][b] = mfma_f16(w[b][s], xf[s & 1][a], acc[a][b]);
+        acc[a][2 * b + (s & 1)] = mfma_f16(w[b][s], xf[a], acc[a][2 * b + (s & 1)]);
         __builtin_amdgcn_sched_barrier(0);
+        if ((s & 1) && b == NW - 1) {
+          xf[a] = *(const u32x4*)(xs + (a >> 1) * KS * 1024 + (a & 1) * kWHalf);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       load_w(op, w, s);
       __builtin_amdgcn_sched_barrier(0);
@@ -264,7 +270,7 @@ struct StreamGemm {
     Operands op;
     operands(op, id);
     op.left_x = op.left_w = ns;
-    u32x4 w[RW][NW][KS], xf[2][MW];
+    u32x4 w[RW][NW][KS], xf[2 * MW];
     // in the order of the loop: the wait counts hold from the first stage on
 #pragma unroll
     for (int st = 0; st < RW; ++st) {
@@ -275,17 +281,15 @@ struct StreamGemm {
       for (int s = 0; s < KS; ++s) load_w(op, w[st], s);
       __builtin_amdgcn_sched_barrier(0);
     }
-    f32x16 acc[MW][NW];
+    f32x4 acc[2 * MW][2 * NW];
 #pragma unroll
-    for (int a = 0; a < MW; ++a)
+    for (int a = 0; a < 2 * MW; ++a)
 #pragma unroll
-      for (int b = 0; b < NW; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-    const char* xb = lds + (threadIdx.x & 63) * 16;
+      for (int b = 0; b < 2 * NW; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const char* xb = lds + frag_lane();
     wait_stage<RW * KS * NW + (RW - 1) * PX>();
 #pragma unroll
-    for (int a = 0; a < MW; ++a) xf[0][a] = *(const u32x4*)(xb + a * KS * 1024);
+    for (int a = 0; a < 2 * MW; ++a) xf[a] = *(const u32x4*)(xb + (a >> 1) * KS * 1024 + (a & 1) * kWHalf);
     int slot = 0, i = 0;
     for (; i + RW <= ns; i += RW) {
 #pragma unroll

@@ -28,9 +28,16 @@ constexpr int kWBlock = 32 * kBK;          // elements of one packed (row tile, 
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
-// (a function of its own: the host pass does not accept the builtin inside templates)
-__device__ __forceinline__ f32x16 mfma_f16(u32x4 a, u32x4 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0); }
+// The GEMM loops multiply 16 x 16 x 32: the same rate and the same operand bytes as 32 x 32 x 16, but half of the accumulator bytes per product.
+// Under a power limit that is speed: MFMA loops on random operands, every CU busy, 1.64 -> 1.95 PFLOP/s from registers, 1.48 -> 1.69 with fragments
+// read from LDS.
+// (A function of its own: the host pass does not accept the builtin inside templates.)
+__device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(as_f16x8(a), as_f16x8(b), c, 0, 0, 0); }
 
-// Accumulator element i of lane `lane` in a 32x32 MFMA tile: row, col inside the tile.
-__device__ __forceinline__ int acc_row(int lane, int i) { return 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3); }
-__device__ __forceinline__ int acc_col(int lane) { return lane & 31; }
+// A fragment of that product is 16 rows of a 32-row tile x two consecutive 1 KiB pieces: byte offset of this lane (row lane % 16, the
+// eight k of group lane / 16), and from the tile's first 16 rows to its last 16.
+__device__ __forceinline__ int frag_lane() { const int lane = threadIdx.x & 63; return (lane >> 5) * 1024 + ((lane >> 4) & 1) * 512 + (lane & 15) * 16; }
+constexpr int kWHalf = 256;
+// Accumulator acc[a][b][e] of C^T: activation row 16 a + acc_col, weight row 16 b + acc_row + e.
+__device__ __forceinline__ int acc_row(int lane) { return 4 * (lane >> 4); }
+__device__ __forceinline__ int acc_col(int lane) { return lane & 15; }

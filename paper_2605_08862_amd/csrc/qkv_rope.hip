@@ -29,33 +29,32 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
   constexpr bool PAIR = G::NW == 2;
   static_assert(G::CT == 4 && (PAIR ? G::WN == 2 : G::WN == 4), "a workgroup's columns are one head");
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
-  const int lane = threadIdx.x & 63, ln = lane & 31, lg = lane >> 5;
+  const int lane = threadIdx.x & 63;
   const size_t tile_bytes = (size_t)(g.K / kBK) * 4096;
   // position t = wn * NW + b of the LDS tiles holds tile wn + 2 b of the head (PAIR), or tile t
   auto operands = [&](typename G::Operands& op, int) {
     G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp,
-                     [&](int t) { return (size_t)(head * 4 + (PAIR ? (t >> 1) + 2 * (t & 1) : t)) * tile_bytes; }, lane * 16u, 0);
+                     [&](int t) { return (size_t)(head * 4 + (PAIR ? (t >> 1) + 2 * (t & 1) : t)) * tile_bytes; }, kWHalf, 0);
   };
-  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int) {
   const int M = min(p.n_rows[0], g.M_max);
-  // Accumulator register i of lane (ln, lg): row m0 + 32 (wm MW + a) + ln, column 32 tile + 8 (i / 4) + 4 lg + (i % 4) of the head.
+  // Accumulator acc[a][b][e]: row m0 + 16 (2 wm MW + a) + acc_col, column 16 b' + acc_row + e of the head, b' = b, or that of the tile.
   const bool is_v = head >= g.Hq + g.Hkv;
   float* s_x = (float*)lds;                             // [BM][kLdx]
   if constexpr (!PAIR) {
     if (!is_v) {
       __syncthreads();                                  // every wave is done reading the loop's LDS stages
 #pragma unroll
-      for (int a = 0; a < G::MW; ++a)
+      for (int a = 0; a < 2 * G::MW; ++a)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *(f32x4*)(s_x + ((wm * G::MW + a) * 32 + ln) * kLdx + 32 * wn + 8 * i4 + 4 * lg) =
-              f32x4{acc[a][0][4 * i4], acc[a][0][4 * i4 + 1], acc[a][0][4 * i4 + 2], acc[a][0][4 * i4 + 3]};
+        for (int b = 0; b < 2; ++b)
+          *(f32x4*)(s_x + ((wm * 2 * G::MW + a) * 16 + acc_col(lane)) * kLdx + 32 * wn + 16 * b + acc_row(lane)) = acc[a][b];
       __syncthreads();
     }
   }
 #pragma unroll
-  for (int a = 0; a < G::MW; ++a) {
-    const int m = m0 + (wm * G::MW + a) * 32 + ln;
+  for (int a = 0; a < 2 * G::MW; ++a) {
+    const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
     if (m >= M) continue;
     size_t pbase = 0;
     int tok = 0;
@@ -80,8 +79,8 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
       }
     };
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int d = 32 * wn + 8 * i4 + 4 * lg;
+    for (int b = 0; b < 2; ++b) {
+      const int d = 32 * wn + 16 * b + acc_row(lane);
       f32x4 c = f32x4{1.f, 1.f, 1.f, 1.f}, sn = f32x4{0.f, 0.f, 0.f, 0.f};
       if (!is_v) {
         c = *(const f32x4*)(g.cos_t + (size_t)m * 64 + (d & 63));
@@ -92,7 +91,7 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
         float y2[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x1 = acc[a][0][4 * i4 + e], x2 = acc[a][1][4 * i4 + e];
+          const float x1 = acc[a][b][e], x2 = acc[a][(2 + b) % (2 * G::NW)][e];
           y[e] = is_v ? x1 : x1 * c[e] - x2 * sn[e];
           y2[e] = is_v ? x2 : x2 * c[e] + x1 * sn[e];
         }
@@ -101,12 +100,12 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
       } else {
         if (is_v) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = acc[a][0][4 * i4 + e];
+          for (int e = 0; e < 4; ++e) y[e] = acc[a][b][e];
         } else {
-          const f32x4 other = *(const f32x4*)(s_x + ((wm * G::MW + a) * 32 + ln) * kLdx + (d ^ 64));
+          const f32x4 other = *(const f32x4*)(s_x + ((wm * 2 * G::MW + a) * 16 + acc_col(lane)) * kLdx + (d ^ 64));
           const float sign = d < 64 ? -1.0f : 1.0f;     // y1 = x1 c - x2 s (columns < 64), y2 = x2 c + x1 s
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = acc[a][0][4 * i4 + e] * c[e] + sign * other[e] * sn[e];
+          for (int e = 0; e < 4; ++e) y[e] = acc[a][b][e] * c[e] + sign * other[e] * sn[e];
         }
         store(d, y);
       }

@@ -54,19 +54,20 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
   const int t_last = (V + 31) / 32 - 1;
   auto operands = [&](typename G::Operands& op, int id) {
     const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT;
-    G::make_operands(op, X, ld, [&](int r) { return min(m0 + r, M - 1); }, W, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, lane * 16u, 0);
+    G::make_operands(op, X, ld, [&](int r) { return min(m0 + r, M - 1); }, W, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, kWHalf, 0);
   };
-  auto finish = [&](f32x16 (&acc)[G::MW][G::NW], int id) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int id) {
   const int m0 = id % m_blocks * G::BM + wave / G::WN * kLmMT * 32;      // first row of this wave
   const int vt = id / m_blocks * G::WN + wave % G::WN;           // statistics tile of this wave
   const int n_wave0 = vt * kLmVtile;
   if (n_wave0 >= V) return;
 
-  // accumulator: rows = vocabulary entries n_wave0 + ni*32 + acc_row, lane column = token
+  // accumulator: acc[a][b][e] = vocabulary entry n_wave0 + 16 b + acc_row + e of token m0 + 16 a + acc_col
+  const int n0 = n_wave0 + acc_row(lane);
   const bool store_vec = (V & 3) == 0 && ((uintptr_t)store & 15) == 0;   // V % 4 == 0: groups of four never straddle V
 #pragma unroll
-  for (int mi = 0; mi < kLmMT; ++mi) {
-    const int m = m0 + mi * 32 + acc_col(lane);
+  for (int a = 0; a < 2 * kLmMT; ++a) {
+    const int m = m0 + a * 16 + acc_col(lane);
     const bool valid = m < M;
     if (STATS) {
       const int tgt = valid ? row_target[m] : -1;
@@ -76,11 +77,11 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
       // no store inside this loop: the draft token's logit is picked up by a select (a conditional store at each of
       // the 32 positions cost 13 us of the 277 us launch)
 #pragma unroll
-      for (int ni = 0; ni < kLmNT; ++ni)
+      for (int b = 0; b < 2 * kLmNT; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int n = n_wave0 + ni * 32 + acc_row(lane, i);
-          const float z = acc[mi][ni][i];
+        for (int e = 0; e < 4; ++e) {
+          const int n = n0 + 16 * b + e;
+          const float z = acc[a][b][e];
           if (n < V) {
             if (z > mx) { mx = z; arg = n; }
             if (n == tgt) { zt = z; hit = true; }
@@ -89,38 +90,36 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
       if (hit) sb.z_target[m] = zt;                    // tgt >= 0 only for valid rows
       if (valid && store && !store_vec) {
 #pragma unroll
-        for (int ni = 0; ni < kLmNT; ++ni)
+        for (int b = 0; b < 2 * kLmNT; ++b)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int n = n_wave0 + ni * 32 + acc_row(lane, i);
-            if (n < V) store[(size_t)m * V + n] = acc[mi][ni][i];
+          for (int e = 0; e < 4; ++e) {
+            const int n = n0 + 16 * b + e;
+            if (n < V) store[(size_t)m * V + n] = acc[a][b][e];
           }
       }
       if (valid && store && store_vec) {
-        // registers 4 i4 .. 4 i4 + 3 of a lane are four consecutive vocabulary entries: 16-byte stores
+        // four consecutive vocabulary entries of a lane: 16-byte stores
 #pragma unroll
-        for (int ni = 0; ni < kLmNT; ++ni)
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            const int n = n_wave0 + ni * 32 + acc_row(lane, 4 * i4);
-            if (n + 3 < V)
-              *(f32x4*)(store + (size_t)m * V + n) =
-                  f32x4{acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2], acc[mi][ni][4 * i4 + 3]};
-          }
+        for (int b = 0; b < 2 * kLmNT; ++b) {
+          const int n = n0 + 16 * b;
+          if (n + 3 < V) *(f32x4*)(store + (size_t)m * V + n) = acc[a][b];
+        }
       }
-      const float mx_o = __shfl_xor(mx, 32);
-      const int arg_o = __shfl_xor(arg, 32);
-      if (mx_o > mx || (mx_o == mx && arg_o < arg)) { mx = mx_o; arg = arg_o; }
+#pragma unroll
+      for (int o = 16; o <= 32; o += 16) {
+        const float mx_o = __shfl_xor(mx, o);
+        const int arg_o = __shfl_xor(arg, o);
+        if (mx_o > mx || (mx_o == mx && arg_o < arg)) { mx = mx_o; arg = arg_o; }
+      }
       float sum = 0.f;
 #pragma unroll
-      for (int ni = 0; ni < kLmNT; ++ni)
+      for (int b = 0; b < 2 * kLmNT; ++b)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int n = n_wave0 + ni * 32 + acc_row(lane, i);
-          if (n < V) sum += __expf((acc[mi][ni][i] - mx) * inv_temp);
-        }
+        for (int e = 0; e < 4; ++e)
+          if (n0 + 16 * b + e < V) sum += __expf((acc[a][b][e] - mx) * inv_temp);
+      sum += __shfl_xor(sum, 16);
       sum += __shfl_xor(sum, 32);
-      if (valid && lane < 32) {
+      if (valid && lane < 16) {
         const size_t o = (size_t)vt * M_max + m;
         sb.part_max[o] = mx;
         sb.part_sum[o] = sum;
@@ -128,23 +127,19 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
       }
     } else {
       if (!valid) continue;
-      // registers 4 i4 .. 4 i4 + 3 of a lane are four consecutive vocabulary entries: 16-byte stores when the
-      // row pitch keeps them aligned
+      // four consecutive vocabulary entries of a lane: 16-byte stores when the row pitch keeps them aligned
       const bool vec = (V & 3) == 0;
 #pragma unroll
-      for (int ni = 0; ni < kLmNT; ++ni)
+      for (int b = 0; b < 2 * kLmNT; ++b) {
+        const int n = n0 + 16 * b;
+        if (vec && n + 3 < V) {
+          *(f32x4*)(store + (size_t)m * V + n) = acc[a][b];
+        } else {
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int n = n_wave0 + ni * 32 + acc_row(lane, 4 * i4);
-          if (vec && n + 3 < V) {
-            *(f32x4*)(store + (size_t)m * V + n) =
-                f32x4{acc[mi][ni][4 * i4], acc[mi][ni][4 * i4 + 1], acc[mi][ni][4 * i4 + 2], acc[mi][ni][4 * i4 + 3]};
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (n + e < V) store[(size_t)m * V + n + e] = acc[mi][ni][4 * i4 + e];
-          }
+          for (int e = 0; e < 4; ++e)
+            if (n + e < V) store[(size_t)m * V + n + e] = acc[a][b][e];
         }
+      }
     }
   }
   };
