@@ -106,6 +106,7 @@ void carve_plan(Carver& w, Plan& p, int B, int M, bool with_attention, int n_lay
   p.row_pos = w.take<int32_t>(M);
   p.row_tok = w.take<int32_t>(M);
   p.row_target = w.take<int32_t>(M);
+  p.row_kv = nullptr;
   if (!with_attention) {
     p.attn_meta = p.item_start = p.item_seq = p.item_chunk = p.attn_queue = nullptr;
     return;
@@ -166,6 +167,7 @@ size_t carve(bs_ctx* c, char* base, size_t bytes, bool fragments, size_t* full) 
   c->attn_scratch = w.take<char>(attention_scratch_bytes(s, B, c->k_max));
   c->n_vtiles = lmhead_vtiles(s.V);
   carve_sampler(w, c->sb, B, M, c->n_vtiles);
+  c->plan.row_kv = c->sb.row_arg;
   if (s.dtype == BS_F32) {
     c->full_logits = w.take<float>((size_t)M * s.V);
   } else {
@@ -429,8 +431,8 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
               s.L, st);
   const bool skinny = c->fragments && skinny_applies(s, M_max) && !c->unfused_qkv;
   const SlabRules rules = skinny ? SlabRules{} : gemm_slab_rules(s, M_max);
-  if (skinny) launch_skinny_embed(s, p, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
-  else launch_embed(s, p, M_max, rules, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  if (skinny) launch_skinny_embed(s, p, c->kv, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
+  else launch_embed(s, p, c->kv, M_max, rules, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool fused_qkv = qkv_rope_applies(s, M_max) && !c->unfused_qkv;
   const bool slab_mode = s.dtype == BS_BF16;   // float32 epilogues go through K-split slabs (see gemm.hip)
   SlabCount pending{0, 0};                      // slabs of the last residual projection not yet added to h
@@ -438,7 +440,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
     { ProfScope ps(c, BS_PROF_EMPTY, st); }
     if (skinny) {
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-        launch_skinny_qkv(s, p, c->kv, M_max, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
+        launch_skinny_qkv(s, p, M_max, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
                           c->q, c->k_pages[l], c->v_pages[l], c->sk, st); }
       launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, kSkinnyRows,
                        c->attn_scratch, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
@@ -453,12 +455,12 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->attn_norm[l], c->a, st);
     if (fused_qkv) {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-      launch_qkv_rope(s, p, c->kv, M_max, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
+      launch_qkv_rope(s, p, M_max, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
     } else {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
       const SlabCount nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
                                        slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.r[SLAB_QKV]);
-      launch_rope_append(s, p, c->kv, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
+      launch_rope_append(s, p, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
     launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, M_max, c->attn_scratch,

@@ -154,6 +154,8 @@ struct Plan {
   int32_t* row_pos;     // [M_max] i in 0..k_b
   int32_t* row_tok;     // [M_max] input token of row r
   int32_t* row_target;  // [M_max] draft token judged by row r (-1: none)
+  int32_t* row_kv;      // [M_max] cache place of row r: page * kPage + token in the page (embedding kernel; on top of SamplerBufs::row_arg, which is
+                        // written after the layers)
   // attention work list (bf16 models): every sequence's token range is cut into chunks of chunk_tiles 32-token
   // tiles; the item at list position i is (sequence item_seq[i], chunk item_chunk[i]) and the list is ordered by
   // decreasing size (full chunks, then the shorter last chunks).  Sequence b has item_start[b+1] - item_start[b]
@@ -224,6 +226,18 @@ inline void attn_plan_constants(AttnPlan& a, int tiles_wg, int q_blocks, int Hkv
   }
 }
 
+struct KvView {
+  int n_pages, n_slots, max_pages;
+  const int32_t* block_table;
+  int32_t* ctx_len;
+};
+
+// Cache place of a row, looked up once per step (block of a sequence -> slot -> page: three dependent loads that every append of every layer waited for).
+__device__ __forceinline__ void row_place(const Plan& p, const KvView& kv, int r) {
+  const int b = p.row_seq[r], pos = p.seq_c[b] + p.row_pos[r];
+  p.row_kv[r] = kv.block_table[(size_t)p.seq_slot[b] * kv.max_pages + pos / kPage] * kPage + pos % kPage;
+}
+
 // cos / sin of the rotary angle of packed row r (absolute position c_b + i) and pair j.  The angle is formed in
 // float64 (at positions of 3e4 a float32 angle is already off by ~2e-3 rad), reduced to [-pi, pi] in float64 and
 // only then handed to the float32 sine / cosine.
@@ -239,12 +253,6 @@ __device__ __forceinline__ void rope_angle(const Plan& p, int r, int j, int half
   cos_t[(size_t)r * half + j] = cs;
   sin_t[(size_t)r * half + j] = sn;
 }
-
-struct KvView {
-  int n_pages, n_slots, max_pages;
-  const int32_t* block_table;
-  int32_t* ctx_len;
-};
 
 struct Shape {
   int L, d, Hq, Hkv, D, F, V, dtype;
@@ -263,10 +271,10 @@ void launch_commit(const Plan& p, const KvView& kv, int B, const int32_t* seq_sl
 void launch_clear_status(int32_t* status, hipStream_t st);
 void launch_kv_lengths(const KvView& kv, int B, const int32_t* seq_slot, int32_t* out, int32_t* status, hipStream_t st);
 // elementwise.hip
-// also fills the step's rotary tables cos_t / sin_t [M_max][D/2] (shared by all layers)
+// also fills the step's rotary tables cos_t / sin_t [M_max][D/2] (shared by all layers) and the rows' cache places
 // rules: those of the step's GEMMs (gemm_slab_rules); their choices are left behind the row count.
 struct SlabRules;
-void launch_embed(const Shape& s, const Plan& p, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
+void launch_embed(const Shape& s, const Plan& p, const KvView& kv, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st);
 // h[r] += sum of n_slabs slabs [M_max, d] (n_slabs may be 0), then out[r] = RMSNorm(h[r]).
 struct SlabCount;
@@ -277,14 +285,14 @@ void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const fl
 // inv_freq: [D/2] float64 table written by launch_rope_table.
 void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st);
 // cos_t / sin_t: [M_max][D/2] tables of the step's packed rows (filled by launch_embed, once per step).
-void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
+void launch_rope_append(const Shape& s, const Plan& p, int M_max, const float* cos_t, const float* sin_t,
                         const float* qkv, const SlabCount& slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,
                     void* k_rows, void* v_rows, bool to_pages, int32_t* status, hipStream_t st);
 // qkv_rope.hip   QKV projection + rotary + KV append in one kernel (bf16 models with head size 128); A = normed
 // rows (float16), Wp = packed wqkv.
 bool qkv_rope_applies(const Shape& s, int M_max);
-void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
+void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
 // Float16 activations of bf16 models (normalised rows, attention output, gated activation, final rows), "chunk order": the eight
 // elements k .. k + 7 (k % 8 == 0) of a row are one 16-byte chunk, and the chunks of one k of all rows are neighbours, ld chunks
@@ -388,11 +396,11 @@ __host__ __device__ __forceinline__ size_t h_frag_index(int row, int k, int nk) 
 struct SkinnyBufs { float* part; int32_t* counters; };   // partial tiles of K splits; arrival counters (zero between launches)
 bool skinny_applies(const Shape& s, int M_max);
 // ssq: [parts][32] sums of squares of the residual's rows over column ranges (embed: 1 part, residual projections: d / 32)
-void launch_skinny_embed(const Shape& s, const Plan& p, const void* embed, float* h, float* ssq, const double* inv_freq,
+void launch_skinny_embed(const Shape& s, const Plan& p, const KvView& kv, const void* embed, float* h, float* ssq, const double* inv_freq,
                          float* cos_t, float* sin_t, hipStream_t st);
 void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, const float* gain,
                               void* out, hipStream_t st);
-void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* h, const float* ssq, int ssq_parts,
+void launch_skinny_qkv(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts,
                        const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages,
                        void* v_pages, const SkinnyBufs& sk, hipStream_t st);
 void launch_skinny_gate_up(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,

@@ -8,7 +8,7 @@
 // Token embedding of every packed row and, in the same launch, the row's rotary cos / sin table entries (the table
 // [M_max][D/2] is shared by all layers of the step).
 template <typename T>
-__global__ void __launch_bounds__(256) embed_kernel(Plan p, int M_max, SlabRules rules, int d, const T* __restrict__ embed, float* __restrict__ h,
+__global__ void __launch_bounds__(256) embed_kernel(Plan p, KvView kv, int M_max, SlabRules rules, int d, const T* __restrict__ embed, float* __restrict__ h,
                                                     int D, const double* __restrict__ inv_freq,
                                                     float* __restrict__ cos_t, float* __restrict__ sin_t) {
   int r = blockIdx.x;
@@ -22,6 +22,7 @@ __global__ void __launch_bounds__(256) embed_kernel(Plan p, int M_max, SlabRules
   const T* src = embed + (size_t)p.row_tok[r] * d;
   float* dst = h + (size_t)r * d;
   for (int i = threadIdx.x; i < d; i += blockDim.x) dst[i] = to_f32<T>(src[i]);
+  if (threadIdx.x == 255) row_place(p, kv, r);
   if ((int)threadIdx.x < D / 2) rope_angle(p, r, threadIdx.x, D / 2, inv_freq, cos_t, sin_t);
 }
 
@@ -218,7 +219,7 @@ __global__ void rope_table_kernel(int D, float theta, double* __restrict__ inv_f
 // elements; a thread has one, a row several workgroups.  Latency bound: the loads of four slabs go out together, before the row is
 // known to be live or its page is known (64 .. 136 rows of the 7B shape, 5 .. 7 slabs one after the other and three items a thread: 8.4 .. 11.8 us).
 template <typename T, typename TQ, typename TP>
-__global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int Hq, int Hkv, int D,
+__global__ void __launch_bounds__(256) rope_append_kernel(Plan p, int Hq, int Hkv, int D,
                                                           const float* __restrict__ cos_t, const float* __restrict__ sin_t,
                                                           const float* __restrict__ qkv, SlabCount rule, size_t slab_stride,
                                                           TQ* __restrict__ q_out, TP* __restrict__ k_pages,
@@ -236,6 +237,7 @@ __global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int
   const int e0 = rot ? 0 : (idx - n_rot) * 4;            // four consecutive v elements of one head
   const float* x = qkv + (size_t)r * (Hq + 2 * Hkv) * D + (rot ? hh * D + j : (Hq + Hkv) * D + e0);
   const int x2_at = rot ? half : 0;
+  const int place = p.row_kv[r];                         // (of a row beyond the count: never used)
   f4 x1 = f4{0.f, 0.f, 0.f, 0.f}, x2 = x1, c = x1, sn = x1;
   if (rot) { c = *(const f4*)(cos_t + (size_t)r * half + j); sn = *(const f4*)(sin_t + (size_t)r * half + j); }
   for (int s0 = 0; s0 < n_slabs; s0 += 4) {              // added in index order; an index past the end is clamped and its value dropped
@@ -271,11 +273,8 @@ __global__ void __launch_bounds__(256) rope_append_kernel(Plan p, KvView kv, int
     }
     return;
   }
-  const int b = p.row_seq[r];
-  const int pos = p.seq_c[b] + p.row_pos[r];
-  const int page = kv.block_table[(size_t)p.seq_slot[b] * kv.max_pages + pos / kPage];
-  const int tok = pos % kPage;
-  const size_t pbase = (size_t)page * kv_page_elems(Hkv, D);
+  const int tok = place & (kPage - 1);
+  const size_t pbase = (size_t)(place / kPage) * kv_page_elems(Hkv, D);
   // rounded to the cache dtype T, stored in the page encoding TP
   auto rt = [](float v) { return to_f32<T>(from_f32<T>(v)); };
   if (rot) {
@@ -400,13 +399,13 @@ __global__ void __launch_bounds__(256) kv_copy_f16_kernel(KvView kv, int Hkv, in
   if (out_of_range) atomicOr(status, BS_FAULT_RANGE);
 }
 
-void launch_embed(const Shape& s, const Plan& p, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
+void launch_embed(const Shape& s, const Plan& p, const KvView& kv, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st) {
   const int grid = M_max + (rules.r[0].at ? 3 : 0);
   if (s.dtype == BS_F32)
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(grid), dim3(256), 0, st, p, M_max, rules, s.d, (const float*)embed, h, s.D, inv_freq, cos_t, sin_t);
+    hipLaunchKernelGGL(embed_kernel<float>, dim3(grid), dim3(256), 0, st, p, kv, M_max, rules, s.d, (const float*)embed, h, s.D, inv_freq, cos_t, sin_t);
   else
-    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(grid), dim3(256), 0, st, p, M_max, rules, s.d, (const bf16*)embed, h, s.D, inv_freq, cos_t, sin_t);
+    hipLaunchKernelGGL(embed_kernel<bf16>, dim3(grid), dim3(256), 0, st, p, kv, M_max, rules, s.d, (const bf16*)embed, h, s.D, inv_freq, cos_t, sin_t);
 }
 void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const float* slabs, const SlabCount& n_slabs,
                     const float* gain, void* out, hipStream_t st) {
@@ -426,15 +425,15 @@ void launch_rmsnorm(const Shape& s, const Plan& p, int M_max, float* h, const fl
 void launch_rope_table(const Shape& s, double* inv_freq, hipStream_t st) {
   hipLaunchKernelGGL(rope_table_kernel, dim3(1), dim3(64), 0, st, s.D, s.theta, inv_freq);
 }
-void launch_rope_append(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* cos_t, const float* sin_t,
+void launch_rope_append(const Shape& s, const Plan& p, int M_max, const float* cos_t, const float* sin_t,
                         const float* qkv, const SlabCount& n_slabs, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const size_t stride = (size_t)M_max * s.Nqkv();
   const int y = ((s.Hq + s.Hkv) * s.D / 8 + s.Hkv * s.D / 4 + 255) / 256;
   if (s.dtype == BS_F32)
-    hipLaunchKernelGGL((rope_append_kernel<float, float, float>), dim3(M_max, y), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
+    hipLaunchKernelGGL((rope_append_kernel<float, float, float>), dim3(M_max, y), dim3(256), 0, st, p, s.Hq, s.Hkv, s.D, cos_t, sin_t,
                        qkv, n_slabs, stride, (float*)q_out, (float*)k_pages, (float*)v_pages);
   else
-    hipLaunchKernelGGL((rope_append_kernel<bf16, f16, f16>), dim3(M_max, y), dim3(256), 0, st, p, kv, s.Hq, s.Hkv, s.D, cos_t, sin_t,
+    hipLaunchKernelGGL((rope_append_kernel<bf16, f16, f16>), dim3(M_max, y), dim3(256), 0, st, p, s.Hq, s.Hkv, s.D, cos_t, sin_t,
                        qkv, n_slabs, stride, (f16*)q_out, (f16*)k_pages, (f16*)v_pages);
 }
 void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n, void* k_pages, void* v_pages,

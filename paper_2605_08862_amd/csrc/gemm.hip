@@ -134,22 +134,22 @@ struct GluArgs {
   f16* out;
   int32_t* status;
 };
-// Tiles id, id + stride, .. of m_blocks x n_blocks, M block fastest, BM rows apart.
+// Tile id of the launch, M block fastest, BM rows apart.
 template <typename G, int BM = G::BM>
-__device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_blocks, int id0, int stride, int n, char* lds) {
+__device__ __forceinline__ void glu_tile(const GluArgs& g, int m_blocks, int id, char* lds) {
   constexpr bool MIX = G::NW == 1;
   const int lane = threadIdx.x & 63;
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
   const size_t tile_bytes = (size_t)(g.K / kBK) * 4096, half = (size_t)(g.F / 32) * tile_bytes;    // up rows behind the gate rows
   const int t_last = g.F / 32 - 1;
-  auto operands = [&](typename G::Operands& op, int id) {
-    const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT;
+  const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT;
+  auto operands = [&](typename G::Operands& op) {
     // position t: features 16 (t0 + t) .. (mixed), or the gate (t even) / up (t odd) rows of features 32 ((t0 + t) / 2) ..
     auto w_at = [&](int t) -> size_t { return min((t0 + t) >> 1, t_last) * tile_bytes + (((t0 + t) & 1) ? (MIX ? 256 : half) : 0); };
     G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp, w_at, MIX ? (uint32_t)half : kWHalf, 0);
   };
-  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int id) {
-    const int m0 = id % m_blocks * BM, t0 = id / m_blocks * G::CT, M = min(*g.n_rows_dev, g.M_max);
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW]) {
+    const int M = min(*g.n_rows_dev, g.M_max);
 #pragma unroll
     for (int a = 0; a < 2 * G::MW; ++a) {
       const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
@@ -166,18 +166,18 @@ __device__ __forceinline__ void glu_tiles(const GluArgs& g, int m_blocks, int n_
       }
     }
   };
-  G::run(id0, stride, n, g.K / 32, lds, operands, finish);
+  G::run(g.K / 32, lds, operands, finish);
 }
-// One tile per workgroup.  A launch with a CU for every workgroup does not wait for the row count before its first loads (rows beyond
+// A launch with a CU for every workgroup (ONE_ROUND) does not wait for the row count before its first loads (rows beyond
 // it are stale rows of the same buffer, each affecting only its own output row).  Where workgroups share a CU, or wait for one, the
 // row blocks beyond the count are left out (1.5B shape, 80 of 720 rows, 420 workgroups, two to a CU: 40.7 us, 25.0 without them).
 constexpr int kFewRows = 320;
-template <typename G>
+template <typename G, bool ONE_ROUND>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_kernel(GluArgs g, int m_blocks, int n_blocks) {
   extern __shared__ __align__(16) char lds[];
-  if (m_blocks * n_blocks > kCUs) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
+  if (!ONE_ROUND) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
   const int id = xcd_flat(m_blocks * n_blocks);
-  if (id >= 0) glu_tiles<G>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
+  if (id >= 0) glu_tile<G>(g, m_blocks, id, lds);
 }
 // The same with a last row block of at most 64 live rows as one of 64 (1.5B shape, 390 of 702 rows: 43 us with the blocks beyond the count and a
 // whole last one, 40.6 here).
@@ -188,24 +188,9 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_t
   const int M = min(*g.n_rows_dev, g.M_max), m_blocks = (M + G::BM - 1) / G::BM;
   const int id = xcd_flat(m_blocks * n_blocks);
   if (id < 0) return;
-  if (M - id % m_blocks * G::BM <= GT::BM) glu_tiles<GT, G::BM>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
-  else glu_tiles<G>(g, m_blocks, n_blocks, id, 1, id + 1, lds);
+  if (M - id % m_blocks * G::BM <= GT::BM) glu_tile<GT, G::BM>(g, m_blocks, id, lds);
+  else glu_tile<G>(g, m_blocks, id, lds);
 }
-// More rows: 192 or 256 rows x 128 features per tile, persistent workgroups, one per CU (rows_by_rounds).
-typedef DmaGemm<2, 2, 2, 4, 6> GemmRows128;
-typedef DmaGemm<3, 2, 2, 4, 5> GemmRows192;
-typedef DmaGemm<4, 2, 2, 4, 4> GemmRows256;
-__global__ void __launch_bounds__(512) glu_rows_kernel(GluArgs g, int n_blocks) {
-  extern __shared__ __align__(16) char lds[];
-  const int M = min(*g.n_rows_dev, g.M_max), bm = rows_by_rounds(M, n_blocks), m_blocks = (M + bm - 1) / bm;
-  int stride, end;
-  const int id = xcd_first(m_blocks * n_blocks, stride, end);
-  if (id >= end) return;
-  if (bm == 128) glu_tiles<GemmRows128>(g, m_blocks, n_blocks, id, stride, end, lds);
-  else if (bm == 256) glu_tiles<GemmRows256>(g, m_blocks, n_blocks, id, stride, end, lds);
-  else glu_tiles<GemmRows192>(g, m_blocks, n_blocks, id, stride, end, lds);
-}
-
 // ---- float32 results (O and down projections, unfused QKV projection): one partial [M_max, N] slab per K split,
 // out[split][m][n]; the consumer (RMSNorm, rotary kernel) sums the slabs.  Float atomics into the residual were measured at
 // ~25 us per launch and are not used.
@@ -217,10 +202,10 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
   const size_t tile_bytes = (size_t)(K / kBK) * 4096;
   const int t0 = nb * G::CT, t_last = N / 32 - 1;
   const int nk = K / kBK, s0 = 2 * (nk * split / n_split), s1 = 2 * (nk * (split + 1) / n_split);
-  auto operands = [&](typename G::Operands& op, int) {
+  auto operands = [&](typename G::Operands& op) {
     G::make_operands(op, A, M_max, [&](int r) { return min(m0 + r, M_max - 1); }, Wp, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, kWHalf, s0);
   };
-  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW]) {
     const int M = min(*n_rows_dev, M_max);
     float* dst = out + (size_t)split * M_max * N;
 #pragma unroll
@@ -235,7 +220,7 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
       }
     }
   };
-  G::run(0, 1, 1, s1 - s0, lds, operands, finish);
+  G::run(s1 - s0, lds, operands, finish);
 }
 // Tile and number of splits fixed by the launch (see glu_kernel).
 template <typename G>
@@ -272,22 +257,18 @@ static int grid8(int n) { return (n + 7) / 8 * 8; }
 template <typename G>
 static void launch_glu_t(const GluArgs& g, hipStream_t st) {
   const int m_blocks = (g.M_max + G::BM - 1) / G::BM, n_blocks = (g.F / 16 + G::CT - 1) / G::CT;
-  static bool done = false;
-  allow_lds(glu_kernel<G>, G::LDS_BYTES, done);
-  hipLaunchKernelGGL(glu_kernel<G>, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
-}
-static void launch_glu_rows(const GluArgs& g, int n128, hipStream_t st) {
-  constexpr int lds = GemmRows128::LDS_BYTES;
-  static_assert(GemmRows192::LDS_BYTES <= lds && GemmRows256::LDS_BYTES <= lds, "");
-  static bool done = false;
-  allow_lds(glu_rows_kernel, lds, done);
-  const int tiles = (g.M_max + 127) / 128 * n128;
-  hipLaunchKernelGGL(glu_rows_kernel, dim3(tiles < kCUs ? grid8(tiles) : kCUs), dim3(512), lds, st, g, n128);
+  auto go = [&](auto kern, bool& done) {
+    allow_lds(kern, G::LDS_BYTES, done);
+    hipLaunchKernelGGL(kern, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
+  };
+  static bool one = false, more = false;
+  if (m_blocks * n_blocks <= kCUs) go(glu_kernel<G, true>, one);
+  else go(glu_kernel<G, false>, more);
 }
 // Measured in us (gate/up of the 1.5B shape, 8960 features, and of the 7B shape, 18944; the loops with weights in registers and
 // activations staged through registers that were here before in brackets; 7B at 64, 288 and 1185 rows and 1.5B from 432 rows in whole steps):
 //   64 rows 13.3 (22.3) / 48.7 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 80.1 (104)
-//   432 rows 28.9 (44.7)    576 rows 35.6 (41.4)    1037 rows 61.0 (73.0)    1185 rows - / 275 (324)    3480 rows 169.5 (190.9)
+//   432 rows 28.9 (44.7)    576 rows 33.9 (41.4)    1037 rows 58.4 (73.0)    1152 rows - / 254 (324)    3480 rows 157.6 (190.9)
 static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const void* A, const void* W, void* out, int32_t* status, hipStream_t st) {
   const GluArgs g{n_rows_dev, M_max, F, K, (const f16*)A, (const f16*)W, (f16*)out, status};
   const int rt = (M_max + 31) / 32, n128 = (F + 127) / 128;
@@ -309,35 +290,38 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     return;
   }
   if (M_max <= kFewRows && wide && mix) {
-    // the same for two or three groups of waves side by side in the rows: 288 rows, launches by themselves, 87 us, 95 with 96-row tiles of 128 features
-    if (rt == 6) launch_glu_t<DmaGemm<3, 1, 2, 5, 7>>(g, st);
-    else if (rt <= 8) launch_glu_t<DmaGemm<4, 1, 2, 5, 6>>(g, st);
+    // the same, for more than seven row tiles with two or three groups of waves side by side in the rows and both operands copied to LDS (192 / 224 rows by
+    // themselves 68 / 74 us, 60.5 / 67 here; 288 rows 87, 95 with 96-row tiles of 128 features)
+    if (rt == 6) launch_glu_t<StreamGemm<6, 1, 5, 4, 2>>(g, st);
+    else if (rt == 7) launch_glu_t<StreamGemm<7, 1, 5, 4, 2>>(g, st);
+    else if (rt == 8) launch_glu_t<DmaGemm<4, 1, 2, 5, 6>>(g, st);
     else if (rt == 9) launch_glu_t<DmaGemm<3, 1, 3, 5, 5>>(g, st);
     else launch_glu_t<DmaGemm<5, 1, 2, 5, 5>>(g, st);
     return;
   }
   if (M_max <= 640) {
-    // 128 features per workgroup; rows by time of a K tile (0.01 us) x rounds of the CUs
-    auto cost = [&](int bm, int t) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * t; };
-    const int c96 = cost(96, 83), c128 = cost(128, 92), c160 = cost(160, 113), c192 = cost(192, 128);
-    if (c192 < c96 && c192 < c128 && c192 < c160) {
-      // more than one round of the CUs: the tile from the step's row count (7B shape, 504 rows, 280 of them live: 140 us with 192 rows, 112 with 128)
-      if ((M_max + 191) / 192 * n128 > kCUs) launch_glu_rows(g, n128, st);
-      else launch_glu_t<GemmRows192>(g, st);
-    } else if (c160 < c96 && c160 < c128) launch_glu_t<StreamGemm<5, 2, 4, 2>>(g, st);
-    else if (c128 < c96) launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st);
-    else launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
+    // 128 features per workgroup; rows by rounds of the CUs x (K tiles x time of one + fill and epilogue), 0.01 us.  96 and 128 rows are four waves, two
+    // workgroups per CU, from 160 rows on eight waves of one weight tile: two waves per SIMD either way (160 rows in four waves, one per SIMD,
+    // 32.2 us where eight take 27.6).  Measured with weights that no cache holds, 96 / 128 / 160 / 192 / 224 rows per workgroup: 7B shape 400 rows 124 / 129 / 112
+    // / 138 / 146 us, 512 rows 153 / 139 / 162 / 132 / 159; 1.5B shape 384 rows 37 / 26.1 / 27 / 32 / 35, 432 rows 37.6 / 38.4 / 27.6 / 32.4 / 35.5,
+    // 576 rows 38.1 / 41.3 / 47 / 33.1 / 37.0, 640 rows 39.3 / 44.2 / 48.9 / 56.8 / 37.9.
+    auto cost = [&](int bm, int t, int fixed) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * (K / kBK * t + fixed); };
+    const int c[5] = {cost(96, 72, 180), cost(128, 80, 167), cost(160, 91, 730), cost(192, 103, 825), cost(224, 128, 680)};
+    int best = 0;
+    for (int i = 1; i < (mix ? 5 : 2); ++i) if (c[i] < c[best]) best = i;
+    if (best == 0) launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
+    else if (best == 1) launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st);
+    else if (best == 2) launch_glu_t<StreamGemm<5, 1, 8, 3>>(g, st);
+    else if (best == 3) launch_glu_t<StreamGemm<6, 1, 8, 3>>(g, st);
+    else launch_glu_t<StreamGemm<7, 1, 8, 2>>(g, st);
     return;
   }
-  // Many rounds of the CUs.  256-row tiles, persistent, for a long K (7B shape, 1185 rows, in one run: 283 us, 290 with 128-row tiles), 128-row
-  // tiles, two workgroups per CU, for a short one, where filling and storing a tile is a larger part (1.5B shape, 1037 rows: 63 us
-  // against 67; 3480 rows: 169.5 against 171).
-  if (K / kBK < 32) {
-    typedef StreamGemm<4, 2, 4, 2> G;
-    hipLaunchKernelGGL((glu_tail_kernel<G, StreamGemm<2, 2, 4, 2>>), dim3(grid8((M_max + G::BM - 1) / G::BM * n128)), dim3(G::THREADS), G::LDS_BYTES, st, g, n128);
-    return;
-  }
-  launch_glu_rows(g, n128, st);
+  // Many rounds of the CUs: 128-row tiles, two workgroups per CU, so that one's fill and epilogue run beside the other's products and the last round
+  // is a fine one.  Against persistent tiles of up to 256 rows, a workgroup per CU: 7B shape, 832 rows 210 / 215 us, 1024 rows 222 / 269, 1152 rows
+  // 264 / 269, 1408 rows 312 / 349, 2176 rows 460 / 503; 1.5B shape, 1037 rows 59 / 65, 2000 rows 98 / 123, 3900 rows 177 / 199 (1.28 PFLOP/s and
+  // the same clock x busy share where both have no rest; 720 rows of the 1.5B shape 43.3 / 40.5).
+  typedef StreamGemm<4, 2, 4, 2> G;
+  hipLaunchKernelGGL((glu_tail_kernel<G, StreamGemm<2, 2, 4, 2>>), dim3(grid8((M_max + G::BM - 1) / G::BM * n128)), dim3(G::THREADS), G::LDS_BYTES, st, g, n128);
 }
 
 template <typename G>
@@ -360,11 +344,11 @@ static void launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, 
   hipLaunchKernelGGL((slab_alt_kernel<G, GA>), dim3(grid8(tiles > rule.cap ? tiles : rule.cap)), dim3(256), lds, st, n_rows_dev, M_max, N, K, (const f16*)A,
                      (const f16*)W, (float*)out, nb, nba, rule.at);
 }
-// Tile and split of a float32-result GEMM: the cheapest of the tiles below by gemm_split_cost, whose times of a K tile are those of
-// launches that fill the CUs once (a tile of 32 MW rows x 128 NW columns).  Measured in us, down projection of the 1.5B and the 7B
-// shape (before, with the loops that staged activations through registers):
-//   64 rows 10.0 (19.2) / 26.7 (38.8)    144 rows 12.8 (20.5) / 35.1 (44.1)    288 rows 16.7 (21.5) / 47.9 (66.3; 57 in whole steps)
-//   576 rows 24.0 (24.6) / 82 (130)    1100 rows 36.0 (48.5) / 147 (159)
+// Tile and split of a float32-result GEMM of at most 640 rows: the cheapest of the tiles below by rounds of the CUs x (K tiles per split x time of
+// one + 3.9 us) + slabs.  The times (and what a slab weighs) are those under which the choices lose least against the fastest of all tiles and
+// splits, measured with weights that no cache holds at 40 .. 640 rows of 1536 x 1536, 2048 x 1536, 1536 x 8960, 3584 x 3584, 4608 x 3584 and 3584 x
+// 18944 (columns x K): 0.8 % on average, 4.7 % with the times of launches by themselves that were here before (7B shape, down projection, 400 rows
+// 66.7 us and six slabs, now 60.4 and three; O projection, 64 rows 8.9 and seven, now 8.1 and four).
 typedef StreamGemm<2, 1, 2, 4> T64x64;
 typedef StreamGemm<2, 1, 4, 4> T64x128;
 typedef StreamGemm<3, 1, 4, 3> T96x128;
@@ -372,22 +356,21 @@ typedef StreamGemm<4, 1, 4, 3> T128x128;
 typedef StreamGemm<5, 1, 4, 3> T160x128;
 typedef StreamGemm<3, 2, 4, 2> T96x256;
 typedef StreamGemm<4, 2, 4, 2> T128x256;
-typedef StreamGemm<5, 2, 4, 2> T160x256;
 struct SlabPick { int tile, split, cost; };
 static SlabPick pick_slab(int M_max, int N, int nk) {
-  static const struct { int bm, bn, t; } cfg[] = {{64, 64, 30}, {64, 128, 35}, {96, 128, 46}, {128, 128, 51}, {160, 128, 68}, {96, 256, 83}, {128, 256, 92}, {160, 256, 113}};
+  static const struct { int bm, bn, t; } cfg[] = {{64, 64, 26}, {64, 128, 43}, {96, 128, 47}, {128, 128, 57}, {160, 128, 67}, {96, 256, 74}, {128, 256, 82}};
   SlabPick best{0, 1, 0x7fffffff};
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 7; ++i) {
     const int tiles = (M_max + cfg[i].bm - 1) / cfg[i].bm * ((N + cfg[i].bn - 1) / cfg[i].bn);
     for (int s = 1; s <= kMaxGemmSplit && (s == 1 || 4 * s <= nk); ++s) {
-      const int c = gemm_split_cost(tiles, nk, 2 * kCUs, s, cfg[i].t, gemm_slab_cost(M_max, N));
+      const int c = (tiles * s + kCUs - 1) / kCUs * ((nk + s - 1) / s * cfg[i].t + 390) + (s - 1) * gemm_slab_cost(M_max, N) * 13 / 10;
       if (c < best.cost) best = SlabPick{i, s, c};
     }
   }
   return best;
 }
 int gemm_slab_time(int M_max, int N, int K) { return pick_slab(M_max, N, K / kBK).cost; }
-enum SlabTile { T_96x256_128x128 = 8, T_96x256_160x128, T_96x256_128x256, T_96x128_128x128, T_96x128_160x128 };   // up to 7: place in pick_slab's list
+enum SlabTile { T_96x256_128x128 = 7, T_96x256_160x128, T_96x256_128x256, T_96x128_128x128, T_96x128_160x128 };   // up to 6: place in pick_slab's list
 static SlabRule slab_rule(int M_max, int N, int nk, int at) {
   if (M_max <= 640) {
     const SlabPick pick = pick_slab(M_max, N, nk);
@@ -436,7 +419,6 @@ static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K
     case 4: BS_SLAB(T160x128); break;
     case 5: BS_SLAB(T96x256); break;
     case 6: BS_SLAB(T128x256); break;
-    case 7: BS_SLAB(T160x256); break;
     case T_96x256_128x128: BS_SLAB_ALT(T96x256, T128x128); break;
     case T_96x256_160x128: BS_SLAB_ALT(T96x256, T160x128); break;
     case T_96x256_128x256: BS_SLAB_ALT(T96x256, T128x256); break;

@@ -11,10 +11,10 @@
 //     stage, between its two steps: the second step already reads the next stage's first fragments, so a stage starts with its
 //     operands in registers, and the slot of the previous stage is free for stage i + NST - 1.
 //   * The tile (MW x NW accumulator tiles per wave, WM x WN waves) is a template parameter: few rows take all rows and few
-//     columns per workgroup, so that a weight is read once and as many CUs stream as columns allow; many rows take 192 x 256 or
-//     256 x 256, where LDS (128 bytes per clock) delivers what the matrix unit asks for.
-// What bounds it (MI355X, 7B shape, gate/up in whole steps): 64 rows 55 -> 48.7 us, 5.6 TB/s of weights: memory.  1185 rows 324 -> 275 us: power (a build
-// that took 295 us took 231 when the activations were zeros and 270 without its loads).
+//     columns per workgroup, so that a weight is read once and as many CUs stream as columns allow.
+// What bounds it (MI355X, 7B shape, gate/up in whole steps): 64 rows 55 -> 48.7 us, 5.6 TB/s of weights: memory.  1152 rows 272 -> 254 us: power.  Whatever
+// the tile, busy share of the matrix units x clock ends at 1.24 GHz (1.28 PFLOP/s); 128 x 256 tiles whose operands come from the first-level cache
+// only reach 1.39, without loads of weights 1.57, without reads of activations from LDS 1.33.
 #pragma once
 #include "gemm_mfma.h"
 
@@ -26,21 +26,7 @@ __device__ __forceinline__ int xcd_flat(int total) {
   return (int)(blockIdx.x / 8) < per_xcd && flat < total ? flat : -1;
 }
 
-// The same for persistent workgroups: first tile of this one, step to its next ones, end of its XCD's range.
-__device__ __forceinline__ int xcd_first(int total, int& stride, int& end) {
-  const int per_xcd = (total + 7) / 8, x = (int)(blockIdx.x % 8);
-  stride = (int)(gridDim.x / 8);                         // the grid is a multiple of 8
-  end = min((x + 1) * per_xcd, total);
-  return x * per_xcd + (int)(blockIdx.x / 8);
-}
 constexpr int kCUs = 256;
-
-// Many rows, one workgroup per CU: the rows per workgroup with the least rounds of the CUs x time of a K tile (0.01 us).
-__host__ __device__ inline int rows_by_rounds(int M, int n_blocks) {
-  auto cost = [&](int bm, int t) { return ((M + bm - 1) / bm * n_blocks + kCUs - 1) / kCUs * t; };
-  const int c128 = cost(128, 100), c192 = cost(192, 128), c256 = cost(256, 170);
-  return c256 <= c192 && c256 <= c128 ? 256 : c192 <= c128 ? 192 : 128;
-}
 
 template <int MW_, int NW_, int WM_, int WN_, int NST_>
 struct DmaGemm {
@@ -82,7 +68,7 @@ struct DmaGemm {
       }
     }
   }
-  // Requests piece j of the next stage into a slot.  Past the last stage of the last tile that one is requested again, into slots
+  // Requests piece j of the next stage into a slot.  Past the last stage that one is requested again, into slots
   // nobody reads: unconditional, so that the wait counts hold.
   __device__ static __forceinline__ void request(Operands& op, char* slot, int j) {
     char* dst = slot + (PIECES % WAVES == 0 ? wave_id() * PPW + j : min(wave_id() * PPW + j, PIECES - 1)) * 1024;
@@ -96,28 +82,19 @@ struct DmaGemm {
 #endif
   }
 
-  // Computes the tiles id, id + stride, .. below n, ns stages of 32 of K each (the same for all).  operands(op, id) sets up a tile's
-  // requests, finish(acc, id) stores it: C^T tiles, accumulator rows = weight rows, lane = activation row.  The tiles are one
-  // stream of stages: while a tile is finished, the first stages of the next one are in flight or have arrived.  finish() must
-  // not use LDS unless there is one tile only (it then needs a barrier first).  All threads must call it.
+  // Computes the workgroup's tile, ns stages of 32 of K.  operands(op) sets up its requests, finish(acc) stores it: C^T tiles, accumulator rows = weight
+  // rows, lane = activation row (acc_row, acc_col).  finish() may use LDS behind a barrier.  All threads must call it.
   template <typename Ops, typename Finish>
-  __device__ static __forceinline__ void run(int id, int stride, int n, int ns, char* lds, Ops operands, Finish finish) {
+  __device__ static __forceinline__ void run(int ns, char* lds, Ops operands, Finish finish) {
     const int wave = wave_id(), lane = frag_lane(), wm = wave / WN, wn = wave % WN;
     Operands op;
-    int rid = id;                                         // tile of the requests
-    operands(op, rid);
+    operands(op);
     op.left = ns;
-    auto advance = [&]() {
-      if (--op.left == 0) {
-        rid += stride;
-        if (rid < n) { operands(op, rid); op.left = ns; }
-      }
-    };
 #pragma unroll
     for (int st = 0; st < NST - 1; ++st) {
 #pragma unroll
       for (int j = 0; j < PPW; ++j) request(op, lds + st * STAGE_BYTES, j);
-      advance();
+      --op.left;
     }
     // The operand with more tiles per wave goes through the registers in two halves (16 of each tile's 32 rows), the fragments of the other
     // one stay for the whole stage and are refilled in place, each after its last product.
@@ -131,50 +108,45 @@ struct DmaGemm {
     for (int i = 0; i < NH; ++i) half[0][i] = *(const u32x4*)(hb + i * 2048);
 #pragma unroll
     for (int i = 0; i < NK; ++i) keep[i] = *(const u32x4*)(kb + i * 1024 - (i & 1) * (1024 - kWHalf));
+    f32x4 acc[2 * MW][2 * NW];
+#pragma unroll
+    for (int a = 0; a < 2 * MW; ++a)
+#pragma unroll
+      for (int b = 0; b < 2 * NW; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
     int slot = 0;
-    for (; id < n; id += stride) {
-      f32x4 acc[2 * MW][2 * NW];
+    for (int i = 0; i < ns; ++i) {
+      const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
 #pragma unroll
-      for (int a = 0; a < 2 * MW; ++a)
+      for (int s = 0; s < 2; ++s) {
+        if (s == 1) {
+          wait_stage<PPW * (NST - 3)>();                  // the next stage is complete, the previous one no longer read
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        const char* hs = s == 0 ? hb + slot * STAGE_BYTES + kWHalf : hb + next * STAGE_BYTES;
+        const char* ks = kb + next * STAGE_BYTES;
 #pragma unroll
-        for (int b = 0; b < 2 * NW; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int i = 0; i < ns; ++i) {
-        const int next = slot + 1 == NST ? 0 : slot + 1, prev = slot == 0 ? NST - 1 : slot - 1;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
+        for (int m = 0; m < NM; ++m) {
+          const int k = m / NH, h = k & 1 ? NH - 1 - m % NH : m % NH, a = XH ? 2 * h + s : k, b = XH ? k : 2 * h + s;
+          if (m < NH) half[1 - s][m] = *(const u32x4*)(hs + m * 2048);
           if (s == 1) {
-            wait_stage<PPW * (NST - 3)>();                // the next stage is complete, the previous one no longer read
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = m * PPW / NM; j < (m + 1) * PPW / NM; ++j) request(op, lds + prev * STAGE_BYTES, j);
           }
-          const char* hs = s == 0 ? hb + slot * STAGE_BYTES + kWHalf : hb + next * STAGE_BYTES;
-          const char* ks = kb + next * STAGE_BYTES;
-#pragma unroll
-          for (int m = 0; m < NM; ++m) {
-            const int k = m / NH, h = m % NH, a = XH ? 2 * h + s : k, b = XH ? k : 2 * h + s;
-            if (m < NH) half[1 - s][m] = *(const u32x4*)(hs + m * 2048);
-            if (s == 1) {
-#pragma unroll
-              for (int j = m * PPW / NM; j < (m + 1) * PPW / NM; ++j) request(op, lds + prev * STAGE_BYTES, j);
-            }
-            acc[a][b] = XH ? mfma_f16(keep[k], half[s][h], acc[a][b]) : mfma_f16(half[s][h], keep[k], acc[a][b]);
+          acc[a][b] = XH ? mfma_f16(keep[k], half[s][h], acc[a][b]) : mfma_f16(half[s][h], keep[k], acc[a][b]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (s == 1 && m % NH == NH - 1) {
+            keep[k] = *(const u32x4*)(ks + k * 1024 - (k & 1) * (1024 - kWHalf));
             __builtin_amdgcn_sched_barrier(0);
-            if (s == 1 && h == NH - 1) {
-              keep[k] = *(const u32x4*)(ks + k * 1024 - (k & 1) * (1024 - kWHalf));
-              __builtin_amdgcn_sched_barrier(0);
-            }
           }
         }
-        slot = next;
-        advance();
       }
-      if (id + stride >= n) {
-        // LDS must not be given away, nor reused, while a request may still write it
-#if defined(__HIP_DEVICE_COMPILE__)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#endif
-      }
-      finish(acc, id);
+      slot = next;
+      --op.left;
     }
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // LDS must not be given away, nor reused, while a request may still write it
+#endif
+    finish(acc);
   }
 };
 
@@ -246,14 +218,14 @@ struct StreamGemm {
       const char* xs = s < KS - 1 ? xb + slot * STAGE_BYTES + (s + 1) * 1024 : xb + next * STAGE_BYTES;
 #pragma unroll
       for (int m = 0; m < NM; ++m) {
-        const int a = m / NW, b = m % NW;
+        const int a = m / NW, b = a & 1 ? NW - 1 - m % NW : m % NW;
         if (s == KS - 1) {
 #pragma unroll
           for (int j = m * PX / NM; j < (m + 1) * PX / NM; ++j) request_x(op, lds + prev * STAGE_BYTES, j);
         }
         acc[a][2 * b + (s & 1)] = mfma_f16(w[b][s], xf[a], acc[a][2 * b + (s & 1)]);
         __builtin_amdgcn_sched_barrier(0);
-        if ((s & 1) && b == NW - 1) {
+        if ((s & 1) && m % NW == NW - 1) {
           xf[a] = *(const u32x4*)(xs + (a >> 1) * KS * 1024 + (a & 1) * kWHalf);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -263,12 +235,12 @@ struct StreamGemm {
     }
     slot = next;
   }
-  // One tile (id): the arguments are those of DmaGemm::run.
+  // The arguments are those of DmaGemm::run.
   template <typename Ops, typename Finish>
-  __device__ static __forceinline__ void run(int id, int, int, int n32, char* lds, Ops operands, Finish finish) {
+  __device__ static __forceinline__ void run(int n32, char* lds, Ops operands, Finish finish) {
     const int ns = n32 / (KS / 2);                        // n32: 32s of K (KS = 4: an even number)
     Operands op;
-    operands(op, id);
+    operands(op);
     op.left_x = op.left_w = ns;
     u32x4 w[RW][NW][KS], xf[2 * MW];
     // in the order of the loop: the wait counts hold from the first stage on
@@ -309,6 +281,6 @@ struct StreamGemm {
 #pragma unroll
         for (int s = 0; s < KS; ++s) asm volatile("" ::"v"(w[r][b][s]));
 #endif
-    finish(acc, id);
+    finish(acc);
   }
 };

@@ -17,11 +17,10 @@ constexpr int kD = 128;
 constexpr int kLdx = kD + 4;                            // padded row (floats) of the exchange buffer
 
 struct QkvArgs {
-  int M_max, K, Hq, Hkv, max_pages;
+  int M_max, K, Hq, Hkv;
   const f16 *A, *Wp;
   const float *cos_t, *sin_t;
   f16 *q_out, *k_pages, *v_pages;
-  const int32_t* block_table;
 };
 
 template <typename G>
@@ -32,14 +31,17 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
   const int lane = threadIdx.x & 63;
   const size_t tile_bytes = (size_t)(g.K / kBK) * 4096;
   // position t = wn * NW + b of the LDS tiles holds tile wn + 2 b of the head (PAIR), or tile t
-  auto operands = [&](typename G::Operands& op, int) {
+  auto operands = [&](typename G::Operands& op) {
     G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp,
                      [&](int t) { return (size_t)(head * 4 + (PAIR ? (t >> 1) + 2 * (t & 1) : t)) * tile_bytes; }, kWHalf, 0);
   };
-  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW]) {
   const int M = min(p.n_rows[0], g.M_max);
   // Accumulator acc[a][b][e]: row m0 + 16 (2 wm MW + a) + acc_col, column 16 b' + acc_row + e of the head, b' = b, or that of the tile.
   const bool is_v = head >= g.Hq + g.Hkv;
+  int place[2 * G::MW];                                 // k or v head: the rows' cache places
+#pragma unroll
+  for (int a = 0; a < 2 * G::MW; ++a) place[a] = head >= g.Hq ? p.row_kv[min(m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane), g.M_max - 1)] : 0;
   float* s_x = (float*)lds;                             // [BM][kLdx]
   if constexpr (!PAIR) {
     if (!is_v) {
@@ -56,13 +58,8 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
   for (int a = 0; a < 2 * G::MW; ++a) {
     const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
     if (m >= M) continue;
-    size_t pbase = 0;
-    int tok = 0;
-    if (head >= g.Hq) {                                 // k or v head: locate the row's cache slot
-      const int b = p.row_seq[m], pos = p.seq_c[b] + p.row_pos[m];
-      tok = pos % kPage;
-      pbase = (size_t)g.block_table[(size_t)p.seq_slot[b] * g.max_pages + pos / kPage] * kv_page_elems(g.Hkv, kD);
-    }
+    const int tok = place[a] & (kPage - 1);
+    const size_t pbase = (size_t)(place[a] / kPage) * kv_page_elems(g.Hkv, kD);
     // four consecutive columns d .. d + 3 of the head
     auto store = [&](int d, const float (&y)[4]) {
       if (head < g.Hq) {
@@ -112,7 +109,7 @@ __device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0
     }
   }
   };
-  G::run(0, 1, 1, g.K / 32, lds, operands, finish);
+  G::run(g.K / 32, lds, operands, finish);
 }
 
 // The row count is only needed for the stores (rows beyond it are stale rows, each affecting only its own output).
@@ -187,22 +184,22 @@ void launch_one(int blocks, int threads, int lds, hipStream_t st, const Args&...
 }  // namespace
 
 // Few rows have too few (rows, head) tiles for 256 CUs: the GEMM split over K and the rotary kernel behind it are then faster, although both
-// together have more launches and latency (the 300 and the 940, in 0.01 us) and the rotary kernel reads the slabs and scatters K and V: 6 us at 64 rows of
-// 4608 columns, 9 at 288 with 2048 cached tokens, 16 with 8192, when the pages are cold.  Steps measured with either route, us per layer, two kernels / fused:
-//   7B shape    72 rows 141 / 145   189 rows 196.7 / 197.3   243 rows 217.3 / 219.9   288 rows 228.9 / 228.7, with 8192 cached tokens 319.2 / 315.3   387 rows 300 / 294
-//   1.5B shape  63 rows 67.0 / 68.3   99 rows 75.2 / 75.8   135 rows 79.7 / 78.4   288 rows 99.1 / 95.3   576 rows 133.6 / 129.0
+// together have more launches and latency (the 300 and the 440, in 0.01 us) and the rotary kernel reads the slabs and scatters K and V.  Steps
+// measured with either route, 2048 cached tokens, us per layer, two kernels / fused:
+//   7B shape    72 rows 138.9 / 143.8   189 rows 196.7 / 197.5   243 rows 212.5 / 215.9   288 rows 223.8 / 225.0   342 rows 277.2 / 276.8   387 rows 316.2 / 312.5
+//   1.5B shape  63 rows 65.0 / 67.5   99 rows 72.5 / 73.1   135 rows 77.4 / 77.7   216 rows 88.6 / 88.1   288 rows 96.9 / 93.5   576 rows 132.3 / 128.5
 bool qkv_rope_applies(const Shape& s, int M_max) {
   if (s.dtype != BS_BF16 || s.D != kD) return false;
   if (M_max > kFewRows) return true;
   int cost;
   pick_rows(M_max, s.Hq + 2 * s.Hkv, s.d / kBK, true, cost);
-  return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 940 + M_max * s.Nqkv() / 5760;
+  return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 440 + M_max * s.Nqkv() / 5760;
 }
 
-void launch_qkv_rope(const Shape& s, const Plan& p, const KvView& kv, int M_max, const void* A, const void* Wp,
+void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const int heads = s.Hq + 2 * s.Hkv;
-  const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, kv.max_pages, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, kv.block_table};
+  const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages};
   if (M_max > kFewRows) {
     constexpr int a = qkv_lds<Rows64>(), b = qkv_lds<Rows128>(), c = qkv_lds<Rows192>(), d = qkv_lds<Rows32>(), ab = a > b ? a : b, cd = c > d ? c : d, lds = ab > cd ? ab : cd;
     static_assert(Rows64::THREADS == 512 && Rows128::THREADS == 512 && 2 * lds <= 160 * 1024, "two workgroups per CU");

@@ -47,16 +47,16 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
   extern __shared__ __align__(16) char lds[];
   const int M = n_rows_dev ? min(*n_rows_dev, M_max) : M_max;
   const int m_blocks = (M + G::BM - 1) / G::BM;
-  const int id0 = xcd_flat(m_blocks * n_blocks);
-  if (id0 < 0) return;
+  const int id = xcd_flat(m_blocks * n_blocks);
+  if (id < 0) return;
   const int wave = G::wave_id(), lane = threadIdx.x & 63;
   const size_t tile_bytes = (size_t)(K / kBK) * 4096;
   const int t_last = (V + 31) / 32 - 1;
-  auto operands = [&](typename G::Operands& op, int id) {
+  auto operands = [&](typename G::Operands& op) {
     const int m0 = id % m_blocks * G::BM, t0 = id / m_blocks * G::CT;
     G::make_operands(op, X, ld, [&](int r) { return min(m0 + r, M - 1); }, W, [&](int t) { return min(t0 + t, t_last) * tile_bytes; }, kWHalf, 0);
   };
-  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW], int id) {
+  auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW]) {
   const int m0 = id % m_blocks * G::BM + wave / G::WN * kLmMT * 32;      // first row of this wave
   const int vt = id / m_blocks * G::WN + wave % G::WN;           // statistics tile of this wave
   const int n_wave0 = vt * kLmVtile;
@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) lmhea
     }
   }
   };
-  G::run(id0, 1, id0 + 1, K / 32, lds, operands, finish);
+  G::run(K / 32, lds, operands, finish);
 }
 
 // ------------------------------------------------------------------ statistics of given float32 logits

@@ -69,10 +69,9 @@ struct WaveSum {
 enum { SK_QKV = 0, SK_RESID = 1 };
 
 struct QkvOut {        // SK_QKV: where the rotated q and the appended k / v go
-  int Hq, Hkv, max_pages;
+  int Hq, Hkv;
   const float *cos_t, *sin_t;
   f16 *q, *k_pages, *v_pages;
-  const int32_t* block_table;
 };
 struct NormIn {        // SK_QKV: float32 residual (fragment order), sums of squares [parts][32] and the gain
   const float *h, *ssq, *gain;
@@ -173,9 +172,9 @@ skinny_kernel(Plan p, int rows, int K, const f16* __restrict__ X, NormIn nin, co
     rot_c = *(const f32x4*)(qo.cos_t + (size_t)min(ln, rows - 1) * 64 + dc);
     rot_s = *(const f32x4*)(qo.sin_t + (size_t)min(ln, rows - 1) * 64 + dc);
     if ((unit >> 2) >= qo.Hq && ln < M) {
-      const int b = p.row_seq[ln], pos = p.seq_c[b] + p.row_pos[ln];
-      tok = pos % kPage;
-      pbase = (size_t)qo.block_table[(size_t)p.seq_slot[b] * qo.max_pages + pos / kPage] * kv_page_elems(qo.Hkv, 128);
+      const int place = p.row_kv[ln];
+      tok = place & (kPage - 1);
+      pbase = (size_t)(place / kPage) * kv_page_elems(qo.Hkv, 128);
     }
     __syncthreads();
     float ss = 0.f;
@@ -387,7 +386,7 @@ void launch_t(int rows, int units, int n_split, int K, const Shape& s, const Pla
 
 // Token embedding into the fragment-ordered residual; rows beyond the step's count become zero rows.  Also the row's sum
 // of squares (part 0) and rotary table entries.
-__global__ void __launch_bounds__(256) embed_frag_kernel(Plan p, int d, const bf16* __restrict__ embed, float* __restrict__ h,
+__global__ void __launch_bounds__(256) embed_frag_kernel(Plan p, KvView kv, int d, const bf16* __restrict__ embed, float* __restrict__ h,
                                                          float* __restrict__ ssq, int D, const double* __restrict__ inv_freq,
                                                          float* __restrict__ cos_t, float* __restrict__ sin_t) {
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4), aligned(2)));   // a caller's array: aligned to its elements only
@@ -406,6 +405,7 @@ __global__ void __launch_bounds__(256) embed_frag_kernel(Plan p, int d, const bf
     *(f32x4*)(h + h_frag_index(r, i, d / kBK)) = v;
   }
   if (!live) return;
+  if (threadIdx.x == 255) row_place(p, kv, r);
   if ((int)threadIdx.x < D / 2) rope_angle(p, r, threadIdx.x, D / 2, inv_freq, cos_t, sin_t);
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
@@ -435,18 +435,18 @@ __global__ void __launch_bounds__(256) final_norm_frag_kernel(Plan p, int d, flo
 
 bool skinny_applies(const Shape& s, int M_max) { return s.dtype == BS_BF16 && s.D == 128 && M_max <= kSkinnyRows && s.d <= 8192; }
 
-void launch_skinny_embed(const Shape& s, const Plan& p, const void* embed, float* h, float* ssq, const double* inv_freq,
+void launch_skinny_embed(const Shape& s, const Plan& p, const KvView& kv, const void* embed, float* h, float* ssq, const double* inv_freq,
                          float* cos_t, float* sin_t, hipStream_t st) {
-  hipLaunchKernelGGL(embed_frag_kernel, dim3(kSkinnyRows), dim3(256), 0, st, p, s.d, (const bf16*)embed, h, ssq, s.D,
+  hipLaunchKernelGGL(embed_frag_kernel, dim3(kSkinnyRows), dim3(256), 0, st, p, kv, s.d, (const bf16*)embed, h, ssq, s.D,
                      inv_freq, cos_t, sin_t);
 }
 void launch_skinny_final_norm(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, const float* gain,
                               void* out, hipStream_t st) {
   hipLaunchKernelGGL(final_norm_frag_kernel, dim3(M_max), dim3(256), 0, st, p, s.d, s.eps, h, ssq, s.d / 32, gain, (f16*)out, M_max);
 }
-void launch_skinny_qkv(const Shape& s, const Plan& p, const KvView& kv, int M_max, const float* h, const float* ssq, int ssq_parts,
+void launch_skinny_qkv(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts,
                        const float* gain, const void* W, const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, const SkinnyBufs& sk, hipStream_t st) {
-  const QkvOut qo{s.Hq, s.Hkv, kv.max_pages, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages, kv.block_table};
+  const QkvOut qo{s.Hq, s.Hkv, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages};
   launch_t<SK_QKV>(M_max, 4 * (s.Hq + 2 * s.Hkv), 1, s.d, s, p, nullptr, NormIn{h, ssq, gain, ssq_parts, s.eps}, W, nullptr, nullptr, qo, sk, st);
 }
 void launch_skinny_gate_up(const Shape& s, const Plan& p, int M_max, const float* h, const float* ssq, int ssq_parts, const float* gain, void* a,
