@@ -278,24 +278,25 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
       float mloc = x[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mloc = fmaxf(mloc, x[i]);
-      mloc = fmaxf(mloc, __shfl_xor(mloc, 32)) * scale_log2e;       // scale > 0 commutes with max
-      const float m_new = fmaxf(m_run[qt], mloc);
-      const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_safe);
+      mloc = max_halves(mloc) * scale_log2e;            // scale > 0 commutes with max
+      if (__any(mloc > m_run[qt] + kLateRescale)) {
+        const float m_new = fmaxf(m_run[qt], mloc);
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run[qt] - m_new);
+        l_run[qt] *= alpha;
+        m_run[qt] = m_new;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[qt][dt][i] *= alpha;
+      }
+      const float m_safe = (m_run[qt] == -INFINITY) ? 0.f : m_run[qt];
       float psum = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         x[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], scale_log2e, -m_safe));   // exp2(-inf) = 0
         psum += x[i];
       }
-      l_run[qt] = l_run[qt] * alpha + psum;             // per lane half; halves are added at the end
-      m_run[qt] = m_new;
-      if (__any(alpha != 1.0f)) {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) o[qt][dt][i] *= alpha;
-      }
+      l_run[qt] += psum;                                // per lane half; halves are added at the end
       pf[qt][0] = pack_f16x8(x);
       pf[qt][1] = pack_f16x8(x + 8);
       __builtin_amdgcn_sched_barrier(0);
@@ -337,7 +338,7 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
     float* mine = s_o + (size_t)wave * ROWS_W * LDO;
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      l_run[qt] += __shfl_xor(l_run[qt], 32);
+      l_run[qt] = sum_halves(l_run[qt]);
       if (lg == 0) {
         s_m[wave * ROWS_W + qt * 32 + ln] = m_run[qt];
         s_l[wave * ROWS_W + qt * 32 + ln] = l_run[qt];

@@ -258,24 +258,25 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
         float mloc = x[0];
 #pragma unroll
         for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, x[r]);
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32)) * scale_log2e;       // scale > 0 commutes with max
-        const float m_new = fmaxf(m_run, mloc);
-        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        mloc = max_halves(mloc) * scale_log2e;           // scale > 0 commutes with max
+        if (__any(mloc > m_run + kLateRescale)) {
+          const float m_new = fmaxf(m_run, mloc);
+          const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+          l_run *= alpha;
+          m_run = m_new;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
+        }
+        const float m_safe = (m_run == -INFINITY) ? 0.f : m_run;
         float psum = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           x[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], scale_log2e, -m_safe));   // exp2(-inf) = 0
           psum += x[r];
         }
-        l_run = l_run * alpha + psum;                    // per lane half; halves are added at the end
-        m_run = m_new;
-        if (__any(alpha != 1.0f)) {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
-        }
+        l_run += psum;                                   // per lane half; halves are added at the end
         f16x8 pf[2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) { pf[0][j] = (f16)x[j]; pf[1][j] = (f16)x[8 + j]; }
@@ -297,7 +298,7 @@ __global__ void __launch_bounds__(512) attn_wide_kernel(const int32_t* __restric
     float* s_l = s_m + 8 * 32;
     {
       float* mine = s_o + (size_t)wave * 32 * LDO;
-      l_run += __shfl_xor(l_run, 32);
+      l_run = sum_halves(l_run);
       if (lg == 0) { s_m[wave * 32 + ln] = m_run; s_l[wave * 32 + ln] = l_run; }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
