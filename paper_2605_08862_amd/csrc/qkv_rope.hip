@@ -4,17 +4,14 @@
 //   (pairs (j, j + 64)), q stored as float16 rows (attention operand), k and v rounded to bf16 and written
 //   into the slot's KV page in the page layout.
 //
-// One workgroup = rows x one head.  The partner of column j (< 64) of a head is two weight tiles further:
-//   two columns of waves (many rows)  wave column w multiplies tiles w and w + 2, so that both halves of a rotation are in one
-//                                     lane and the epilogue needs no exchange;
-//   four columns of waves (fewer rows) one tile each; the waves exchange their accumulators through LDS once.
+// One workgroup = rows x one or two heads.  The partner of column j (< 64) of a head is two weight tiles further: a wave's 32-row weight tile is put
+// together from 16 columns and their 16 partners by the addresses, so that both halves of a rotation are in one lane.
 // The float32 projection never goes to memory and q, k, v are rounded exactly once, after the rotation.
 #include "gemm_dma.h"
-#include <type_traits>
+#include <initializer_list>
 
 namespace {
 constexpr int kD = 128;
-constexpr int kLdx = kD + 4;                            // padded row (floats) of the exchange buffer
 
 struct QkvArgs {
   int M_max, K, Hq, Hkv;
@@ -24,90 +21,66 @@ struct QkvArgs {
 };
 
 template <typename G>
-__device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0, int head, char* lds) {
-  constexpr bool PAIR = G::NW == 2;
-  static_assert(G::CT == 4 && (PAIR ? G::WN == 2 : G::WN == 4), "a workgroup's columns are one head");
+__device__ __forceinline__ void qkv_tile(const Plan& p, const QkvArgs& g, int m0, int head0, char* lds) {
+  static_assert(G::CT % 4 == 0, "a workgroup's columns are heads");
   const int wave = G::wave_id(), wm = wave / G::WN, wn = wave % G::WN;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, heads = g.Hq + 2 * g.Hkv;
   const size_t tile_bytes = (size_t)(g.K / kBK) * 4096;
-  // position t = wn * NW + b of the LDS tiles holds tile wn + 2 b of the head (PAIR), or tile t
+  // position t: columns 16 (t % 4) .. and 16 (t % 4) + 64 .. of head head0 + t / 4
   auto operands = [&](typename G::Operands& op) {
     G::make_operands(op, g.A, g.M_max, [&](int r) { return min(m0 + r, g.M_max - 1); }, g.Wp,
-                     [&](int t) { return (size_t)(head * 4 + (PAIR ? (t >> 1) + 2 * (t & 1) : t)) * tile_bytes; }, kWHalf, 0);
+                     [&](int t) { return (size_t)(min(head0 + t / 4, heads - 1) * 4 + (t >> 1 & 1)) * tile_bytes + (t & 1) * kWHalf; }, 2u * (uint32_t)tile_bytes, 0);
   };
   auto finish = [&](f32x4 (&acc)[2 * G::MW][2 * G::NW]) {
-  const int M = min(p.n_rows[0], g.M_max);
-  // Accumulator acc[a][b][e]: row m0 + 16 (2 wm MW + a) + acc_col, column 16 b' + acc_row + e of the head, b' = b, or that of the tile.
-  const bool is_v = head >= g.Hq + g.Hkv;
-  int place[2 * G::MW];                                 // k or v head: the rows' cache places
+    const int M = min(p.n_rows[0], g.M_max);
+    // a wave's columns lie in one head
+    static_assert(G::NW <= 4 && 4 % G::NW == 0, "");
+    const int head = head0 + wn * G::NW / 4;
+    if (G::CT > 4 && head >= heads) return;             // an odd number of heads
+    const bool is_v = head >= g.Hq + g.Hkv;
+    int place[2 * G::MW];                               // k or v head: the rows' cache places
 #pragma unroll
-  for (int a = 0; a < 2 * G::MW; ++a) place[a] = head >= g.Hq ? p.row_kv[min(m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane), g.M_max - 1)] : 0;
-  float* s_x = (float*)lds;                             // [BM][kLdx]
-  if constexpr (!PAIR) {
-    if (!is_v) {
-      __syncthreads();                                  // every wave is done reading the loop's LDS stages
+    for (int a = 0; a < 2 * G::MW; ++a) place[a] = head >= g.Hq ? p.row_kv[min(m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane), g.M_max - 1)] : 0;
 #pragma unroll
-      for (int a = 0; a < 2 * G::MW; ++a)
+    for (int a = 0; a < 2 * G::MW; ++a) {
+      const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
+      if (m >= M) continue;
+      const int tok = place[a] & (kPage - 1);
+      const size_t pbase = (size_t)(place[a] / kPage) * kv_page_elems(g.Hkv, kD);
+      // four consecutive columns d .. d + 3 of the head
+      auto store = [&](int d, const float (&y)[4]) {
+        if (head < g.Hq) {
+          *(f16x4*)(g.q_out + ((size_t)m * g.Hq + head) * kD + d) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
+          return;
+        }
+        // bf16-rounded values in float16 encoding (page format)
+        const f16x4 v = to_f16x4_guarded((float)(bf16)y[0], (float)(bf16)y[1], (float)(bf16)y[2], (float)(bf16)y[3], p.status);
+        if (!is_v) {
+          *(f16x4*)(g.k_pages + pbase + k_index_bf16(kD, head - g.Hq, tok, d)) = v;
+        } else {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-          *(f32x4*)(s_x + ((wm * 2 * G::MW + a) * 16 + acc_col(lane)) * kLdx + 32 * wn + 16 * b + acc_row(lane)) = acc[a][b];
-      __syncthreads();
-    }
-  }
+          for (int e = 0; e < 4; ++e) g.v_pages[pbase + v_index_bf16(kD, head - g.Hq - g.Hkv, tok, d + e)] = v[e];
+        }
+      };
 #pragma unroll
-  for (int a = 0; a < 2 * G::MW; ++a) {
-    const int m = m0 + (wm * 2 * G::MW + a) * 16 + acc_col(lane);
-    if (m >= M) continue;
-    const int tok = place[a] & (kPage - 1);
-    const size_t pbase = (size_t)(place[a] / kPage) * kv_page_elems(g.Hkv, kD);
-    // four consecutive columns d .. d + 3 of the head
-    auto store = [&](int d, const float (&y)[4]) {
-      if (head < g.Hq) {
-        *(f16x4*)(g.q_out + ((size_t)m * g.Hq + head) * kD + d) = to_f16x4_guarded(y[0], y[1], y[2], y[3], p.status);
-        return;
-      }
-      // bf16-rounded values in float16 encoding (page format)
-      const f16x4 v = to_f16x4_guarded((float)(bf16)y[0], (float)(bf16)y[1], (float)(bf16)y[2], (float)(bf16)y[3], p.status);
-      if (!is_v) {
-        *(f16x4*)(g.k_pages + pbase + k_index_bf16(kD, head - g.Hq, tok, d)) = v;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) g.v_pages[pbase + v_index_bf16(kD, head - g.Hq - g.Hkv, tok, d + e)] = v[e];
-      }
-    };
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int d = 32 * wn + 16 * b + acc_row(lane);
-      f32x4 c = f32x4{1.f, 1.f, 1.f, 1.f}, sn = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (!is_v) {
-        c = *(const f32x4*)(g.cos_t + (size_t)m * 64 + (d & 63));
-        sn = *(const f32x4*)(g.sin_t + (size_t)m * 64 + (d & 63));
-      }
-      float y[4];
-      if constexpr (PAIR) {
-        float y2[4];
+      for (int b = 0; b < G::NW; ++b) {
+        const int d = 16 * ((wn * G::NW + b) % 4) + acc_row(lane);
+        f32x4 c = f32x4{1.f, 1.f, 1.f, 1.f}, sn = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (!is_v) {
+          c = *(const f32x4*)(g.cos_t + (size_t)m * 64 + d);
+          sn = *(const f32x4*)(g.sin_t + (size_t)m * 64 + d);
+        }
+        float y[4], y2[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float x1 = acc[a][b][e], x2 = acc[a][(2 + b) % (2 * G::NW)][e];
+          const float x1 = acc[a][2 * b][e], x2 = acc[a][2 * b + 1][e];
           y[e] = is_v ? x1 : x1 * c[e] - x2 * sn[e];
           y2[e] = is_v ? x2 : x2 * c[e] + x1 * sn[e];
         }
         store(d, y);
         store(d + 64, y2);
-      } else {
-        if (is_v) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = acc[a][b][e];
-        } else {
-          const f32x4 other = *(const f32x4*)(s_x + ((wm * 2 * G::MW + a) * 16 + acc_col(lane)) * kLdx + (d ^ 64));
-          const float sign = d < 64 ? -1.0f : 1.0f;     // y1 = x1 c - x2 s (columns < 64), y2 = x2 c + x1 s
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = acc[a][b][e] * c[e] + sign * other[e] * sn[e];
-        }
-        store(d, y);
       }
     }
-  }
   };
   G::run(g.K / 32, lds, operands, finish);
 }
@@ -150,11 +123,7 @@ __host__ __device__ inline int pick_rows(int M, int heads, int nk, bool few, int
   return bm;
 }
 constexpr int kFewRows = 640;
-template <typename G> constexpr int qkv_lds() {
-  constexpr int x = G::NW == 2 ? 0 : G::BM * kLdx * 4;  // exchange buffer
-  return G::LDS_BYTES > x ? G::LDS_BYTES : x;
-}
-// Many rows: the rows of a tile from the step's row count.
+// More rows than that, but few tiles: the rows of a tile from the step's row count.
 __global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, QkvArgs g) {
   extern __shared__ __align__(16) char lds[];
   const int M = min(p.n_rows[0], g.M_max), heads = g.Hq + 2 * g.Hkv;
@@ -174,6 +143,49 @@ __global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, Q
   if (threadIdx.x >= 512) return;
   if (bm == 64) qkv_tile<Rows64>(p, g, m0, head, lds);
   else qkv_tile<Rows128>(p, g, m0, head, lds);
+}
+// Many rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count: rounds of the CUs x K tiles x time
+// of one + fill and epilogue, 0.01 us.  The tiles above read 1.5 fragments from LDS per product and are bound by that, these 0.6 .. 1.  Times are
+// those of the loops with float32 results and weights that no cache holds, 64 / 96 / 128 / 160 / 192 rows of a head and 128 rows of two heads:
+//   36 heads, K 3584   720 rows 40.6 / 44.8 / 32.0 / 33.0 / 38.3 / 45.8 us   1152 rows 58 / 51 / 58 / 56 / 40.8 / 47.5   1500 rows 77 / 67 / 59 / 63 / 74 / 48.2
+//   16 heads, K 1536   816 rows 12.8 / 13.7 / 14.6 / 15.6 / 17.5 / 22.1   1037 rows 16.7 / 15.1 / 14.3 / 16.9 / 17.9 / 22.2   3740 rows 41 / 38 / 34 / 34 / 34 / 28.1
+typedef StreamGemm<2, 1, 4, 4> Many64;
+typedef StreamGemm<3, 1, 4, 3> Many96;
+typedef StreamGemm<4, 1, 4, 3> Many128;
+typedef StreamGemm<5, 1, 4, 3> Many160;
+typedef StreamGemm<6, 1, 4, 4, 2> Many192;
+typedef StreamGemm<4, 2, 4, 2> Many128x2;
+struct ManyPick { int rows, heads, blocks; };
+__host__ __device__ inline ManyPick pick_many(int M, int heads, int nk) {
+  ManyPick best{64, 1, 0};
+  int least = 0x7fffffff;
+  auto consider = [&](int bm, int hp, int t, int fixed) {
+    const int n = (M + bm - 1) / bm * ((heads + hp - 1) / hp), c = (n + kCUs - 1) / kCUs * nk * t + fixed;
+    if (c < least) { least = c; best = ManyPick{bm, hp, n}; }
+  };
+  consider(64, 1, 36, 400);
+  consider(96, 1, 44, 500);
+  consider(128, 1, 50, 400);
+  consider(160, 1, 58, 550);
+  consider(192, 1, 68, 600);
+  consider(128, 2, 80, 600);
+  return best;
+}
+// (Steps with fewer tiles stay where they were: 1024 rows of a model of ten heads are 80.)
+inline bool many_rows(int M_max, int heads) { return M_max > kFewRows && (M_max + 127) / 128 * heads >= 96; }
+__global__ void __launch_bounds__(256, 2) qkv_many_kernel(Plan p, QkvArgs g) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(p.n_rows[0], g.M_max);
+  const ManyPick t = pick_many(M, g.Hq + 2 * g.Hkv, g.K / kBK);
+  const int id = xcd_flat(t.blocks), m_blocks = (M + t.rows - 1) / t.rows;
+  if (id < 0) return;
+  const int m0 = id % m_blocks * t.rows, head = id / m_blocks * t.heads;
+  if (t.heads == 2) qkv_tile<Many128x2>(p, g, m0, head, lds);
+  else if (t.rows == 192) qkv_tile<Many192>(p, g, m0, head, lds);
+  else if (t.rows == 160) qkv_tile<Many160>(p, g, m0, head, lds);
+  else if (t.rows == 128) qkv_tile<Many128>(p, g, m0, head, lds);
+  else if (t.rows == 96) qkv_tile<Many96>(p, g, m0, head, lds);
+  else qkv_tile<Many64>(p, g, m0, head, lds);
 }
 template <auto KERN, typename... Args>
 void launch_one(int blocks, int threads, int lds, hipStream_t st, const Args&... args) {
@@ -200,15 +212,28 @@ void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const void* A, co
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const int heads = s.Hq + 2 * s.Hkv;
   const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages};
+  constexpr auto most = [](std::initializer_list<int> v) { int m = 0; for (int x : v) m = x > m ? x : m; return m; };
+  if (many_rows(M_max, heads)) {
+    constexpr int lds = most({Many64::LDS_BYTES, Many96::LDS_BYTES, Many128::LDS_BYTES, Many160::LDS_BYTES, Many192::LDS_BYTES, Many128x2::LDS_BYTES});
+    static_assert(2 * lds <= 160 * 1024, "two workgroups per CU");
+    // the most workgroups that any row count takes; the choice changes only with the number of tiles of some size, multiples of 32 rows
+    int blocks = 0;
+    for (int M = 32; M < M_max + 32; M += 32) {
+      const int n = pick_many(M < M_max ? M : M_max, heads, s.d / kBK).blocks;
+      blocks = n > blocks ? n : blocks;
+    }
+    launch_one<qkv_many_kernel>(blocks, 256, lds, st, p, g);
+    return;
+  }
   if (M_max > kFewRows) {
-    constexpr int a = qkv_lds<Rows64>(), b = qkv_lds<Rows128>(), c = qkv_lds<Rows192>(), d = qkv_lds<Rows32>(), ab = a > b ? a : b, cd = c > d ? c : d, lds = ab > cd ? ab : cd;
+    constexpr int lds = most({Rows32::LDS_BYTES, Rows64::LDS_BYTES, Rows128::LDS_BYTES, Rows192::LDS_BYTES});
     static_assert(Rows64::THREADS == 512 && Rows128::THREADS == 512 && 2 * lds <= 160 * 1024, "two workgroups per CU");
     const int tiles = (M_max + 63) / 64 * heads;
     launch_one<qkv_rows_kernel>(tiles > kRows32Tiles ? tiles : kRows32Tiles, Rows192::THREADS, lds, st, p, g);
     return;
   }
   int cost;
-#define BS_QKV(G_) do { const int mb = (M_max + G_::BM - 1) / G_::BM; launch_one<qkv_kernel<G_>>(mb * heads, G_::THREADS, qkv_lds<G_>(), st, p, g, mb); } while (0)
+#define BS_QKV(G_) do { const int mb = (M_max + G_::BM - 1) / G_::BM; launch_one<qkv_kernel<G_>>(mb * heads, G_::THREADS, G_::LDS_BYTES, st, p, g, mb); } while (0)
   switch (pick_rows(M_max, heads, s.d / kBK, true, cost)) {
     case 32: BS_QKV(Few32); break;
     case 64: BS_QKV(Few64); break;

@@ -67,3 +67,21 @@ def test_normalisation_of_four_rows_per_workgroup(n_last):
     desc = W.shape("mini_bf16", n_layers=1, d_model=320, n_q_heads=6, n_kv_heads=2, d_ffn=448, vocab=333)
     k_b = [16] * 92 + [n_last] + [0] * 35
     _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(8).integers(0, 40, 128)], k_b=k_b, k_max=16, seed=95, q_mode="onehot", check_kv=False)
+
+
+@pytest.mark.parametrize("k_b", [[14] * 36 + [0] * 7, [14] * 41 + [13, 0], [16] * 56 + [0] * 12, [16] * 67 + [15, 0], [16] * 87 + [15, 0], [16] * 126 + [15, 0]])
+def test_qkv_tiles_of_many_rows(k_b):
+    """27 heads (an odd number), 18 K tiles: 64 rows of a head (547 of 645 rows), 96 (630), 128 (964 of 1156), 160 (1156 of 1173), 192 (1496 of 1513) and 128
+    rows of two heads (2159 of 2176)."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=1152, n_q_heads=21, n_kv_heads=3, d_ffn=448, vocab=333)
+    ctx = [int(x) for x in np.random.default_rng(9).integers(0, 70, len(k_b))]
+    _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=max(k_b), seed=96, q_mode="onehot", check_kv=len(k_b) == 43)
+
+
+@pytest.mark.parametrize("d_model,d_ffn,n_seq", [(1536, 8960, 48), (1536, 8960, 64), (1536, 8960, 71), (320, 18944, 20), (320, 18944, 24)])
+def test_gate_up_tiles_of_eight_waves_and_of_one_row_block(d_model, d_ffn, n_seq):
+    """24 K tiles, 70 column blocks of 128 features: eight waves on 160 (423 of 432 rows), 192 (567) and 224 rows (630).  1184 columns of 16 features: one
+    block of 192 and of 224 rows (171 and 207 live) with the weights in registers."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=6, n_kv_heads=2, d_ffn=d_ffn, vocab=333)
+    ctx = [int(x) for x in np.random.default_rng(10).integers(0, 70, n_seq)]
+    _run_case(desc, ctx_lens=ctx, k_b=[8] * (n_seq - 2) + [7, 0], k_max=8, seed=97, q_mode="onehot", check_kv=False)
