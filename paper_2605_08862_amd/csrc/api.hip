@@ -438,12 +438,14 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   SlabCount pending{0, 0};                      // slabs of the last residual projection not yet added to h
   for (int l = 0; l < s.L; ++l) {
     { ProfScope ps(c, BS_PROF_EMPTY, st); }
+    ReadAhead ahead{nullptr, 0};
+    if (s.dtype == BS_BF16) ahead = ReadAhead{c->wo[l], packed_weight_elems(s.d, s.Hq * s.D) * sizeof(uint16_t)};
     if (skinny) {
       { ProfScope ps(c, BS_PROF_GEMM_QKV, st);
         launch_skinny_qkv(s, p, M_max, c->h, c->ssq, l == 0 ? 1 : s.d / 32, c->attn_norm[l], c->wqkv[l], c->rope_cos, c->rope_sin,
                           c->q, c->k_pages[l], c->v_pages[l], c->sk, st); }
       launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, kSkinnyRows,
-                       c->attn_scratch, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
+                       c->attn_scratch, ahead, c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
       { ProfScope ps(c, BS_PROF_GEMM_O, st);
         launch_skinny_resid(s, p, M_max, s.Hq * s.D, c->attn_out, c->wo[l], c->h, c->ssq, c->sk, st); }
       { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
@@ -463,7 +465,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
       launch_rope_append(s, p, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
-    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, M_max, c->attn_scratch,
+    launch_attention(s, p, c->kv, l, B, c->B_max, k_max, M_max, c->q, c->k_pages[l], c->v_pages[l], c->attn_out, M_max, c->attn_scratch, ahead,
                      c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
     { ProfScope ps(c, BS_PROF_GEMM_O, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],

@@ -411,12 +411,14 @@ void launch_skinny_resid(const Shape& s, const Plan& p, int M_max, int K, const 
 // out_ld: ld of the output rows (bf16 models: chunk order, act_index).
 // attention_plan_params gives the work-list parameters launch_plan needs for the same (B, k_max);
 // launch_attention_init clears the completion counters once, at context creation.
+// ahead: weights that the launches behind this one will stream, for workgroups that have no unit (attention.hip).
 AttnPlan attention_plan_params(const Shape& s, int B, int k_max);
+struct ReadAhead { const void* base; size_t bytes; };
 void launch_attention_init(const Shape& s, int B_max, void* scratch, hipStream_t st);
 void launch_zero_i32(int32_t* p, int n, hipStream_t st);
 void launch_attention(const Shape& s, const Plan& p, const KvView& kv, int layer, int B, int B_max, int k_max, int M_max,
                       const void* q, const void* k_pages, const void* v_pages, void* out, int out_ld, void* scratch,
-                      void* prof_token, hipStream_t st);
+                      const ReadAhead& ahead, void* prof_token, hipStream_t st);
 void attention_prof_mark(void* token, hipStream_t st, bool begin);   // api.hip: event pair around the main kernel
 size_t attention_scratch_bytes(const Shape& s, int B_max, int k_max);
 // sampler.hip
