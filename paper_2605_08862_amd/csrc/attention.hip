@@ -127,6 +127,19 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
     const int qr = qb * RP + wr;
     if (qr >= R) return;
     const uint32_t step = (uint32_t)Hkv * RP * q_blocks;       // partial rows from one chunk to the next
+    // the first group of chunks is requested with the maxima: one trip to memory, not two
+    wt_f32x2 ml[GC];
+    f32x4 v[GC][CPT];
+    auto load_group = [&](int c0) {
+#pragma unroll
+      for (int u = 0; u < GC; ++u) {
+        const uint32_t r = min(c0 + u, n_ch - 1) * step + qr;
+        ml[u] = wt_load2(bm, r * 8);
+#pragma unroll
+        for (int j = 0; j < CPT; ++j) v[u][j] = wt_load4(bo, (r * D + (sub + j * TPR) * 4) * 4);
+      }
+    };
+    load_group(0);
     float mt = -INFINITY;
     for (int c0 = 0; c0 < n_ch; c0 += 8) {
       float m[8];
@@ -140,15 +153,7 @@ __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restric
 #pragma unroll
     for (int j = 0; j < CPT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0; c0 < n_ch; c0 += GC) {
-      wt_f32x2 ml[GC];
-      f32x4 v[GC][CPT];
-#pragma unroll
-      for (int u = 0; u < GC; ++u) {
-        const uint32_t r = min(c0 + u, n_ch - 1) * step + qr;
-        ml[u] = wt_load2(bm, r * 8);
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) v[u][j] = wt_load4(bo, (r * D + (sub + j * TPR) * 4) * 4);
-      }
+      if (c0 > 0) load_group(c0);
 #pragma unroll
       for (int u = 0; u < GC; ++u) {
         if (c0 + u >= n_ch || ml[u][0] == -INFINITY) continue;
