@@ -14,16 +14,18 @@ __device__ __forceinline__ float silu_fast(float x) { return x * __builtin_amdgc
 // One workgroup = 32 rows x 32 output columns (EPI_SWIGLU: 32 gate and the 32 up columns of the same features), its eight
 // waves split K and meet in LDS at the end.  The products run on the float32 MFMA (32x32x2: float32 operands, float32
 // accumulation).  The contraction index is permuted the same way for both operands (lane group g multiplies k = 8 i + 4 g + j), so
-// that a lane loads 16 bytes of its row at a time; a wave keeps eight loads of each operand in flight.  These models are
+// that a lane loads 16 bytes of its row at a time; a wave keeps U loads of each operand in flight, eight, or four where it has no
+// more (with eight the others were loaded again).  These models are
 // small (the parity configuration), so latency is what bounds a launch: with 64 x 64 tiles on plain FMAs, one to four
 // workgroups walked K alone.  20 rows, d_model 256, FFN 1024: O / down projections 62.5 us before (mean of the two), 9.1 us
-// here; gate / up 28.9 and 9.4 us; QKV and the 4096-token LM head 26.2 and 6.5 us.
+// here; gate / up 28.9 and 9.4 us; QKV and the 4096-token LM head 26.2 and 6.5 us.  Four loads instead of eight for K = 256: O 5.7 -> 5.1, gate / up 10.0 -> 7.2, QKV
+// 6.4 -> 4.9, LM head 6.7 -> 5.2 (sixteen for K = 1024: 12.2 -> 13.6).
 constexpr int kF32Waves = 8;
-template <int EPI>
+template <int EPI, int U>
 __global__ void __launch_bounds__(64 * kF32Waves) gemm_f32_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K,
                                                                   const float* __restrict__ A, const float* __restrict__ W,
                                                                   float* __restrict__ out) {
-  constexpr int NB = (EPI == EPI_SWIGLU) ? 2 : 1, U = 8;
+  constexpr int NB = (EPI == EPI_SWIGLU) ? 2 : 1;
   __shared__ f32x4 s_part[kF32Waves][NB][4][64];
   const int M = n_rows_dev ? min(*n_rows_dev, M_max) : M_max;
   const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
@@ -432,8 +434,13 @@ static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K
 
 template <int EPI>
 static void launch_f32(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, hipStream_t st) {
-  hipLaunchKernelGGL(gemm_f32_kernel<EPI>, dim3((N + 31) / 32, (M_max + 31) / 32), dim3(64 * kF32Waves), 0, st, n_rows_dev, M_max, N, K,
-                     (const float*)A, (const float*)W, (float*)out);
+  const int loads = (K / 8 + kF32Waves - 1) / kF32Waves;           // of a wave, per operand
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((N + 31) / 32, (M_max + 31) / 32), dim3(64 * kF32Waves), 0, st, n_rows_dev, M_max, N, K,
+                       (const float*)A, (const float*)W, (float*)out);
+  };
+  if (loads <= 4) go(gemm_f32_kernel<EPI, 4>);
+  else go(gemm_f32_kernel<EPI, 8>);
 }
 
 SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
