@@ -430,7 +430,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
   launch_plan(p, c->kv, B, k_max, s.V, seq_slot, last_token, draft_tokens, draft_len, true, attention_plan_params(s, B, k_max),
               s.L, st);
   const bool skinny = c->fragments && skinny_applies(s, M_max) && !c->unfused_qkv;
-  const SlabRules rules = skinny ? SlabRules{} : gemm_slab_rules(s, M_max);
+  const StepRules rules = skinny ? StepRules{} : step_rules(s, M_max);
   if (skinny) launch_skinny_embed(s, p, c->kv, c->embed, c->h, c->ssq, c->inv_freq, c->rope_cos, c->rope_sin, st);
   else launch_embed(s, p, c->kv, M_max, rules, c->embed, c->h, c->inv_freq, c->rope_cos, c->rope_sin, st);
   const bool fused_qkv = qkv_rope_applies(s, M_max) && !c->unfused_qkv;
@@ -457,11 +457,11 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->attn_norm[l], c->a, st);
     if (fused_qkv) {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
-      launch_qkv_rope(s, p, M_max, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
+      launch_qkv_rope(s, p, M_max, rules.qkv, c->a, c->wqkv[l], c->rope_cos, c->rope_sin, c->q, c->k_pages[l], c->v_pages[l], st);
     } else {
       ProfScope ps(c, BS_PROF_GEMM_QKV, st);
       const SlabCount nq = launch_gemm(s.dtype, EPI_STORE_F32, p.n_rows, M_max, s.Nqkv(), s.d, c->a, c->wqkv[l],
-                                       slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.r[SLAB_QKV]);
+                                       slab_mode ? (void*)c->slabs : (void*)c->qkv, p.status, st, rules.slab[SLAB_QKV]);
       launch_rope_append(s, p, M_max, c->rope_cos, c->rope_sin, slab_mode ? c->slabs : c->qkv, nq, c->q,
                          c->k_pages[l], c->v_pages[l], st);
     }
@@ -469,13 +469,13 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
                      c->prof_class == BS_PROF_ATTENTION ? (void*)c : nullptr, st);
     { ProfScope ps(c, BS_PROF_GEMM_O, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.Hq * s.D, c->attn_out, c->wo[l],
-                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.r[SLAB_O]); }
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.slab[SLAB_O]); }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->mlp_norm[l], c->a, st);
     { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
       launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, c->w_gate_up[l], c->act, p.status, st); }
     { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
-                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.r[SLAB_DOWN]); }
+                            slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.slab[SLAB_DOWN]); }
   }
   if (skinny) launch_skinny_final_norm(s, p, M_max, c->h, c->ssq, c->final_norm, c->hf, st);
   else launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->final_norm, c->hf, st);

@@ -144,7 +144,7 @@ template <> __host__ __device__ __forceinline__ int v_index<bf16>(int D, int h, 
 // ---------------------------------------------------------------------------------------------
 struct Plan {
   int32_t* status;      // [1]   BS_FAULT_* bits (sticky until polled)
-  int32_t* n_rows;      // [5]   M, T_d, choices of the slab GEMMs (SlabRule)
+  int32_t* n_rows;      // [6]   M, T_d, choices of the slab GEMMs (SlabRule) and of the QKV projection (TileRule)
   int32_t* row_start;   // [B+1] first packed row of sequence b (k_b+1 rows each)
   int32_t* draft_start; // [B+1] first packed draft row of sequence b (k_b rows each)
   int32_t* seq_k;       // [B]   validated k_b (-1: sequence skipped)
@@ -272,9 +272,9 @@ void launch_clear_status(int32_t* status, hipStream_t st);
 void launch_kv_lengths(const KvView& kv, int B, const int32_t* seq_slot, int32_t* out, int32_t* status, hipStream_t st);
 // elementwise.hip
 // also fills the step's rotary tables cos_t / sin_t [M_max][D/2] (shared by all layers) and the rows' cache places
-// rules: those of the step's GEMMs (gemm_slab_rules); their choices are left behind the row count.
-struct SlabRules;
-void launch_embed(const Shape& s, const Plan& p, const KvView& kv, int M_max, const SlabRules& rules, const void* embed, float* h, const double* inv_freq,
+// rules: those of the step's GEMMs (step_rules); their choices are left behind the row count.
+struct StepRules;
+void launch_embed(const Shape& s, const Plan& p, const KvView& kv, int M_max, const StepRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st);
 // h[r] += sum of n_slabs slabs [M_max, d] (n_slabs may be 0), then out[r] = RMSNorm(h[r]).
 struct SlabCount;
@@ -292,7 +292,9 @@ void launch_kv_copy(const Shape& s, const KvView& kv, int slot, int pos0, int n,
 // qkv_rope.hip   QKV projection + rotary + KV append in one kernel (bf16 models with head size 128); A = normed
 // rows (float16), Wp = packed wqkv.
 bool qkv_rope_applies(const Shape& s, int M_max);
-void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const void* A, const void* Wp,
+struct TileRule;
+TileRule qkv_rope_rule(const Shape& s, int M_max);       // of the step; at == 0: the launch needs none
+void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const TileRule& rule, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st);
 // Float16 activations of bf16 models (normalised rows, attention output, gated activation, final rows), "chunk order": the eight
 // elements k .. k + 7 (k % 8 == 0) of a row are one 16-byte chunk, and the chunks of one k of all rows are neighbours, ld chunks
@@ -315,6 +317,7 @@ __device__ __forceinline__ void store_chunk_pair(f16* out, int row, int col, int
 }
 // gemm.hip   C[M,N] (+)= A[M,K] * W[N,K]^T with an epilogue.  float32 models: A, W float32 row-major.
 // bf16 models: A float16 in chunk order with ld = M_max, W the packed float16 copy made by launch_pack_weight.
+constexpr int kCUs = 256;
 enum GemmEpilogue { EPI_RESID_ADD = 1, EPI_SWIGLU = 2, EPI_STORE_F32 = 3 };
 constexpr int kMaxGemmSplit = 8;
 // Time of a float32-result GEMM launch in units of 0.01 us, without its fixed part: rounds of the CUs (cap = two workgroups per CU)
@@ -375,8 +378,47 @@ struct SlabCount {
 };
 // The GEMMs of a layer that write slabs.
 enum SlabGemm { SLAB_QKV = 0, SLAB_O = 1, SLAB_DOWN = 2 };
-struct SlabRules { SlabRule r[3]; };
-SlabRules gemm_slab_rules(const Shape& s, int M_max);
+// Tile of a launch whose best one depends on the step's row count, decided on the device like a slab choice (evaluated by every workgroup of every
+// layer, a choice between six tiles had 283 instructions in front of the first load, 156 now): the tile of least time, rounds of the CUs x K tiles x time of one + what is not
+// per K tile (fill, epilogue), 0.01 us.
+struct TileRule {
+  static constexpr int kMost = 8;
+  struct Tile { int rows, blocks, t, fixed; };           // blocks: column blocks of the matrix
+  int at = 0, grid = 0;                                  // where the choice is; most workgroups that any row count of the step takes
+  int nk = 0, n = 0;
+  Tile tile[kMost] = {};
+  __host__ __device__ int blocks(int i, int M) const { return (M + tile[i].rows - 1) / tile[i].rows * tile[i].blocks; }
+  __host__ __device__ long long cost(int i, int M) const { return (long long)((blocks(i, M) + kCUs - 1) / kCUs) * (nk * tile[i].t) + tile[i].fixed; }
+  __host__ __device__ int choice(int M) const {
+    int best = 0;
+    long long least = 0;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+      if (i >= n) break;
+      const long long c = cost(i, M);
+      if (i == 0 || c < least) { best = i; least = c; }
+    }
+    return best;
+  }
+  // The choice changes only where the number of row blocks of some tile does: behind multiples of 32 rows.
+  void size_grid(int M_max) {
+    grid = 0;
+    for (int M = 32; M < M_max + 32; M += 32) {
+      const int m = M < M_max ? M : M_max, b = blocks(choice(m), m);
+      grid = b > grid ? b : grid;
+    }
+  }
+};
+// The rules of a step, made once on the host, and the place of each choice behind the row count and the number of drafts (Plan::n_rows).
+struct StepRules { SlabRule slab[3]; TileRule qkv; };
+enum StepChoice { CHOICE_SLABS = 2, CHOICE_QKV = CHOICE_SLABS + 3 };
+void gemm_slab_rules(const Shape& s, int M_max, SlabRule (&r)[3]);
+inline StepRules step_rules(const Shape& s, int M_max) {
+  StepRules r;
+  gemm_slab_rules(s, M_max, r.slab);
+  r.qkv = qkv_rope_rule(s, M_max);
+  return r;
+}
 // status: the step's device status word (float16-range faults of the float16 epilogues).  rule: gemm_slab_rules, made once per step
 // (EPI_RESID_ADD / EPI_STORE_F32 of bf16 models; made in each launch it kept steps of small models waiting for the host).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
 // and the consumer sums them), none where `out` was updated in place (float32 models).

@@ -404,11 +404,11 @@ static SlabRule slab_rule(int M_max, int N, int nk, int at) {
   }
   return r;
 }
-constexpr int kChoiceAt = 2;                             // Plan::n_rows: rows, drafts, then a choice per SlabGemm
-SlabRules gemm_slab_rules(const Shape& s, int M_max) {
-  if (s.dtype != BS_BF16) return SlabRules{};
-  return SlabRules{{slab_rule(M_max, s.Nqkv(), s.d / kBK, kChoiceAt + SLAB_QKV), slab_rule(M_max, s.d, s.Hq * s.D / kBK, kChoiceAt + SLAB_O),
-                    slab_rule(M_max, s.d, s.F / kBK, kChoiceAt + SLAB_DOWN)}};
+void gemm_slab_rules(const Shape& s, int M_max, SlabRule (&r)[3]) {
+  if (s.dtype != BS_BF16) return;
+  r[SLAB_QKV] = slab_rule(M_max, s.Nqkv(), s.d / kBK, CHOICE_SLABS + SLAB_QKV);
+  r[SLAB_O] = slab_rule(M_max, s.d, s.Hq * s.D / kBK, CHOICE_SLABS + SLAB_O);
+  r[SLAB_DOWN] = slab_rule(M_max, s.d, s.F / kBK, CHOICE_SLABS + SLAB_DOWN);
 }
 static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& r, hipStream_t st) {
 #define BS_SLAB(T_) launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r.fixed, st)

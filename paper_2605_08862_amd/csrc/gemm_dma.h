@@ -26,8 +26,6 @@ __device__ __forceinline__ int xcd_flat(int total) {
   return (int)(blockIdx.x / 8) < per_xcd && flat < total ? flat : -1;
 }
 
-constexpr int kCUs = 256;
-
 template <int MW_, int NW_, int WM_, int WN_, int NST_>
 struct DmaGemm {
   static constexpr int MW = MW_, NW = NW_, WM = WM_, WN = WN_, NST = NST_;

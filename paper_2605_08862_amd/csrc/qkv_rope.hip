@@ -144,8 +144,7 @@ __global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, Q
   if (bm == 64) qkv_tile<Rows64>(p, g, m0, head, lds);
   else qkv_tile<Rows128>(p, g, m0, head, lds);
 }
-// Many rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count: rounds of the CUs x K tiles x time
-// of one + fill and epilogue, 0.01 us.  The tiles above read 1.5 fragments from LDS per product and are bound by that, these 0.6 .. 1.  Times are
+// Many rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count (TileRule).  The tiles above read 1.5 fragments from LDS per product and are bound by that, these 0.6 .. 1.  Times are
 // those of the loops with float32 results and weights that no cache holds, 64 / 96 / 128 / 160 / 192 rows of a head and 128 rows of two heads:
 //   36 heads, K 3584   720 rows 40.6 / 44.8 / 32.0 / 33.0 / 38.3 / 45.8 us   1152 rows 58 / 51 / 58 / 56 / 40.8 / 47.5   1500 rows 77 / 67 / 59 / 63 / 74 / 48.2
 //   16 heads, K 1536   816 rows 12.8 / 13.7 / 14.6 / 15.6 / 17.5 / 22.1   1037 rows 16.7 / 15.1 / 14.3 / 16.9 / 17.9 / 22.2   3740 rows 41 / 38 / 34 / 34 / 34 / 28.1
@@ -155,37 +154,25 @@ typedef StreamGemm<4, 1, 4, 3> Many128;
 typedef StreamGemm<5, 1, 4, 3> Many160;
 typedef StreamGemm<6, 1, 4, 4, 2> Many192;
 typedef StreamGemm<4, 2, 4, 2> Many128x2;
-struct ManyPick { int rows, heads, blocks; };
-__host__ __device__ inline ManyPick pick_many(int M, int heads, int nk) {
-  ManyPick best{64, 1, 0};
-  int least = 0x7fffffff;
-  auto consider = [&](int bm, int hp, int t, int fixed) {
-    const int n = (M + bm - 1) / bm * ((heads + hp - 1) / hp), c = (n + kCUs - 1) / kCUs * nk * t + fixed;
-    if (c < least) { least = c; best = ManyPick{bm, hp, n}; }
-  };
-  consider(64, 1, 36, 400);
-  consider(96, 1, 44, 500);
-  consider(128, 1, 50, 400);
-  consider(160, 1, 58, 550);
-  consider(192, 1, 68, 600);
-  consider(128, 2, 80, 600);
-  return best;
-}
 // (Steps with fewer tiles stay where they were: 1024 rows of a model of ten heads are 80.)
 inline bool many_rows(int M_max, int heads) { return M_max > kFewRows && (M_max + 127) / 128 * heads >= 96; }
-__global__ void __launch_bounds__(256, 2) qkv_many_kernel(Plan p, QkvArgs g) {
+// The tile at the place of the step's choice; HP heads per workgroup.
+template <typename G, int HP = G::CT / 4>
+__device__ __forceinline__ void qkv_many_tile(const Plan& p, const QkvArgs& g, int M, char* lds) {
+  const int m_blocks = (M + G::BM - 1) / G::BM, id = xcd_flat(m_blocks * ((g.Hq + 2 * g.Hkv + HP - 1) / HP));
+  if (id >= 0) qkv_tile<G>(p, g, id % m_blocks * G::BM, id / m_blocks * HP, lds);
+}
+__global__ void __launch_bounds__(256, 2) qkv_many_kernel(Plan p, QkvArgs g, int at) {
   extern __shared__ __align__(16) char lds[];
   const int M = min(p.n_rows[0], g.M_max);
-  const ManyPick t = pick_many(M, g.Hq + 2 * g.Hkv, g.K / kBK);
-  const int id = xcd_flat(t.blocks), m_blocks = (M + t.rows - 1) / t.rows;
-  if (id < 0) return;
-  const int m0 = id % m_blocks * t.rows, head = id / m_blocks * t.heads;
-  if (t.heads == 2) qkv_tile<Many128x2>(p, g, m0, head, lds);
-  else if (t.rows == 192) qkv_tile<Many192>(p, g, m0, head, lds);
-  else if (t.rows == 160) qkv_tile<Many160>(p, g, m0, head, lds);
-  else if (t.rows == 128) qkv_tile<Many128>(p, g, m0, head, lds);
-  else if (t.rows == 96) qkv_tile<Many96>(p, g, m0, head, lds);
-  else qkv_tile<Many64>(p, g, m0, head, lds);
+  switch (p.n_rows[at]) {                                // places in qkv_rope_rule's list
+    case 0: qkv_many_tile<Many64>(p, g, M, lds); break;
+    case 1: qkv_many_tile<Many96>(p, g, M, lds); break;
+    case 2: qkv_many_tile<Many128>(p, g, M, lds); break;
+    case 3: qkv_many_tile<Many160>(p, g, M, lds); break;
+    case 4: qkv_many_tile<Many192>(p, g, M, lds); break;
+    default: qkv_many_tile<Many128x2>(p, g, M, lds);
+  }
 }
 template <auto KERN, typename... Args>
 void launch_one(int blocks, int threads, int lds, hipStream_t st, const Args&... args) {
@@ -208,21 +195,24 @@ bool qkv_rope_applies(const Shape& s, int M_max) {
   return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 440 + M_max * s.Nqkv() / 5760;
 }
 
-void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const void* A, const void* Wp,
+TileRule qkv_rope_rule(const Shape& s, int M_max) {
+  const int heads = s.Hq + 2 * s.Hkv, pairs = (heads + 1) / 2;
+  TileRule r;
+  if (s.dtype != BS_BF16 || s.D != kD || !many_rows(M_max, heads)) return r;
+  r = TileRule{CHOICE_QKV, 0, s.d / kBK, 6, {{64, heads, 36, 400}, {96, heads, 44, 500}, {128, heads, 50, 400}, {160, heads, 58, 550}, {192, heads, 68, 600}, {128, pairs, 80, 600}}};
+  r.size_grid(M_max);
+  return r;
+}
+
+void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const TileRule& rule, const void* A, const void* Wp,
                      const float* cos_t, const float* sin_t, void* q_out, void* k_pages, void* v_pages, hipStream_t st) {
   const int heads = s.Hq + 2 * s.Hkv;
   const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages};
   constexpr auto most = [](std::initializer_list<int> v) { int m = 0; for (int x : v) m = x > m ? x : m; return m; };
-  if (many_rows(M_max, heads)) {
+  if (rule.at) {
     constexpr int lds = most({Many64::LDS_BYTES, Many96::LDS_BYTES, Many128::LDS_BYTES, Many160::LDS_BYTES, Many192::LDS_BYTES, Many128x2::LDS_BYTES});
     static_assert(2 * lds <= 160 * 1024, "two workgroups per CU");
-    // the most workgroups that any row count takes; the choice changes only with the number of tiles of some size, multiples of 32 rows
-    int blocks = 0;
-    for (int M = 32; M < M_max + 32; M += 32) {
-      const int n = pick_many(M < M_max ? M : M_max, heads, s.d / kBK).blocks;
-      blocks = n > blocks ? n : blocks;
-    }
-    launch_one<qkv_many_kernel>(blocks, 256, lds, st, p, g);
+    launch_one<qkv_many_kernel>(rule.grid, 256, lds, st, p, g, rule.at);
     return;
   }
   if (M_max > kFewRows) {
