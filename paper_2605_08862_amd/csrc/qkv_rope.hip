@@ -92,70 +92,38 @@ __global__ void __launch_bounds__(G::THREADS) qkv_kernel(Plan p, QkvArgs g, int 
   const int id = xcd_flat(m_blocks * (g.Hq + 2 * g.Hkv));
   if (id >= 0) qkv_tile<G>(p, g, id % m_blocks * G::BM, id / m_blocks, lds);
 }
-// Rows of a workgroup's tile, with the time of one K tile in 0.01 us when a launch fills the CUs once.  The first stages, the epilogue
-// and the launch's ragged start take as long as about 8 K tiles.  Measured, 16 heads, K 1536 / 36 heads, K 3584:
+// Up to 640 rows the tile follows from the row limit: time of one K tile in 0.01 us when a launch fills the CUs once; the first stages, the
+// epilogue and the launch's ragged start take as long as about 8 K tiles.  Measured, 16 heads, K 1536 / 36 heads, K 3584:
 //   432 rows  32: 11.8 us, 64: 14.6, 128: 18.9     576 rows  32: 15.8, 64: 15.0, 128: 18.0
-//   1024 rows 64: 15.5, 128: 18.5, 192: 22         2048 rows 64: 26.3, 128: 20.2, 192: 24     3700 rows 64: 48, 128: 33.5, 192: 46
-//   64 rows   32: 24, 64: 28.5     288 rows 32: 35, 64: 26.6     816 rows 64: 50, 128: 36, 192: 41
-//   1185 rows 64: 73, 128: 57, 192: 49             2048 rows 64: 119, 128: 86, 192: 90
-// 128 and 192 rows are eight and twelve waves of two accumulator tiles and 80 KB, so that two workgroups share a CU and one's epilogue
-// runs beside the other's loop.  In four waves of six tiles 192 rows take 54 us at 1185 rows, 57 at 3700; 256 rows in one workgroup
-// per CU take 51 and 33, but a kernel that offers them has one workgroup per CU for every tile (128 rows: 62 and 39).
-// Up to 640 rows the weights of the small tiles are in registers (StreamGemm).  Beyond, the tile is chosen on the device: a workgroup
-// has twelve waves, of which four or eight leave at once where the tile has eight or four.  32 rows are for steps with few live rows.
+//   64 rows   32: 24, 64: 28.5     288 rows 32: 35, 64: 26.6
+// 128 rows are eight waves of two accumulator tiles and 80 KB, so that two workgroups share a CU and one's epilogue runs beside the other's loop; the
+// weights of the small tiles are in registers (StreamGemm).
 typedef StreamGemm<1, 1, 4, 6> Few32;
 typedef StreamGemm<2, 1, 4, 4> Few64;
-typedef DmaGemm<1, 1, 1, 4, 8> Rows32;
-typedef DmaGemm<1, 1, 2, 4, 6> Rows64;
 typedef DmaGemm<1, 2, 4, 2, 5> Rows128;
-typedef DmaGemm<1, 2, 6, 2, 4> Rows192;
-__host__ __device__ inline int rows_cost(int M, int bm, int heads, int nk, int t) { return ((M + bm - 1) / bm * heads + kCUs - 1) / kCUs * (nk + 8) * t; }
-constexpr int kRows32Tiles = 2 * kCUs;                   // most 32-row tiles that the launch of the device's choice is sized for
-__host__ __device__ inline int pick_rows(int M, int heads, int nk, bool few, int& cost) {
+inline int pick_rows(int M, int heads, int nk, int& cost) {
+  auto time = [&](int bm, int t) { return ((M + bm - 1) / bm * heads + kCUs - 1) / kCUs * (nk + 8) * t; };
   int bm = 128;
-  cost = rows_cost(M, 128, heads, nk, 48);
-  int c = rows_cost(M, 64, heads, nk, 37);
+  cost = time(128, 48);
+  int c = time(64, 37);
   if (c < cost) { bm = 64; cost = c; }
-  c = rows_cost(M, 32, heads, nk, 31);
-  if ((few || (M + 31) / 32 * heads <= kRows32Tiles) && c < cost) { bm = 32; cost = c; }
-  c = rows_cost(M, 192, heads, nk, 72);
-  if (!few && c < cost) { bm = 192; cost = c; }
+  c = time(32, 31);
+  if (c < cost) { bm = 32; cost = c; }
   return bm;
 }
 constexpr int kFewRows = 640;
-// More rows than that, but few tiles: the rows of a tile from the step's row count.
-__global__ void __launch_bounds__(Rows192::THREADS, 6) qkv_rows_kernel(Plan p, QkvArgs g) {
-  extern __shared__ __align__(16) char lds[];
-  const int M = min(p.n_rows[0], g.M_max), heads = g.Hq + 2 * g.Hkv;
-  int cost;
-  const int bm = pick_rows(M, heads, g.K / kBK, false, cost), m_blocks = (M + bm - 1) / bm;
-  const int id = xcd_flat(m_blocks * heads);
-  if (id < 0) return;
-  const int m0 = id % m_blocks * bm, head = id / m_blocks;
-  if (bm == 192) {
-    qkv_tile<Rows192>(p, g, m0, head, lds);
-    return;
-  }
-  if (bm == 32) {
-    if (threadIdx.x < Rows32::THREADS) qkv_tile<Rows32>(p, g, m0, head, lds);
-    return;
-  }
-  if (threadIdx.x >= 512) return;
-  if (bm == 64) qkv_tile<Rows64>(p, g, m0, head, lds);
-  else qkv_tile<Rows128>(p, g, m0, head, lds);
-}
-// Many rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count (TileRule).  The tiles above read 1.5 fragments from LDS per product and are bound by that, these 0.6 .. 1.  Times are
-// those of the loops with float32 results and weights that no cache holds, 64 / 96 / 128 / 160 / 192 rows of a head and 128 rows of two heads:
-//   36 heads, K 3584   720 rows 40.6 / 44.8 / 32.0 / 33.0 / 38.3 / 45.8 us   1152 rows 58 / 51 / 58 / 56 / 40.8 / 47.5   1500 rows 77 / 67 / 59 / 63 / 74 / 48.2
-//   16 heads, K 1536   816 rows 12.8 / 13.7 / 14.6 / 15.6 / 17.5 / 22.1   1037 rows 16.7 / 15.1 / 14.3 / 16.9 / 17.9 / 22.2   3740 rows 41 / 38 / 34 / 34 / 34 / 28.1
-typedef StreamGemm<2, 1, 4, 4> Many64;
+// More rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count (TileRule).  Rows128 reads 1.5 fragments
+// from LDS per product and is bound by that, these 0.6 .. 1.  Times of the kernels by themselves, weights that no cache holds, 32 / 64 / 96 / 128 / 160 / 192 rows of a
+// head and 128 rows of two heads (the rule's times lose least against the fastest tile over 20 .. 4352 rows of 8 shapes, from 12 heads and K 512 to 48 heads and K 4096):
+//   16 heads, K 1536   128 rows 11.6 / 13.9 / 14.4 / 19.3 / 19.7 / 19.8 / 29.8 us   505 rows 11.8 / 13.9 / 14.8 / 19.2 / 18.4 / 22.1 / 28.9   824 rows 16.2 / 13.9 / 15.7 / 17.2 / 18.6 / 21.6 / 28.8
+//                      1200 rows 24.6 / 19.2 / 17.2 / 18.2 / 21.0 / 22.9 / 29.7   2720 rows 46.9 / 34.1 / 30.5 / 36.2 / 34.6 / 27.7 / 32.5
+//   36 heads, K 3584   128 rows 22.8 / 27.0 / 26.5 / 37.4 / 38.0 / 37.9 / 55.4 us   281 rows 35.0 / 25.3 / 32.1 / 28.8 / 38.9 / 37.7 / 50.1   720 rows 62.8 / 42.4 / 47.0 / 35.2 / 36.4 / 42.1 / 51.5
+//                      1200 rows 101 / 64.4 / 53.3 / 58.9 / 63.4 / 48.0 / 53.2   1632 rows 124 / 84.3 / 73.4 / 64.7 / 69.0 / 75.9 / 57.0
 typedef StreamGemm<3, 1, 4, 3> Many96;
 typedef StreamGemm<4, 1, 4, 3> Many128;
 typedef StreamGemm<5, 1, 4, 3> Many160;
 typedef StreamGemm<6, 1, 4, 4, 2> Many192;
 typedef StreamGemm<4, 2, 4, 2> Many128x2;
-// (Steps with fewer tiles stay where they were: 1024 rows of a model of ten heads are 80.)
-inline bool many_rows(int M_max, int heads) { return M_max > kFewRows && (M_max + 127) / 128 * heads >= 96; }
 // The tile at the place of the step's choice; HP heads per workgroup.
 template <typename G, int HP = G::CT / 4>
 __device__ __forceinline__ void qkv_many_tile(const Plan& p, const QkvArgs& g, int M, char* lds) {
@@ -166,11 +134,12 @@ __global__ void __launch_bounds__(256, 2) qkv_many_kernel(Plan p, QkvArgs g, int
   extern __shared__ __align__(16) char lds[];
   const int M = min(p.n_rows[0], g.M_max);
   switch (p.n_rows[at]) {                                // places in qkv_rope_rule's list
-    case 0: qkv_many_tile<Many64>(p, g, M, lds); break;
-    case 1: qkv_many_tile<Many96>(p, g, M, lds); break;
-    case 2: qkv_many_tile<Many128>(p, g, M, lds); break;
-    case 3: qkv_many_tile<Many160>(p, g, M, lds); break;
-    case 4: qkv_many_tile<Many192>(p, g, M, lds); break;
+    case 0: qkv_many_tile<Few32>(p, g, M, lds); break;
+    case 1: qkv_many_tile<Few64>(p, g, M, lds); break;
+    case 2: qkv_many_tile<Many96>(p, g, M, lds); break;
+    case 3: qkv_many_tile<Many128>(p, g, M, lds); break;
+    case 4: qkv_many_tile<Many160>(p, g, M, lds); break;
+    case 5: qkv_many_tile<Many192>(p, g, M, lds); break;
     default: qkv_many_tile<Many128x2>(p, g, M, lds);
   }
 }
@@ -191,15 +160,16 @@ bool qkv_rope_applies(const Shape& s, int M_max) {
   if (s.dtype != BS_BF16 || s.D != kD) return false;
   if (M_max > kFewRows) return true;
   int cost;
-  pick_rows(M_max, s.Hq + 2 * s.Hkv, s.d / kBK, true, cost);
+  pick_rows(M_max, s.Hq + 2 * s.Hkv, s.d / kBK, cost);
   return cost + 300 <= gemm_slab_time(M_max, s.Nqkv(), s.d) + 440 + M_max * s.Nqkv() / 5760;
 }
 
 TileRule qkv_rope_rule(const Shape& s, int M_max) {
   const int heads = s.Hq + 2 * s.Hkv, pairs = (heads + 1) / 2;
   TileRule r;
-  if (s.dtype != BS_BF16 || s.D != kD || !many_rows(M_max, heads)) return r;
-  r = TileRule{CHOICE_QKV, 0, s.d / kBK, 6, {{64, heads, 36, 400}, {96, heads, 44, 500}, {128, heads, 50, 400}, {160, heads, 58, 550}, {192, heads, 68, 600}, {128, pairs, 80, 600}}};
+  if (s.dtype != BS_BF16 || s.D != kD || M_max <= kFewRows) return r;
+  r = TileRule{CHOICE_QKV, 0, s.d / kBK, 7, {{32, heads, 27, 300}, {64, heads, 33, 375}, {96, heads, 44, 449}, {128, heads, 51, 585}, {160, heads, 61, 567}, {192, heads, 61, 936},
+                                            {128, pairs, 73, 1091}}};
   r.size_grid(M_max);
   return r;
 }
@@ -210,21 +180,14 @@ void launch_qkv_rope(const Shape& s, const Plan& p, int M_max, const TileRule& r
   const QkvArgs g{M_max, s.d, s.Hq, s.Hkv, (const f16*)A, (const f16*)Wp, cos_t, sin_t, (f16*)q_out, (f16*)k_pages, (f16*)v_pages};
   constexpr auto most = [](std::initializer_list<int> v) { int m = 0; for (int x : v) m = x > m ? x : m; return m; };
   if (rule.at) {
-    constexpr int lds = most({Many64::LDS_BYTES, Many96::LDS_BYTES, Many128::LDS_BYTES, Many160::LDS_BYTES, Many192::LDS_BYTES, Many128x2::LDS_BYTES});
+    constexpr int lds = most({Few32::LDS_BYTES, Few64::LDS_BYTES, Many96::LDS_BYTES, Many128::LDS_BYTES, Many160::LDS_BYTES, Many192::LDS_BYTES, Many128x2::LDS_BYTES});
     static_assert(2 * lds <= 160 * 1024, "two workgroups per CU");
     launch_one<qkv_many_kernel>(rule.grid, 256, lds, st, p, g, rule.at);
     return;
   }
-  if (M_max > kFewRows) {
-    constexpr int lds = most({Rows32::LDS_BYTES, Rows64::LDS_BYTES, Rows128::LDS_BYTES, Rows192::LDS_BYTES});
-    static_assert(Rows64::THREADS == 512 && Rows128::THREADS == 512 && 2 * lds <= 160 * 1024, "two workgroups per CU");
-    const int tiles = (M_max + 63) / 64 * heads;
-    launch_one<qkv_rows_kernel>(tiles > kRows32Tiles ? tiles : kRows32Tiles, Rows192::THREADS, lds, st, p, g);
-    return;
-  }
   int cost;
 #define BS_QKV(G_) do { const int mb = (M_max + G_::BM - 1) / G_::BM; launch_one<qkv_kernel<G_>>(mb * heads, G_::THREADS, G_::LDS_BYTES, st, p, g, mb); } while (0)
-  switch (pick_rows(M_max, heads, s.d / kBK, true, cost)) {
+  switch (pick_rows(M_max, heads, s.d / kBK, cost)) {
     case 32: BS_QKV(Few32); break;
     case 64: BS_QKV(Few64); break;
     default: BS_QKV(Rows128);

@@ -51,7 +51,7 @@ def classify(names):
         cls = None
         if "attn_mfma_kernel" in n or "attn_wide_kernel" in n:
             cls, marker = "attention", "attention"
-        elif "qkv_kernel" in n or "qkv_many_kernel" in n or "qkv_rows_kernel" in n or "rope_append_kernel" in n or "skinny_kernelILi0E" in n:
+        elif "qkv_kernel" in n or "qkv_many_kernel" in n or "rope_append_kernel" in n or "skinny_kernelILi0E" in n:
             cls = "gemm_qkv"
         elif re.search(r"glu_(rows_|tail_)?kernel", n):
             cls, marker = "gemm_gate_up", "gate_up"

@@ -45,6 +45,12 @@ def slab_choice(eng, which):
     return v >> 4, v & 15
 
 
+def tile_choice(eng, which):
+    """Place in its rule's list of the tile that the device chose for the last verify step's QKV projection."""
+    at = {"qkv": 5}[which]
+    return int(debug_buffer(eng, 10, at + 1).view(torch.int32)[at].item())
+
+
 def pack_rows(last_token, draft_tokens, draft_len):
     """Token block [last, drafts...] per sequence."""
     return [np.concatenate([[last_token[b]], draft_tokens[b][:draft_len[b]]]).astype(np.int64)

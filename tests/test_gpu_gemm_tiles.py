@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2605_08862_amd import workloads as W
+from tests import helpers as H
 from tests.test_gpu_bf16 import _run_case
 
 pytestmark = pytest.mark.gpu
@@ -71,11 +72,20 @@ def test_normalisation_of_four_rows_per_workgroup(n_last):
 
 @pytest.mark.parametrize("k_b", [[14] * 36 + [0] * 7, [14] * 41 + [13, 0], [16] * 56 + [0] * 12, [16] * 67 + [15, 0], [16] * 87 + [15, 0], [16] * 126 + [15, 0]])
 def test_qkv_tiles_of_many_rows(k_b):
-    """27 heads (an odd number), 18 K tiles: 64 rows of a head (547 of 645 rows), 96 (630), 128 (964 of 1156), 160 (1156 of 1173), 192 (1496 of 1513) and 128
+    """27 heads (an odd number), 18 K tiles: 64 rows of a head (547 of 645 rows), 96 (630, 1496 of 1513), 128 (964 of 1156), 160 (1156 of 1173) and 128
     rows of two heads (2159 of 2176)."""
     desc = W.shape("mini_bf16", n_layers=1, d_model=1152, n_q_heads=21, n_kv_heads=3, d_ffn=448, vocab=333)
     ctx = [int(x) for x in np.random.default_rng(9).integers(0, 70, len(k_b))]
     _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=max(k_b), seed=96, q_mode="onehot", check_kv=len(k_b) == 43)
+
+
+@pytest.mark.parametrize("d_model,heads,k_b,choice", [(1152, (21, 3), [14] + [1] + [0] * 41, 0), (320, (6, 2), [14] * 2 + [3] + [0] * 40, 0), (1536, (42, 6), [14] * 44 + [13, 0], 5)])
+def test_qkv_tiles_of_few_rows_and_of_192(d_model, heads, k_b, choice):
+    """Row limits 645 and 690: 32 rows of a head for steps with few live rows (27 heads, 58 rows; ten heads, 74), 192 rows (54 heads, 24 K tiles, 675 rows)."""
+    desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=heads[0], n_kv_heads=heads[1], d_ffn=448, vocab=333)
+    ctx, seen = [int(x) for x in np.random.default_rng(9).integers(0, 70, len(k_b))], []
+    _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=14, seed=98, q_mode="onehot", check_kv=True, after_step=lambda eng: seen.append(H.tile_choice(eng, "qkv")))
+    assert seen == [choice]
 
 
 @pytest.mark.parametrize("d_model,d_ffn,n_seq", [(1536, 8960, 48), (1536, 8960, 64), (1536, 8960, 71), (320, 18944, 20), (320, 18944, 24)])

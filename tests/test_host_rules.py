@@ -38,6 +38,21 @@ def test_attention_chunk_rule_compares_times_and_avoids_second_rounds(tmp_path):
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
 
 
+def test_tile_rules_fit_their_grids_and_follow_few_rows(tmp_path):
+    """(The rules are the library's own: the program is linked against it.)"""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "tile_rule_check")
+    src = os.path.join(ROOT, "tests", "host", "tile_rule_check.cpp")
+    r = subprocess.run([hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Wno-unused-result", src, "-L" + os.path.dirname(BLD.LIB), "-l:" + os.path.basename(BLD.LIB),
+                        "-Wl,-rpath," + os.path.dirname(BLD.LIB), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("source, kernel, limit, kernels", [("gemm.hip", r"slab_(alt_)?kernel", 300, 12), ("elementwise.hip", r"rmsnorm_(rows_)?kernel|rope_append_kernel", 200, 11),
                                                             ("qkv_rope.hip", r"qkv_many_kernel", 200, 1)])
 def test_launch_rules_are_not_evaluated_in_front_of_the_loads(tmp_path, source, kernel, limit, kernels):
