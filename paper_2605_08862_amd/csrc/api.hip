@@ -472,7 +472,7 @@ bs_status bs_verify_step(bs_ctx* c, int B, const int32_t* seq_slot, const int32_
                             slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.slab[SLAB_O]); }
     launch_rmsnorm(s, p, M_max, c->h, c->slabs, pending, c->mlp_norm[l], c->a, st);
     { ProfScope ps(c, BS_PROF_GEMM_GATE_UP, st);
-      launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, c->w_gate_up[l], c->act, p.status, st); }
+      launch_gemm(s.dtype, EPI_SWIGLU, p.n_rows, M_max, s.F, s.d, c->a, c->w_gate_up[l], c->act, p.status, st, SlabRule{}, rules.glu); }
     { ProfScope ps(c, BS_PROF_GEMM_DOWN, st);
       pending = launch_gemm(s.dtype, EPI_RESID_ADD, p.n_rows, M_max, s.d, s.F, c->act, c->w_down[l],
                             slab_mode ? (void*)c->slabs : (void*)c->h, p.status, st, rules.slab[SLAB_DOWN]); }

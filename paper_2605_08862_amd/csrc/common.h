@@ -144,7 +144,7 @@ template <> __host__ __device__ __forceinline__ int v_index<bf16>(int D, int h, 
 // ---------------------------------------------------------------------------------------------
 struct Plan {
   int32_t* status;      // [1]   BS_FAULT_* bits (sticky until polled)
-  int32_t* n_rows;      // [6]   M, T_d, choices of the slab GEMMs (SlabRule) and of the QKV projection (TileRule)
+  int32_t* n_rows;      // [7]   M, T_d, choices of the slab GEMMs (SlabRule), the QKV and the gate/up projection (TileRule)
   int32_t* row_start;   // [B+1] first packed row of sequence b (k_b+1 rows each)
   int32_t* draft_start; // [B+1] first packed draft row of sequence b (k_b rows each)
   int32_t* seq_k;       // [B]   validated k_b (-1: sequence skipped)
@@ -387,6 +387,8 @@ struct TileRule {
   int at = 0, grid = 0;                                  // where the choice is; most workgroups that any row count of the step takes
   int nk = 0, n = 0;
   Tile tile[kMost] = {};
+  int waves = 4;                                         // of a workgroup
+  int fixed = 0;                                         // at == 0: the launcher's tile for the row limit (0: one row block)
   __host__ __device__ int blocks(int i, int M) const { return (M + tile[i].rows - 1) / tile[i].rows * tile[i].blocks; }
   __host__ __device__ long long cost(int i, int M) const { return (long long)((blocks(i, M) + kCUs - 1) / kCUs) * (nk * tile[i].t) + tile[i].fixed; }
   __host__ __device__ int choice(int M) const {
@@ -410,20 +412,22 @@ struct TileRule {
   }
 };
 // The rules of a step, made once on the host, and the place of each choice behind the row count and the number of drafts (Plan::n_rows).
-struct StepRules { SlabRule slab[3]; TileRule qkv; };
-enum StepChoice { CHOICE_SLABS = 2, CHOICE_QKV = CHOICE_SLABS + 3 };
+struct StepRules { SlabRule slab[3]; TileRule qkv, glu; };
+enum StepChoice { CHOICE_SLABS = 2, CHOICE_QKV = CHOICE_SLABS + 3, CHOICE_GLU };
 void gemm_slab_rules(const Shape& s, int M_max, SlabRule (&r)[3]);
+TileRule gate_up_rule(const Shape& s, int M_max);        // at == 0: one row block, or a float32 model
 inline StepRules step_rules(const Shape& s, int M_max) {
   StepRules r;
   gemm_slab_rules(s, M_max, r.slab);
   r.qkv = qkv_rope_rule(s, M_max);
+  r.glu = gate_up_rule(s, M_max);
   return r;
 }
-// status: the step's device status word (float16-range faults of the float16 epilogues).  rule: gemm_slab_rules, made once per step
-// (EPI_RESID_ADD / EPI_STORE_F32 of bf16 models; made in each launch it kept steps of small models waiting for the host).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
+// status: the step's device status word (float16-range faults of the float16 epilogues).  rule, glu: step_rules, made once per step
+// (EPI_RESID_ADD / EPI_STORE_F32 and EPI_SWIGLU of bf16 models; made in each launch it kept steps of small models waiting for the host).  Returns the slabs written (these GEMMs: `out` is the slab buffer [split][M_max][N]
 // and the consumer sums them), none where `out` was updated in place (float32 models).
 SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                      int32_t* status, hipStream_t st, const SlabRule& rule = SlabRule{});
+                      int32_t* status, hipStream_t st, const SlabRule& rule = SlabRule{}, const TileRule& glu = TileRule{});
 // time (0.01 us, without the fixed part of a launch) of an EPI_STORE_F32 launch of at most 640 rows
 int gemm_slab_time(int M_max, int N, int K);
 size_t packed_weight_elems(int N, int K);

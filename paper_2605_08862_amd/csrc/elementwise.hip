@@ -5,7 +5,7 @@
 #include "common.h"
 #include <type_traits>
 
-constexpr int kRuleGroups = 4;
+constexpr int kRuleGroups = 5;
 // Token embedding of every packed row and, in the same launch, the row's rotary cos / sin table entries (the table
 // [M_max][D/2] is shared by all layers of the step).
 template <typename T>
@@ -19,6 +19,7 @@ __global__ void __launch_bounds__(256) embed_kernel(Plan p, KvView kv, int M_max
     for (int i = 0; i < 3; ++i)
       if (r == M_max + i && rules.slab[i].at) p.n_rows[rules.slab[i].at] = pack_choice(rules.slab[i].choice(p.n_rows[0]));
     if (r == M_max + 3 && rules.qkv.at) p.n_rows[rules.qkv.at] = rules.qkv.choice(p.n_rows[0]);
+    if (r == M_max + 4 && rules.glu.at) p.n_rows[rules.glu.at] = rules.glu.choice(p.n_rows[0]);
     return;
   }
   if (r >= p.n_rows[0]) return;
@@ -404,7 +405,7 @@ __global__ void __launch_bounds__(256) kv_copy_f16_kernel(KvView kv, int Hkv, in
 
 void launch_embed(const Shape& s, const Plan& p, const KvView& kv, int M_max, const StepRules& rules, const void* embed, float* h, const double* inv_freq,
                   float* cos_t, float* sin_t, hipStream_t st) {
-  const int grid = M_max + (rules.slab[0].at || rules.qkv.at ? kRuleGroups : 0);
+  const int grid = M_max + (rules.slab[0].at || rules.qkv.at || rules.glu.at ? kRuleGroups : 0);
   if (s.dtype == BS_F32)
     hipLaunchKernelGGL(embed_kernel<float>, dim3(grid), dim3(256), 0, st, p, kv, M_max, rules, s.d, (const float*)embed, h, s.D, inv_freq, cos_t, sin_t);
   else

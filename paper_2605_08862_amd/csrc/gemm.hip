@@ -170,28 +170,59 @@ __device__ __forceinline__ void glu_tile(const GluArgs& g, int m_blocks, int id,
   };
   G::run(g.K / 32, lds, operands, finish);
 }
-// A launch with a CU for every workgroup (ONE_ROUND) does not wait for the row count before its first loads (rows beyond
-// it are stale rows of the same buffer, each affecting only its own output row).  Where workgroups share a CU, or wait for one, the
-// row blocks beyond the count are left out (1.5B shape, 80 of 720 rows, 420 workgroups, two to a CU: 40.7 us, 25.0 without them).
+// Tile fixed by the launch, a CU for every workgroup: it does not wait for the row count before its first loads (rows beyond it are stale rows of the
+// same buffer, each affecting only its own output row).
 constexpr int kFewRows = 320;
-template <typename G, bool ONE_ROUND>
+template <typename G>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_kernel(GluArgs g, int m_blocks, int n_blocks) {
   extern __shared__ __align__(16) char lds[];
-  if (!ONE_ROUND) m_blocks = (min(*g.n_rows_dev, g.M_max) + G::BM - 1) / G::BM;
   const int id = xcd_flat(m_blocks * n_blocks);
   if (id >= 0) glu_tile<G>(g, m_blocks, id, lds);
 }
-// The same with a last row block of at most 64 live rows as one of 64 (1.5B shape, 390 of 702 rows: 43 us with the blocks beyond the count and a
-// whole last one, 40.6 here).
-template <typename G, typename GT>
-__global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) glu_tail_kernel(GluArgs g, int n_blocks) {
-  static_assert(GT::CT == G::CT && GT::THREADS == G::THREADS && GT::LDS_BYTES <= G::LDS_BYTES && G::LDS_BYTES <= 64 * 1024, "");
-  extern __shared__ __align__(16) char lds[];
-  const int M = min(*g.n_rows_dev, g.M_max), m_blocks = (M + G::BM - 1) / G::BM;
-  const int id = xcd_flat(m_blocks * n_blocks);
+// Rows and columns of a workgroup from the step's row count (glu_rule; Plan::n_rows[at]: place in its list).  Row blocks beyond the count are left out, and a
+// last one of at most GT::BM live rows is one of GT (1.5B shape, 390 of 702 rows: 43 us with a whole last one, 40.6 here).
+template <typename G, typename GT = G>
+__device__ __forceinline__ void glu_rows(const GluArgs& g, int M, char* lds) {
+  static_assert(GT::CT == G::CT && GT::THREADS == G::THREADS && GT::LDS_BYTES <= G::LDS_BYTES, "");
+  const int m_blocks = (M + G::BM - 1) / G::BM, id = xcd_flat(m_blocks * ((g.F / 16 + G::CT - 1) / G::CT));
   if (id < 0) return;
-  if (M - id % m_blocks * G::BM <= GT::BM) glu_tile<GT, G::BM>(g, m_blocks, id, lds);
+  if (!std::is_same<G, GT>::value && M - id % m_blocks * G::BM <= GT::BM) glu_tile<GT, G::BM>(g, m_blocks, id, lds);
   else glu_tile<G>(g, m_blocks, id, lds);
+}
+// Four waves, two workgroups per CU: one's fill and epilogue run beside the other's products, and the last round of the CUs is a fine one.  64 features
+// per workgroup (weights of 16 in a wave) for few row blocks, 128 for many.
+typedef StreamGemm<3, 2, 4, 2> Glu96;
+typedef StreamGemm<4, 2, 4, 2> Glu128;
+typedef StreamGemm<2, 1, 4, 4> Glu64x64;
+typedef StreamGemm<6, 1, 4, 4, 2> Glu192x64;
+__global__ void __launch_bounds__(256, 2) glu_w4_kernel(GluArgs g, int at) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(*g.n_rows_dev, g.M_max);
+  switch (g.n_rows_dev[at]) {
+    case 0: glu_rows<Glu96>(g, M, lds); break;
+    case 1: glu_rows<Glu128, StreamGemm<2, 2, 4, 2>>(g, M, lds); break;
+    case 2: glu_rows<Glu64x64>(g, M, lds); break;
+    default: glu_rows<Glu192x64>(g, M, lds);
+  }
+}
+// Eight waves of one weight tile each, one workgroup per CU: a weight is read by fewer workgroups, and its round by a whole CU.
+typedef StreamGemm<3, 1, 8, 3> Wide96;
+typedef StreamGemm<4, 1, 8, 3> Wide128;
+typedef StreamGemm<5, 1, 8, 3> Wide160;
+typedef StreamGemm<6, 1, 8, 3> Wide192;
+typedef StreamGemm<7, 1, 8, 2> Wide224;
+typedef DmaGemm<4, 2, 2, 4, 4> Wide256;
+__global__ void __launch_bounds__(512, 2) glu_w8_kernel(GluArgs g, int at) {
+  extern __shared__ __align__(16) char lds[];
+  const int M = min(*g.n_rows_dev, g.M_max);
+  switch (g.n_rows_dev[at]) {
+    case 0: glu_rows<Wide96>(g, M, lds); break;
+    case 1: glu_rows<Wide128>(g, M, lds); break;
+    case 2: glu_rows<Wide160>(g, M, lds); break;
+    case 3: glu_rows<Wide192>(g, M, lds); break;
+    case 4: glu_rows<Wide224>(g, M, lds); break;
+    default: glu_rows<Wide256>(g, M, lds);
+  }
 }
 // ---- float32 results (O and down projections, unfused QKV projection): one partial [M_max, N] slab per K split,
 // out[split][m][n]; the consumer (RMSNorm, rotary kernel) sums the slabs.  Float atomics into the residual were measured at
@@ -224,7 +255,7 @@ __device__ __forceinline__ void slab_tile(const int32_t* __restrict__ n_rows_dev
   };
   G::run(s1 - s0, lds, operands, finish);
 }
-// Tile and number of splits fixed by the launch (see glu_kernel).
+// Tile and number of splits fixed by the launch, which does not wait for the row count either.
 template <typename G>
 __global__ void __launch_bounds__(G::THREADS, (G::WGS * G::WAVES + 3) / 4) slab_kernel(const int32_t* __restrict__ n_rows_dev, int M_max, int N, int K, const f16* __restrict__ A,
                                                           const f16* __restrict__ Wp, float* __restrict__ out, int n_blocks, int n_split) {
@@ -259,24 +290,65 @@ static int grid8(int n) { return (n + 7) / 8 * 8; }
 template <typename G>
 static void launch_glu_t(const GluArgs& g, hipStream_t st) {
   const int m_blocks = (g.M_max + G::BM - 1) / G::BM, n_blocks = (g.F / 16 + G::CT - 1) / G::CT;
-  auto go = [&](auto kern, bool& done) {
-    allow_lds(kern, G::LDS_BYTES, done);
-    hipLaunchKernelGGL(kern, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
-  };
-  static bool one = false, more = false;
-  if (m_blocks * n_blocks <= kCUs) go(glu_kernel<G, true>, one);
-  else go(glu_kernel<G, false>, more);
+  static bool done = false;
+  allow_lds(glu_kernel<G>, G::LDS_BYTES, done);
+  hipLaunchKernelGGL(glu_kernel<G>, dim3(grid8(m_blocks * n_blocks)), dim3(G::THREADS), G::LDS_BYTES, st, g, m_blocks, n_blocks);
 }
 // Measured in us (gate/up of the 1.5B shape, 8960 features, and of the 7B shape, 18944; the loops with weights in registers and
 // activations staged through registers that were here before in brackets; 7B at 64, 288 and 1185 rows and 1.5B from 432 rows in whole steps):
 //   64 rows 13.3 (22.3) / 48.7 (55.0)    144 rows 18.6 (28.7) / 59.4 (73.4)    288 rows 22.9 (31.6) / 80.1 (104)
 //   432 rows 28.9 (44.7)    576 rows 33.9 (41.4)    1037 rows 58.4 (73.0)    1152 rows - / 254 (324)    3480 rows 157.6 (190.9)
-static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const void* A, const void* W, void* out, int32_t* status, hipStream_t st) {
+static bool glu_wide(int F) { return F / 16 > 3 * kCUs; }   // more columns than 256 workgroups of three waves with 16 features each take
+static bool glu_mix(int F, int K) { return packed_weight_elems(F, K) * 2 < ((size_t)1 << 32); }   // the mixed tiles address the up rows with a 32-bit offset
+// One row block for all rows of the limit (a wide matrix: up to 320 rows), columns in steps of 16 features per wave: launch_glu.  Where a tile of at most 192 rows takes one
+// round of the CUs, up to 640 rows, it is fixed, too: a launch that reads the step's choice first took 0.4 us more (1.5B shape, 576 rows).  Otherwise the tile follows from the step's
+// row count, in one of two launch shapes: four waves and two workgroups per CU, or eight and one.  Measured by themselves with weights that no cache holds, us,
+// 96 / 128 rows x 128 features and 64 / 192 rows x 64 in four waves | 96 / 128 / 160 / 192 / 224 / 256 rows x 128 features in eight:
+//   8960 x 1536,   43 rows  21.3 / 21.2 / 14.1 / 16.1 | 21.3 / 21.4 / 22.4 / 23.3 / 29.2 / 30.4
+//   8960 x 1536,  134 rows  22.1 / 21.9 / 21.8 / 19.4 | 22 / 21.8 / 26.6 / 27.3 / 30.9 / 32
+//   8960 x 1536,  277 rows  23.5 / 23.3 / 31.6 / 31.6 | 24.3 / 23.6 / 27.4 / 29.4 / 34.2 / 37.3
+//   8960 x 1536,  432 rows  38.3 / 38.1 / 40.6 / 33.6 | 39.1 / 39.7 / 28.3 / 31.9 / 35 / 38.2
+//   8960 x 1536, 1037 rows  64.4 / 59.4 / 85.3 / 64 | 68.7 / 66.8 / 57.6 / 63.6 / 70.4 / 76.5
+//   18944 x 3584,   43 rows  52.6 / 52.6 / 63.5 / 80 | 52.3 / 52.4 / 54.5 / 56.6 / 72.6 / 78.1
+//   18944 x 3584,  134 rows  90.4 / 88 / 90.4 / 80.9 | 90.6 / 101 / 63.3 / 64.9 / 75 / 78.4
+//   18944 x 3584,  240 rows  89.3 / 102 / 114 / 101 | 90.7 / 108 / 113 / 120 / 142 / 80.4
+//   18944 x 3584,  277 rows  94.2 / 92.4 / 133 / 103 | 95.8 / 98 / 118 / 122 / 143 / 156
+//   18944 x 3584,  505 rows  153 / 138 / 214 / 151 | 159 / 153 / 162 / 131 / 153 / 160
+//   18944 x 3584, 1037 rows  271 / 253 / 394 / 256 | 282 / 279 / 278 / 261 / 236 / 261
+//   18944 x 3584, 2000 rows  465 / 436 / 757 / 481 | 486 / 492 / 456 / 467 / 452 / 438
+// The times of the rule lose least against the fastest tile, of each shape and of both, at 16 .. 3000 rows of those and of 11008 x 4096, 5632 x 2048, 9728 x 2560 and 1408 x 512
+// (features x K).  The launch shape can only follow from the row limit: the faster one there (among tiles of 128 rows and more: with fewer, eight waves gain nothing).
+//   Fewer than 32 K tiles: four waves above 640 rows, where eight gain 3 % of a full step at best and lose 10 % at 3/4 of the limit (8960 x 1536, 800 of 1037 rows 42.3 / 46.9 us).
+//   More: eight waves also where a full step loses up to 6 %, since steps of few live rows gain more (18944 x 3584, 134 of 714 rows 63.3 / 80.9, all 720 169 / 174; 11008 x 4096, 505 of
+//   720 rows 92 / 112), but above 1280 rows only where it gains 3 % (18944 x 3584, 1500 rows 343 / 314: the last round of whole CUs).
+// Tiles fixed by the row limit up to 640 rows, and of 128 rows above, were here before: 7B shape, 280 of 504 rows 124 us (96), 134 of 714 rows 99 (66); 1.5B shape, 197 of 639 rows 33.6 (22).
+static TileRule glu_rule(int M_max, int F, int K) {
+  TileRule r;
+  const bool mix = glu_mix(F, K);
+  if (mix && ((M_max + 31) / 32 <= 5 || (M_max <= kFewRows && glu_wide(F)))) return r;
+  const int n64 = F / 64, n128 = (F + 127) / 128, nk = K / kBK;
+  const TileRule w4{CHOICE_GLU, 0, nk, mix ? 4 : 2, {{96, n128, 78, 350}, {128, n128, 78, 400}, {64, n64, 40, 300}, {192, n64, 70, 400}}};
+  const TileRule w8{CHOICE_GLU, 0, nk, 6, {{96, n128, 80, 550}, {128, n128, 90, 630}, {160, n128, 102, 710}, {192, n128, 112, 790}, {224, n128, 132, 870}, {256, n128, 135, 950}}};
+  if (M_max <= 640) {
+    const TileRule one{0, 0, nk, mix ? 4 : 2, {w4.tile[0], w4.tile[1], w8.tile[2], w8.tile[3]}};
+    const int c = one.choice(M_max);
+    if (one.blocks(c, M_max) <= kCUs) { r.fixed = 1 + c; return r; }
+  }
+  r = w4;
+  if (mix) {
+    const int per_cent = nk < 32 ? (M_max <= 640 ? 100 : 0) : M_max <= 1280 ? 106 : 97;
+    long long least = w8.cost(1, M_max);
+    for (int i = 2; i < w8.n; ++i) least = w8.cost(i, M_max) < least ? w8.cost(i, M_max) : least;
+    if (least * 100 <= r.cost(r.choice(M_max), M_max) * per_cent) { r = w8; r.waves = 8; }
+  }
+  r.size_grid(M_max);
+  return r;
+}
+static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const void* A, const void* W, void* out, int32_t* status, const TileRule& rule, hipStream_t st) {
   const GluArgs g{n_rows_dev, M_max, F, K, (const f16*)A, (const f16*)W, (f16*)out, status};
-  const int rt = (M_max + 31) / 32, n128 = (F + 127) / 128;
-  const bool wide = F / 16 > 3 * kCUs;                   // more columns than 256 workgroups of three waves with 16 features each take
-  const bool mix = packed_weight_elems(F, K) * 2 < ((size_t)1 << 32);      // the mixed tiles address the up rows with a 32-bit offset
-  if (rt <= 5 && mix) {
+  const int rt = (M_max + 31) / 32;
+  const bool wide = glu_wide(F);
+  if (!rule.at && !rule.fixed && rt <= 5) {
     // one row block, columns in steps of 16 features per wave: one workgroup per CU
     if (wide) {
       if (rt <= 2) launch_glu_t<StreamGemm<2, 1, 5, 3>>(g, st);
@@ -291,7 +363,14 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     }
     return;
   }
-  if (M_max <= kFewRows && wide && mix) {
+  switch (rule.fixed) {
+    case 1: launch_glu_t<Glu96>(g, st); return;
+    case 2: launch_glu_t<Glu128>(g, st); return;
+    case 3: launch_glu_t<Wide160>(g, st); return;
+    case 4: launch_glu_t<Wide192>(g, st); return;
+    default: break;
+  }
+  if (!rule.at) {
     // the same, for more than seven row tiles with two or three groups of waves side by side in the rows and both operands copied to LDS (192 / 224 rows by
     // themselves 68 / 74 us, 60.5 / 67 here; 288 rows 87, 95 with 96-row tiles of 128 features)
     if (rt == 6) launch_glu_t<StreamGemm<6, 1, 5, 4, 2>>(g, st);
@@ -301,29 +380,18 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
     else launch_glu_t<DmaGemm<5, 1, 2, 5, 5>>(g, st);
     return;
   }
-  if (M_max <= 640) {
-    // 128 features per workgroup; rows by rounds of the CUs x (K tiles x time of one + fill and epilogue), 0.01 us.  96 and 128 rows are four waves, two
-    // workgroups per CU, from 160 rows on eight waves of one weight tile: two waves per SIMD either way (160 rows in four waves, one per SIMD,
-    // 32.2 us where eight take 27.6).  Measured with weights that no cache holds, 96 / 128 / 160 / 192 / 224 rows per workgroup: 7B shape 400 rows 124 / 129 / 112
-    // / 138 / 146 us, 512 rows 153 / 139 / 162 / 132 / 159; 1.5B shape 384 rows 37 / 26.1 / 27 / 32 / 35, 432 rows 37.6 / 38.4 / 27.6 / 32.4 / 35.5,
-    // 576 rows 38.1 / 41.3 / 47 / 33.1 / 37.0, 640 rows 39.3 / 44.2 / 48.9 / 56.8 / 37.9.
-    auto cost = [&](int bm, int t, int fixed) { return ((M_max + bm - 1) / bm * n128 + kCUs - 1) / kCUs * (K / kBK * t + fixed); };
-    const int c[5] = {cost(96, 72, 180), cost(128, 80, 167), cost(160, 91, 730), cost(192, 103, 825), cost(224, 128, 680)};
-    int best = 0;
-    for (int i = 1; i < (mix ? 5 : 2); ++i) if (c[i] < c[best]) best = i;
-    if (best == 0) launch_glu_t<StreamGemm<3, 2, 4, 2>>(g, st);
-    else if (best == 1) launch_glu_t<StreamGemm<4, 2, 4, 2>>(g, st);
-    else if (best == 2) launch_glu_t<StreamGemm<5, 1, 8, 3>>(g, st);
-    else if (best == 3) launch_glu_t<StreamGemm<6, 1, 8, 3>>(g, st);
-    else launch_glu_t<StreamGemm<7, 1, 8, 2>>(g, st);
+  static bool w4 = false, w8 = false;
+  if (rule.waves == 8) {
+    constexpr int lds = Wide256::LDS_BYTES;
+    static_assert(Wide96::LDS_BYTES <= lds && Wide128::LDS_BYTES <= lds && Wide160::LDS_BYTES <= lds && Wide192::LDS_BYTES <= lds && Wide224::LDS_BYTES <= lds, "");
+    allow_lds(glu_w8_kernel, lds, w8);
+    hipLaunchKernelGGL(glu_w8_kernel, dim3(grid8(rule.grid)), dim3(512), lds, st, g, rule.at);
     return;
   }
-  // Many rounds of the CUs: 128-row tiles, two workgroups per CU, so that one's fill and epilogue run beside the other's products and the last round
-  // is a fine one.  Against persistent tiles of up to 256 rows, a workgroup per CU: 7B shape, 832 rows 210 / 215 us, 1024 rows 222 / 269, 1152 rows
-  // 264 / 269, 1408 rows 312 / 349, 2176 rows 460 / 503; 1.5B shape, 1037 rows 59 / 65, 2000 rows 98 / 123, 3900 rows 177 / 199 (1.28 PFLOP/s and
-  // the same clock x busy share where both have no rest; 720 rows of the 1.5B shape 43.3 / 40.5).
-  typedef StreamGemm<4, 2, 4, 2> G;
-  hipLaunchKernelGGL((glu_tail_kernel<G, StreamGemm<2, 2, 4, 2>>), dim3(grid8((M_max + G::BM - 1) / G::BM * n128)), dim3(G::THREADS), G::LDS_BYTES, st, g, n128);
+  constexpr int lds = Glu192x64::LDS_BYTES;
+  static_assert(Glu96::LDS_BYTES <= lds && Glu128::LDS_BYTES <= lds && Glu64x64::LDS_BYTES <= lds && 2 * lds <= 160 * 1024, "");
+  allow_lds(glu_w4_kernel, lds, w4);
+  hipLaunchKernelGGL(glu_w4_kernel, dim3(grid8(rule.grid)), dim3(256), lds, st, g, rule.at);
 }
 
 template <typename G>
@@ -410,6 +478,7 @@ void gemm_slab_rules(const Shape& s, int M_max, SlabRule (&r)[3]) {
   r[SLAB_O] = slab_rule(M_max, s.d, s.Hq * s.D / kBK, CHOICE_SLABS + SLAB_O);
   r[SLAB_DOWN] = slab_rule(M_max, s.d, s.F / kBK, CHOICE_SLABS + SLAB_DOWN);
 }
+TileRule gate_up_rule(const Shape& s, int M_max) { return s.dtype == BS_BF16 ? glu_rule(M_max, s.F, s.d) : TileRule{}; }
 static SlabCount launch_slabs(const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out, const SlabRule& r, hipStream_t st) {
 #define BS_SLAB(T_) launch_slab<T_>(n_rows_dev, M_max, N, K, A, W, out, r.fixed, st)
 #define BS_SLAB_ALT(G_, T_) launch_slab_alt<G_, T_>(n_rows_dev, M_max, N, K, A, W, out, r, st)
@@ -444,7 +513,7 @@ static void launch_f32(const int32_t* n_rows_dev, int M_max, int N, int K, const
 }
 
 SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, int M_max, int N, int K, const void* A, const void* W, void* out,
-                      int32_t* status, hipStream_t st, const SlabRule& rule) {
+                      int32_t* status, hipStream_t st, const SlabRule& rule, const TileRule& glu) {
   const SlabCount none{0, 0};
   if (dtype == BS_F32) {
     if (epi == EPI_SWIGLU) launch_f32<EPI_SWIGLU>(n_rows_dev, M_max, N, K, A, W, out, st);
@@ -453,6 +522,6 @@ SlabCount launch_gemm(int dtype, GemmEpilogue epi, const int32_t* n_rows_dev, in
     return none;
   }
   if (epi != EPI_SWIGLU) return launch_slabs(n_rows_dev, M_max, N, K, A, W, out, rule, st);
-  launch_glu(n_rows_dev, M_max, N, K, A, W, out, status, st);
+  launch_glu(n_rows_dev, M_max, N, K, A, W, out, status, glu, st);
   return none;
 }

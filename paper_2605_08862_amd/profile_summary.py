@@ -53,7 +53,7 @@ def classify(names):
             cls, marker = "attention", "attention"
         elif "qkv_kernel" in n or "qkv_many_kernel" in n or "rope_append_kernel" in n or "skinny_kernelILi0E" in n:
             cls = "gemm_qkv"
-        elif re.search(r"glu_(rows_|tail_)?kernel", n):
+        elif re.search(r"glu_(w4_|w8_)?kernel", n):
             cls, marker = "gemm_gate_up", "gate_up"
         elif re.search(r"slab_(alt_)?kernel", n) or "skinny_kernelILi1E" in n:
             # a layer's order: QKV (where it is not the fused kernel), attention, O, gate/up, down

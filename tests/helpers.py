@@ -46,8 +46,8 @@ def slab_choice(eng, which):
 
 
 def tile_choice(eng, which):
-    """Place in its rule's list of the tile that the device chose for the last verify step's QKV projection."""
-    at = {"qkv": 5}[which]
+    """Place in its rule's list of the tile that the device chose for the last verify step's QKV ("qkv") or gate/up projection ("glu")."""
+    at = {"qkv": 5, "glu": 6}[which]
     return int(debug_buffer(eng, 10, at + 1).view(torch.int32)[at].item())
 
 

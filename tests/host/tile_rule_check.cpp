@@ -30,6 +30,25 @@ int main() {
       if (!q.at) { std::printf("%s: no QKV rule at %d\n", sh.name, M_max); return 1; }
       if (!check(q, M_max, sh.name)) return 1;
     }
+  for (const auto& sh : shapes)
+    for (int M_max : {33, 160, 161, 252, 320, 321, 432, 504, 576, 639, 641, 663, 702, 816, 1088, 1280, 1513, 2176, 4352}) {
+      const TileRule g = gate_up_rule(sh.s, M_max);
+      if (M_max > 320 && !g.at && !g.fixed) { std::printf("%s: no gate/up rule at %d\n", sh.name, M_max); return 1; }
+      if (g.at && !check(g, M_max, sh.name)) return 1;
+      if (g.at && g.waves != 4 && g.waves != 8) return 1;
+    }
+  for (int M_max : {432, 576})
+    if (gate_up_rule(shapes[0].s, M_max).at) { std::printf("1.5B, %d rows: a launch of one round of the CUs waits for the row count\n", M_max); return 1; }
+  struct { int shape, M_max, M, waves, rows; } glu[] = {{1, 504, 280, 8, 96}, {1, 576, 346, 8, 128}, {1, 714, 134, 8, 160}, {1, 1224, 240, 8, 256}, {0, 639, 197, 8, 96}, {0, 612, 68, 8, 96}, {0, 2176, 128, 4, 192},
+                                                        {0, 952, 56, 4, 64}, {3, 432, 108, 8, 96}, {3, 952, 505, 8, 256}};
+  for (const auto& e : glu) {
+    const TileRule g = gate_up_rule(shapes[e.shape].s, e.M_max);
+    const int rows = g.tile[g.choice(e.M)].rows;
+    if (rows != e.rows || g.waves != e.waves) {
+      std::printf("gate/up of %d of %d rows, %s: %d rows in %d waves, %d in %d expected\n", e.M, e.M_max, shapes[e.shape].name, rows, g.waves, e.rows, e.waves);
+      return 1;
+    }
+  }
   struct { int shape, M_max, M, rows; } qkv[] = {{0, 2176, 128, 32}, {0, 952, 56, 32}, {0, 663, 367, 32}, {1, 714, 134, 32}, {1, 1088, 166, 32}, {2, 1024, 64, 32}};
   for (const auto& e : qkv) {
     const TileRule q = qkv_rope_rule(shapes[e.shape].s, e.M_max);

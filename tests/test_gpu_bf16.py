@@ -145,7 +145,7 @@ def test_mini_many_ragged_sequences():
 @pytest.mark.parametrize("fill", ["full", "mixed", "plain"])
 def test_wide_model_large_row_limit(fill):
     """Row limit 48 x 17 = 816 > 640 on a one-layer model that is wide enough (d = 3840) for the large-batch launch
-    paths at a size the oracle still finishes in seconds: the persistent gate/up kernel, and the residual projections
+    paths at a size the oracle still finishes in seconds: the gate/up projection in four waves, and the residual projections
     whose K split is decided on the device from the step's row count: for the O projection (K = 2048) one, two (mixed lengths, about
     430 rows) and six slabs (plain decodes only, 48 rows) of 128-row tiles.  (Row tiles that change: test_row_tile_from_the_row_count.)"""
     desc = W.shape("mini_bf16", n_layers=1, d_model=3840, n_q_heads=16, n_kv_heads=4, d_ffn=512, vocab=640)

@@ -38,8 +38,8 @@ def test_splits_from_the_row_count(d_ffn, fill):
 @pytest.mark.parametrize("d_model,k_b", [(320, [14] * 11 + [3] + [0] * 31), (320, [14] * 8 + [0] * 35), (2048, [0] * 43), (2048, [14] * 8 + [1] + [0] * 34),
                                          (2048, [14] * 8 + [0] * 35)])
 def test_gate_up_row_blocks_with_few_live_rows(d_model, k_b):
-    """Row limit 645.  Short K: a last row block of 72 live rows, whose workgroups compute 128, and one of 27, where they compute 64, with the blocks
-    behind it left out.  Long K: all rows in one block of 128 (43 rows), and 156 and 155 rows in one of 192."""
+    """Row limit 645.  Short K (four waves): 200 and 155 live rows in 64-row blocks, the blocks behind them left out.  Long K (eight waves): 43, 156 and 155 live
+    rows in 96-row blocks.  (Last blocks of 128 rows with few live ones: test_gate_up_tile_of_the_row_count.)"""
     desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=14, n_kv_heads=2, d_ffn=6400, vocab=333)
     _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(5).integers(0, 70, 43)], k_b=k_b, k_max=14, seed=92, q_mode="onehot", check_kv=False)
 
@@ -54,12 +54,32 @@ def test_lm_head_columns_per_workgroup(vocab, n_seq, k_max):
     _run_case(desc, ctx_lens=ctx, k_b=[k_max] * (n_seq - 1) + [0], k_max=k_max, seed=93, q_mode="onehot", check_kv=False)
 
 
-@pytest.mark.parametrize("n_draft", [8, 4, 2])
-def test_gate_up_rows_from_the_row_count_below_640(n_draft):
-    """Row limit 504, 148 column blocks: 192-row tiles are two rounds of the CUs at the limit, so the tile follows from the row count:
-    192 rows of 504 (three blocks) and of 168 (one), 128 of 280."""
-    desc = W.shape("mini_bf16", n_layers=1, d_model=192, n_q_heads=6, n_kv_heads=2, d_ffn=18944, vocab=333)
-    _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(6).integers(0, 70, 56)], k_b=[n_draft] * 56, k_max=8, seed=94, q_mode="onehot", check_kv=False)
+@pytest.mark.parametrize("n_draft,choice", [(8, 1), (4, 0), (2, 2)])
+def test_gate_up_rows_from_the_row_count_below_640(n_draft, choice):
+    """Row limit 504, 148 column blocks of 128 features, three K tiles: the tile follows from the row count, 128 rows for 504, 96 for 280, 64 rows of 64
+    features for 168."""
+    desc, seen = W.shape("mini_bf16", n_layers=1, d_model=192, n_q_heads=6, n_kv_heads=2, d_ffn=18944, vocab=333), []
+    _run_case(desc, ctx_lens=[int(x) for x in np.random.default_rng(6).integers(0, 70, 56)], k_b=[n_draft] * 56, k_max=8, seed=94, q_mode="onehot", check_kv=False,
+              after_step=lambda eng: seen.append(H.tile_choice(eng, "glu")))
+    assert seen == [choice]
+
+
+@pytest.mark.parametrize("d_model,d_ffn,n_seq,k_max,live,choice", [
+    (1600, 8896, 42, 16, 42, 2), (1600, 8896, 42, 16, 150, 3), (1600, 8896, 42, 16, 250, 0), (1600, 8896, 42, 16, 300, 1), (1600, 8896, 42, 16, 340, 1), (1664, 8896, 42, 16, 500, 3),
+    (1600, 8896, 64, 9, 64, 0), (1664, 8896, 64, 9, 280, 0), (1664, 8896, 64, 9, 303, 1), (1600, 8896, 64, 9, 425, 2), (1664, 8896, 64, 9, 558, 3), (1600, 8896, 64, 9, 631, 4),
+    (2112, 9664, 78, 8, 695, 5)])
+def test_gate_up_tile_of_the_row_count(d_model, d_ffn, n_seq, k_max, live, choice):
+    """Widths that 128 features do not divide (a last column block of 64), 25, 26 and 33 K tiles (1, 2 and 0 modulo three, odd and even).  Row limit 714, four waves: 64 x 64, 192 x 64 (one
+    and three row blocks), 96 x 128 and 128 x 128 (rows x features), the last block of 128 with 44 live rows, computed as 64, and with 84.  Row limits 567 and 640, eight waves:
+    96 (one row block and three), 128, 160, 192 and 224 rows; row limit 702, long K: 256 rows."""
+    left, k_b = live - n_seq, []
+    for _ in range(n_seq):
+        k_b.append(min(k_max, left))
+        left -= k_b[-1]
+    desc, seen = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=6, n_kv_heads=2, d_ffn=d_ffn, vocab=333), []
+    ctx = [int(x) for x in np.random.default_rng(11).integers(0, 70, n_seq)]
+    _run_case(desc, ctx_lens=ctx, k_b=k_b, k_max=k_max, seed=99, q_mode="onehot", check_kv=False, after_step=lambda eng: seen.append(H.tile_choice(eng, "glu")))
+    assert seen == [choice]
 
 
 @pytest.mark.parametrize("n_last", [0, 1, 2, 3])
@@ -88,10 +108,12 @@ def test_qkv_tiles_of_few_rows_and_of_192(d_model, heads, k_b, choice):
     assert seen == [choice]
 
 
-@pytest.mark.parametrize("d_model,d_ffn,n_seq", [(1536, 8960, 48), (1536, 8960, 64), (1536, 8960, 71), (320, 18944, 20), (320, 18944, 24)])
+@pytest.mark.parametrize("d_model,d_ffn,n_seq", [(1536, 8960, 48), (1536, 8960, 64), (1536, 8960, 71), (320, 18944, 20), (320, 18944, 24), (1600, 8896, 48), (1664, 8896, 63),
+                                                 (1600, 8896, 30), (1664, 8896, 42)])
 def test_gate_up_tiles_of_eight_waves_and_of_one_row_block(d_model, d_ffn, n_seq):
-    """24 K tiles, 70 column blocks of 128 features: eight waves on 160 (423 of 432 rows), 192 (567) and 224 rows (630).  1184 columns of 16 features: one
-    block of 192 and of 224 rows (171 and 207 live) with the weights in registers."""
+    """24 K tiles, 70 column blocks of 128 features: eight waves on 160 (423 of 432 rows), 192 (567) and, chosen by the device, 224 rows (630).  1184 columns of 16 features: one
+    block of 192 and of 224 rows (171 and 207 live) with the weights in registers.  A last column block of 64 features, 25 and 26 K tiles (1 and 2 modulo three): 160 and 192 rows
+    in eight waves, 96 (261 of 270 rows) and 128 (369 of 378) in four, all fixed by the row limit."""
     desc = W.shape("mini_bf16", n_layers=1, d_model=d_model, n_q_heads=6, n_kv_heads=2, d_ffn=d_ffn, vocab=333)
     ctx = [int(x) for x in np.random.default_rng(10).integers(0, 70, n_seq)]
     _run_case(desc, ctx_lens=ctx, k_b=[8] * (n_seq - 2) + [7, 0], k_max=8, seed=97, q_mode="onehot", check_kv=False)

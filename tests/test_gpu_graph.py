@@ -91,7 +91,7 @@ def test_step_replays_from_a_hip_graph(shape, q_mode):
 @pytest.mark.parametrize("Bn,mixed", [(48, None), (66, [15] * 42 + [0] * 24)])
 def test_replay_with_changing_row_counts_on_the_large_batch_paths(Bn, mixed):
     """The captured step has fixed grids; the row count lives on the device.  On a model wide enough for the
-    large-batch launch paths (row limits 48 x 17 = 816 and 66 x 17 = 1122 > 640: persistent gate/up kernel whose row tile follows
+    large-batch launch paths (row limits 48 x 17 = 816 and 66 x 17 = 1122 > 640: QKV and gate/up projections whose tile follows
     the row count, residual projections whose K split does, RMSNorm summing that many slabs) the draft lengths are rewritten between
     replays - every block full (816 and 1122 rows), mixed (about 430, and 696, where O takes another row tile than before and after), no
     drafts at all (48 and 66) - and each replay must equal the eager step on the same inputs bit for bit."""
