@@ -205,13 +205,14 @@ __global__ void __launch_bounds__(256, 2) glu_w4_kernel(GluArgs g, int at) {
     default: glu_rows<Glu192x64>(g, M, lds);
   }
 }
-// Eight waves of one weight tile each, one workgroup per CU: a weight is read by fewer workgroups, and its round by a whole CU.
+// Eight waves of one weight tile each, or two (256 features), one workgroup per CU: a weight is read by fewer workgroups, and its round by a whole CU.
 typedef StreamGemm<3, 1, 8, 3> Wide96;
 typedef StreamGemm<4, 1, 8, 3> Wide128;
 typedef StreamGemm<5, 1, 8, 3> Wide160;
 typedef StreamGemm<6, 1, 8, 3> Wide192;
 typedef StreamGemm<7, 1, 8, 2> Wide224;
 typedef DmaGemm<4, 2, 2, 4, 4> Wide256;
+typedef StreamGemm<4, 2, 8, 2> Wide128x256;
 __global__ void __launch_bounds__(512, 2) glu_w8_kernel(GluArgs g, int at) {
   extern __shared__ __align__(16) char lds[];
   const int M = min(*g.n_rows_dev, g.M_max);
@@ -221,7 +222,8 @@ __global__ void __launch_bounds__(512, 2) glu_w8_kernel(GluArgs g, int at) {
     case 2: glu_rows<Wide160>(g, M, lds); break;
     case 3: glu_rows<Wide192>(g, M, lds); break;
     case 4: glu_rows<Wide224>(g, M, lds); break;
-    default: glu_rows<Wide256>(g, M, lds);
+    case 5: glu_rows<Wide256>(g, M, lds); break;
+    default: glu_rows<Wide128x256>(g, M, lds);
   }
 }
 // ---- float32 results (O and down projections, unfused QKV projection): one partial [M_max, N] slab per K split,
@@ -302,33 +304,34 @@ static bool glu_wide(int F) { return F / 16 > 3 * kCUs; }   // more columns than
 static bool glu_mix(int F, int K) { return packed_weight_elems(F, K) * 2 < ((size_t)1 << 32); }   // the mixed tiles address the up rows with a 32-bit offset
 // One row block for all rows of the limit (a wide matrix: up to 320 rows), columns in steps of 16 features per wave: launch_glu.  Where a tile of at most 192 rows takes one
 // round of the CUs, up to 640 rows, it is fixed, too: a launch that reads the step's choice first took 0.4 us more (1.5B shape, 576 rows).  Otherwise the tile follows from the step's
-// row count, in one of two launch shapes: four waves and two workgroups per CU, or eight and one.  Measured by themselves with weights that no cache holds, us,
-// 96 / 128 rows x 128 features and 64 / 192 rows x 64 in four waves | 96 / 128 / 160 / 192 / 224 / 256 rows x 128 features in eight:
-//   8960 x 1536,   43 rows  21.3 / 21.2 / 14.1 / 16.1 | 21.3 / 21.4 / 22.4 / 23.3 / 29.2 / 30.4
-//   8960 x 1536,  134 rows  22.1 / 21.9 / 21.8 / 19.4 | 22 / 21.8 / 26.6 / 27.3 / 30.9 / 32
-//   8960 x 1536,  277 rows  23.5 / 23.3 / 31.6 / 31.6 | 24.3 / 23.6 / 27.4 / 29.4 / 34.2 / 37.3
-//   8960 x 1536,  432 rows  38.3 / 38.1 / 40.6 / 33.6 | 39.1 / 39.7 / 28.3 / 31.9 / 35 / 38.2
-//   8960 x 1536, 1037 rows  64.4 / 59.4 / 85.3 / 64 | 68.7 / 66.8 / 57.6 / 63.6 / 70.4 / 76.5
-//   18944 x 3584,   43 rows  52.6 / 52.6 / 63.5 / 80 | 52.3 / 52.4 / 54.5 / 56.6 / 72.6 / 78.1
-//   18944 x 3584,  134 rows  90.4 / 88 / 90.4 / 80.9 | 90.6 / 101 / 63.3 / 64.9 / 75 / 78.4
-//   18944 x 3584,  240 rows  89.3 / 102 / 114 / 101 | 90.7 / 108 / 113 / 120 / 142 / 80.4
-//   18944 x 3584,  277 rows  94.2 / 92.4 / 133 / 103 | 95.8 / 98 / 118 / 122 / 143 / 156
-//   18944 x 3584,  505 rows  153 / 138 / 214 / 151 | 159 / 153 / 162 / 131 / 153 / 160
-//   18944 x 3584, 1037 rows  271 / 253 / 394 / 256 | 282 / 279 / 278 / 261 / 236 / 261
-//   18944 x 3584, 2000 rows  465 / 436 / 757 / 481 | 486 / 492 / 456 / 467 / 452 / 438
-// The times of the rule lose least against the fastest tile, of each shape and of both, at 16 .. 3000 rows of those and of 11008 x 4096, 5632 x 2048, 9728 x 2560 and 1408 x 512
-// (features x K).  The launch shape can only follow from the row limit: the faster one there (among tiles of 128 rows and more: with fewer, eight waves gain nothing).
-//   Fewer than 32 K tiles: four waves above 640 rows, where eight gain 3 % of a full step at best and lose 10 % at 3/4 of the limit (8960 x 1536, 800 of 1037 rows 42.3 / 46.9 us).
-//   More: eight waves also where a full step loses up to 6 %, since steps of few live rows gain more (18944 x 3584, 134 of 714 rows 63.3 / 80.9, all 720 169 / 174; 11008 x 4096, 505 of
-//   720 rows 92 / 112), but above 1280 rows only where it gains 3 % (18944 x 3584, 1500 rows 343 / 314: the last round of whole CUs).
-// Tiles fixed by the row limit up to 640 rows, and of 128 rows above, were here before: 7B shape, 280 of 504 rows 124 us (96), 134 of 714 rows 99 (66); 1.5B shape, 197 of 639 rows 33.6 (22).
+// row count, in one of two launch shapes: four waves and two workgroups per CU, or eight and one.  Measured by themselves with weights that no cache holds, us (rows x features),
+// 96 / 128 x 128 and 64 / 192 x 64 in four waves | 96 / 128 / 160 / 192 / 224 / 256 x 128 and 128 x 256 in eight:
+//    8960 x 1536,   43 rows  21.2 / 21.2 / 14.1 / 16.2 | 21.1 / 21.3 / 22.3 / 23.3 / 29.6 / 30.6 / 36
+//    8960 x 1536,  128 rows  21.9 / 25.8 / 24.3 / 19 | 21.5 / 25.4 / 25.9 / 26.4 / 30.9 / 32.3 / 41.4
+//    8960 x 1536,  277 rows  23.5 / 23.3 / 31.7 / 33.2 | 24.1 / 24.8 / 27.7 / 30.1 / 35.3 / 38.8 / 38.9
+//    8960 x 1536,  432 rows  38.4 / 38.5 / 40.7 / 34.2 | 39.2 / 40.9 / 29 / 32.3 / 35.6 / 38.8 / 40
+//    8960 x 1536, 1037 rows  65.4 / 59.5 / 86 / 63.7 | 67.8 / 67.4 / 58.1 / 64.1 / 71.1 / 77.5 / 72.3
+//   18944 x 3584,   43 rows  52.7 / 52.5 / 63.7 / 85.4 | 52.4 / 52.5 / 54.3 / 56.9 / 75.7 / 83.9 / 85.8
+//   18944 x 3584,  144 rows  91 / 88.3 / 90.9 / 89.2 | 93.9 / 103 / 64 / 64.8 / 76.2 / 80.9 / 87.3
+//   18944 x 3584,  256 rows  91 / 105 / 117 / 102 | 92.5 / 110 / 115 / 120 / 144 / 81.9 / 93.4
+//   18944 x 3584,  320 rows  120 / 96 / 137 / 110 | 122 / 104 / 122 / 125 / 145 / 157 / 92.5
+//   18944 x 3584,  505 rows  156 / 141 / 217 / 145 | 162 / 155 / 164 / 133 / 159 / 166 / 173
+//   18944 x 3584, 1037 rows  272 / 260 / 399 / 255 | 285 / 282 / 279 / 261 / 239 / 276 / 255
+//   18944 x 3584, 1500 rows  377 / 319 / 554 / 357 | 403 / 352 / 350 / 342 / 373 / 343 / 343
+//   11008 x 4096,  505 rows  123 / 112 / 151 / 112 | 121 / 118 / 123 / 131 / 145 / 93.6 / 105
+// The times of the rule lose least against the fastest tile, of each shape and of both, at 16 .. 4352 rows of those and of 5632 x 2048, 9728 x 2560 and 1408 x 512 (features x K).  The
+// launch shape can only follow from the row limit: the faster one there.  Above 640 rows eight waves are also taken at up to 6 % more time of a full step, since steps of few live rows lose
+// more without them (18944 x 3584, 144 rows: 82 .. 90 us in four waves, 64 in eight), but with fewer than 32 K tiles four waves, where eight gain 3 % of a full step at best and lose up to
+// 10 % of others (8960 x 1536, 1200 rows 60.4 / 67.6 us).
+// Tiles fixed by the row limit up to 640 rows, and of 128 rows above, were here before: 7B shape, 280 of 504 rows 129 us (102), 134 of 714 rows 99 (75); 1.5B shape, 197 of 639 rows 34 (25).
 static TileRule glu_rule(int M_max, int F, int K) {
   TileRule r;
   const bool mix = glu_mix(F, K);
   if (mix && ((M_max + 31) / 32 <= 5 || (M_max <= kFewRows && glu_wide(F)))) return r;
   const int n64 = F / 64, n128 = (F + 127) / 128, nk = K / kBK;
-  const TileRule w4{CHOICE_GLU, 0, nk, mix ? 4 : 2, {{96, n128, 78, 350}, {128, n128, 78, 400}, {64, n64, 40, 300}, {192, n64, 70, 400}}};
-  const TileRule w8{CHOICE_GLU, 0, nk, 6, {{96, n128, 80, 550}, {128, n128, 90, 630}, {160, n128, 102, 710}, {192, n128, 112, 790}, {224, n128, 132, 870}, {256, n128, 135, 950}}};
+  const TileRule w4{CHOICE_GLU, 0, nk, mix ? 4 : 2, {{96, n128, 78, 350}, {128, n128, 78, 483}, {64, n64, 45, 200}, {192, n64, 66, 612}}};
+  const TileRule w8{CHOICE_GLU, 0, nk, 7, {{96, n128, 75, 539}, {128, n128, 86, 709}, {160, n128, 105, 571}, {192, n128, 112, 940}, {224, n128, 134, 819}, {256, n128, 141, 915},
+                                          {128, (F + 255) / 256, 145, 722}}};
   if (M_max <= 640) {
     const TileRule one{0, 0, nk, mix ? 4 : 2, {w4.tile[0], w4.tile[1], w8.tile[2], w8.tile[3]}};
     const int c = one.choice(M_max);
@@ -336,10 +339,8 @@ static TileRule glu_rule(int M_max, int F, int K) {
   }
   r = w4;
   if (mix) {
-    const int per_cent = nk < 32 ? (M_max <= 640 ? 100 : 0) : M_max <= 1280 ? 106 : 97;
-    long long least = w8.cost(1, M_max);
-    for (int i = 2; i < w8.n; ++i) least = w8.cost(i, M_max) < least ? w8.cost(i, M_max) : least;
-    if (least * 100 <= r.cost(r.choice(M_max), M_max) * per_cent) { r = w8; r.waves = 8; }
+    const int per_cent = M_max <= 640 ? 100 : nk >= 32 ? 106 : 0;
+    if (w8.cost(w8.choice(M_max), M_max) * 100 <= w4.cost(w4.choice(M_max), M_max) * per_cent) { r = w8; r.waves = 8; }
   }
   r.size_grid(M_max);
   return r;
@@ -383,7 +384,7 @@ static void launch_glu(const int32_t* n_rows_dev, int M_max, int F, int K, const
   static bool w4 = false, w8 = false;
   if (rule.waves == 8) {
     constexpr int lds = Wide256::LDS_BYTES;
-    static_assert(Wide96::LDS_BYTES <= lds && Wide128::LDS_BYTES <= lds && Wide160::LDS_BYTES <= lds && Wide192::LDS_BYTES <= lds && Wide224::LDS_BYTES <= lds, "");
+    static_assert(Wide96::LDS_BYTES <= lds && Wide128::LDS_BYTES <= lds && Wide160::LDS_BYTES <= lds && Wide192::LDS_BYTES <= lds && Wide224::LDS_BYTES <= lds && Wide128x256::LDS_BYTES <= lds, "");
     allow_lds(glu_w8_kernel, lds, w8);
     hipLaunchKernelGGL(glu_w8_kernel, dim3(grid8(rule.grid)), dim3(512), lds, st, g, rule.at);
     return;

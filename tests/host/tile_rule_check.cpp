@@ -39,7 +39,7 @@ int main() {
     }
   for (int M_max : {432, 576})
     if (gate_up_rule(shapes[0].s, M_max).at) { std::printf("1.5B, %d rows: a launch of one round of the CUs waits for the row count\n", M_max); return 1; }
-  struct { int shape, M_max, M, waves, rows; } glu[] = {{1, 504, 280, 8, 96}, {1, 576, 346, 8, 128}, {1, 714, 134, 8, 160}, {1, 1224, 240, 8, 256}, {0, 639, 197, 8, 96}, {0, 612, 68, 8, 96}, {0, 2176, 128, 4, 192},
+  struct { int shape, M_max, M, waves, rows; } glu[] = {{1, 504, 280, 8, 128}, {1, 576, 346, 8, 128}, {1, 714, 134, 8, 160}, {1, 1224, 240, 8, 256}, {0, 639, 197, 8, 96}, {0, 612, 68, 8, 96}, {0, 2176, 128, 4, 192},
                                                         {0, 952, 56, 4, 64}, {3, 432, 108, 8, 96}, {3, 952, 505, 8, 256}};
   for (const auto& e : glu) {
     const TileRule g = gate_up_rule(shapes[e.shape].s, e.M_max);

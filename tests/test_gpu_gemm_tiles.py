@@ -67,11 +67,11 @@ def test_gate_up_rows_from_the_row_count_below_640(n_draft, choice):
 @pytest.mark.parametrize("d_model,d_ffn,n_seq,k_max,live,choice", [
     (1600, 8896, 42, 16, 42, 2), (1600, 8896, 42, 16, 150, 3), (1600, 8896, 42, 16, 250, 0), (1600, 8896, 42, 16, 300, 1), (1600, 8896, 42, 16, 340, 1), (1664, 8896, 42, 16, 500, 3),
     (1600, 8896, 64, 9, 64, 0), (1664, 8896, 64, 9, 280, 0), (1664, 8896, 64, 9, 303, 1), (1600, 8896, 64, 9, 425, 2), (1664, 8896, 64, 9, 558, 3), (1600, 8896, 64, 9, 631, 4),
-    (2112, 9664, 78, 8, 695, 5)])
+    (3200, 10944, 56, 8, 470, 5), (2112, 9664, 78, 8, 695, 6)])
 def test_gate_up_tile_of_the_row_count(d_model, d_ffn, n_seq, k_max, live, choice):
-    """Widths that 128 features do not divide (a last column block of 64), 25, 26 and 33 K tiles (1, 2 and 0 modulo three, odd and even).  Row limit 714, four waves: 64 x 64, 192 x 64 (one
+    """Widths that 128 features do not divide (a last column block of 64; of 256: of 192), 25, 26 and 33 K tiles (1, 2 and 0 modulo three, odd and even).  Row limit 714, four waves: 64 x 64, 192 x 64 (one
     and three row blocks), 96 x 128 and 128 x 128 (rows x features), the last block of 128 with 44 live rows, computed as 64, and with 84.  Row limits 567 and 640, eight waves:
-    96 (one row block and three), 128, 160, 192 and 224 rows; row limit 702, long K: 256 rows."""
+    96 (one row block and three), 128, 160, 192 and 224 rows; long K, row limits 504 and 702: 256 rows, and 128 rows x 256 features."""
     left, k_b = live - n_seq, []
     for _ in range(n_seq):
         k_b.append(min(k_max, left))

@@ -29,7 +29,7 @@ def dma_events(mw, nw, wm, wn, nst):
 # kernels whose loops are not named in the symbol: the tiles of the declarations next to them, StreamGemm and DmaGemm
 STREAMS = {"qkv_many_kernel": [(1, 1, 4, 6, 4), (2, 1, 4, 4, 4), (3, 1, 4, 3, 4), (4, 1, 4, 3, 4), (5, 1, 4, 3, 4), (6, 1, 4, 4, 2), (4, 2, 4, 2, 4)],
            "glu_w4_kernel": [(3, 2, 4, 2, 4), (4, 2, 4, 2, 4), (2, 2, 4, 2, 4), (2, 1, 4, 4, 4), (6, 1, 4, 4, 2)],
-           "glu_w8_kernel": [(3, 1, 8, 3, 4), (4, 1, 8, 3, 4), (5, 1, 8, 3, 4), (6, 1, 8, 3, 4), (7, 1, 8, 2, 4)]}
+           "glu_w8_kernel": [(3, 1, 8, 3, 4), (4, 1, 8, 3, 4), (5, 1, 8, 3, 4), (6, 1, 8, 3, 4), (7, 1, 8, 2, 4), (4, 2, 8, 2, 4)]}
 LOOPS = {"glu_w8_kernel": [(4, 2, 2, 4, 4)]}
 
 
