@@ -33,7 +33,7 @@
 // float32 models use the plain kernel in attn_simple.h.
 #include "attn_simple.h"
 #include "attn_wide.h"
-#include "gemm_mfma.h"
+#include "attn_softmax.h"
 #include <type_traits>
 
 namespace {
@@ -45,20 +45,6 @@ __device__ __forceinline__ f16x8 pack_f16x8(const float* v) {
   return r;
 }
 }  // namespace
-
-// NQ: query-row tiles (of 32) handled by one wave; QG: groups of waves, each group owning NQ of the
-// workgroup's NQ*QG query tiles (tokens are split across the 4/QG waves of a group).
-// A unit = (work item, KV head) is covered by q_blocks workgroups (NQ*QG query tiles each).  Workgroups of
-// different query blocks stream the same K/V; the one-dimensional grid is decoded so that all workgroups of a
-// unit run on the same XCD (ids are dealt round-robin to the 8 XCDs) and are dispatched back to back, so the
-// second reader hits that XCD's L2 and HBM is still read once.
-// Partials (sequences with several chunks): part_ml [slot][Hkv][RPT][2], part_o [slot][Hkv][RPT][D], RPT =
-// 32 * (query tiles of a unit); counters [sequence][Hkv][q_blocks], zero between launches; queue [8]: next
-// position of every XCD's queue, zeroed by the plan kernel for every layer of the step.
-// The read-only index arrays arrive as separate __restrict__ arguments (not inside the by-value Plan / KvView
-// structs): only then can the compiler prove that the kernel's own stores never alias them, and only then do the
-// per-tile block-table lookups stay scalar loads inside the persistent loop.  A vector load of a page id in the
-// tile loop must be waited for with vmcnt(0), which serialises the K/V prefetch.
 
 // A launch of few units leaves most CUs, and the memory, idle for as long as its chain of latencies takes (one sequence of 1000 tokens, 1.5B heads: 8
 // workgroups, 11 us).  Workgroups without a unit read the weights of the launch behind this one, the O projection, into the memory-side cache (256 MB), up
@@ -80,6 +66,19 @@ __device__ __forceinline__ void read_ahead(const Ahead& a, int chunk_tiles, int 
   }
 }
 
+// NQ: query-row tiles (of 32) handled by one wave; QG: groups of waves, each group owning NQ of the
+// workgroup's NQ*QG query tiles (tokens are split across the 4/QG waves of a group).
+// A unit = (work item, KV head) is covered by q_blocks workgroups (NQ*QG query tiles each).  Workgroups of
+// different query blocks stream the same K/V; the one-dimensional grid is decoded so that all workgroups of a
+// unit run on the same XCD (ids are dealt round-robin to the 8 XCDs) and are dispatched back to back, so the
+// second reader hits that XCD's L2 and HBM is still read once.
+// Partials (sequences with several chunks): part_ml [slot][Hkv][RPT][2], part_o [slot][Hkv][RPT][D], RPT =
+// 32 * (query tiles of a unit); counters [sequence][Hkv][q_blocks], zero between launches; queue [8]: next
+// position of every XCD's queue, zeroed by the plan kernel for every layer of the step.
+// The read-only index arrays arrive as separate __restrict__ arguments (not inside the by-value Plan / KvView
+// structs): only then can the compiler prove that the kernel's own stores never alias them, and only then do the
+// per-tile block-table lookups stay scalar loads inside the persistent loop.  A vector load of a page id in the
+// tile loop must be waited for with vmcnt(0), which serialises the K/V prefetch.
 template <int NQ, int QG, int D>
 __global__ void __launch_bounds__(256) attn_mfma_kernel(const int32_t* __restrict__ seq_k, const int32_t* __restrict__ seq_c,
                                                         const int32_t* __restrict__ row_start, const int32_t* __restrict__ seq_slot,

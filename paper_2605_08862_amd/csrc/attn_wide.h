@@ -27,7 +27,7 @@
 // 256 of 8192 tokens (1.5B heads) 384 .. 389 and 390 .. 391, 8 of 20000 88 .. 89 and 88 .. 89; so they did with a higher wave priority for one wave of a SIMD.
 // Units with one query tile run as NQT = 2 with the second wave of each pair only loading.
 #pragma once
-#include "gemm_mfma.h"
+#include "attn_softmax.h"
 
 // Waits until at most N of this wave's requests are in flight, then for the other waves.
 template <int N> __device__ __forceinline__ void wait_shares() {

@@ -419,7 +419,7 @@ static void launch_slab_alt(const int32_t* n_rows_dev, int M_max, int N, int K, 
 // one + 3.9 us) + slabs.  The times (and what a slab weighs) are those under which the choices lose least against the fastest of all tiles and
 // splits, measured with weights that no cache holds at 40 .. 640 rows of 1536 x 1536, 2048 x 1536, 1536 x 8960, 3584 x 3584, 4608 x 3584 and 3584 x
 // 18944 (columns x K): 0.8 % on average, 4.7 % with the times of launches by themselves that were here before (7B shape, down projection, 400 rows
-// 66.7 us and six slabs, now 60.4 and three; O projection, 64 rows 8.9 and seven, now 8.1 and four).
+// 66.7 us and six slabs, now 60.4 and three; O projection, 64 rows 8.9 and seven, now 8.1 and four).  On 13 more matrices from 512 x 1024 to 6144 x 4096 they lose 1.2 %.
 typedef StreamGemm<2, 1, 2, 4> T64x64;
 typedef StreamGemm<2, 1, 4, 4> T64x128;
 typedef StreamGemm<3, 1, 4, 3> T96x128;
@@ -450,6 +450,7 @@ static SlabRule slab_rule(int M_max, int N, int nk, int at) {
     return r;
   }
   const int nb128 = (N + 127) / 128, nb256 = (N + 255) / 256;
+  // (The times of a K tile here are from launches by themselves on loops of 32 x 32 x 16 products; those of pick_slab have been measured since, these not.)
   // The first tile: 96 rows x 256 columns, 128 where the row limit has too few of those to fill the CUs (two layers of d = 256, 390 of
   // 702 rows: O and down 6.6 us with 256 columns or 128 rows, 5.6 here; 1.5B shape 10.1 and 22.9, 9.7 and 23.3).  96 x 128 takes 43 per K tile where it is
   // the better one.

@@ -3,14 +3,14 @@
 //   C^T[N, M] = W[N, K] * X[M, K]^T      W = packed weights (gemm_mfma.h), X = activations in chunk order (act_index).
 //
 // Why this shape.
-//   * Both operands lie in memory in MFMA fragment order, so a fragment (1 KiB: 32 rows x 16 of K) is one load instruction
-//     whose bytes land in LDS as they are: no registers hold what is in flight, no LDS stores are issued, and every LDS read is a
-//     conflict-free 1 KiB sweep.  Loops with the weights in a register ring (three tiles of them plus the activations' staging
-//     registers) had 8 .. 24 KiB per wave in flight; here it is up to 130 KiB per CU, whatever the accumulators take.
-//   * A stage is 32 of K (two MFMA steps) of every row tile; NST stages are in LDS, NST - 2 of them in flight.  One barrier per
-//     stage, between its two steps: the second step already reads the next stage's first fragments, so a stage starts with its
+//   * Both operands lie in memory in MFMA operand order, so a piece (1 KiB: 32 rows x 16 of K) is one load instruction
+//     whose bytes land in LDS as they are: no registers hold what is in flight, no LDS stores are issued.  A fragment of a 16 x 16 x 32 product is 16 rows of
+//     two consecutive pieces, four runs of 256 bytes, and its LDS read is free of conflicts (frag_lane).  Loops with the weights in a register ring (three tiles of them plus the
+//     activations' staging registers) had 8 .. 24 KiB per wave in flight; here it is up to 130 KiB per CU, whatever the accumulators take.
+//   * A stage is 32 of K (two pieces) of every row tile; NST stages are in LDS, NST - 2 of them in flight.  It is computed in two steps, 16 rows of each tile of
+//     one operand in each.  One barrier per stage, between its two steps: the second step already reads the next stage's first fragments, so a stage starts with its
 //     operands in registers, and the slot of the previous stage is free for stage i + NST - 1.
-//   * The tile (MW x NW accumulator tiles per wave, WM x WN waves) is a template parameter: few rows take all rows and few
+//   * The tile (MW x NW accumulator tiles of 32 x 32 per wave, WM x WN waves) is a template parameter: few rows take all rows and few
 //     columns per workgroup, so that a weight is read once and as many CUs stream as columns allow.
 // What bounds it (MI355X, 7B shape, gate/up in whole steps): 64 rows 55 -> 48.7 us, 5.6 TB/s of weights: memory.  1152 rows 272 -> 254 us: power.  Whatever
 // the tile, busy share of the matrix units x clock ends at 1.24 GHz (1.28 PFLOP/s); 128 x 256 tiles whose operands come from the first-level cache
@@ -153,7 +153,7 @@ struct DmaGemm {
 // of weights are in registers or in flight, as many stages of activations in LDS, one tile per workgroup.
 template <int MW_, int NW_, int WN_, int RW_, int KS_ = 4>
 struct StreamGemm {
-  static constexpr int MW = MW_, NW = NW_, WM = 1, WN = WN_, RW = RW_, NSX = RW + 1, KS = KS_;   // KS: MFMA steps (16 of K) of a stage
+  static constexpr int MW = MW_, NW = NW_, WM = 1, WN = WN_, RW = RW_, NSX = RW + 1, KS = KS_;   // KS: pieces (16 of K) of a stage, and its steps
   static constexpr int RT = MW, CT = NW * WN, BM = 32 * RT, WAVES = WN, THREADS = 64 * WAVES;
   static constexpr int PIECES = KS * MW, PX = (PIECES + WAVES - 1) / WAVES;
   static constexpr int STAGE_BYTES = PIECES * 1024, LDS_BYTES = NSX * STAGE_BYTES;

@@ -8,10 +8,11 @@
 //
 // Weights are re-packed once (at context creation) into MFMA operand order: for each (32-row tile, 64-wide K tile) a
 // 4 KiB block [s = 0..3][lane = 0..63][8 halves], blocks of one row tile consecutive along K.  A row tile is a purely
-// sequential stream of 1 KiB fragments (32 rows x 16 of K).  The contraction index inside a K tile is permuted: MFMA step s of
-// lane group g multiplies k = 32 g + 8 s + j.  Activations have the same order of k (act_index).
-// The products are mfma(W, X): the accumulator holds C^T tiles (rows = weight rows, lane = activation row), which makes
-// per-row reductions over N lane-private.  Main loops: gemm_dma.h, skinny.hip.
+// sequential stream of 1 KiB pieces (32 rows x 16 of K).  The contraction index inside a K tile is permuted: piece s of
+// lane group g (lane / 32) holds k = 32 g + 8 s + j.  Activations have the same order of k (act_index).  A 16 x 16 x 32 product reads 16 rows of two
+// consecutive pieces (frag_lane): lane groups 0 .. 3 of 16 lanes have the k of group 0 and 1 of piece s, then of piece s + 1, for both operands alike.
+// The products are mfma(W, X): the accumulator holds C^T tiles (rows = weight rows, lane % 16 = activation row), so that a lane has four consecutive
+// columns of a row and a reduction over the columns of a tile takes the four lanes of a row together.  Main loops: gemm_dma.h, skinny.hip.
 #pragma once
 #include "common.h"
 
@@ -27,31 +28,6 @@ constexpr int kBK = 64;                    // K tile (elements)
 constexpr int kWBlock = 32 * kBK;          // elements of one packed (row tile, K tile) block
 
 __device__ __forceinline__ f16x8 as_f16x8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
-
-// The two halves of a wave (lanes l and l + 32) without a trip through LDS.  swap_halves(a, b): first result: a in the lower half and b of the lower
-// half in the upper one; second: a of the upper half in the lower one and b in the upper half.
-__device__ __forceinline__ u32x2 swap_halves(uint32_t a, uint32_t b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-  return u32x2{r[0], r[1]};
-#else
-  return u32x2{a, b};
-#endif
-}
-__device__ __forceinline__ float max_halves(float v) {
-  const u32x2 r = swap_halves(__float_as_uint(v), __float_as_uint(v));
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_halves(float v) {
-  const u32x2 r = swap_halves(__float_as_uint(v), __float_as_uint(v));
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Online softmax of the attention kernels: accumulators and sums are rescaled only when a row's maximum has risen by more than 2^8 over the one they
-// refer to (log2 units).  Probabilities are then up to 256 and not up to 1, sums and accumulators by the same factor: float16 and float32 round
-// them just as well, and small ones are further from float16's subnormals.  With the rescaling at every rise (64 multiplications per tile and
-// wave), one of 32 rows rose in most tiles of a chunk.
-constexpr float kLateRescale = 8.f;
 
 // The GEMM loops multiply 16 x 16 x 32: the same rate and the same operand bytes as 32 x 32 x 16, but half of the accumulator bytes per product.
 // Under a power limit that is speed: MFMA loops on random operands, every CU busy, 1.64 -> 1.95 PFLOP/s from registers, 1.48 -> 1.69 with fragments
