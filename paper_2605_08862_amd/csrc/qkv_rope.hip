@@ -114,7 +114,7 @@ inline int pick_rows(int M, int heads, int nk, int& cost) {
 constexpr int kFewRows = 640;
 // More rows: four waves, weights in registers, two workgroups per CU, rows and heads of a tile from the step's row count (TileRule).  Rows128 reads 1.5 fragments
 // from LDS per product and is bound by that, these 0.6 .. 1.  Times of the kernels by themselves, weights that no cache holds, 32 / 64 / 96 / 128 / 160 / 192 rows of a
-// head and 128 rows of two heads (the rule's times lose least against the fastest tile over 20 .. 4352 rows of 8 shapes, from 12 heads and K 512 to 48 heads and K 4096):
+// head and 128 rows of two heads (the rule's times are fitted to 20 .. 4352 rows of 8 shapes, from 12 heads and K 512 to 48 heads and K 4096):
 //   16 heads, K 1536   128 rows 11.6 / 13.9 / 14.4 / 19.3 / 19.7 / 19.8 / 29.8 us   505 rows 11.8 / 13.9 / 14.8 / 19.2 / 18.4 / 22.1 / 28.9   824 rows 16.2 / 13.9 / 15.7 / 17.2 / 18.6 / 21.6 / 28.8
 //                      1200 rows 24.6 / 19.2 / 17.2 / 18.2 / 21.0 / 22.9 / 29.7   2720 rows 46.9 / 34.1 / 30.5 / 36.2 / 34.6 / 27.7 / 32.5
 //   36 heads, K 3584   128 rows 22.8 / 27.0 / 26.5 / 37.4 / 38.0 / 37.9 / 55.4 us   281 rows 35.0 / 25.3 / 32.1 / 28.8 / 38.9 / 37.7 / 50.1   720 rows 62.8 / 42.4 / 47.0 / 35.2 / 36.4 / 42.1 / 51.5
@@ -168,8 +168,10 @@ TileRule qkv_rope_rule(const Shape& s, int M_max) {
   const int heads = s.Hq + 2 * s.Hkv, pairs = (heads + 1) / 2;
   TileRule r;
   if (s.dtype != BS_BF16 || s.D != kD || M_max <= kFewRows) return r;
-  r = TileRule{CHOICE_QKV, 0, s.d / kBK, 7, {{32, heads, 27, 300}, {64, heads, 33, 375}, {96, heads, 44, 449}, {128, heads, 51, 585}, {160, heads, 61, 567}, {192, heads, 61, 936},
-                                            {128, pairs, 73, 1091}}};
+  // A further round also costs the change of workgroups, about two K tiles: counted without it, up to 6 K tiles took too many rounds (10 heads, K 256,
+  // 2176 rows: 32 rows 10.1 us, 96 rows, taken now, 8.5; tiles taken with K below 512 were 3.4 % from the fastest, now 0.5; from 512 on 0.14 and 0.20).
+  r = TileRule{CHOICE_QKV, 0, s.d / kBK + 2, 7, {{32, heads, 27, 246}, {64, heads, 33, 309}, {96, heads, 44, 361}, {128, heads, 51, 483}, {160, heads, 61, 445}, {192, heads, 61, 814},
+                                                {128, pairs, 73, 1071}}};
   r.size_grid(M_max);
   return r;
 }

@@ -49,7 +49,8 @@ int main() {
       return 1;
     }
   }
-  struct { int shape, M_max, M, rows; } qkv[] = {{0, 2176, 128, 32}, {0, 952, 56, 32}, {0, 663, 367, 32}, {1, 714, 134, 32}, {1, 1088, 166, 32}, {2, 1024, 64, 32}};
+  struct { int shape, M_max, M, rows; } qkv[] = {{0, 2176, 128, 32}, {0, 952, 56, 32}, {0, 663, 367, 32}, {1, 714, 134, 32}, {1, 1088, 166, 32}, {2, 1024, 64, 32},
+                                                       {2, 2176, 2176, 96}, {2, 2176, 824, 64}};
   for (const auto& e : qkv) {
     const TileRule q = qkv_rope_rule(shapes[e.shape].s, e.M_max);
     const int rows = q.tile[q.choice(e.M)].rows;
